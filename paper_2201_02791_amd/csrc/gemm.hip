@@ -10,256 +10,398 @@
 //   rel_outer    C_r = sum_{runs s of r} Z_s^T G_{dst(s)}        grouped over relations, (d_in x d_out) each
 //   coeff        da = C Vflat^T                                  (2R x d_in d_out) (d_in d_out x B)
 //
-// One kernel template: 128x128 block tile, 4 wavefronts in a 2x2 grid, each wavefront owns a
-// 64x64 sub-tile as 2x2 v_mfma_f32_32x32x2_f32 accumulators.  Operands are staged through LDS
-// K-major (As[k][m], Bs[k][n]) so that the MFMA operand reads are 32 consecutive floats.
-// Operand loaders and the epilogue are small functors, so the concatenated operands
-// ([V|W0], [dP|G]) are never materialised.  This file is the fp32 path; workloads with bf16
-// messages use the bf16 matrix-core kernels of gemm_bf16.hip.
+// One kernel template: 128x128 block tile, 4 wavefronts in a 2x2 grid, each wavefront owns a 64x64 sub-tile as
+// 2x2 accumulators of 32x32.  The fp32 operands are split into three bf16 parts each on their way into LDS and
+// multiplied on the bf16 matrix cores (split_bf16.h: six products per term, fp32 accuracy).  Operand loaders and the
+// epilogue are small functors, so the concatenated operands ([V|W0], [dP|G]) are never materialised.  This file is
+// the fp32 path; workloads with bf16 messages use the bf16 matrix-core kernels of gemm_bf16.hip.
 #include "common.h"
+#include "split_bf16.h"
+
+#include <type_traits>
 
 namespace {
 
-typedef float floatx16 __attribute__((ext_vector_type(16)));
+constexpr int BM = 128, BN = 128, BK = 16, GT = 256;
+constexpr int LP = 48;                      // bytes per row of a part in LDS: 16 bf16 and 16 bytes of padding, an odd
+                                            // multiple of 16, so that 16-byte reads of 8 rows touch every bank once
+constexpr int PLANE = 128 * LP;             // one part of a 128-row operand tile
+constexpr int FLUSH = 8;                    // steps after which the matrix cores' sums move to a second set (below)
 
-constexpr int BM = 128, BN = 128, BK = 16, PADL = 4, GT = 256;
+// ---- operands.  An operand is seen as rows x (rows of the output for A, its columns for B) times the contraction
+// index k, and its memory is contiguous either along k (KC) or along x.  Extents along the contiguous index are
+// multiples of 4.  bind(g) selects group g's matrix.
+//   KC:  start(c, ps, x) sets up row x (in range) as piece ps of cursor c; at(c, ps, k) is where its k.. lie; k does not
+//        decrease from call to call
+//   !KC: start(c, x) sets up columns x..; row(k) is the stored row of contraction index k; at(c, row)
+// Cursors hold addresses, so that a step's loads cost an addition each.  el(x, k): one element.
 
-// ---- operand sources: load4(row, col) returns 4 consecutive elements along the contiguous
-// dimension starting at (row, col); out-of-range -> zeros.  Contiguous extents are multiples of 4.
-
-// Hooks every source and epilogue has: limit_rows(e) hides rows >= e (a row tile that ends inside the
-// block), bind(g) selects group g's matrix or output.  No-ops where they mean nothing.
-struct SrcRowMajorF32 {          // X[r][c], c contiguous
-    const float *p; int64_t rows; int32_t cols;
-    __device__ __forceinline__ void limit_rows(int64_t e) { if (e < rows) rows = e; }
-    __device__ __forceinline__ void bind(int32_t) {}
-    __device__ __forceinline__ float4 load4(int64_t r, int32_t c) const
-    {
-        if (r >= rows || c >= cols) return make_float4(0.f, 0.f, 0.f, 0.f);
-        return *reinterpret_cast<const float4 *>(p + r * cols + c);
-    }
+struct RowsK {                  // KC: rows of p, ld apart, optionally picked through a list
+    static constexpr bool KC = true;
+    const float *__restrict__ p; int64_t ld; const int32_t *__restrict__ idx; int64_t gstride;
+    struct Cur { const float *q[2]; };
+    __device__ __forceinline__ void bind(int32_t g) { p += g * gstride; }
+    __device__ __forceinline__ void start(Cur &c, int ps, int64_t x) const { c.q[ps] = p + (idx ? (int64_t)idx[x] : x) * ld; }
+    __device__ __forceinline__ const float *at(Cur &c, int ps, int32_t k) const { return c.q[ps] + k; }
+    __device__ __forceinline__ float el(int64_t x, int64_t k) const { return p[(idx ? (int64_t)idx[x] : x) * ld + k]; }
 };
-
-// [V_1 .. V_B | W0] viewed as a (d_in x (B+1) d_out) matrix, column index contiguous inside a block
-struct SrcWcat {
+struct XcatK {                  // KC: row x of [dP | G]
+    static constexpr bool KC = true;
+    const float *dP, *G; int32_t d_out, bd;
+    struct Cur { const float *a[2], *g[2]; };
+    __device__ __forceinline__ void bind(int32_t) {}
+    __device__ __forceinline__ void start(Cur &c, int ps, int64_t x) const { c.a[ps] = dP + x * bd; c.g[ps] = G + x * d_out - bd; }
+    __device__ __forceinline__ const float *at(Cur &c, int ps, int32_t k) const { return (k < bd ? c.a[ps] : c.g[ps]) + k; }
+    __device__ __forceinline__ float el(int64_t x, int64_t k) const { return k < bd ? dP[x * bd + k] : G[x * d_out + k - bd]; }
+};
+struct WcatK {                  // KC: row x of every V_b, then of W_0, end to end
+    static constexpr bool KC = true;
     const float *V, *W0; int32_t d_in, d_out, B;
-    __device__ __forceinline__ void limit_rows(int64_t) {}
+    struct Cur { int64_t x[2]; int32_t b, kb; };
     __device__ __forceinline__ void bind(int32_t) {}
-    __device__ __forceinline__ float4 load4(int64_t k, int32_t c) const
+    __device__ __forceinline__ void start(Cur &c, int ps, int64_t x) const { c.x[ps] = x * d_out; c.b = 0; c.kb = 0; }
+    __device__ __forceinline__ const float *at(Cur &c, int ps, int32_t k) const
     {
-        int32_t nc = (B + 1) * d_out;
-        if (k >= d_in || c >= nc) return make_float4(0.f, 0.f, 0.f, 0.f);
-        int32_t b = c / d_out, cc = c - b * d_out;
-        const float *base = b < B ? V + ((int64_t)b * d_in + k) * d_out : W0 + k * d_out;
-        return *reinterpret_cast<const float4 *>(base + cc);
+        while (k - c.kb >= d_out) { c.kb += d_out; ++c.b; }
+        return (c.b < B ? V + (int64_t)c.b * d_in * d_out : W0) + c.x[ps] + (k - c.kb);
+    }
+    __device__ __forceinline__ float el(int64_t x, int64_t k) const
+    {
+        const int64_t b = k / d_out;
+        return (b < B ? V + b * d_in * d_out : W0)[x * d_out + k - b * d_out];
     }
 };
-
-// [dP | G] viewed as an (N x (B+1) d_out) matrix, both fp32
-struct SrcXcat {
-    const float *dP; const float *G; int64_t rows; int32_t d_out, B;
-    __device__ __forceinline__ void limit_rows(int64_t) {}
+struct RowsX {                  // x-contiguous: row k of p, ld apart, optionally picked through a list
+    static constexpr bool KC = false;
+    const float *__restrict__ p; int64_t ld; const int32_t *__restrict__ idx; int64_t gstride;
+    struct Cur { const float *q; };
+    __device__ __forceinline__ void bind(int32_t g) { p += g * gstride; }
+    __device__ __forceinline__ void start(Cur &c, int32_t x) const { c.q = p + x; }
+    __device__ __forceinline__ int32_t row(int64_t k) const { return idx ? idx[k] : (int32_t)k; }
+    __device__ __forceinline__ const float *at(const Cur &c, int32_t row) const { return c.q + row * ld; }
+    __device__ __forceinline__ float el(int64_t x, int64_t k) const { return p[row(k) * ld + x]; }
+};
+struct XcatX {                  // x-contiguous: row k of [dP | G]
+    static constexpr bool KC = false;
+    const float *dP, *G; int32_t d_out, bd;
+    struct Cur { const float *q; int32_t ld; };
     __device__ __forceinline__ void bind(int32_t) {}
-    __device__ __forceinline__ float4 load4(int64_t r, int32_t c) const
-    {
-        int32_t bd = B * d_out;
-        if (r >= rows || c >= bd + d_out) return make_float4(0.f, 0.f, 0.f, 0.f);
-        if (c >= bd) return *reinterpret_cast<const float4 *>(G + r * d_out + (c - bd));
-        return *reinterpret_cast<const float4 *>(dP + r * bd + c);
-    }
+    __device__ __forceinline__ void start(Cur &c, int32_t x) const { c.q = x < bd ? dP + x : G + (x - bd); c.ld = x < bd ? bd : d_out; }
+    __device__ __forceinline__ int32_t row(int64_t k) const { return (int32_t)k; }
+    __device__ __forceinline__ const float *at(const Cur &c, int32_t row) const { return c.q + (int64_t)row * c.ld; }
+    __device__ __forceinline__ float el(int64_t x, int64_t k) const { return x < bd ? dP[k * bd + x] : G[k * d_out + x - bd]; }
 };
-
-// rows of X picked through an index list: row k is X[idx[k]]
-struct SrcGatherRows {
-    const float *X; const int32_t *idx; int64_t n_idx; int32_t cols;
-    __device__ __forceinline__ void limit_rows(int64_t e) { if (e < n_idx) n_idx = e; }
+struct WcatX {                  // x-contiguous: row k of [V_1 .. V_B | W_0]
+    static constexpr bool KC = false;
+    const float *V, *W0; int32_t d_in, d_out, B;
+    struct Cur { const float *q; };
     __device__ __forceinline__ void bind(int32_t) {}
-    __device__ __forceinline__ float4 load4(int64_t k, int32_t c) const
+    __device__ __forceinline__ void start(Cur &c, int32_t x) const
     {
-        if (k >= n_idx || c >= cols) return make_float4(0.f, 0.f, 0.f, 0.f);
-        return *reinterpret_cast<const float4 *>(X + (int64_t)idx[k] * cols + c);
+        const int32_t b = x / d_out;
+        c.q = (b < B ? V + (int64_t)b * d_in * d_out : W0) + (x - b * d_out);
+    }
+    __device__ __forceinline__ int32_t row(int64_t k) const { return (int32_t)k; }
+    __device__ __forceinline__ const float *at(const Cur &c, int32_t row) const { return c.q + (int64_t)row * d_out; }
+    __device__ __forceinline__ float el(int64_t x, int64_t k) const
+    {
+        const int64_t b = x / d_out;
+        return (b < B ? V + b * d_in * d_out : W0)[k * d_out + x - b * d_out];
     }
 };
 
-// one (rows x cols) matrix per group, W[g][r][c]
-struct SrcGroupMat {
-    const float *W; int32_t rows, cols;
-    __device__ __forceinline__ void limit_rows(int64_t) {}
-    __device__ __forceinline__ void bind(int32_t g) { W += (int64_t)g * rows * cols; }
-    __device__ __forceinline__ float4 load4(int64_t r, int32_t c) const
-    {
-        if (r >= rows || c >= cols) return make_float4(0.f, 0.f, 0.f, 0.f);
-        return *reinterpret_cast<const float4 *>(W + r * cols + c);
-    }
-};
-
-// ---- epilogues: store(m, n, value); bind(g) tells a grouped launch which group the block works on
+// ---- outputs: column n's address in row 0 and its row pitch; bind(g) selects the group of a grouped launch
 struct EpiProject {             // columns < B*d_out go to P, the rest to Self
-    float *P; float *Self; int64_t rows; int32_t d_out, B;
+    float *P, *Self; int32_t d_out, bd;
     __device__ __forceinline__ void bind(int32_t) {}
-    __device__ __forceinline__ void limit_rows(int64_t) {}
-    __device__ __forceinline__ void store(int64_t m, int32_t n, float v) const
-    {
-        int32_t bd = B * d_out;
-        if (m >= rows || n >= bd + d_out) return;
-        if (n >= bd) Self[m * d_out + (n - bd)] = v;
-        else P[m * bd + n] = v;
-    }
+    __device__ __forceinline__ float *column(int32_t n, int64_t &ld) const { ld = n < bd ? bd : d_out; return n < bd ? P + n : Self + (n - bd); }
+    __device__ __forceinline__ void put(float *q, float v) const { *q = v; }
 };
-
 struct EpiWeightGrad {          // atomic accumulation of split-K partial tiles
     float *dV, *dW0; int32_t d_in, d_out, B;
     __device__ __forceinline__ void bind(int32_t) {}
-    __device__ __forceinline__ void limit_rows(int64_t) {}
-    __device__ __forceinline__ void store(int64_t m, int32_t n, float v) const
+    __device__ __forceinline__ float *column(int32_t n, int64_t &ld) const
     {
-        int32_t bd = B * d_out;
-        if (m >= d_in || n >= bd + d_out) return;
-        int32_t b = n / d_out, c = n - b * d_out;
-        float *dst = b < B ? dV + ((int64_t)b * d_in + m) * d_out + c : dW0 + m * d_out + c;
-        unsafeAtomicAdd(dst, v);
+        const int32_t b = n / d_out;
+        ld = d_out;
+        return (b < B ? dV + (int64_t)b * d_in * d_out : dW0) + (n - b * d_out);
     }
+    __device__ __forceinline__ void put(float *q, float v) const { unsafeAtomicAdd(q, v); }
 };
-
-struct EpiRowMajor {
-    float *out; int64_t rows; int32_t cols;
+struct EpiRows {                // streamed out: the next kernel reads it once
+    float *out; int64_t cols;
     __device__ __forceinline__ void bind(int32_t) {}
-    __device__ __forceinline__ void limit_rows(int64_t e) { if (e < rows) rows = e; }
-    __device__ __forceinline__ void store(int64_t m, int32_t n, float v) const
-    {
-        if (m < rows && n < cols) __builtin_nontemporal_store(v, out + m * cols + n);
-    }
+    __device__ __forceinline__ float *column(int32_t n, int64_t &ld) const { ld = cols; return out + n; }
+    __device__ __forceinline__ void put(float *q, float v) const { __builtin_nontemporal_store(v, q); }
+};
+struct EpiRowsAtomic {          // split-K partial tiles; one matrix per group, gstride apart
+    float *out; int64_t cols, gstride;
+    __device__ __forceinline__ void bind(int32_t g) { out += g * gstride; }
+    __device__ __forceinline__ float *column(int32_t n, int64_t &ld) const { ld = cols; return out + n; }
+    __device__ __forceinline__ void put(float *q, float v) const { unsafeAtomicAdd(q, v); }
 };
 
-struct EpiRowMajorAtomic {      // split-K partial tiles
-    float *out; int64_t rows; int32_t cols;
-    __device__ __forceinline__ void bind(int32_t) {}
-    __device__ __forceinline__ void limit_rows(int64_t) {}
-    __device__ __forceinline__ void store(int64_t m, int32_t n, float v) const
-    {
-        if (m < rows && n < cols) unsafeAtomicAdd(out + m * cols + n, v);
-    }
+// A launch is (row tiles) x (column tiles) x (splits) blocks in one dimension.  Row tile x holds rows x * BM.. or, with
+// a tile list (mt_beg non-null), rows [mt_beg[x], mt_end[x]) of group mt_id[x] (at most BM rows): A and the output are
+// cut at the tile's end, B is the group's matrix.  The contraction range of split z is [z*kchunk, min((z+1)*kchunk, K)),
+// or, in a grouped launch (g_beg non-null), [g_beg[z], g_end[z]) with the epilogue bound to group g_id[z].
+struct GemmGrid {
+    int32_t tiles_m, tiles_n, splits;
+    int64_t K, kchunk;
+    const int32_t *g_id, *g_beg, *g_end, *mt_id, *mt_beg, *mt_end;
 };
 
-struct EpiRelOuter {            // C[group] (d_in x d_out) accumulates the chunks of one relation
-    float *C; int32_t d_in, d_out; int32_t group;
-    __device__ __forceinline__ void bind(int32_t g) { group = g; }
-    __device__ __forceinline__ void limit_rows(int64_t) {}
-    __device__ __forceinline__ void store(int64_t m, int32_t n, float v) const
-    {
-        if (m < d_in && n < d_out) unsafeAtomicAdd(C + ((int64_t)group * d_in + m) * d_out + n, v);
-    }
-};
-
-// A(m,k): A_KCONTIG ? srcA.load4(m, k) along k : srcA.load4(k, m) along m
-// B(k,n): B_KCONTIG ? srcB.load4(n, k) along k : srcB.load4(k, n) along n
-// The contraction range of block z is [z*kchunk, min((z+1)*kchunk, K)), or, in a grouped launch
-// (g_beg non-null), [g_beg[z], g_end[z]) with the epilogue bound to group g_id[z].
-template <class SA, bool A_KCONTIG, class SB, bool B_KCONTIG, class EPI>
-__global__ __launch_bounds__(GT) void k_gemm(SA srcA, SB srcB, EPI epi, int64_t K, int64_t kchunk,
-                                             const int32_t *__restrict__ g_id = nullptr,
-                                             const int32_t *__restrict__ g_beg = nullptr,
-                                             const int32_t *__restrict__ g_end = nullptr,
-                                             const int32_t *__restrict__ mt_id = nullptr,
-                                             const int32_t *__restrict__ mt_beg = nullptr,
-                                             const int32_t *__restrict__ mt_end = nullptr)
+// C (+)= A B^T, A (M x K), B (N x K).
+// Steps of 16 k: a step's operands are split into LDS ([part][row][k]) one step ahead of their use, their loads are issued
+// two steps further ahead into registers (two sets, used in turn; past the range's end the last step is loaded again, so
+// that nothing in the loop is conditional and the waits for one set leave the other in flight).  Two LDS buffers, one
+// barrier per step; 74 KB, two blocks per compute unit.
+// A wavefront leaves out the 32-wide parts of its sub-tile that lie past the operands' ends (width 200 is 7 such parts,
+// not 8; a relation with 30 runs one of 4).
+// What the matrix cores cut off when they add products to a larger sum is cut off downwards, whatever the signs: over
+// thousands of steps and blocks it adds up (3e-6 in the weight gradients of 5.8 M rows, where fp32 steps give 1e-6).
+// Every FLUSH steps (half of a short contraction's) the sums therefore move to a second set by an ordinary addition and
+// start again from zero, and every other such group is formed with A negated and subtracted, so that what is cut off
+// cancels.
+// What bounds it: with rows of 128 floats the bytes moved (60 M edges, 5.8 M runs: a layer's six products take 7.0 ms at
+// about 4 TB/s; with fp32 matrix-core steps they took 8.6); with wider rows what a wavefront issues around the
+// matrix-core steps (splitting, addresses, the sums' moves: 9 vector instructions for each, where up to 6 would hide).
+// 352 k runs of 474 relations at width 200, microseconds with fp32 steps / now: rel_outer 570 / 380, apply_rel 427 /
+// 319, apply_rel_t 406 / 270; against fp64 the gradients are off by 3e-7 there, 5e-7 before.
+template <class SA, class SB, class EPI>
+__global__ __launch_bounds__(GT, 2) void k_gemm(SA A, SB B, EPI epi, int32_t M_, int32_t N_, GemmGrid g)
 {
-    __shared__ __attribute__((aligned(16))) float As[BK][BM + PADL];
-    __shared__ __attribute__((aligned(16))) float Bs[BK][BN + PADL];
+    __shared__ __attribute__((aligned(16))) unsigned char lds[2][6 * PLANE];      // [buffer][A's parts, B's parts]
 
-    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-    const int wm = w >> 1, wn = w & 1;
-    // row tiles: blockIdx.x * BM, or, with a tile list (mt_beg non-null), rows [mt_beg[x], mt_end[x]) of
-    // group mt_id[x] (at most BM rows): A and the output are cut at the tile's end, B is the group's matrix
-    int64_t m0 = (int64_t)blockIdx.x * BM;
-    if (mt_beg) {
-        m0 = mt_beg[blockIdx.x];
-        const int64_t me = mt_end[blockIdx.x];
-        srcA.limit_rows(me); epi.limit_rows(me); srcB.bind(mt_id[blockIdx.x]);
-    }
-    const int32_t n0 = blockIdx.y * BN;
-    int64_t kbeg = (int64_t)blockIdx.z * kchunk;
-    int64_t kend = (kbeg + kchunk < K) ? kbeg + kchunk : K;
-    if (g_beg) { kbeg = g_beg[blockIdx.z]; kend = g_end[blockIdx.z]; epi.bind(g_id[blockIdx.z]); }
+    const int t = threadIdx.x, lane = t & 63, half = lane >> 5;
+    const int w = __builtin_amdgcn_readfirstlane(t >> 6), wm = w >> 1, wn = w & 1;
+    // block id -> (row tile, column tile, split).  Workgroup i runs on XCD i % 8: the tiles that read the same rows of
+    // a long operand (the column tiles of a row tile; all tiles of a split) run on one XCD one after another, and the
+    // rows come from its L2 all but once.
+    const bool by_split = g.splits > 1 || g.g_beg;
+    const int32_t per = by_split ? g.tiles_m * g.tiles_n : g.tiles_n;
+    const int32_t slot = blockIdx.x / 8, unit = slot / per * 8 + blockIdx.x % 8, in_unit = slot % per;
+    const int32_t tn = in_unit % g.tiles_n, tm = by_split ? in_unit / g.tiles_n : unit, sp = by_split ? unit : 0;
+    if (tm >= g.tiles_m || sp >= g.splits) return;            // padding blocks of the last units
+    int64_t m0 = (int64_t)tm * BM, m_end = M_;
+    if (g.mt_beg) { m0 = g.mt_beg[tm]; m_end = g.mt_end[tm]; B.bind(g.mt_id[tm]); }
+    const int32_t n0 = tn * BN;
+    int64_t kbeg = sp * g.kchunk;
+    int64_t kend = (kbeg + g.kchunk < g.K) ? kbeg + g.kchunk : g.K;
+    if (g.g_beg) { kbeg = g.g_beg[sp]; kend = g.g_end[sp]; epi.bind(g.g_id[sp]); }
+    if (kbeg >= kend) return;
+    const int64_t klast = kbeg + (kend - 1 - kbeg) / BK * BK;         // the last step's first k
 
-    floatx16 acc[2][2];
+    // ---- global -> registers -> LDS.  k-contiguous operands: 4 lanes share a row's 16 k, a thread takes two rows 64
+    // apart.  x-contiguous operands: a wavefront takes 4 consecutive k, a lane 2 columns of each, so that a lane ends
+    // up with runs of 4 k as the matrix cores want them (one column and 8 k per lane: twice the loads, 20 % slower).
+    // Rows, columns and k past the operands' ends repeat the last ones; such rows only feed results that are dropped,
+    // such k are zeroed on the way into LDS.
+    typename SA::Cur ca;
+    typename SB::Cur cb;
+    int32_t rowa[2][4], rowb[2][4];      // by the parity of the step they belong to
+    auto pick = [&](auto &S, int32_t (&row)[4], int64_t k0) __attribute__((always_inline)) {
+        if constexpr (!std::decay_t<decltype(S)>::KC) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+            for (int q = 0; q < 4; ++q) { const int64_t k = k0 + w * 4 + q; row[q] = S.row(k < kend ? k : kend - 1); }
+        }
+    };
+    auto start = [&](auto &S, auto &c, int64_t x0, int64_t x_last) __attribute__((always_inline)) {
+        if constexpr (std::decay_t<decltype(S)>::KC) {
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-
-    // ---- global -> registers: the chunk after the one being multiplied is always in flight
-    float4 ra[2], rb[2];
-    auto fetch = [&](int64_t k0) {
-#pragma unroll
-        for (int ps = 0; ps < 2; ++ps) {
-            if (A_KCONTIG) {
-                int m = (t >> 2) + ps * 64, k4 = (t & 3) * 4;
-                ra[ps] = (k0 + k4 < kend) ? srcA.load4(m0 + m, (int32_t)(k0 + k4)) : make_float4(0.f, 0.f, 0.f, 0.f);
-            } else {
-                int k = (t >> 5) + ps * 8, m4 = (t & 31) * 4;
-                ra[ps] = (k0 + k < kend) ? srcA.load4(k0 + k, (int32_t)(m0 + m4)) : make_float4(0.f, 0.f, 0.f, 0.f);
+            for (int ps = 0; ps < 2; ++ps) {
+                const int64_t x = x0 + (t >> 2) + ps * 64;
+                S.start(c, ps, x < x_last ? x : x_last);
             }
-            if (B_KCONTIG) {
-                int n = (t >> 2) + ps * 64, k4 = (t & 3) * 4;
-                rb[ps] = (k0 + k4 < kend) ? srcB.load4(n0 + n, (int32_t)(k0 + k4)) : make_float4(0.f, 0.f, 0.f, 0.f);
-            } else {
-                int k = (t >> 5) + ps * 8, n4 = (t & 31) * 4;
-                rb[ps] = (k0 + k < kend) ? srcB.load4(k0 + k, n0 + n4) : make_float4(0.f, 0.f, 0.f, 0.f);
+        } else {
+            const int32_t x = (int32_t)x0 + lane * 2;
+            S.start(c, x < (int32_t)x_last ? x : (int32_t)x_last - 1);
+        }
+    };
+    auto load = [&](auto &S, auto &c, const int32_t (&row)[4], float4 (&r)[2], int64_t k0) __attribute__((always_inline)) {
+        if constexpr (std::decay_t<decltype(S)>::KC) {
+            int32_t k = (int32_t)k0 + (t & 3) * 4;
+            if (k > (int32_t)kend - 4) k = (int32_t)kend - 4;
+#pragma unroll
+            for (int ps = 0; ps < 2; ++ps) r[ps] = *reinterpret_cast<const float4 *>(S.at(c, ps, k));
+        } else {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const float2 v = *reinterpret_cast<const float2 *>(S.at(c, row[q]));
+                if (q & 1) { r[q >> 1].z = v.x; r[q >> 1].w = v.y; }
+                else { r[q >> 1].x = v.x; r[q >> 1].y = v.y; }
             }
         }
     };
-    if (kbeg < kend) fetch(kbeg);
-    for (int64_t k0 = kbeg; k0 < kend; k0 += BK) {
-        __syncthreads();      // previous tile fully consumed
+    auto stage = [&](auto &S, unsigned char *L, const float4 (&r)[2], int64_t k0, float sign) __attribute__((always_inline)) {
+        if constexpr (std::decay_t<decltype(S)>::KC) {
+            const float on = k0 + (t & 3) * 4 < kend ? sign : 0.f;
 #pragma unroll
-        for (int ps = 0; ps < 2; ++ps) {
-            if (A_KCONTIG) {
-                int m = (t >> 2) + ps * 64, k4 = (t & 3) * 4;
-                As[k4 + 0][m] = ra[ps].x; As[k4 + 1][m] = ra[ps].y;
-                As[k4 + 2][m] = ra[ps].z; As[k4 + 3][m] = ra[ps].w;
-            } else {
-                int k = (t >> 5) + ps * 8, m4 = (t & 31) * 4;
-                *reinterpret_cast<float4 *>(&As[k][m4]) = ra[ps];
+            for (int ps = 0; ps < 2; ++ps) {
+                const Split3 lo = split_pair(r[ps].x * on, r[ps].y * on), hi = split_pair(r[ps].z * on, r[ps].w * on);
+#pragma unroll
+                for (int p = 0; p < 3; ++p)
+                    *reinterpret_cast<uint2 *>(L + p * PLANE + ((t >> 2) + ps * 64) * LP + (t & 3) * 8) = make_uint2(lo.w[p], hi.w[p]);
             }
-            if (B_KCONTIG) {
-                int n = (t >> 2) + ps * 64, k4 = (t & 3) * 4;
-                Bs[k4 + 0][n] = rb[ps].x; Bs[k4 + 1][n] = rb[ps].y;
-                Bs[k4 + 2][n] = rb[ps].z; Bs[k4 + 3][n] = rb[ps].w;
-            } else {
-                int k = (t >> 5) + ps * 8, n4 = (t & 31) * 4;
-                *reinterpret_cast<float4 *>(&Bs[k][n4]) = rb[ps];
+        } else {
+            const int64_t left = kend - k0 - w * 4;         // of this wavefront's 4 k
+            const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
+            float4 u = r[0], v = r[1];
+            if (left < 4) {
+                if (left < 1) u = z; else if (left < 2) { u.z = 0.f; u.w = 0.f; }
+                if (left < 3) v = z; else { v.z = 0.f; v.w = 0.f; }
+            }
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                const Split3 lo = c ? split_pair(u.y * sign, u.w * sign) : split_pair(u.x * sign, u.z * sign);
+                const Split3 hi = c ? split_pair(v.y * sign, v.w * sign) : split_pair(v.x * sign, v.z * sign);
+#pragma unroll
+                for (int p = 0; p < 3; ++p)
+                    *reinterpret_cast<uint2 *>(L + p * PLANE + (lane * 2 + c) * LP + w * 8) = make_uint2(lo.w[p], hi.w[p]);
             }
         }
-        __syncthreads();
-        if (k0 + BK < kend) fetch(k0 + BK);
-        // ---- LDS -> matrix cores.  32x32x2: lane l supplies A[m = l%32][k = l/32], B[k = l/32][n = l%32]
+    };
+    auto at_most = [&](int64_t k) { return k < klast ? k : klast; };
+    float4 ra[2][2], rb[2][2];
+    // step number j's loads; its rows were picked with step j - 1's, ahead of those loads: a wavefront's memory operations
+    // retire in order, and waiting for an index behind them would wait for them too
+    auto load_step = [&](int par, int64_t k0) __attribute__((always_inline)) {
+        pick(A, rowa[par ^ 1], at_most(k0 + BK));
+        pick(B, rowb[par ^ 1], at_most(k0 + BK));
+        load(A, ca, rowa[par], ra[par], at_most(k0));
+        load(B, cb, rowb[par], rb[par], at_most(k0));
+    };
+    start(A, ca, m0, m_end - 1);
+    start(B, cb, n0, N_ - 1);
+    pick(A, rowa[0], kbeg);
+    pick(B, rowb[0], kbeg);
+    load_step(0, kbeg);
+    load_step(1, kbeg + BK);
+    stage(A, lds[0], ra[0], kbeg, 1.f);
+    stage(B, lds[0] + 3 * PLANE, rb[0], kbeg, 1.f);
+    load_step(0, kbeg + 2 * BK);
+    __syncthreads();
+
+    const int off_a = (wm * 64 + (lane & 31)) * LP + half * 16, off_b = 3 * PLANE + (wn * 64 + (lane & 31)) * LP + half * 16;
+    split_floatx16 tot[2][2], acc[2][2];
+    const int64_t n_steps = (kend - kbeg + BK - 1) / BK;
+    const int group = n_steps <= 2 * FLUSH ? (int)(n_steps + 1) / 2 : FLUSH;      // steps per group, two groups at least
+    // NI, NJ: 32-wide parts of this wavefront's sub-tile that hold rows (columns) of the output
+    auto contract = [&](auto ni, auto nj) __attribute__((always_inline)) {
+        constexpr int NI = decltype(ni)::value, NJ = decltype(nj)::value;
 #pragma unroll
-        for (int kk = 0; kk < BK; kk += 2) {
-            int ka = kk + (lane >> 5);
-            float a0 = As[ka][wm * 64 + (lane & 31)];
-            float a1 = As[ka][wm * 64 + 32 + (lane & 31)];
-            float b0 = Bs[ka][wn * 64 + (lane & 31)];
-            float b1 = Bs[ka][wn * 64 + 32 + (lane & 31)];
-            acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, b0, acc[0][0], 0, 0, 0);
-            acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, b1, acc[0][1], 0, 0, 0);
-            acc[1][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1, b0, acc[1][0], 0, 0, 0);
-            acc[1][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1, b1, acc[1][1], 0, 0, 0);
+        for (int i = 0; i < NI; ++i)
+#pragma unroll
+            for (int j = 0; j < NJ; ++j)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) { tot[i][j][v] = 0.f; acc[i][j][v] = 0.f; }
+        auto step = [&](int64_t k0, int cur, float next_sign) __attribute__((always_inline)) {
+            const unsigned char *L = lds[cur];
+            uint4 a[2][3], b[2][3];
+#pragma unroll
+            for (int p = 0; p < 3; ++p) {
+#pragma unroll
+                for (int i = 0; i < NI; ++i) a[i][p] = *reinterpret_cast<const uint4 *>(L + off_a + p * PLANE + i * 32 * LP);
+#pragma unroll
+                for (int j = 0; j < NJ; ++j) b[j][p] = *reinterpret_cast<const uint4 *>(L + off_b + p * PLANE + j * 32 * LP);
+            }
+            stage(A, lds[cur ^ 1], ra[cur ^ 1], k0 + BK, next_sign);
+            stage(B, lds[cur ^ 1] + 3 * PLANE, rb[cur ^ 1], k0 + BK, 1.f);
+            load_step(cur ^ 1, k0 + 3 * BK);
+#pragma unroll
+            for (int p = 0; p < SPLIT_TERMS; ++p)
+#pragma unroll
+                for (int i = 0; i < NI; ++i)
+#pragma unroll
+                    for (int j = 0; j < NJ; ++j) acc[i][j] = split_mfma(a[i][split_pa(p)], b[j][split_pb(p)], acc[i][j]);
+            __syncthreads();
+        };
+        float sign = 1.f;
+        auto flush = [&]() __attribute__((always_inline)) {
+#pragma unroll
+            for (int i = 0; i < NI; ++i)
+#pragma unroll
+                for (int j = 0; j < NJ; ++j)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) { tot[i][j][v] = fmaf(sign, acc[i][j][v], tot[i][j][v]); acc[i][j][v] = 0.f; }
+        };
+        int left = group;
+        auto one = [&](int64_t k0, int cur) __attribute__((always_inline)) {
+            step(k0, cur, left == 1 ? -sign : sign);
+            if (--left == 0) { flush(); left = group; sign = -sign; }
+        };
+        int64_t k0 = kbeg;
+        for (; k0 + BK < kend; k0 += 2 * BK) {
+            one(k0, 0);
+            one(k0 + BK, 1);
         }
-    }
+        if (k0 < kend) one(k0, 0);
+        if (left != group) flush();
+    };
+    using I0 = std::integral_constant<int, 0>;
+    using I1 = std::integral_constant<int, 1>;
+    using I2 = std::integral_constant<int, 2>;
+    const int64_t m_left = m_end - m0 - wm * 64;
+    const int32_t n_left = N_ - n0 - wn * 64;
+    const int mi = m_left > 32 ? 2 : m_left > 0 ? 1 : 0, nj = n_left > 32 ? 2 : n_left > 0 ? 1 : 0;
+    if (mi == 0 || nj == 0) contract(I0{}, I0{});        // every wavefront moves operands and meets the barriers
+    else if (mi == 2 && nj == 2) contract(I2{}, I2{});
+    else if (mi == 2) contract(I2{}, I1{});
+    else if (nj == 2) contract(I1{}, I2{});
+    else contract(I1{}, I1{});
+
     // ---- epilogue.  D register v of lane l is row 8*(v/4) + 4*(l/32) + v%4, column l%32.
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int j = 0; j < 2; ++j) {
+            if (i >= mi || j >= nj) continue;
+            const int64_t mb = m0 + wm * 64 + i * 32;
+            const int32_t n = n0 + wn * 64 + j * 32 + (lane & 31);
+            bool odd = false;
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                int row = wm * 64 + i * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-                int col = wn * 64 + j * 32 + (lane & 31);
-                epi.store(m0 + row, n0 + col, acc[i][j][v]);
+            for (int v = 0; v < 16; ++v) odd |= split_not_finite(tot[i][j][v]);
+            if (__any(odd)) {        // an infinity, a NaN or an overflow among the terms: these sums again, in fp32
+                split_floatx16 f;
+#pragma unroll
+                for (int v = 0; v < 16; ++v) f[v] = 0.f;
+                const int64_t m = mb + (lane & 31);
+                for (int64_t k = kbeg + half; k - half < kend; k += 2) {
+                    const float x = m < m_end && k < kend ? A.el(m, k) : 0.f, y = n < N_ && k < kend ? B.el(n, k) : 0.f;
+                    f = __builtin_amdgcn_mfma_f32_32x32x2f32(x, y, f, 0, 0, 0);
+                }
+#pragma unroll
+                for (int v = 0; v < 16; ++v) if (split_not_finite(tot[i][j][v])) tot[i][j][v] = f[v];
             }
+            if (n >= N_) continue;
+            int64_t ld;
+            float *q = epi.column(n, ld);
+            q += (mb + 4 * half) * ld;
+            if (mb + 32 <= m_end) {
+#pragma unroll
+                for (int v = 0; v < 16; ++v) epi.put(q + (8 * (v >> 2) + (v & 3)) * ld, tot[i][j][v]);
+            } else {
+                const int32_t left = (int32_t)(m_end - mb) - 4 * half;
+#pragma unroll
+                for (int v = 0; v < 16; ++v)
+                    if (8 * (v >> 2) + (v & 3) < left) epi.put(q + (8 * (v >> 2) + (v & 3)) * ld, tot[i][j][v]);
+            }
+        }
+}
+
+// row tiles x column tiles x splits of a launch, numbered as k_gemm reads them
+template <class SA, class SB, class EPI>
+int run_gemm(const SA &sa, const SB &sb, const EPI &ep, int64_t rows, int32_t cols, GemmGrid g, hipStream_t st)
+{
+    if (!g.mt_beg) g.tiles_m = (int32_t)cdiv(rows, BM);
+    g.tiles_n = (int32_t)cdiv(cols, BN);
+    const bool by_split = g.splits > 1 || g.g_beg;
+    const int64_t per = by_split ? (int64_t)g.tiles_m * g.tiles_n : g.tiles_n, units = by_split ? g.splits : g.tiles_m;
+    const int64_t blocks = cdiv(units, 8) * 8 * per;
+    KGE_REQUIRE(rows <= 0x7fffffffLL && blocks <= 0x7fffffffLL, KGE_ERANGE, "too many tiles for one launch");
+    k_gemm<SA, SB, EPI><<<(unsigned)blocks, GT, 0, st>>>(sa, sb, ep, (int32_t)rows, cols, g);
+    KGE_LAUNCH_CHECK();
+    return KGE_OK;
 }
 
 __global__ void k_zero16(float4 *p, int64_t n4)
@@ -305,15 +447,11 @@ int launch_project(const float *H, int64_t N, int32_t d_in, int32_t d_out, int32
                    const float *W0, float *P, float *Self, hipStream_t st)
 {
     if (N == 0) return KGE_OK;
-    int32_t nc = (B + 1) * d_out;
-    dim3 grid((unsigned)cdiv(N, BM), (unsigned)cdiv(nc, BN), 1);
-    SrcRowMajorF32 sa{H, N, d_in};
-    SrcWcat sb{V, W0, d_in, d_out, B};
+    RowsK sa{H, d_in, nullptr, 0};
+    WcatX sb{V, W0, d_in, d_out, B};
     KGE_PROF("project", st);
-    EpiProject ep{P, Self, N, d_out, B};
-    k_gemm<SrcRowMajorF32, true, SrcWcat, false, EpiProject><<<grid, GT, 0, st>>>(sa, sb, ep, d_in, d_in);
-    KGE_LAUNCH_CHECK();
-    return KGE_OK;
+    EpiProject ep{P, Self, d_out, B * d_out};
+    return run_gemm(sa, sb, ep, N, (B + 1) * d_out, GemmGrid{0, 0, 1, d_in, d_in}, st);
 }
 
 int launch_weight_grad(const float *H, int64_t N, int32_t d_in, int32_t d_out, int32_t B,
@@ -331,14 +469,11 @@ int launch_weight_grad(const float *H, int64_t N, int32_t d_in, int32_t d_out, i
     int64_t kchunk = cdiv(cdiv(N, splits), BK) * BK;
     if (kchunk < 4 * BK) kchunk = 4 * BK;
     splits = cdiv(N, kchunk);
-    dim3 grid((unsigned)cdiv(d_in, BM), (unsigned)cdiv(nc, BN), (unsigned)splits);
-    SrcRowMajorF32 sa{H, N, d_in};
+    RowsX sa{H, d_in, nullptr, 0};
+    XcatX sb{dP, G, d_out, B * d_out};
     EpiWeightGrad ep{dV, dW0, d_in, d_out, B};
     KGE_PROF("weight_grad", st);
-    SrcXcat sb{dP, G, N, d_out, B};
-    k_gemm<SrcRowMajorF32, false, SrcXcat, false, EpiWeightGrad><<<grid, GT, 0, st>>>(sa, sb, ep, N, kchunk);
-    KGE_LAUNCH_CHECK();
-    return KGE_OK;
+    return run_gemm(sa, sb, ep, d_in, nc, GemmGrid{0, 0, (int32_t)splits, N, kchunk}, st);
 }
 
 int launch_input_grad(const float *dP, const float *G, int64_t N, int32_t d_in,
@@ -347,14 +482,11 @@ int launch_input_grad(const float *dP, const float *G, int64_t N, int32_t d_in,
 {
     if (N == 0) return KGE_OK;
     int32_t nc = (B + 1) * d_out;
-    dim3 grid((unsigned)cdiv(N, BM), (unsigned)cdiv(d_in, BN), 1);
-    SrcWcat sb{V, W0, d_in, d_out, B};
-    EpiRowMajor ep{dH, N, d_in};
+    XcatK sa{dP, G, d_out, B * d_out};
+    WcatK sb{V, W0, d_in, d_out, B};
+    EpiRows ep{dH, d_in};
     KGE_PROF("input_grad", st);
-    SrcXcat sa{dP, G, N, d_out, B};
-    k_gemm<SrcXcat, true, SrcWcat, true, EpiRowMajor><<<grid, GT, 0, st>>>(sa, sb, ep, nc, nc);
-    KGE_LAUNCH_CHECK();
-    return KGE_OK;
+    return run_gemm(sa, sb, ep, N, d_in, GemmGrid{0, 0, 1, nc, nc}, st);
 }
 
 int launch_rel_outer(const kge_partition *p, const float *Z, const float *G, int32_t d_in, int32_t d_out,
@@ -365,18 +497,12 @@ int launch_rel_outer(const kge_partition *p, const float *Z, const float *G, int
     int rc = launch_fill_zero(C, sizeof(float) * (size_t)R2 * dd, st);
     if (rc != KGE_OK) return rc;
     if (p->n_seg == 0 || p->n_relc == 0) return KGE_OK;
-    KGE_REQUIRE(p->n_relc <= 65535, KGE_ERANGE, "too many relation chunks (%d) for one launch", p->n_relc);
-    {
-        dim3 grid((unsigned)cdiv(d_in, BM), (unsigned)cdiv(d_out, BN), (unsigned)p->n_relc);
-        SrcRowMajorF32 sa{Z, p->n_seg, d_in};
-        SrcGatherRows sb{G, p->seg_dst, p->n_seg, d_out};
-        EpiRelOuter ep{C, d_in, d_out, 0};
-        KGE_PROF("rel_outer", st);
-        k_gemm<SrcRowMajorF32, false, SrcGatherRows, false, EpiRelOuter><<<grid, GT, 0, st>>>(
-            sa, sb, ep, p->n_seg, 0, p->relc_rel, p->relc_beg, p->relc_end);
-        KGE_LAUNCH_CHECK();
-    }
-    return KGE_OK;
+    RowsX sa{Z, d_in, nullptr, 0};
+    RowsX sb{G, d_out, p->seg_dst, 0};
+    EpiRowsAtomic ep{C, d_out, dd};
+    KGE_PROF("rel_outer", st);
+    return run_gemm(
+        sa, sb, ep, d_in, d_out, GemmGrid{0, 0, p->n_relc, p->n_seg, 0, p->relc_rel, p->relc_beg, p->relc_end}, st);
 }
 
 int launch_coeff_contract(const kge_partition *p, const float *C, const float *V, int32_t d_in, int32_t d_out,
@@ -393,15 +519,12 @@ int launch_coeff_contract(const kge_partition *p, const float *C, const float *V
         int64_t kchunk = cdiv(cdiv(dd, splits), BK) * BK;
         if (kchunk < 4 * BK) kchunk = 4 * BK;
         splits = cdiv(dd, kchunk);
-        dim3 grid((unsigned)cdiv(R2, BM), (unsigned)cdiv(B, BN), (unsigned)splits);
-        SrcRowMajorF32 sa{C, R2, (int32_t)dd};
-        SrcRowMajorF32 sb{V, B, (int32_t)dd};
-        EpiRowMajorAtomic ep{da, R2, B};
+        RowsK sa{C, dd, nullptr, 0};
+        RowsK sb{V, dd, nullptr, 0};
+        EpiRowsAtomic ep{da, B, 0};
         KGE_PROF("coeff_contract", st);
-        k_gemm<SrcRowMajorF32, true, SrcRowMajorF32, true, EpiRowMajorAtomic><<<grid, GT, 0, st>>>(sa, sb, ep, dd, kchunk);
-        KGE_LAUNCH_CHECK();
+        return run_gemm(sa, sb, ep, R2, B, GemmGrid{0, 0, (int32_t)splits, dd, kchunk}, st);
     }
-    return KGE_OK;
 }
 
 // ---- relation-weight order ------------------------------------------------------------------
@@ -538,21 +661,22 @@ int launch_basis_grad_from_relations(const float *a, int32_t R2, int32_t B, cons
     return rc;
 }
 
+// the row tiles of the per-run products: <= 128 consecutive runs of one relation each
+static GemmGrid rel_tiles(const kge_partition *p, int32_t K)
+{
+    return GemmGrid{p->n_relt, 0, 1, K, K, nullptr, nullptr, nullptr, p->relt_rel, p->relt_beg, p->relt_end};
+}
+
 // U[s] = Z[s] Wrel[rel(s)]   (S x d_in) -> (S x d_out), one row tile per (relation, <= 128 runs)
 int launch_apply_relation_weights(const kge_partition *p, const float *Z, const float *Wrel, int32_t d_in,
                                   int32_t d_out, float *U, hipStream_t st)
 {
     if (p->n_relt == 0) return KGE_OK;
-    KGE_REQUIRE(cdiv(d_out, BN) <= 65535, KGE_ERANGE, "d_out too large");
-    dim3 grid((unsigned)p->n_relt, (unsigned)cdiv(d_out, BN), 1);
-    SrcRowMajorF32 sa{Z, p->n_seg, d_in};
-    SrcGroupMat sb{Wrel, d_in, d_out};
-    EpiRowMajor ep{U, p->n_seg, d_out};
+    RowsK sa{Z, d_in, nullptr, 0};
+    RowsX sb{Wrel, d_out, nullptr, (int64_t)d_in * d_out};
+    EpiRows ep{U, d_out};
     KGE_PROF("apply_rel", st);
-    k_gemm<SrcRowMajorF32, true, SrcGroupMat, false, EpiRowMajor><<<grid, GT, 0, st>>>(
-        sa, sb, ep, d_in, d_in, nullptr, nullptr, nullptr, p->relt_rel, p->relt_beg, p->relt_end);
-    KGE_LAUNCH_CHECK();
-    return KGE_OK;
+    return run_gemm(sa, sb, ep, p->n_seg, d_out, rel_tiles(p, d_in), st);
 }
 
 // dZ[s] = G[dst(s)] Wrel[rel(s)]^T   (S x d_out) -> (S x d_in)
@@ -560,13 +684,9 @@ int launch_apply_relation_weights_t(const kge_partition *p, const float *G, cons
                                     int32_t d_out, float *dZ, hipStream_t st)
 {
     if (p->n_relt == 0) return KGE_OK;
-    dim3 grid((unsigned)p->n_relt, (unsigned)cdiv(d_in, BN), 1);
-    SrcGatherRows sa{G, p->seg_dst, p->n_seg, d_out};
-    SrcGroupMat sb{Wrel, d_in, d_out};
-    EpiRowMajor ep{dZ, p->n_seg, d_in};
+    RowsK sa{G, d_out, p->seg_dst, 0};
+    RowsK sb{Wrel, d_out, nullptr, (int64_t)d_in * d_out};
+    EpiRows ep{dZ, d_in};
     KGE_PROF("apply_rel_t", st);
-    k_gemm<SrcGatherRows, true, SrcGroupMat, true, EpiRowMajor><<<grid, GT, 0, st>>>(
-        sa, sb, ep, d_out, d_out, nullptr, nullptr, nullptr, p->relt_rel, p->relt_beg, p->relt_end);
-    KGE_LAUNCH_CHECK();
-    return KGE_OK;
+    return run_gemm(sa, sb, ep, p->n_seg, d_in, rel_tiles(p, d_out), st);
 }
