@@ -3,14 +3,16 @@
 //
 // A query (fixed entity f, relation r, answer a) scores every entity e as  sum_k (H[f][k] M[r][k]) H[e][k]:
 // with the query vectors Q = H[f] * M[r] gathered once, all scores are the product Q H^T.  That
-// (queries x entities) matrix is never stored: k_eval_count computes it tile by tile on the fp32
-// matrix cores and keeps, per query, only how many entries lie above / exactly at the answer's score.
-// What the filtered setting removes - the known answers of the same (f, r), a handful per query - is
-// scored again, one wavefront per query, by k_eval_pairs and subtracted.  Both kernels build a score
-// from the same sequence of v_mfma_f32_32x32x2_f32 steps (k ascending, two k per step, fp32
-// accumulator starting at zero), so a pair gets the same bits in both and the subtraction is exact.
+// (queries x entities) matrix is never stored: k_eval_count computes it tile by tile on the matrix cores and
+// keeps, per query, only how many entries lie above / exactly at the answer's score.
+// What the filtered setting removes - the known answers of the same (f, r), from none to thousands per query - is
+// scored again by k_eval_pairs and subtracted.  Both kernels build a score from the same sequence of steps (fp32
+// numbers split into three bf16 parts, split_bf16.h; k ascending, 16 k per step, six products per step, fp32
+// accumulator starting at zero; a score that is not finite from v_mfma_f32_32x32x2_f32 steps, two k each), so a pair
+// gets the same bits in both and the subtraction is exact.
 // The same per-query kernel ranks against explicit candidate lists.
 #include "common.h"
+#include "split_bf16.h"
 
 #include <algorithm>
 #include <cmath>
@@ -34,20 +36,30 @@ struct kge_eval_filter {
 
 namespace {
 
-typedef float floatx16 __attribute__((ext_vector_type(16)));
-
-// tail queries of all test triples first, then the head queries
+// tail queries of all test triples first, then the head queries; their query vectors Q[q][:] = H[fixed][:] * M[rel][:]
+// (one thread per 4 columns) and cleared counters
 __global__ void k_eval_queries(const int32_t *__restrict__ th, const int32_t *__restrict__ tr,
-                               const int32_t *__restrict__ tt, int64_t n_test, int32_t *__restrict__ fixed,
-                               int32_t *__restrict__ rel, int32_t *__restrict__ answer)
+                               const int32_t *__restrict__ tt, int64_t n_test, const float4 *__restrict__ H,
+                               const float4 *__restrict__ M, int32_t d4, int32_t *__restrict__ fixed,
+                               int32_t *__restrict__ rel, int32_t *__restrict__ answer, float4 *__restrict__ Q,
+                               unsigned *__restrict__ cnt_gt, unsigned *__restrict__ cnt_eq)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= 2 * n_test) return;
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t >= 2 * n_test * d4) return;
+    const int64_t i = t / d4;
+    const int32_t c = (int32_t)(t - i * d4);
     const bool head_query = i >= n_test;
     const int64_t j = head_query ? i - n_test : i;
-    fixed[i] = head_query ? tt[j] : th[j];
-    rel[i] = tr[j];
-    answer[i] = head_query ? th[j] : tt[j];
+    const int32_t f = head_query ? tt[j] : th[j], r = tr[j];
+    const float4 h = H[(int64_t)f * d4 + c], m = M[(int64_t)r * d4 + c];
+    Q[t] = make_float4(h.x * m.x, h.y * m.y, h.z * m.z, h.w * m.w);
+    if (c == 0) {
+        fixed[i] = f;
+        rel[i] = r;
+        answer[i] = head_query ? th[j] : tt[j];
+        cnt_gt[i] = 0u;
+        cnt_eq[i] = 0u;
+    }
 }
 
 // Q[q][:] = H[fixed[q]][:] * M[rel[q]][:], one thread per 4 columns
@@ -63,24 +75,69 @@ __global__ void k_eval_qvec(const float4 *__restrict__ H, const float4 *__restri
     Q[t] = make_float4(h.x * m.x, h.y * m.y, h.z * m.z, h.w * m.w);
 }
 
-// Scores of one query row against one entity per column lane % 32 (ent < 0: no entity, score 0).  Every
-// row of the matrix-core tile carries the same query, so each lane ends up with its column's score.
-// Step s multiplies k = 2 s (lanes 0..31) and k = 2 s + 1 (lanes 32..63), as k_eval_count does.
+// 8 consecutive k of a row from k (past the width: the row's last ones; no condition stands around the loads, so that
+// they can be in flight together), and their three parts, scaled by 0 or 1
+struct Row8 { float4 x, y; };
+__device__ __forceinline__ Row8 row_of(const float *__restrict__ row, int32_t k, int32_t d)
+{
+    Row8 r;
+    r.x = *reinterpret_cast<const float4 *>(row + (k < d ? k : d - 4));
+    r.y = *reinterpret_cast<const float4 *>(row + (k + 4 < d ? k + 4 : d - 4));
+    return r;
+}
+struct Parts8 { uint4 p[3]; };
+__device__ __forceinline__ Parts8 parts_of(const Row8 &r, float sx, float sy)
+{
+    const Split3 a = split_pair(r.x.x * sx, r.x.y * sx), b = split_pair(r.x.z * sx, r.x.w * sx);
+    const Split3 c = split_pair(r.y.x * sy, r.y.y * sy), e = split_pair(r.y.z * sy, r.y.w * sy);
+    Parts8 q;
+#pragma unroll
+    for (int p = 0; p < 3; ++p) q.p[p] = make_uint4(a.w[p], b.w[p], c.w[p], e.w[p]);
+    return q;
+}
+
+// Scores of 32 (query, entity) pairs: lane l and lane l + 32 name pair l (qrow its query vector, ent its entity; ent < 0:
+// no pair, any score).  Row l of the matrix-core tile is the pair's query and column l its entity, so the scores lie on the
+// diagonal; the rest of the tile is not used.  Lanes 0..31 supply k = 16 s .. 16 s + 7 of step s and lanes 32..63 the
+// next 8, as in k_eval_count; every lane gets its pair's score.
+__device__ __forceinline__ float diagonal(const split_floatx16 &acc, int lane)
+{
+    const int c = lane & 31, v = (c >> 3) * 4 + (c & 3);       // register v of the half (c / 4) % 2 is row c
+    float s = acc[0];
+#pragma unroll
+    for (int u = 1; u < 16; ++u) s = v == u ? acc[u] : s;
+    return __shfl(s, c + 32 * ((c >> 2) & 1), 64);
+}
 __device__ __forceinline__ float pair_scores(const float *__restrict__ qrow, const float *__restrict__ H,
                                              int32_t ent, int32_t d, int lane)
 {
-    floatx16 acc;
+    split_floatx16 acc;
 #pragma unroll
     for (int v = 0; v < 16; ++v) acc[v] = 0.f;
-    const bool odd = (lane >> 5) != 0;
+    const int half = lane >> 5;
     const float *hb = H + (int64_t)(ent < 0 ? 0 : ent) * d;
-    for (int32_t k0 = 0; k0 < d; k0 += 4) {
-        const float4 qa = *reinterpret_cast<const float4 *>(qrow + k0);
-        const float4 ba = ent >= 0 ? *reinterpret_cast<const float4 *>(hb + k0) : make_float4(0.f, 0.f, 0.f, 0.f);
-        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(odd ? qa.y : qa.x, odd ? ba.y : ba.x, acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(odd ? qa.w : qa.z, odd ? ba.w : ba.z, acc, 0, 0, 0);
+    // two steps in flight ahead of the one being multiplied: the rows are gathered, and a tile is one chain
+    Row8 q0 = row_of(qrow, 8 * half, d), h0 = row_of(hb, 8 * half, d);
+    Row8 q1 = row_of(qrow, 16 + 8 * half, d), h1 = row_of(hb, 16 + 8 * half, d);
+    for (int32_t k0 = 0; k0 < d; k0 += 16) {
+        const int32_t k = k0 + 8 * half;
+        const Parts8 q = parts_of(q0, 1.f, 1.f), h = parts_of(h0, k < d ? 1.f : 0.f, k + 4 < d ? 1.f : 0.f);
+        q0 = q1; h0 = h1;
+        q1 = row_of(qrow, k + 32, d);
+        h1 = row_of(hb, k + 32, d);
+#pragma unroll
+        for (int p = 0; p < SPLIT_TERMS; ++p) acc = split_mfma(q.p[split_pb(p)], h.p[split_pa(p)], acc);
     }
-    return acc[0];
+    float s = diagonal(acc, lane);
+    if (__any(ent >= 0 && split_not_finite(s))) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+        for (int32_t k0 = 0; k0 < d; k0 += 2)
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(qrow[k0 + half], hb[k0 + half], acc, 0, 0, 0);
+        const float f = diagonal(acc, lane);
+        if (split_not_finite(s)) s = f;
+    }
+    return s;
 }
 
 __device__ __forceinline__ int64_t lower_bound_i64(const int64_t *__restrict__ a, int64_t n, int64_t x)
@@ -97,41 +154,70 @@ struct FilterTables {
     const int64_t *key[2]; const int32_t *val[2]; int64_t n[2]; int64_t N; int32_t R;
 };
 
-// One wavefront per query: the answer's score, then the known answers of the query's (fixed entity,
-// relation) 32 entities at a time.  Counts those other than the answer that score above / exactly at it.
-__global__ __launch_bounds__(256) void k_eval_pairs(const float *__restrict__ Q, const float *__restrict__ H,
+// The answers' scores and, among the known answers of each query's (fixed entity, relation), how many others score
+// above / exactly at them.  A block takes PQ queries.  Their answers are one matrix-core tile of 32 pairs; the known
+// answers of all its queries are laid end to end and cut into such tiles, dealt out over the block's wavefronts: most
+// lists hold a handful of entities (a tile of their own would be nearly empty) and a hub's hundreds are not one
+// wavefront's chain.  Bound by the splitting of the pairs' rows.  40,932 queries of the 14,541-entity graph at width 200:
+// 676 us with one wavefront and one tile per query and fp32 steps, 198 now (545 with
+// conditions around the row loads: each then waits for the last).
+constexpr int PQ = 32, PW = 8;             // queries and wavefronts of a block
+__global__ __launch_bounds__(64 * PW) void k_eval_pairs(const float *__restrict__ Q, const float *__restrict__ H,
                                                     int32_t d, int64_t nq, int64_t n_test,
                                                     const int32_t *__restrict__ fixed, const int32_t *__restrict__ rel,
                                                     const int32_t *__restrict__ answer, FilterTables ft,
                                                     float *__restrict__ s_answer, int32_t *__restrict__ out_gt,
                                                     int32_t *__restrict__ out_eq)
 {
-    const int lane = threadIdx.x & 63;
-    const int64_t q = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (q >= nq) return;                                    // whole wavefronts leave
-    const float *qrow = Q + q * d;
-    const int32_t ans = answer[q];
-    float st = pair_scores(qrow, H, (lane & 31) == 0 ? ans : -1, d, lane);
-    st = __shfl(st, 0, 64);
-    const int side = q >= n_test ? 1 : 0;
-    const int64_t base = ((int64_t)fixed[q] * ft.R + rel[q]) * ft.N;
-    const int64_t lo = lower_bound_i64(ft.key[side], ft.n[side], base);
-    const int64_t hi = lower_bound_i64(ft.key[side], ft.n[side], base + ft.N);
-    const int32_t *list = ft.val[side];
-    int gt = 0, eq = 0;
-    for (int64_t b = lo; b < hi; b += 32) {                 // bounds are the same in every lane
-        const int64_t i = b + (lane & 31);
-        int32_t e = i < hi ? list[i] : -1;
-        if (e == ans) e = -1;
-        const float s = pair_scores(qrow, H, e, d, lane);
-        const unsigned long long mg = __ballot(e >= 0 && s > st), me = __ballot(e >= 0 && s == st);
-        gt += __popc((unsigned)mg);                         // lanes 32..63 repeat lanes 0..31
-        eq += __popc((unsigned)me);
+    __shared__ int64_t bound[2 * PQ];
+    __shared__ int32_t ptr[PQ + 1], gt_s[PQ], eq_s[PQ];
+    __shared__ float thr[PQ];
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+    const int64_t q0 = (int64_t)blockIdx.x * PQ;
+    const int n_here = (int)(nq - q0 < PQ ? nq - q0 : PQ);
+    if (t < 2 * PQ) {                                       // ends of the queries' ranges in the tables, by wavefront 0
+        const int i = t >> 1;
+        int64_t pos = 0;
+        if (i < n_here) {
+            const int side = q0 + i >= n_test ? 1 : 0;
+            const int64_t base = ((int64_t)fixed[q0 + i] * ft.R + rel[q0 + i]) * ft.N;
+            pos = lower_bound_i64(ft.key[side], ft.n[side], (t & 1) ? base + ft.N : base);
+        }
+        bound[t] = pos;
+    } else if (w == 1) {                                    // the answers' scores, by wavefront 1
+        const int i = lane & 31;
+        const float s = pair_scores(Q + (q0 + (i < n_here ? i : 0)) * d, H, i < n_here ? answer[q0 + i] : -1, d, lane);
+        if (lane < n_here) { thr[lane] = s; s_answer[q0 + lane] = s; }
+    } else if (w == 2 && lane < PQ) {
+        gt_s[lane] = 0; eq_s[lane] = 0;
     }
-    if (lane == 0) {
-        s_answer[q] = st;
-        out_gt[q] = gt; out_eq[q] = eq;
+    __syncthreads();
+    if (w == 0) {                                           // where each query's known answers start in the block's row
+        int x = lane < PQ ? (int)(bound[2 * lane + 1] - bound[2 * lane]) : 0;
+        const int own = x;
+        for (int off = 1; off < PQ; off <<= 1) { const int y = __shfl_up(x, off, 64); if (lane >= off) x += y; }
+        if (lane < PQ) { ptr[lane] = x - own; if (lane == PQ - 1) ptr[PQ] = x; }
     }
+    __syncthreads();
+    const int n_pairs = ptr[PQ];
+    for (int b = w * 32; b < n_pairs; b += PW * 32) {        // bounds are the same in every lane
+        const int at = b + (lane & 31);
+        int i = 0;                                          // the last query that starts at or before `at`
+#pragma unroll
+        for (int step = PQ / 2; step > 0; step >>= 1) if (ptr[i + step] <= at) i += step;
+        int32_t e = -1;
+        if (at < n_pairs) {
+            e = ft.val[q0 + i >= n_test ? 1 : 0][bound[2 * i] + (at - ptr[i])];
+            if (e == answer[q0 + i]) e = -1;
+        }
+        const float s = pair_scores(Q + (q0 + i) * d, H, e, d, lane);
+        if (lane < 32 && e >= 0) {
+            if (s > thr[i]) atomicAdd(gt_s + i, 1);
+            if (s == thr[i]) atomicAdd(eq_s + i, 1);
+        }
+    }
+    __syncthreads();
+    if (t < n_here) { out_gt[q0 + t] = gt_s[t]; out_eq[q0 + t] = eq_s[t]; }
 }
 
 // Candidate lists: one wavefront per query, LPR lanes per entity row (LPR * 4 >= min(d, 256) columns at a
@@ -197,137 +283,193 @@ __global__ __launch_bounds__(256) void k_eval_candidates(const float4 *__restric
     if (lane == 0) { out_gt[q] = gt; out_eq[q] = eq; }
 }
 
-// ---- all entities: 128 queries x 128 entities per tile, 4 wavefronts in a 2 x 2 grid, each with 2 x 2
-// 32x32x2 accumulators; 16-deep k chunks staged through LDS k-major.  A block walks `tiles_per_block`
-// consecutive entity tiles and keeps its counts in registers: one packed word per accumulator row
-// (low half: entries above the answer, high half: entries equal to it).
-constexpr int EBM = 128, EBN = 128, EBK = 16, EPAD = 4;
-constexpr int ETR = EBK / 4, ERP = 256 / ETR, ENP = EBM / ERP;      // threads per row piece, rows per pass, passes
+// ---- all entities.  A block of 8 wavefronts takes QN queries and walks `tiles_per_block` consecutive tiles of EM
+// entities; a wavefront owns WI x WJ accumulators of 32 entities x 32 queries, the wavefronts 2 x 4 of those.  The query
+// is the accumulator's column, so a lane has one threshold and one pair of counts per 32 queries, kept in registers over
+// all tiles.  16-deep steps: a step's rows are split into LDS ([part][row][k], two buffers) one step ahead, their loads
+// issued one step before that, one barrier per step, also from one tile to the next.
+// Bound by the matrix cores (six bf16 products per term; every split row is used by 256 rows of the other side, so the
+// splitting hides behind them).  20,000 queries x 1 M entities at width 256: 49-51 ms (205 TFLOP/s, 1.2 PFLOP/s of
+// bf16 products: what a library's bf16 product of random 8192 x 8192 matrices reaches here); with fp32 steps 88.6 ms.
+constexpr int ELP = 48;                       // bytes per LDS row: 16 bf16 and 16 of padding (an odd multiple of 16)
 
-template <bool DUMP>
-__global__ __launch_bounds__(256, 2) void k_eval_count(const float *__restrict__ Q, int64_t nq,
+template <int WI, int WJ, bool DUMP>
+__global__ __launch_bounds__(512, 2) void k_eval_count(const float *__restrict__ Q, int64_t nq,
                                                     const float *__restrict__ H, int64_t N, int32_t d,
                                                     const float *__restrict__ s_answer, int32_t tiles_per_block,
                                                     int32_t n_col_tiles, int32_t n_row_tiles, int32_t n_col_chunks,
                                                     unsigned *__restrict__ cnt_gt,
                                                     unsigned *__restrict__ cnt_eq, float *__restrict__ dump)
 {
-    __shared__ __attribute__((aligned(16))) float As[EBK][EBM + EPAD];
-    __shared__ __attribute__((aligned(16))) float Bs[EBK][EBN + EPAD];
-    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-    const int wm = w >> 1, wn = w & 1, half = lane >> 5;
+    constexpr int EM = 64 * WI, QN = 128 * WJ, NA = EM / 128, NB = QN / 128;
+    constexpr int PA = EM * ELP, PB = QN * ELP, BUF = 3 * (PA + PB);       // bytes of a part of either operand, of a buffer
+    __shared__ __attribute__((aligned(16))) unsigned char lds[2 * BUF];
+    const int t = threadIdx.x, lane = t & 63, half = lane >> 5;
+    const int w = __builtin_amdgcn_readfirstlane(t >> 6), we = w >> 2, wq = w & 3;
     // block id -> (query tile, chunk of entity tiles).  Workgroup i runs on XCD i % 8, each with its own L2.
-    // The (query tile, chunk) space is cut into 8 x 8 patches; a patch goes to one XCD and is what that XCD
-    // runs at a time (64 blocks), so its L2 holds 8 query tiles, re-read at every entity tile, and 8 streams
-    // of entity tiles, each shared by 8 blocks - instead of 64 unrelated query tiles that do not fit.
+    // The (query tile, chunk) space is cut into 8 x 4 patches; a patch goes to one XCD and is what that XCD
+    // runs at a time (32 blocks), so its L2 holds 8 query tiles, re-read at every entity tile, and 4 streams
+    // of entity tiles, each shared by 8 blocks.
     const int64_t slot = blockIdx.x / 8, xcd = blockIdx.x % 8;
-    const int64_t patch = (slot / 64) * 8 + xcd;
-    const int r64 = (int)(slot % 64);
+    const int64_t patch = (slot / 32) * 8 + xcd;
+    const int r32 = (int)(slot % 32);
     const int64_t patches_r = (n_row_tiles + 7) / 8;
-    const int64_t row_tile = (patch % patches_r) * 8 + r64 % 8;
-    const int64_t chunk = (patch / patches_r) * 8 + r64 / 8;
+    const int64_t row_tile = (patch % patches_r) * 8 + r32 % 8;
+    const int64_t chunk = (patch / patches_r) * 4 + r32 / 8;
     if (row_tile >= n_row_tiles || chunk >= n_col_chunks) return;      // padding blocks of the edge patches
-    const int64_t m0 = row_tile * EBM;
-
-    // D register v of lane l of accumulator (i, j): row 32 i + 8 (v / 4) + 4 (l / 32) + v % 4, column 32 j + l % 32
-    // the answers' scores of the tile's queries wait in LDS for the comparisons (rows past the end: +inf)
-    __shared__ float thr_s[EBM];
-    if (t < EBM) thr_s[t] = m0 + t < nq ? s_answer[m0 + t] : INFINITY;
-    unsigned cnt[2][16];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) cnt[i][v] = 0u;
-
+    const int64_t q0 = row_tile * QN;
     const int32_t ct_beg = (int32_t)chunk * tiles_per_block;
     const int32_t ct_end = ct_beg + tiles_per_block < n_col_tiles ? ct_beg + tiles_per_block : n_col_tiles;
-    const int32_t nk = (d + EBK - 1) / EBK;
-    const int64_t n_it = (int64_t)(ct_end - ct_beg) * nk;      // k chunks of all tiles, in one sequence
 
-    // operand pieces of this thread: rows r_ld + ERP * pass of the tile, 4 consecutive k from k_ld
-    const int r_ld = t / ETR, k_ld = (t % ETR) * 4;
-    float4 ra[ENP], rb[ENP];
-    auto fetch = [&](int32_t ct, int32_t kc) {
-        const int32_t k = kc * EBK + k_ld;
-        const int64_t n0 = (int64_t)ct * EBN;
+    // rows r_ld + 128 * pass of either operand, 4 consecutive k; rows and k past the end repeat the last ones (such
+    // rows are not counted, such k are zeroed in the entities)
+    const int r_ld = t >> 2, k_ld = (t & 3) * 4;
+    const float *qb = Q + q0 * d;
+    const uint32_t q_last = (uint32_t)(nq - 1 - q0 < QN - 1 ? nq - 1 - q0 : QN - 1);
+    float4 ra[NA], rb[NB];
+    int32_t lt = ct_beg, lk = 0, sk = 0;                    // tile and k of the next load, k of the next staging
+    auto load = [&]() __attribute__((always_inline)) {
+        const uint32_t k = (uint32_t)(lk + k_ld < d ? lk + k_ld : d - 4);
+        const float *hb = H + (int64_t)lt * EM * d;
+        const int64_t more = N - 1 - (int64_t)lt * EM;
+        const uint32_t e_last = (uint32_t)(more < EM - 1 ? more : EM - 1);
 #pragma unroll
-        for (int ps = 0; ps < ENP; ++ps) {
-            const int64_t m = m0 + r_ld + ps * ERP, n = n0 + r_ld + ps * ERP;
-            ra[ps] = (m < nq && k < d) ? *reinterpret_cast<const float4 *>(Q + m * d + k) : make_float4(0.f, 0.f, 0.f, 0.f);
-            rb[ps] = (n < N && k < d) ? *reinterpret_cast<const float4 *>(H + n * d + k) : make_float4(0.f, 0.f, 0.f, 0.f);
+        for (int ps = 0; ps < NA; ++ps)
+            ra[ps] = *reinterpret_cast<const float4 *>(hb + (min((uint32_t)(r_ld + ps * 128), e_last) * (uint32_t)d + k));
+#pragma unroll
+        for (int ps = 0; ps < NB; ++ps)
+            rb[ps] = *reinterpret_cast<const float4 *>(qb + (min((uint32_t)(r_ld + ps * 128), q_last) * (uint32_t)d + k));
+        lk += 16;
+        if (lk >= d) { lk = 0; if (lt + 1 < ct_end) ++lt; }
+    };
+    auto stage = [&](unsigned char *L) __attribute__((always_inline)) {
+        const float on = sk + k_ld < d ? 1.f : 0.f;
+        unsigned char *at = L + r_ld * ELP + k_ld * 2;
+#pragma unroll
+        for (int ps = 0; ps < NA; ++ps) {
+            const Split3 x = split_pair(ra[ps].x * on, ra[ps].y * on), y = split_pair(ra[ps].z * on, ra[ps].w * on);
+#pragma unroll
+            for (int p = 0; p < 3; ++p) *reinterpret_cast<uint2 *>(at + p * PA + ps * 128 * ELP) = make_uint2(x.w[p], y.w[p]);
         }
+#pragma unroll
+        for (int ps = 0; ps < NB; ++ps) {
+            const Split3 x = split_pair(rb[ps].x, rb[ps].y), y = split_pair(rb[ps].z, rb[ps].w);
+#pragma unroll
+            for (int p = 0; p < 3; ++p) *reinterpret_cast<uint2 *>(at + 3 * PA + p * PB + ps * 128 * ELP) = make_uint2(x.w[p], y.w[p]);
+        }
+        sk = sk + 16 < d ? sk + 16 : 0;
     };
 
-    floatx16 acc[2][2];
-    if (n_it > 0) fetch(ct_beg, 0);
-    int32_t ct = ct_beg, kc = 0;          // the chunk being multiplied
-    for (int64_t it = 0; it < n_it; ++it) {
-        if (kc == 0) {
+    float thr[WJ];
+    unsigned gt[WJ], eq[WJ];
 #pragma unroll
-            for (int i = 0; i < 2; ++i)
+    for (int j = 0; j < WJ; ++j) {
+        const int64_t q = q0 + (wq * WJ + j) * 32 + (lane & 31);
+        thr[j] = q < nq ? s_answer[q] : INFINITY;
+        gt[j] = eq[j] = 0u;
+    }
+    split_floatx16 acc[WI][WJ];
+    auto clear = [&]() __attribute__((always_inline)) {
 #pragma unroll
-                for (int j = 0; j < 2; ++j)
+        for (int i = 0; i < WI; ++i)
 #pragma unroll
-                    for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+            for (int j = 0; j < WJ; ++j)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+    };
+    // the tile's scores are complete: compare and count.  Register v of lane l: entity 8 (v / 4) + 4 (l / 32) + v % 4
+    // of 32, query l % 32 of 32
+    auto count = [&](int32_t ct) __attribute__((always_inline)) {
+        const int64_t e0 = (int64_t)ct * EM + we * WI * 32;
+        float most = 0.f;          // v_maximum3_f32: two scores per instruction, a NaN stays
+#pragma unroll
+        for (int i = 0; i < WI; ++i)
+#pragma unroll
+            for (int j = 0; j < WJ; ++j)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) most = __builtin_elementwise_maximum(most, __builtin_fabsf(acc[i][j][v]));
+        if (__any(split_not_finite(most))) {          // an infinity, a NaN or an overflow among the terms: such scores again, in fp32
+#pragma unroll
+            for (int i = 0; i < WI; ++i)
+#pragma unroll
+                for (int j = 0; j < WJ; ++j) {
+                    split_floatx16 f;
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) f[v] = 0.f;
+                    const int64_t e = e0 + i * 32 + (lane & 31), q = q0 + (wq * WJ + j) * 32 + (lane & 31);
+                    const float *hp = H + (e < N ? e : N - 1) * d, *qr = Q + (q < nq ? q : nq - 1) * d;
+                    for (int32_t k = half; k < d; k += 2) f = __builtin_amdgcn_mfma_f32_32x32x2f32(hp[k], qr[k], f, 0, 0, 0);
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) if (split_not_finite(acc[i][j][v])) acc[i][j][v] = f[v];
+                }
         }
-        __syncthreads();                  // the previous chunk has been consumed
+        const int32_t left = N - e0 < (int64_t)WI * 32 ? (int32_t)(N - e0) : WI * 32;      // entities of this wavefront's part
 #pragma unroll
-        for (int ps = 0; ps < ENP; ++ps) {
-            const int r = r_ld + ps * ERP;
-            As[k_ld + 0][r] = ra[ps].x; As[k_ld + 1][r] = ra[ps].y; As[k_ld + 2][r] = ra[ps].z; As[k_ld + 3][r] = ra[ps].w;
-            Bs[k_ld + 0][r] = rb[ps].x; Bs[k_ld + 1][r] = rb[ps].y; Bs[k_ld + 2][r] = rb[ps].z; Bs[k_ld + 3][r] = rb[ps].w;
-        }
-        __syncthreads();
-        const int32_t kc_next = kc + 1 < nk ? kc + 1 : 0, ct_next = kc + 1 < nk ? ct : ct + 1;
-        if (it + 1 < n_it) fetch(ct_next, kc_next);      // in flight while the matrix cores work
+        for (int i = 0; i < WI; ++i)
 #pragma unroll
-        for (int kk = 0; kk < EBK; kk += 2) {
-            const int ka = kk + half;
-            const float a0 = As[ka][wm * 64 + (lane & 31)], a1 = As[ka][wm * 64 + 32 + (lane & 31)];
-            const float b0 = Bs[ka][wn * 64 + (lane & 31)], b1 = Bs[ka][wn * 64 + 32 + (lane & 31)];
-            acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, b0, acc[0][0], 0, 0, 0);
-            acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, b1, acc[0][1], 0, 0, 0);
-            acc[1][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1, b0, acc[1][0], 0, 0, 0);
-            acc[1][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1, b1, acc[1][1], 0, 0, 0);
-        }
-        if (kc == nk - 1) {               // the tile's scores are complete: compare and count
-            const int64_t n0 = (int64_t)ct * EBN;
+            for (int v = 0; v < 16; ++v) {
+                const int row = i * 32 + 8 * (v >> 2) + 4 * half + (v & 3);
+                const bool in = left == WI * 32 || row < left;
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const int64_t col = n0 + wn * 64 + j * 32 + (lane & 31);
-                if (col < N) {
-#pragma unroll
-                    for (int i = 0; i < 2; ++i)
-#pragma unroll
-                        for (int v = 0; v < 16; ++v) {
-                            const float s = acc[i][j][v];
-                            const float th = thr_s[wm * 64 + i * 32 + 8 * (v >> 2) + 4 * half + (v & 3)];
-                            cnt[i][v] += s > th ? 1u : (s == th ? 65536u : 0u);
-                            if (DUMP) {
-                                const int64_t row = m0 + wm * 64 + i * 32 + 8 * (v >> 2) + 4 * half + (v & 3);
-                                if (row < nq) dump[row * N + col] = s;
-                            }
-                        }
+                for (int j = 0; j < WJ; ++j) {
+                    gt[j] += in && acc[i][j][v] > thr[j] ? 1u : 0u;
+                    eq[j] += in && acc[i][j][v] == thr[j] ? 1u : 0u;
+                    if (DUMP) {
+                        const int64_t q = q0 + (wq * WJ + j) * 32 + (lane & 31);
+                        if (in && q < nq) dump[q * N + e0 + row] = acc[i][j][v];
+                    }
                 }
             }
-        }
-        kc = kc_next; ct = ct_next;
-    }
-    // sum each row's packed word over the 32 lanes that share it (at most 64 entries per tile and
-    // tiles_per_block <= 512: neither half overflows), then one atomic per row, wavefront and field
+        clear();
+    };
+
+    if (ct_beg < ct_end) {
+        load();
+        stage(lds);
+        load();
+        clear();
+        __syncthreads();
+        const int off_a = (we * WI * 32 + (lane & 31)) * ELP + half * 16, off_b = 3 * PA + (wq * WJ * 32 + (lane & 31)) * ELP + half * 16;
+        int32_t ct = ct_beg, kc = 0;
+        int cur = 0;
+        while (true) {
+            const unsigned char *L = lds + cur;
+            cur ^= BUF;
+            uint4 a[WI][3], b[WJ][3];
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+            for (int p = 0; p < 3; ++p) {
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            unsigned x = cnt[i][v];
+                for (int i = 0; i < WI; ++i) a[i][p] = *reinterpret_cast<const uint4 *>(L + off_a + p * PA + i * 32 * ELP);
 #pragma unroll
-            for (int off = 16; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
-            const int64_t row = m0 + wm * 64 + i * 32 + 8 * (v >> 2) + 4 * half + (v & 3);
-            if ((lane & 31) == 0 && row < nq) {
-                if (x & 0xFFFFu) atomicAdd(cnt_gt + row, x & 0xFFFFu);
-                if (x >> 16) atomicAdd(cnt_eq + row, x >> 16);
+                for (int j = 0; j < WJ; ++j) b[j][p] = *reinterpret_cast<const uint4 *>(L + off_b + p * PB + j * 32 * ELP);
             }
+            stage(lds + cur);
+            load();
+#pragma unroll
+            for (int p = 0; p < SPLIT_TERMS; ++p)
+#pragma unroll
+                for (int i = 0; i < WI; ++i)
+#pragma unroll
+                    for (int j = 0; j < WJ; ++j) acc[i][j] = split_mfma(a[i][split_pa(p)], b[j][split_pb(p)], acc[i][j]);
+            kc += 16;
+            if (kc >= d) {
+                count(ct);
+                kc = 0;
+                if (++ct == ct_end) break;
+            }
+            __syncthreads();
         }
+    }
+#pragma unroll
+    for (int j = 0; j < WJ; ++j) {
+        gt[j] += __shfl_xor(gt[j], 32, 64);
+        eq[j] += __shfl_xor(eq[j], 32, 64);
+        const int64_t q = q0 + (wq * WJ + j) * 32 + (lane & 31);
+        if (lane < 32 && q < nq) {
+            if (gt[j]) atomicAdd(cnt_gt + q, gt[j]);
+            if (eq[j]) atomicAdd(cnt_eq + q, eq[j]);
+        }
+    }
 }
 
 // higher = above - above among the filtered; equal = equal - equal among the filtered - the answer itself
@@ -344,27 +486,45 @@ __global__ void k_eval_finish(const unsigned *__restrict__ cnt_gt, const unsigne
 
 struct Ks { int32_t k[8]; int32_t n; };
 
-// one block: sums of 1 / rank and of [rank <= k] in double, fixed order
-__global__ __launch_bounds__(256) void k_eval_metrics(const int32_t *__restrict__ higher,
+// one block: sums of 1 / rank and of [rank <= k] in double, fixed order.  16 wavefronts with 4 queries of a thread in
+// flight: the walk over the counts is a chain of memory round trips otherwise.
+__global__ __launch_bounds__(1024) void k_eval_metrics(const int32_t *__restrict__ higher,
                                                        const int32_t *__restrict__ equal, int64_t nq, Ks ks,
                                                        double *__restrict__ out)
 {
-    __shared__ double red[9][256];
+    __shared__ double red[16][9];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     double s[9];
+#pragma unroll
     for (int j = 0; j < 9; ++j) s[j] = 0.0;
-    for (int64_t q = threadIdx.x; q < nq; q += 256) {
-        const double r = 1.0 + (double)higher[q] + 0.5 * (double)equal[q];
-        s[0] += 1.0 / r;
-        for (int j = 0; j < ks.n; ++j) s[1 + j] += r <= (double)ks.k[j] ? 1.0 : 0.0;
+    for (int64_t q0 = threadIdx.x; q0 < nq; q0 += 4096) {
+        int32_t h[4], e[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int64_t q = q0 + u * 1024;
+            h[u] = q < nq ? higher[q] : -1;
+            e[u] = q < nq ? equal[q] : 0;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            if (q0 + u * 1024 >= nq) break;
+            const double r = 1.0 + (double)h[u] + 0.5 * (double)e[u];
+            s[0] += 1.0 / r;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) s[1 + j] += j < ks.n && r <= (double)ks.k[j] ? 1.0 : 0.0;
+        }
     }
-    for (int j = 0; j <= ks.n; ++j) red[j][threadIdx.x] = s[j];
+#pragma unroll
+    for (int j = 0; j < 9; ++j) {
+        for (int off = 32; off > 0; off >>= 1) s[j] += __shfl_xor(s[j], off, 64);
+        if (lane == 0) red[w][j] = s[j];
+    }
     __syncthreads();
-    for (int off = 128; off > 0; off >>= 1) {
-        if ((int)threadIdx.x < off)
-            for (int j = 0; j <= ks.n; ++j) red[j][threadIdx.x] += red[j][threadIdx.x + off];
-        __syncthreads();
+    if ((int)threadIdx.x <= ks.n) {
+        double x = 0.0;
+        for (int i = 0; i < 16; ++i) x += red[i][threadIdx.x];
+        out[threadIdx.x] = nq > 0 ? x / (double)nq : 0.0;
     }
-    if ((int)threadIdx.x <= ks.n) out[threadIdx.x] = nq > 0 ? red[threadIdx.x][0] / (double)nq : 0.0;
 }
 
 struct EvalWs {
@@ -403,29 +563,38 @@ int check_ws(void *workspace, size_t ws_bytes, int64_t nq, int32_t d, EvalWs *w)
     return KGE_OK;
 }
 
+template <int WI, int WJ>
+int launch_count_tiles(const float *Q, int64_t nq, const float *H, int64_t N, int32_t d, const float *s_answer,
+                       unsigned *cnt_gt, unsigned *cnt_eq, float *dump, hipStream_t st)
+{
+    const int64_t row_tiles = cdiv(nq, 128 * WJ), col_tiles = cdiv(N, 64 * WI);
+    // about 2048 blocks (8 rounds of one per compute unit) when there is that much work, the chunk count a multiple
+    // of the patch width when it exceeds it
+    int64_t col_chunks = cdiv(2048, row_tiles);
+    if (col_chunks > 4) col_chunks = cdiv(col_chunks, 4) * 4;
+    if (col_chunks > col_tiles) col_chunks = col_tiles;
+    const int64_t tpb = cdiv(col_tiles, col_chunks);
+    col_chunks = cdiv(col_tiles, tpb);
+    const int64_t patches = cdiv(row_tiles, 8) * cdiv(col_chunks, 4);
+    const int64_t blocks = cdiv(patches, 8) * 8 * 32;        // whole rounds of 8 patches, 32 blocks each
+    KGE_REQUIRE(blocks <= 0x7FFFFFFFll, KGE_ERANGE, "evaluation grid too large");
+    if (dump)
+        k_eval_count<WI, WJ, true><<<(unsigned)blocks, 512, 0, st>>>(Q, nq, H, N, d, s_answer, (int32_t)tpb, (int32_t)col_tiles,
+                                                                    (int32_t)row_tiles, (int32_t)col_chunks, cnt_gt, cnt_eq, dump);
+    else
+        k_eval_count<WI, WJ, false><<<(unsigned)blocks, 512, 0, st>>>(Q, nq, H, N, d, s_answer, (int32_t)tpb, (int32_t)col_tiles,
+                                                                     (int32_t)row_tiles, (int32_t)col_chunks, cnt_gt, cnt_eq, nullptr);
+    KGE_LAUNCH_CHECK();
+    return KGE_OK;
+}
+
 int launch_count(const float *Q, int64_t nq, const float *H, int64_t N, int32_t d, const float *s_answer,
                  unsigned *cnt_gt, unsigned *cnt_eq, float *dump, hipStream_t st)
 {
-    const int64_t row_tiles = cdiv(nq, EBM), col_tiles = cdiv(N, EBN);
-    // about 4096 blocks (16 per compute unit) when there is that much work, the chunk count a multiple of
-    // the patch width when it exceeds it; a block's packed counters hold 512 tiles
-    int64_t col_chunks = cdiv(4096, row_tiles);
-    if (col_chunks > 8) col_chunks = cdiv(col_chunks, 8) * 8;
-    if (col_chunks > col_tiles) col_chunks = col_tiles;
-    int64_t tpb = cdiv(col_tiles, col_chunks);
-    if (tpb > 512) tpb = 512;
-    col_chunks = cdiv(col_tiles, tpb);
-    const int64_t patches = cdiv(row_tiles, 8) * cdiv(col_chunks, 8);
-    const int64_t blocks = cdiv(patches, 8) * 8 * 64;        // whole rounds of 8 patches, 64 blocks each
-    KGE_REQUIRE(blocks <= 0x7FFFFFFFll, KGE_ERANGE, "evaluation grid too large");
-    if (dump)
-        k_eval_count<true><<<(unsigned)blocks, 256, 0, st>>>(Q, nq, H, N, d, s_answer, (int32_t)tpb, (int32_t)col_tiles,
-                                                            (int32_t)row_tiles, (int32_t)col_chunks, cnt_gt, cnt_eq, dump);
-    else
-        k_eval_count<false><<<(unsigned)blocks, 256, 0, st>>>(Q, nq, H, N, d, s_answer, (int32_t)tpb, (int32_t)col_tiles,
-                                                             (int32_t)row_tiles, (int32_t)col_chunks, cnt_gt, cnt_eq, nullptr);
-    KGE_LAUNCH_CHECK();
-    return KGE_OK;
+    // 256 x 256 tiles halve the splitting per product; with fewer of them than compute units (256) most of the chip
+    // would wait for them, and 128 x 128 tiles spread the work
+    if (cdiv(nq, 256) * cdiv(N, 256) >= 256) return launch_count_tiles<4, 2>(Q, nq, H, N, d, s_answer, cnt_gt, cnt_eq, dump, st);
+    return launch_count_tiles<2, 1>(Q, nq, H, N, d, s_answer, cnt_gt, cnt_eq, dump, st);
 }
 
 int rank_all(const kge_eval_filter *f, const float *H, int64_t N, int32_t d, const float *M, int32_t R,
@@ -450,16 +619,11 @@ int rank_all(const kge_eval_filter *f, const float *H, int64_t N, int32_t d, con
     unsigned *cnt_gt = (unsigned *)(ws + w.off_cnt_gt), *cnt_eq = (unsigned *)(ws + w.off_cnt_eq);
     {
         KGE_PROF("eval_queries", st);
-        k_eval_queries<<<(unsigned)cdiv(nq, 256), 256, 0, st>>>(test_h, test_r, test_t, n_test, fixed, rel, answer);
-        KGE_LAUNCH_CHECK();
-        k_eval_qvec<<<(unsigned)cdiv(nq * (d / 4), 256), 256, 0, st>>>((const float4 *)H, (const float4 *)M, fixed, rel, nq,
-                                                                      d / 4, (float4 *)Q);
+        k_eval_queries<<<(unsigned)cdiv(nq * (d / 4), 256), 256, 0, st>>>(test_h, test_r, test_t, n_test, (const float4 *)H,
+                                                                         (const float4 *)M, d / 4, fixed, rel, answer,
+                                                                         (float4 *)Q, cnt_gt, cnt_eq);
         KGE_LAUNCH_CHECK();
     }
-    rc = launch_fill_zero(cnt_gt, (size_t)nq * 4, st);
-    if (rc != KGE_OK) return rc;
-    rc = launch_fill_zero(cnt_eq, (size_t)nq * 4, st);
-    if (rc != KGE_OK) return rc;
     {
         KGE_PROF("eval_pairs", st);
         FilterTables ft;
@@ -467,7 +631,7 @@ int rank_all(const kge_eval_filter *f, const float *H, int64_t N, int32_t d, con
             ft.key[sde] = f ? f->key[sde] : nullptr; ft.val[sde] = f ? f->val[sde] : nullptr; ft.n[sde] = f ? f->n[sde] : 0;
         }
         ft.N = N; ft.R = R;
-        k_eval_pairs<<<(unsigned)cdiv(nq, 4), 256, 0, st>>>(Q, H, d, nq, n_test, fixed, rel, answer, ft,
+        k_eval_pairs<<<(unsigned)cdiv(nq, PQ), 64 * PW, 0, st>>>(Q, H, d, nq, n_test, fixed, rel, answer, ft,
                                                            dump_answer ? dump_answer : s, sub_gt, sub_eq);
         KGE_LAUNCH_CHECK();
     }
@@ -648,7 +812,7 @@ extern "C" int kge_eval_metrics(const int32_t *higher, const int32_t *equal, int
     Ks k;
     k.n = n_ks;
     for (int j = 0; j < 8; ++j) k.k[j] = j < n_ks ? ks[j] : 0;
-    k_eval_metrics<<<1, 256, 0, (hipStream_t)stream>>>(higher, equal, n_queries, k, out);
+    k_eval_metrics<<<1, 1024, 0, (hipStream_t)stream>>>(higher, equal, n_queries, k, out);
     KGE_LAUNCH_CHECK();
     return KGE_OK;
 }
