@@ -175,7 +175,6 @@ void layout(const kge_partition *p, const kge_layer *layers, int32_t n_layers, i
     // partial results of the units of heavy rows; the three users never overlap in time
     size_t part = (size_t)p->hv_dm.n_units * max_dout;
     if ((size_t)p->hv_sm.n_units * max_bd > part) part = (size_t)p->hv_sm.n_units * max_bd;
-    if ((size_t)p->hv_seg.n_units * max_B > part) part = (size_t)p->hv_seg.n_units * max_B;
     if ((size_t)p->hv_seg.n_units * max_zd > part) part = (size_t)p->hv_seg.n_units * max_zd;
     if (max_u > 0 && (size_t)p->hv_dr.n_units * max_dout > part) part = (size_t)p->hv_dr.n_units * max_dout;
     if (max_u > 0 && (size_t)p->hv_sm.n_units * max_dout > part) part = (size_t)p->hv_sm.n_units * max_dout;
@@ -429,21 +428,17 @@ extern "C" int kge_rgcn_backward(const kge_partition *p, const kge_cgraph *cg, c
             }
             continue;
         }
-        rc = launch_coeff_grad(p, P, bf, Gl, L.n_bases, L.d_out, seg, part, grads[l].da, kge_cgraph_layer(cg, l), st);
-        if (rc != KGE_OK) return rc;
         const int64_t bd = (int64_t)L.n_bases * L.d_out;
-        if (bf && gather_transpose_bf16_supported(L.n_bases, L.d_out)) {
-            // the bf16 copy of G first (behind the dP columns of the same matrix): the transposed sums gather it
-            if (!g_bf) rc = launch_append_g_bf16(Gl, p->n_vert, L.d_out, L.n_bases, dP, st);
-            if (rc != KGE_OK) return rc;
+        const bool on_cores = bf && gather_transpose_bf16_supported(L.n_bases, L.d_out);      // dP on the matrix cores
+        rc = launch_project_first_backward(p, P, bf, Gl, L.a, L.n_bases, L.d_out, seg, part, grads[l].da, on_cores ? nullptr : dP,
+                                           bf ? bd + L.d_out : bd, kge_cgraph_layer(cg, l), st);
+        if (rc != KGE_OK) return rc;
+        // the bf16 copy of G (behind the dP columns of the same matrix): the matrix-core form gathers it
+        if (bf && !g_bf) rc = launch_append_g_bf16(Gl, p->n_vert, L.d_out, L.n_bases, dP, st);
+        if (rc != KGE_OK) return rc;
+        if (on_cores) {
             rc = launch_gather_transpose_bf16(p, (const uint16_t *)dP + bd, bd + L.d_out, L.a, L.n_bases, L.d_out, dP,
                                               bd + L.d_out, part, kge_cgraph_layer(cg, l), st);
-            if (rc != KGE_OK) return rc;
-        } else {
-            rc = launch_gather_transpose(p, Gl, L.a, L.n_bases, L.d_out, dP, bf ? bd + L.d_out : bd, bf, part,
-                                         kge_cgraph_layer(cg, l), st);
-            if (rc != KGE_OK) return rc;
-            if (bf && !g_bf) rc = launch_append_g_bf16(Gl, p->n_vert, L.d_out, L.n_bases, dP, st);
             if (rc != KGE_OK) return rc;
         }
         if (bf) {

@@ -146,9 +146,6 @@ int launch_gather_forward(const kge_partition *p, const void *P, int msg_bf16, c
 // G = dHout * act'(Hout) (ReLU: Hout > 0)
 int launch_act_backward(const float *dHout, const float *Hout, int act, int64_t n, float *G,
                         hipStream_t st);
-// dP[j][b][:] = sum_{e out of j} a[rel_e][b] invc_e G[dst_e][:]
-// `partial`: [hv_sm.n_units][B*d] floats of scratch
-// dP rows are `ld` elements apart (B*d, or (B+1)*d when G is appended behind them)
 // rel_outer_bf16.hip: C[r] += sum over relation r's runs of X[xidx ? xidx[s] : s]^T G[seg_dst[s]] (bf16 rows, fp32 C)
 bool rel_outer_bf16_supported(int32_t d_in, int32_t d_out);
 int launch_rel_outer_rows_bf16(const kge_partition *p, const void *X, int64_t ldx, const int32_t *xidx, const void *G,
@@ -156,17 +153,18 @@ int launch_rel_outer_rows_bf16(const kge_partition *p, const void *X, int64_t ld
 // C[g] += X^T Y_g for every d_out-wide column block g of Y's rows; the last block's sum to C_last when non-null
 int launch_col_blocks_outer_bf16(const void *X, int64_t rows, const void *Y, int64_t ldy, int32_t n_groups,
                                  int32_t d_in, int32_t d_out, float *C, float *C_last, hipStream_t st);
+// dP[j][b][:] = sum_{e out of j} a[rel_e][b] invc_e G[dst_e][:] on the matrix cores
+// `partial`: [hv_sm.n_units][B*d] floats of scratch
+// dP rows are `ld` elements apart ((B+1)*d: G is appended behind them)
 bool gather_transpose_bf16_supported(int32_t B, int32_t d);
 int launch_gather_transpose_bf16(const kge_partition *p, const void *Gbf, int64_t ldg, const float *a, int32_t B,
                                  int32_t d, void *dP, int64_t ld, float *partial, const uint8_t *active, hipStream_t st);
-int launch_gather_transpose(const kge_partition *p, const float *G, const float *a, int32_t B,
-                            int32_t d, void *dP, int64_t ld, int msg_bf16, float *partial,
-                            const uint8_t *active, hipStream_t st);
-// da[r][b] = sum_{runs (r,i)} invc sum_{j in run} <P[j][b][:], G[i][:]> ; seg_scratch [S][B] floats
-// seg_scratch [S][B] floats; `partial`: [hv_seg.n_units][B] floats
-int launch_coeff_grad(const kge_partition *p, const void *P, int msg_bf16, const float *G,
-                      int32_t B, int32_t d, float *seg_scratch, float *partial, float *da,
-                      const uint8_t *active, hipStream_t st);
+// da[r][b] = sum_{edges e of r} invc_e <P[src_e][b][:], G[dst_e][:]> and, where dP is given, dP (fp32, or bf16 with bf16
+// messages): dP[j][b][:] = sum_{e out of j} a[rel_e][b] invc_e G[dst_e][:], rows ld elements apart.  dP null: bf16 messages
+// only.  seg_scratch [S][B] floats; `partial`: [hv_sm.n_units][B*d] floats
+int launch_project_first_backward(const kge_partition *p, const void *P, int msg_bf16, const float *G, const float *a,
+                                  int32_t B, int32_t d, float *seg_scratch, float *partial, float *da, void *dP, int64_t ld,
+                                  const uint8_t *active, hipStream_t st);
 
 // cgraph.hip: per-batch computational sub-graph ------------------------------
 // flag row of layer `layer` (device pointer; -1: the first layer's input rows the batch reads), or null when cg is null

@@ -277,112 +277,168 @@ __global__ void k_act_backward(const float4 *__restrict__ dH, const float4 *__re
     }
 }
 
-// ------------------------------------------------------------------ transposed gather
-// One wavefront per (source row work, chunk of bases) on the source-major view:
-//   dP[j][b][:] = sum_{e out of j} a[rel_e][b] invc_e G[dst_e][:]
-// A G row (fp32) is covered by LPR lanes x 4 floats.  Of the 64/LPR lane groups, GBT take
-// different bases (NB bases each, so a chunk is GBT*NB bases) and the other 64/(LPR*GBT) take
-// different edges; UE rounds of edges are in flight at a time.
-// GIN: the gathered rows are bf16 instead of fp32.
-template <bool BF16, bool GIN, int LPR, int NB, int UE>
-__global__ __launch_bounds__(64 * WPB) void k_gather_t(
-    const int32_t *__restrict__ sm_ptr, const int32_t *__restrict__ sm_dst,
-    const int32_t *__restrict__ sm_rel, const float *__restrict__ sm_invc, int64_t N,
-    int32_t n_units, const int32_t *__restrict__ hv_row, const int32_t *__restrict__ hv_unit_ptr,
-    const int32_t *__restrict__ unit_hv,
-    const void *__restrict__ Gv, const float *__restrict__ a, int32_t B, int32_t d, int32_t n_chunks,
-    int32_t gbt_count, void *__restrict__ dP, int64_t ld, float *__restrict__ partial,
-    const uint8_t *__restrict__ active, const uint8_t *__restrict__ row_active)
+// ------------------------------------------------------------------ backward pass of the neighbour sum, by source
+// One wavefront per (source row work, chunk of bases) on the source-major view, whose edges are grouped by relation.
+// With y = sum over the edges of one relation out of source j of (1/c_e) G[dst_e][:],
+//   dP[j][b][:] += a[rel][b] y       and       da[rel][b] += < P[j][b][:], y >,
+// so the gathered rows are read once for both, P[j] once per source (not once per edge out of it), and a relation's edges
+// cost one product per basis.  The dot products of a group go to the scratch row of the run that its first edge lies in
+// (atomically: another source's group may use the same row; runs are sorted by relation and k_coeff_reduce adds up a
+// relation's rows), after a chunk of 64 edges, so that no atomic stands between the gathered loads.
+// A row is covered by LPR lanes of 4 columns, the 64 / LPR lane groups take NB bases each (16 per wavefront at most).
+// DP = false: the dot products only (dP comes from the matrix-core kernel below).
+// Bound by the vector instructions of the groups (most sources have one edge of a relation), the rows coming from the
+// caches.  544 k edges, 10 bases, d = 200, fp32: 361 us, where one kernel per gradient took 728 + 425; 2 M edges, 16 bases,
+// d = 128, bf16 messages: 748 against 1125 + 867.
+template <int OFF> __device__ __forceinline__ float lane_xor(float x)
 {
-    constexpr int NG = 64 / LPR;
-    const int lane = threadIdx.x & 63;
-    const int64_t wid_all = (int64_t)blockIdx.x * WPB + (threadIdx.x >> 6);
-    const int64_t wid = wid_all / n_chunks;
-    const int bc = (int)(wid_all - wid * n_chunks);
-    const RowWork rw = row_work(wid, sm_ptr, N, n_units, hv_row, hv_unit_ptr, unit_hv);
-    if (rw.row < 0) return;
-    if (row_active && !row_active[rw.row]) return;       // the row is not needed: left unwritten
-    const int kl = lane % LPR, g = lane / LPR;
-    const int GBT = gbt_count, GET = NG / GBT;
-    const int gbt = g % GBT, get = g / GBT;
-    const bool kact = kl * 4 < d;
-    const int b0 = (bc * GBT + gbt) * NB;
-
-    float acc[NB][4];
+    if constexpr (OFF == 1) return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0xb1, 0xf, 0xf, true));
+    else if constexpr (OFF == 2) return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x4e, 0xf, 0xf, true));
+    else return __shfl_xor(x, OFF, 64);
+}
+// sums of K per-lane values (a power of two, at most LPR) over LPR consecutive lanes: lane l gets sum l % K
+template <int K, int LPR, int OFF = 1> __device__ __forceinline__ float sums_over_lanes(const float *v, int lane)
+{
+    if constexpr (K > 1) {
+        float h[K / 2];
 #pragma unroll
-    for (int n = 0; n < NB; ++n)
+        for (int i = 0; i < K / 2; ++i) {
+            const bool odd = (lane & OFF) != 0;
+            h[i] = (odd ? v[2 * i + 1] : v[2 * i]) + lane_xor<OFF>(odd ? v[2 * i] : v[2 * i + 1]);
+        }
+        return sums_over_lanes<K / 2, LPR, OFF * 2>(h, lane);
+    } else if constexpr (OFF < LPR) {
+        const float s = v[0] + lane_xor<OFF>(v[0]);
+        return sums_over_lanes<1, LPR, OFF * 2>(&s, lane);
+    } else {
+        return v[0];
+    }
+}
+
+template <bool BF16, int LPR, int NB, bool DP>
+__global__ __launch_bounds__(64 * WPB) void k_source_backward(
+    const int32_t *__restrict__ sm_ptr, const int32_t *__restrict__ sm_dst, const int32_t *__restrict__ sm_rel,
+    const float *__restrict__ sm_invc, const int32_t *__restrict__ sm_seg, int64_t N,
+    int32_t n_units, const int32_t *__restrict__ hv_row, const int32_t *__restrict__ hv_unit_ptr,
+    const int32_t *__restrict__ unit_hv, const float *__restrict__ G, const float *__restrict__ a,
+    const void *__restrict__ P, int32_t B, int32_t d, int32_t n_chunks, void *__restrict__ dP, int64_t ld,
+    float *__restrict__ partial, float *__restrict__ seg_out, const uint8_t *__restrict__ active)
+{
+    constexpr int NG = 64 / LPR, NBT = NG * NB, U = 4;
+    constexpr int KA = NB == 12 ? 8 : NB, KB = NB == 12 ? 4 : 0;      // dot products reduced together
+    __shared__ float dots[WPB][64][NBT];
+    __shared__ int32_t dot_seg[WPB][64];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int64_t wid_all = (int64_t)blockIdx.x * WPB + wv;
+    const int64_t wid = wid_all / n_chunks;
+    const int b0 = (int)(wid_all - wid * n_chunks) * NBT;
+    const RowWork rw = row_work(wid, sm_ptr, N, n_units, hv_row, hv_unit_ptr, unit_hv);
+    if (rw.row < 0) return;                              // whole wavefronts leave; the kernel has no block barrier
+    const int kl = lane % LPR, g = lane / LPR;
+    const bool kact = kl * 4 < d;
+    const int col = kact ? kl * 4 : 0;
+    const int nbs = B - b0 < NBT ? B - b0 : NBT;         // bases of this chunk
+
+    float pv[NB][4], acc[NB][4];
+#pragma unroll
+    for (int n = 0; n < NB; ++n) {
+        const int b = b0 + g * NB + n;
+        const int64_t o = (rw.row * B + (b < B ? b : B - 1)) * d + col;
+        float4 x;
+        if (BF16) {
+            const uint2 r = *reinterpret_cast<const uint2 *>(reinterpret_cast<const uint16_t *>(P) + o);
+            x = make_float4(__uint_as_float(r.x << 16), __uint_as_float(r.x & 0xffff0000u),
+                            __uint_as_float(r.y << 16), __uint_as_float(r.y & 0xffff0000u));
+        } else {
+            x = *reinterpret_cast<const float4 *>(reinterpret_cast<const float *>(P) + o);
+        }
+        pv[n][0] = kact ? x.x : 0.f; pv[n][1] = kact ? x.y : 0.f; pv[n][2] = kact ? x.z : 0.f; pv[n][3] = kact ? x.w : 0.f;
 #pragma unroll
         for (int v = 0; v < 4; ++v) acc[n][v] = 0.f;
+    }
 
     for (int32_t e0 = rw.beg; e0 < rw.end; e0 += 64) {
         const int cnt = min(64, rw.end - e0);
-        int32_t my_dst = 0, my_rel = 0;
+        int32_t my_dst = 0, my_rel = 0, my_seg = 0;
         float my_w = 0.f;
         if (lane < cnt) {
-            my_dst = sm_dst[e0 + lane]; my_rel = sm_rel[e0 + lane]; my_w = sm_invc ? sm_invc[e0 + lane] : 1.f;
+            my_dst = sm_dst[e0 + lane]; my_rel = sm_rel[e0 + lane]; my_w = sm_invc[e0 + lane]; my_seg = sm_seg[e0 + lane];
             if (active && !active[my_dst]) my_dst = -1;   // destination outside the sub-graph: G row is zero
         }
-        const int rounds = (cnt + GET - 1) / GET;       // uniform trip count
-        for (int r0 = 0; r0 < rounds; r0 += UE) {
-            float4 gv[UE];
-            float w[UE];
-            const float *arow[UE];
+        int n_grp = 0;
+        int32_t cur_rel = -1, cur_seg = 0;               // uniform over the wavefront
+        float4 y = make_float4(0.f, 0.f, 0.f, 0.f);
+        auto flush = [&]() __attribute__((always_inline)) {
+            const float *ar = a + (int64_t)cur_rel * B;
+            float part[NB];
 #pragma unroll
-            for (int u = 0; u < UE; ++u) {
-                const int el = (r0 + u) * GET + get;
-                const bool ok = (r0 + u < rounds) && el < cnt;
-                const int els = ok ? el : 0;
-                int32_t dst, rel;
-                float ww;
-                if (NG == 1) {            // one lane group: the edge is wavefront-uniform (scalar path)
-                    dst = __builtin_amdgcn_readlane(my_dst, els);
-                    rel = __builtin_amdgcn_readlane(my_rel, els);
-                    ww = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(my_w), els));
-                } else {
-                    dst = __shfl(my_dst, els, 64);
-                    rel = __shfl(my_rel, els, 64);
-                    ww = __shfl(my_w, els, 64);
+            for (int n = 0; n < NB; ++n) {
+                if (DP) {
+                    float c = ar[min(b0 + n, B - 1)];    // scalar loads: every lane group's coefficients, then its own
+#pragma unroll
+                    for (int h = 1; h < NG; ++h) c = g == h ? ar[min(b0 + h * NB + n, B - 1)] : c;
+                    acc[n][0] = fmaf(c, y.x, acc[n][0]); acc[n][1] = fmaf(c, y.y, acc[n][1]);
+                    acc[n][2] = fmaf(c, y.z, acc[n][2]); acc[n][3] = fmaf(c, y.w, acc[n][3]);
                 }
-                // a slot without an edge (or an edge into a row outside the sub-graph) reads row 0 with weight 0,
-                // a lane past the row's width its start: the load itself is unconditional
-                const bool live = ok && dst >= 0;
-                w[u] = live ? ww : 0.f;
-                arow[u] = a + (int64_t)rel * B;
-                const int64_t goff = (int64_t)(live ? dst : 0) * d + (kact ? kl * 4 : 0);
-                if (GIN) {
-                    const uint2 x = *reinterpret_cast<const uint2 *>(reinterpret_cast<const uint16_t *>(Gv) + goff);
-                    gv[u] = make_float4(__uint_as_float(x.x << 16), __uint_as_float(x.x & 0xffff0000u),
-                                        __uint_as_float(x.y << 16), __uint_as_float(x.y & 0xffff0000u));
-                } else {
-                    gv[u] = *reinterpret_cast<const float4 *>(reinterpret_cast<const float *>(Gv) + goff);
-                }
+                part[n] = fmaf(pv[n][3], y.w, fmaf(pv[n][2], y.z, fmaf(pv[n][1], y.y, pv[n][0] * y.x)));
             }
+            const float s = sums_over_lanes<KA, LPR>(part, lane);
+            if (kl < KA) dots[wv][n_grp][g * NB + kl] = s;
+            if constexpr (KB > 0) {
+                const float s2 = sums_over_lanes<KB, LPR>(part + KA, lane);
+                if (kl < KB) dots[wv][n_grp][g * NB + KA + kl] = s2;
+            }
+            if (lane == 0) dot_seg[wv][n_grp] = cur_seg;
+            ++n_grp;
+        };
+        float4 nxt[U];
+        auto fetch = [&](int q0) __attribute__((always_inline)) {
 #pragma unroll
-            for (int u = 0; u < UE; ++u)
+            for (int u = 0; u < U; ++u) {
+                const int32_t dst = __builtin_amdgcn_readlane(my_dst, min(q0 + u, cnt - 1));
+                nxt[u] = *reinterpret_cast<const float4 *>(G + (int64_t)(dst < 0 ? 0 : dst) * d + col);
+            }
+        };
+        fetch(0);
+        for (int q0 = 0; q0 < cnt; q0 += U) {
+            float4 row[U];
 #pragma unroll
-                for (int n = 0; n < NB; ++n) {
-                    const float cv = arow[u][b0 + n < B ? b0 + n : B - 1];
-                    const float c = (b0 + n < B) ? cv * w[u] : 0.f;
-                    acc[n][0] = fmaf(c, gv[u].x, acc[n][0]); acc[n][1] = fmaf(c, gv[u].y, acc[n][1]);
-                    acc[n][2] = fmaf(c, gv[u].z, acc[n][2]); acc[n][3] = fmaf(c, gv[u].w, acc[n][3]);
+            for (int u = 0; u < U; ++u) row[u] = nxt[u];
+            fetch(q0 + U);                               // past the chunk: its last edge again
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int el = q0 + u;
+                if (el >= cnt || __builtin_amdgcn_readlane(my_dst, el) < 0) continue;
+                const int32_t rel = __builtin_amdgcn_readlane(my_rel, el);
+                const float w = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(my_w), el));
+                if (rel != cur_rel) {
+                    if (cur_rel >= 0) flush();
+                    cur_rel = rel;
+                    cur_seg = __builtin_amdgcn_readlane(my_seg, el);
+                    y = make_float4(0.f, 0.f, 0.f, 0.f);
                 }
+                y.x = fmaf(w, row[u].x, y.x); y.y = fmaf(w, row[u].y, y.y);
+                y.z = fmaf(w, row[u].z, y.z); y.w = fmaf(w, row[u].w, y.w);
+            }
         }
+        if (cur_rel >= 0) flush();
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        for (int i = lane; i < n_grp * nbs; i += 64) {
+            const int q = i / nbs, n = i - q * nbs;
+            unsafeAtomicAdd(seg_out + (int64_t)dot_seg[wv][q] * B + b0 + n, dots[wv][q][n]);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     }
-    // fold the edge groups together (fixed order)
-    for (int off = LPR * GBT; off < 64; off <<= 1)
-#pragma unroll
-        for (int n = 0; n < NB; ++n)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) acc[n][v] += __shfl_xor(acc[n][v], off, 64);
-    if (!kact || get != 0) return;
+    if (!DP || !kact) return;
 #pragma unroll
     for (int n = 0; n < NB; ++n) {
-        if (b0 + n >= B) continue;
+        const int b = b0 + g * NB + n;
+        if (b >= B) continue;
         if (rw.unit >= 0) {
-            *reinterpret_cast<float4 *>(partial + ((int64_t)rw.unit * B + b0 + n) * d + kl * 4) =
+            *reinterpret_cast<float4 *>(partial + ((int64_t)rw.unit * B + b) * d + kl * 4) =
                 make_float4(acc[n][0], acc[n][1], acc[n][2], acc[n][3]);
         } else {
-            const int64_t o = (int64_t)rw.row * ld + (int64_t)(b0 + n) * d + kl * 4;
+            const int64_t o = (int64_t)rw.row * ld + (int64_t)b * d + kl * 4;
             if (BF16) {
                 uint2 x;
                 x.x = pack_bf16x2(acc[n][0], acc[n][1]); x.y = pack_bf16x2(acc[n][2], acc[n][3]);
@@ -395,129 +451,8 @@ __global__ __launch_bounds__(64 * WPB) void k_gather_t(
     }
 }
 
-// The same transposed gather for many bases (B >= 32) on the matrix cores: for one source,
-//   dP[j] (B x d) = W^T (B x deg) * Gg (deg x d),  W[e][b] = a[rel_e][b] invc_e,  Gg[e] = G[dst_e],
-// a small dense product whose inner dimension is the source's out-degree.  v_mfma_f32_32x32x2_f32
-// keeps fp32 inputs; one wavefront owns a (32 bases x 128 columns) block = 1 x 4 tiles and walks
-// the edges two at a time (lane half h supplies edge k+h: 32 coefficients and 32 columns of G).
-typedef float gt_floatx16 __attribute__((ext_vector_type(16)));
 
-template <bool BF16, bool GIN, int NBT>
-__global__ __launch_bounds__(64 * WPB) void k_gather_t_mfma(
-    const int32_t *__restrict__ sm_ptr, const int32_t *__restrict__ sm_dst,
-    const int32_t *__restrict__ sm_rel, const float *__restrict__ sm_invc, int64_t N,
-    int32_t n_units, const int32_t *__restrict__ hv_row, const int32_t *__restrict__ hv_unit_ptr,
-    const int32_t *__restrict__ unit_hv,
-    const void *__restrict__ Gv, const float *__restrict__ a, int32_t B, int32_t d, int32_t n_bchunks,
-    int32_t n_cchunks, void *__restrict__ dP, int64_t ld, float *__restrict__ partial,
-    const uint8_t *__restrict__ active, const uint8_t *__restrict__ row_active)
-{
-    constexpr int UK = 4;                                  // edge pairs in flight
-    __shared__ float stage[WPB][32][36];                   // one 32x32 tile per wavefront (bf16 epilogue)
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int64_t wid_all = (int64_t)blockIdx.x * WPB + wv;
-    const int n_chunks = n_bchunks * n_cchunks;
-    const int64_t wid = wid_all / n_chunks;
-    const int chunk = (int)(wid_all - wid * n_chunks);
-    const int bchunk = chunk / n_cchunks, cchunk = chunk - bchunk * n_cchunks;
-    const RowWork rw = row_work(wid, sm_ptr, N, n_units, hv_row, hv_unit_ptr, unit_hv);
-    if (rw.row < 0) return;
-    if (row_active && !row_active[rw.row]) return;
-    const int h = lane >> 5, l32 = lane & 31;
-    const int bbase = bchunk * 32 * NBT, cbase = cchunk * 128;
-
-    gt_floatx16 acc[NBT][4];
-#pragma unroll
-    for (int t = 0; t < NBT; ++t)
-#pragma unroll
-        for (int c = 0; c < 4; ++c)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[t][c][v] = 0.f;
-
-    for (int32_t e0 = rw.beg; e0 < rw.end; e0 += 64) {
-        const int cnt = min(64, rw.end - e0);
-        int32_t my_dst = 0, my_rel = 0;
-        float my_w = 0.f;
-        if (lane < cnt) {
-            my_dst = sm_dst[e0 + lane]; my_rel = sm_rel[e0 + lane]; my_w = sm_invc ? sm_invc[e0 + lane] : 1.f;
-            if (active && !active[my_dst]) my_dst = -1;   // destination outside the sub-graph: G row is zero
-        }
-        for (int k0 = 0; k0 < cnt; k0 += 2 * UK) {
-            float wa[UK][NBT], gb[UK][4];
-#pragma unroll
-            for (int u = 0; u < UK; ++u) {
-                const int el = k0 + 2 * u + h;
-                const bool ok = el < cnt;
-                const int els = ok ? el : 0;
-                const int32_t dst = __shfl(my_dst, els, 64);
-                const int32_t rel = __shfl(my_rel, els, 64);
-                const float wsh = __shfl(my_w, els, 64);       // every lane takes part: a shuffle under a
-                const bool live = ok && dst >= 0;              // condition would read zeros from idle lanes
-                const float ww = live ? wsh : 0.f;
-#pragma unroll
-                for (int t = 0; t < NBT; ++t) {
-                    const int b = bbase + t * 32 + l32;
-                    wa[u][t] = (live && b < B) ? a[(int64_t)rel * B + b] * ww : 0.f;
-                }
-#pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    const int col = cbase + c * 32 + l32;
-                    gb[u][c] = 0.f;
-                    if (live && col < d)
-                        gb[u][c] = GIN ? __uint_as_float((uint32_t)reinterpret_cast<const uint16_t *>(Gv)[(int64_t)dst * d + col] << 16)
-                                       : reinterpret_cast<const float *>(Gv)[(int64_t)dst * d + col];
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < UK; ++u)
-#pragma unroll
-                for (int t = 0; t < NBT; ++t)
-#pragma unroll
-                    for (int c = 0; c < 4; ++c)
-                        acc[t][c] = __builtin_amdgcn_mfma_f32_32x32x2f32(wa[u][t], gb[u][c], acc[t][c], 0, 0, 0);
-        }
-    }
-    // D register v of lane l: base 8*(v/4) + 4*(l/32) + v%4, column l%32 of its tile
-#pragma unroll
-    for (int t = 0; t < NBT; ++t)
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const int tb = bbase + t * 32, tc = cbase + c * 32;
-            if (tb >= B || tc >= d) continue;              // uniform
-            if (rw.unit >= 0 || !BF16) {
-#pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const int b = tb + 8 * (v >> 2) + 4 * h + (v & 3), col = tc + l32;
-                    if (b < B && col < d) {
-                        if (rw.unit >= 0) partial[((int64_t)rw.unit * B + b) * d + col] = acc[t][c][v];
-                        else reinterpret_cast<float *>(dP)[(int64_t)rw.row * ld + (int64_t)b * d + col] = acc[t][c][v];
-                    }
-                }
-            } else {
-                // through LDS so that each lane writes 16 consecutive bf16 of one base row
-                __builtin_amdgcn_wave_barrier();
-#pragma unroll
-                for (int v = 0; v < 16; ++v) stage[wv][8 * (v >> 2) + 4 * h + (v & 3)][l32] = acc[t][c][v];
-                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                const int br = lane >> 1, c16 = (lane & 1) * 16;
-                const float4 x0 = *reinterpret_cast<const float4 *>(&stage[wv][br][c16]);
-                const float4 x1 = *reinterpret_cast<const float4 *>(&stage[wv][br][c16 + 4]);
-                const float4 x2 = *reinterpret_cast<const float4 *>(&stage[wv][br][c16 + 8]);
-                const float4 x3 = *reinterpret_cast<const float4 *>(&stage[wv][br][c16 + 12]);
-                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-                if (tb + br < B) {
-                    uint16_t *q = reinterpret_cast<uint16_t *>(dP) + (int64_t)rw.row * ld + (int64_t)(tb + br) * d + tc + c16;
-                    *reinterpret_cast<uint4 *>(q) = make_uint4(pack_bf16x2(x0.x, x0.y), pack_bf16x2(x0.z, x0.w),
-                                                               pack_bf16x2(x1.x, x1.y), pack_bf16x2(x1.z, x1.w));
-                    *reinterpret_cast<uint4 *>(q + 8) = make_uint4(pack_bf16x2(x2.x, x2.y), pack_bf16x2(x2.z, x2.w),
-                                                                   pack_bf16x2(x3.x, x3.y), pack_bf16x2(x3.z, x3.w));
-                }
-            }
-        }
-}
-
-// The same per-source product for workloads that keep messages in bf16, on v_mfma_f32_32x32x16_bf16:
+// dP with bf16 messages and many bases, a small dense product per source, on v_mfma_f32_32x32x16_bf16:
 //   dP[j] (B x d, bf16) = W^T (B x deg) * Gg (deg x d),  W[e][b] = a[rel_e][b] invc_e (rounded to bf16),  Gg[e] = Gbf[dst_e].
 // One block of four wavefronts per (source or heavy unit, chunk of 64 bases, chunk of 256 columns).  The block
 // stages up to 32 edges at a time in LDS, as they lie in memory and with 16-byte loads: the gathered rows of G
@@ -526,6 +461,7 @@ __global__ __launch_bounds__(64 * WPB) void k_gather_t_mfma(
 // operand; wavefront w owns bases 32 (w / 2) .. and columns 128 (w % 2) ..: one coefficient operand feeds four
 // products.  Sixteen edges per matrix-core instruction instead of two, and the gathered rows are read once per
 // block instead of once per wavefront.
+typedef float gt_floatx16 __attribute__((ext_vector_type(16)));
 constexpr int GTB_EP = 32;                 // edges per pass
 constexpr int GTB_PG = 256 + 32;           // LDS pitches, elements: 64 bytes modulo 256 (the four rows that 16
 constexpr int GTB_PC = 64 + 96;            // lanes read at once fall in different quarters of the banks)
@@ -872,115 +808,6 @@ __global__ void k_run_mean_finish(int32_t n_hv, const int32_t *__restrict__ hv_r
 }
 
 // ------------------------------------------------------------------ coefficient gradient
-// One wavefront per (relation, destination) run s = (r, i) (or per unit of a long run):
-//   seg_out[s][b] = invc_s * sum_{j in run} < P[j][b][:], G[i][:] >
-// and da[r][b] is the sum of seg_out over the runs of relation r (k_coeff_reduce).
-// UB basis slots x UE edge rounds are in flight at a time.
-template <bool BF16, int LPR, int UB, int UE>
-__global__ __launch_bounds__(64 * WPB) void k_coeff_seg(
-    const int32_t *__restrict__ seg_ptr, const int32_t *__restrict__ seg_dst,
-    const float *__restrict__ inv_c, const int32_t *__restrict__ col_src, int64_t S,
-    int32_t n_units, const int32_t *__restrict__ hv_row, const int32_t *__restrict__ hv_unit_ptr,
-    const int32_t *__restrict__ unit_hv,
-    const void *__restrict__ P, const float *__restrict__ G, int32_t B, int32_t d, int32_t gb_count,
-    float *__restrict__ seg_out, float *__restrict__ partial, const uint8_t *__restrict__ active)
-{
-    constexpr int VEC = MsgRow<BF16>::VEC;
-    constexpr int NG = 64 / LPR;
-    const int lane = threadIdx.x & 63;
-    const int64_t wid = (int64_t)blockIdx.x * WPB + (threadIdx.x >> 6);
-    const RowWork rw = row_work(wid, seg_ptr, S, n_units, hv_row, hv_unit_ptr, unit_hv);
-    if (rw.row < 0) return;
-    if (active && !active[seg_dst[rw.row]]) {           // destination outside the sub-graph: G row is zero
-        if (rw.unit < 0)
-            for (int b = lane; b < B; b += 64) seg_out[rw.row * B + b] = 0.f;
-        return;
-    }
-    const int kl = lane % LPR, g = lane / LPR;
-    const int GB = gb_count, GE = NG / GB;
-    const int gb = g % GB, ge = g / GB;
-    const bool kact = kl * VEC < d;
-    const int nb = (B + GB - 1) / GB;
-
-    const int32_t i = seg_dst[rw.row];
-    const float scale = rw.unit >= 0 ? 1.f : inv_c[rw.row];
-    float gv[VEC];
-#pragma unroll
-    for (int v = 0; v < VEC; ++v) gv[v] = 0.f;
-    if (kact) {
-#pragma unroll
-        for (int v4 = 0; v4 < VEC; v4 += 4) {
-            float4 x = *reinterpret_cast<const float4 *>(G + (int64_t)i * d + kl * VEC + v4);
-            gv[v4] = x.x; gv[v4 + 1] = x.y; gv[v4 + 2] = x.z; gv[v4 + 3] = x.w;
-        }
-    }
-    const int len = rw.end - rw.beg;
-    const int erounds = (len + GE - 1) / GE;
-    float *dst_out = rw.unit >= 0 ? partial + (int64_t)rw.unit * B : seg_out + rw.row * B;
-    for (int bi0 = 0; bi0 < nb; bi0 += UB) {
-        float part[UB];
-#pragma unroll
-        for (int u = 0; u < UB; ++u) part[u] = 0.f;
-        for (int er0 = 0; er0 < erounds; er0 += UE) {
-            uint4 raw[UE][UB];
-#pragma unroll
-            for (int x = 0; x < UE; ++x) {
-                const int el = (er0 + x) * GE + ge;
-                const bool eok = el < len;
-                const int32_t src = eok ? col_src[rw.beg + el] : 0;
-#pragma unroll
-                for (int u = 0; u < UB; ++u) {
-                    const int b = (bi0 + u) * GB + gb;
-                    raw[x][u] = make_uint4(0u, 0u, 0u, 0u);
-                    if (eok && kact && (bi0 + u) < nb && b < B)
-                        raw[x][u] = MsgRow<BF16>::load_raw(P, ((int64_t)src * B + b) * d + kl * VEC);
-                }
-            }
-#pragma unroll
-            for (int x = 0; x < UE; ++x)
-#pragma unroll
-                for (int u = 0; u < UB; ++u) {
-                    float val[VEC];
-                    MsgRow<BF16>::unpack(raw[x][u], val);
-#pragma unroll
-                    for (int v = 0; v < VEC; ++v) part[u] = fmaf(val[v], gv[v], part[u]);
-                }
-        }
-        // sum over the LPR lanes of a row and over the GE edge groups; skip the offsets that
-        // would mix different bases (LPR .. LPR*GB/2)
-#pragma unroll
-        for (int u = 0; u < UB; ++u) {
-#pragma unroll
-            for (int off = 1; off < LPR; off <<= 1) part[u] += __shfl_xor(part[u], off, 64);
-            for (int off = LPR * GB; off < 64; off <<= 1) part[u] += __shfl_xor(part[u], off, 64);
-        }
-        if (kl == 0 && ge == 0) {
-#pragma unroll
-            for (int u = 0; u < UB; ++u) {
-                const int b = (bi0 + u) * GB + gb;
-                if ((bi0 + u) < nb && b < B) dst_out[b] = scale * part[u];
-            }
-        }
-    }
-}
-
-// Long runs: seg_out[s][b] = invc_s * sum of the run's unit partials.
-__global__ void k_coeff_finish(int32_t n_hv, const int32_t *__restrict__ hv_row,
-                               const int32_t *__restrict__ hv_unit_ptr, const float *__restrict__ partial,
-                               const float *__restrict__ inv_c, int32_t B, float *__restrict__ seg_out,
-                               const int32_t *__restrict__ seg_dst, const uint8_t *__restrict__ active)
-{
-    const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= (int64_t)n_hv * B) return;
-    const int32_t h = (int32_t)(idx / B);
-    const int b = (int)(idx - (int64_t)h * B);
-    const int64_t row = hv_row[h];
-    if (active && !active[seg_dst[row]]) { seg_out[row * B + b] = 0.f; return; }
-    float s = 0.f;
-    for (int32_t u = hv_unit_ptr[h]; u < hv_unit_ptr[h + 1]; ++u) s += partial[(int64_t)u * B + b];
-    seg_out[row * B + b] = inv_c[row] * s;
-}
-
 // da[r][b] += sum of seg_out[s][b] over one chunk of relation r's runs (the partition's chunk list: every chunk lies
 // in one relation).  A run's B values are covered by TPR threads of V floats each (V = 4 when B is a multiple
 // of 4); the block's 256 / TPR run slots walk the chunk with four rows in flight per thread.
@@ -1140,96 +967,95 @@ int launch_act_backward(const float *dHout, const float *Hout, int act, int64_t 
 
 // A CSR view whose rows each sum coefficient-weighted rows of another matrix:
 //   out[row][b][:] = sum_{q in row} a[rel[q]][b] * w[q] * X[idx[q]][:]       (w = 1 if null)
-struct TView {
-    const int32_t *ptr, *idx, *rel;
-    const float *w;
-    int64_t n_rows;
-    const kge_heavy_index *hx;
-    const char *name;
-};
-
-template <bool BF16, bool GIN, int LPR>
-static int launch_gather_t_nb(const TView &vw, const void *G, const float *a, int32_t B, int32_t d,
-                              void *dP, int64_t ld, float *partial, const uint8_t *active,
-                              const uint8_t *row_active, hipStream_t st)
+static int launch_gather_t_finish(const kge_partition *p, const float *partial, int32_t bd, void *dP, int64_t ld, bool bf16,
+                                  hipStream_t st)
 {
-    constexpr int NG = 64 / LPR;
-    const int64_t N = vw.n_rows;
-    const kge_heavy_index &hx = *vw.hx;
-    KGE_PROF(vw.name, st);
-    // NB bases per lane (a power of two, at most 16); lane groups first cover the bases of a row,
-    // the remaining groups split the edges
-#define GT_CALL(NBV, UEV)                                                                             \
-    {                                                                                                 \
-        int gbt = 1;                                                                                  \
-        while (gbt * 2 <= NG && gbt * NBV < B) gbt *= 2;                                              \
-        const int n_chunks = (B + gbt * NBV - 1) / (gbt * NBV);                                       \
-        const int64_t waves = (N + hx.n_units) * n_chunks;                                            \
-        KGE_REQUIRE(cdiv(waves, WPB) < 0x7fffffffLL, KGE_ERANGE, "grid too large");                   \
-        k_gather_t<BF16, GIN, LPR, NBV, UEV><<<(unsigned)cdiv(waves, WPB), 64 * WPB, 0, st>>>(              \
-            vw.ptr, vw.idx, vw.rel, vw.w, N, hx.n_units, hx.hv_row, hx.hv_unit_ptr,                   \
-            hx.unit_hv, G, a, B, d, n_chunks, gbt, dP, ld, partial, active, row_active);              \
-    }
-    if (B >= 16) GT_CALL(16, 2)
-    else if (B >= 8) GT_CALL(8, 4)
-    else if (B >= 4) GT_CALL(4, 4)
-    else if (B >= 2) GT_CALL(2, 8)
-    else GT_CALL(1, 8)
-#undef GT_CALL
+    const kge_heavy_index &hx = p->hv_sm;
+    if (hx.n_hv == 0) return KGE_OK;
+    KGE_PROF("gather_t_fin", st);
+    const int64_t n = (int64_t)hx.n_hv * (bd / 4);
+    if (bf16) k_gather_t_finish<true><<<(unsigned)cdiv(n, 256), 256, 0, st>>>(hx.n_hv, hx.hv_row, hx.hv_unit_ptr, partial, bd, dP, ld, nullptr);
+    else k_gather_t_finish<false><<<(unsigned)cdiv(n, 256), 256, 0, st>>>(hx.n_hv, hx.hv_row, hx.hv_unit_ptr, partial, bd, dP, ld, nullptr);
     KGE_LAUNCH_CHECK();
     return KGE_OK;
 }
 
-static int launch_tview(const TView &vw, const void *G, int g_bf16, const float *a, int32_t B, int32_t d,
-                        void *dP, int64_t ld, int msg_bf16, float *partial, const uint8_t *active,
-                        const uint8_t *row_active, hipStream_t st)
+template <bool BF16, int LPR, int NB, bool DP>
+static int launch_source_backward_nb(const kge_partition *p, const float *G, const float *a, const void *P, int32_t B, int32_t d,
+                                     void *dP, int64_t ld, float *partial, float *seg_scratch, const uint8_t *active, hipStream_t st)
 {
-    KGE_REQUIRE(!g_bf16 || msg_bf16, KGE_EINVAL, "bf16 input rows are only used with bf16 output");
-    if (vw.n_rows == 0) return KGE_OK;
-    const int lpr = pow2_at_least((d + 3) / 4);
-    KGE_REQUIRE(lpr <= 64, KGE_EINVAL, "feature width %d too large for the transposed aggregation kernel", d);
-    int rc = KGE_OK;
-    if (B >= 32 && d % 32 == 0) {
-        // many bases: the per-source product runs on the matrix cores
-        const kge_heavy_index &hxm = *vw.hx;
-        const int n_bchunks = (B + 31) / 32, n_cchunks = (d + 127) / 128;
-        const int64_t waves = (vw.n_rows + hxm.n_units) * n_bchunks * n_cchunks;
-        KGE_REQUIRE(cdiv(waves, WPB) < 0x7fffffffLL, KGE_ERANGE, "grid too large");
-        KGE_PROF(vw.name, st);
-#define GTM_ARGS vw.ptr, vw.idx, vw.rel, vw.w, vw.n_rows, hxm.n_units, hxm.hv_row, hxm.hv_unit_ptr, \
-                 hxm.unit_hv, G, a, B, d, n_bchunks, n_cchunks, dP, ld, partial, active, row_active
-        if (g_bf16) k_gather_t_mfma<true, true, 1><<<(unsigned)cdiv(waves, WPB), 64 * WPB, 0, st>>>(GTM_ARGS);
-        else if (msg_bf16) k_gather_t_mfma<true, false, 1><<<(unsigned)cdiv(waves, WPB), 64 * WPB, 0, st>>>(GTM_ARGS);
-        else k_gather_t_mfma<false, false, 1><<<(unsigned)cdiv(waves, WPB), 64 * WPB, 0, st>>>(GTM_ARGS);
-#undef GTM_ARGS
-        KGE_LAUNCH_CHECK();
-    } else if (g_bf16) { DISPATCH_LPR(lpr, (rc = launch_gather_t_nb<true, true, L>(vw, G, a, B, d, dP, ld, partial, active, row_active, st))); }
-    else if (msg_bf16) { DISPATCH_LPR(lpr, (rc = launch_gather_t_nb<true, false, L>(vw, G, a, B, d, dP, ld, partial, active, row_active, st))); }
-    else { DISPATCH_LPR(lpr, (rc = launch_gather_t_nb<false, false, L>(vw, G, a, B, d, dP, ld, partial, active, row_active, st))); }
-    if (rc != KGE_OK) return rc;
-    const kge_heavy_index &hx = *vw.hx;
-    if (hx.n_hv > 0) {
-        KGE_PROF("gather_t_fin", st);
-        const int bd = B * d;
-        const int64_t n = (int64_t)hx.n_hv * (bd / 4);
-        if (msg_bf16) k_gather_t_finish<true><<<(unsigned)cdiv(n, 256), 256, 0, st>>>(hx.n_hv, hx.hv_row, hx.hv_unit_ptr, partial, bd, dP, ld, row_active);
-        else k_gather_t_finish<false><<<(unsigned)cdiv(n, 256), 256, 0, st>>>(hx.n_hv, hx.hv_row, hx.hv_unit_ptr, partial, bd, dP, ld, row_active);
-        KGE_LAUNCH_CHECK();
-    }
+    const kge_heavy_index &hx = p->hv_sm;
+    const int n_chunks = (int)cdiv(B, 64 / LPR * NB);
+    const int64_t blocks = cdiv((p->n_vert + hx.n_units) * n_chunks, WPB);
+    KGE_REQUIRE(blocks < 0x7fffffffLL, KGE_ERANGE, "grid too large");
+    KGE_PROF(DP ? "gather_t" : "coeff_seg", st);
+    k_source_backward<BF16, LPR, NB, DP><<<(unsigned)blocks, 64 * WPB, 0, st>>>(
+        p->sm_ptr, p->sm_dst, p->sm_rel, p->sm_invc, p->sm_seg, p->n_vert, hx.n_units, hx.hv_row, hx.hv_unit_ptr, hx.unit_hv, G, a,
+        P, B, d, n_chunks, dP, ld, partial, seg_scratch, active);
+    KGE_LAUNCH_CHECK();
     return KGE_OK;
 }
 
-int launch_gather_transpose(const kge_partition *p, const float *G, const float *a, int32_t B, int32_t d,
-                            void *dP, int64_t ld, int msg_bf16, float *partial, const uint8_t *active,
-                            hipStream_t st)
+// the fewest bases per lane that cover B in one chunk, 16 per wavefront at most; the dot products alone: always those 16
+template <bool BF16, bool DP>
+static int launch_source_backward(const kge_partition *p, const float *G, const float *a, const void *P, int32_t B, int32_t d,
+                                  void *dP, int64_t ld, float *partial, float *seg_scratch, const uint8_t *active, hipStream_t st)
 {
-    const TView vw{p->sm_ptr, p->sm_dst, p->sm_rel, p->sm_invc, p->n_vert, &p->hv_sm, "gather_t"};
-    return launch_tview(vw, G, 0, a, B, d, dP, ld, msg_bf16, partial, active, nullptr, st);
+#define SB_CALL(LPRV, NBV) return launch_source_backward_nb<BF16, LPRV, NBV, DP>(p, G, a, P, B, d, dP, ld, partial, seg_scratch, active, st)
+    if (d > 128) {
+        if constexpr (DP) {
+            if (B <= 2) SB_CALL(64, 2);
+            if (B <= 4) SB_CALL(64, 4);
+            if (B <= 8) SB_CALL(64, 8);
+            if (B <= 12) SB_CALL(64, 12);
+        }
+        SB_CALL(64, 16);
+    } else if (d > 64) {
+        if constexpr (DP) {
+            if (B <= 2) SB_CALL(32, 1);
+            if (B <= 4) SB_CALL(32, 2);
+            if (B <= 8) SB_CALL(32, 4);
+        }
+        SB_CALL(32, 8);
+    } else if (d > 32) {
+        if constexpr (DP) {
+            if (B <= 4) SB_CALL(16, 1);
+            if (B <= 8) SB_CALL(16, 2);
+        }
+        SB_CALL(16, 4);
+    }
+    if constexpr (DP) if (B <= 8) SB_CALL(8, 1);
+    SB_CALL(8, 2);
+#undef SB_CALL
 }
 
-// The bf16 form: Gbf = the bf16 copy of G, rows `ldg` elements apart.  Takes the matrix-core kernel above when the
-// layer has at least 32 bases and a width that is a multiple of 32; other shapes convert nothing and go the
-// general way from the fp32 G.
+int launch_project_first_backward(const kge_partition *p, const void *P, int msg_bf16, const float *G, const float *a,
+                                  int32_t B, int32_t d, float *seg_scratch, float *partial, float *da, void *dP, int64_t ld,
+                                  const uint8_t *active, hipStream_t st)
+{
+    const int64_t S = p->n_seg;
+    int rc = launch_fill_zero(da, sizeof(float) * (size_t)2 * p->n_relations * B, st);
+    if (rc != KGE_OK) return rc;
+    KGE_REQUIRE(B <= 256 && d <= 256, KGE_EINVAL, "more than 256 bases or a wider row than 256 are not supported");
+    if (p->n_vert == 0) return KGE_OK;
+    rc = launch_fill_zero(seg_scratch, sizeof(float) * (size_t)S * B, st);
+    if (rc != KGE_OK) return rc;
+    if (!dP) rc = launch_source_backward<true, false>(p, G, a, P, B, d, dP, ld, partial, seg_scratch, active, st);
+    else if (msg_bf16) rc = launch_source_backward<true, true>(p, G, a, P, B, d, dP, ld, partial, seg_scratch, active, st);
+    else rc = launch_source_backward<false, true>(p, G, a, P, B, d, dP, ld, partial, seg_scratch, active, st);
+    if (rc == KGE_OK && dP) rc = launch_gather_t_finish(p, partial, B * d, dP, ld, msg_bf16 != 0, st);
+    if (rc != KGE_OK || p->n_relc == 0) return rc;
+    KGE_PROF("coeff_reduce", st);
+    if (B % 4 == 0) k_coeff_reduce<4><<<(unsigned)p->n_relc, 256, 0, st>>>(p->relc_rel, p->relc_beg, p->relc_end, seg_scratch, B,
+                                                                    pow2_at_least(B / 4), da);
+    else k_coeff_reduce<1><<<(unsigned)p->n_relc, 256, 0, st>>>(p->relc_rel, p->relc_beg, p->relc_end, seg_scratch, B,
+                                                                pow2_at_least(B), da);
+    KGE_LAUNCH_CHECK();
+    return KGE_OK;
+}
+
+// The bf16 form of dP: Gbf = the bf16 copy of G, rows `ldg` elements apart.  For layers with at least 32 bases and a width
+// that is a multiple of 32; other shapes go the general way from the fp32 G.
 bool gather_transpose_bf16_supported(int32_t B, int32_t d) { return B >= 32 && d % 32 == 0 && d >= 32; }
 
 int launch_gather_transpose_bf16(const kge_partition *p, const void *Gbf, int64_t ldg, const float *a, int32_t B,
@@ -1251,72 +1077,7 @@ int launch_gather_transpose_bf16(const kge_partition *p, const void *Gbf, int64_
                                                          n_cchunks, reinterpret_cast<uint16_t *>(dP), ld, partial, active);
         KGE_LAUNCH_CHECK();
     }
-    if (hx.n_hv > 0) {
-        KGE_PROF("gather_t_fin", st);
-        const int bd = B * d;
-        const int64_t n = (int64_t)hx.n_hv * (bd / 4);
-        k_gather_t_finish<true><<<(unsigned)cdiv(n, 256), 256, 0, st>>>(hx.n_hv, hx.hv_row, hx.hv_unit_ptr, partial, bd, dP, ld, nullptr);
-        KGE_LAUNCH_CHECK();
-    }
-    return KGE_OK;
-}
-
-template <bool BF16, int LPR>
-static int launch_coeff_seg(const kge_partition *p, const void *P, const float *G, int32_t B, int32_t d,
-                            int gbc, float *seg_scratch, float *partial, const uint8_t *active, hipStream_t st)
-{
-    const int64_t S = p->n_seg;
-    const kge_heavy_index &hx = p->hv_seg;
-    const unsigned grid = (unsigned)cdiv(S + hx.n_units, WPB);
-    const int nb = (B + gbc - 1) / gbc;
-#define CS_ARGS p->seg_ptr, p->seg_dst, p->inv_c, p->col_src, S, hx.n_units, hx.hv_row, hx.hv_unit_ptr, hx.unit_hv, \
-                P, G, B, d, gbc, seg_scratch, partial, active
-    // base slots x edges in flight per wavefront: with many bases, eight slots of one edge at a time (most runs
-    // have one edge; 212 against 225 ms per launch at 25 M runs, 64 bases, d = 256; 4 x 1: 221, 8 x 2: 220, 16 x 1: 215)
-    if (nb >= 8) k_coeff_seg<BF16, LPR, 8, 1><<<grid, 64 * WPB, 0, st>>>(CS_ARGS);
-    else if (nb >= 4) k_coeff_seg<BF16, LPR, 4, 2><<<grid, 64 * WPB, 0, st>>>(CS_ARGS);
-    else if (nb >= 2) k_coeff_seg<BF16, LPR, 2, 4><<<grid, 64 * WPB, 0, st>>>(CS_ARGS);
-    else k_coeff_seg<BF16, LPR, 1, 8><<<grid, 64 * WPB, 0, st>>>(CS_ARGS);
-#undef CS_ARGS
-    KGE_LAUNCH_CHECK();
-    return KGE_OK;
-}
-
-int launch_coeff_grad(const kge_partition *p, const void *P, int msg_bf16, const float *G, int32_t B,
-                      int32_t d, float *seg_scratch, float *partial, float *da, const uint8_t *active,
-                      hipStream_t st)
-{
-    const int64_t S = p->n_seg;
-    const int32_t R2 = 2 * p->n_relations;
-    int rc = launch_fill_zero(da, sizeof(float) * (size_t)R2 * B, st);
-    if (rc != KGE_OK) return rc;
-    if (S == 0) return KGE_OK;
-    KGE_REQUIRE(B <= 256, KGE_EINVAL, "more than 256 bases are not supported");
-    const int vec = msg_bf16 ? 8 : 4;
-    const int lpr = pow2_at_least((d + vec - 1) / vec);
-    KGE_REQUIRE(lpr <= 64, KGE_EINVAL, "feature width %d too large for the coefficient-gradient kernel", d);
-    const int gbc = largest_pow2_dividing(B, 64 / lpr);
-    {
-        KGE_PROF("coeff_seg", st);
-        if (msg_bf16) { DISPATCH_LPR(lpr, (rc = launch_coeff_seg<true, L>(p, P, G, B, d, gbc, seg_scratch, partial, active, st))); }
-        else { DISPATCH_LPR(lpr, (rc = launch_coeff_seg<false, L>(p, P, G, B, d, gbc, seg_scratch, partial, active, st))); }
-    }
-    if (rc != KGE_OK) return rc;
-    const kge_heavy_index &hx = p->hv_seg;
-    if (hx.n_hv > 0) {
-        KGE_PROF("coeff_fin", st);
-        const int64_t n = (int64_t)hx.n_hv * B;
-        k_coeff_finish<<<(unsigned)cdiv(n, 256), 256, 0, st>>>(hx.n_hv, hx.hv_row, hx.hv_unit_ptr, partial, p->inv_c, B, seg_scratch, p->seg_dst, active);
-        KGE_LAUNCH_CHECK();
-    }
-    if (p->n_relc == 0) return KGE_OK;
-    KGE_PROF("coeff_reduce", st);
-    if (B % 4 == 0) k_coeff_reduce<4><<<(unsigned)p->n_relc, 256, 0, st>>>(p->relc_rel, p->relc_beg, p->relc_end, seg_scratch, B,
-                                                                    pow2_at_least(B / 4), da);
-    else k_coeff_reduce<1><<<(unsigned)p->n_relc, 256, 0, st>>>(p->relc_rel, p->relc_beg, p->relc_end, seg_scratch, B,
-                                                                pow2_at_least(B), da);
-    KGE_LAUNCH_CHECK();
-    return KGE_OK;
+    return launch_gather_t_finish(p, partial, B * d, dP, ld, true, st);
 }
 
 // Z[s][:] = invc_s * sum_{j in run s} H[j][:]; H and Z fp32, or both bf16; `partial`: [hv_seg.n_units][d] floats

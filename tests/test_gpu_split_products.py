@@ -14,7 +14,7 @@ pytestmark = pytest.mark.gpu
 TOL = 4e-6
 
 
-def layer(n, R, m, di, do, B, order, H0, dH, V, a, W0):
+def layer(n, R, m, di, do, B, order, H0, dH, V, a, W0, msg=0):
     import torch
     from paper_2201_02791_amd import binding as kb
     rng = np.random.default_rng(n + di)
@@ -24,11 +24,11 @@ def layer(n, R, m, di, do, B, order, H0, dH, V, a, W0):
     part, opart = kb.build_partition(head, rel, tail, n, R), orc.build_partition(head, rel, tail, n, R)
     t = lambda x: torch.from_numpy(np.ascontiguousarray(x)).cuda()  # noqa: E731
     lay = [dict(V=t(V), a=t(a), W0=t(W0), act=kb.ACT_IDENTITY, order=order)]
-    ws = torch.zeros(kb.workspace_bytes(part, lay), dtype=torch.uint8, device="cuda")
+    ws = torch.zeros(kb.workspace_bytes(part, lay, msg), dtype=torch.uint8, device="cuda")
     H, G, out, dH0 = t(H0), t(dH), torch.empty(n, do, device="cuda"), torch.empty(n, di, device="cuda")
     grads = [{k: torch.empty_like(lay[0][k[1:]]) for k in ("dV", "da", "dW0")}]
-    kb.rgcn_forward(part, lay, H, ws, out)
-    kb.rgcn_backward(part, lay, H, ws, G, grads, dH0)
+    kb.rgcn_forward(part, lay, H, ws, out, msg)
+    kb.rgcn_backward(part, lay, H, ws, G, grads, dH0, msg)
     torch.cuda.synchronize()
     got = dict(out=out.cpu().numpy(), dH0=dH0.cpu().numpy(), **{k: v.cpu().numpy() for k, v in grads[0].items()})
     with np.errstate(all="ignore"):
