@@ -296,7 +296,7 @@ int kge_sample_negatives(const kge_partition *p, const int32_t *pos_core_idx, in
  *   dM and the loss are accumulated with fp32 atomics in both forms.
  *
  * kge_score_index_create allocates the scratch for batches of at most max_pos positives with at most max_neg
- * negatives each and embedding width d (about (n_neg + 2) x 36 bytes + 8 d bytes per positive, plus 4 N bytes);
+ * negatives each and embedding width d (about (n_neg + 2) x 20 bytes + 8 d + 16 bytes per positive, plus 4 N bytes);
  * once per trainer, synchronous; free with kge_score_index_destroy.
  */
 int kge_score_index_create(const kge_partition *p, int64_t max_pos, int32_t max_neg, int32_t d,

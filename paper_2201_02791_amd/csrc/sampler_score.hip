@@ -17,10 +17,8 @@ struct kge_score_index {
     uint32_t *keys[2], *vals[2];   // [max_occ] entity of each occurrence / occurrence id; ping-pong buffers of the sort
     uint32_t *sort_ws;             // radix_scratch_words(max_occ)
     int32_t *ent_ptr;              // [N + 1] range of each entity in the sorted occurrence list
-    uint32_t *slot_of;             // [max_occ] position of each occurrence in the list sorted by entity
-    int4 *recs;                    // [max_occ] in sorted order, what the occurrence adds: x = the positive's entity on the
-                                   // other side (a negative: its row of H, times M_r, is what the delta multiplies) or
-                                   // -1 - (row of rows[]) for a positive's own end; y = relation; z = bits of delta
+    float *deltas;                 // [max_occ] delta of each negative, sign set where the head was replaced
+    int4 *triples;                 // [max_pos] head, relation and tail of each positive
     uint32_t *pkeys[2], *pvals[2]; // [max_pos] the batch's positives sorted by relation (ping-pong buffers)
     float *rows;                   // [2 max_pos][d] per positive q: the summed rows for its head (2q) and its tail (2q+1)
     float *dm_part;                // [KGE_SCORE_MAX_BLOCKS][d] one partial relation-gradient row per scoring block,
@@ -280,13 +278,6 @@ __global__ void k_score_rel_keys(const int32_t *__restrict__ core_r, const int32
     vals[q] = (uint32_t)q;
 }
 
-// slot_of[sorted[i]] = i
-__global__ void k_invert_permutation(const uint32_t *__restrict__ sorted, int64_t n, uint32_t *__restrict__ slot_of)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) slot_of[sorted[i]] = (uint32_t)i;
-}
-
 __device__ __forceinline__ float dot4(const float4 a, const float4 b, const float4 c)
 {
     return fmaf(a.x * b.x, c.x, fmaf(a.y * b.y, c.y, fmaf(a.z * b.z, c.z, a.w * b.w * c.w)));
@@ -335,9 +326,13 @@ constexpr int DS_WAVES = 4;      // wavefronts per block of the scoring kernel b
 // waits on a second memory access; the negatives' rows arrive eight at a time in two register buffers - the
 // next eight are in flight while the current eight are scored.  Their eight scores are summed across the lanes
 // together (reduce8), and the loss terms and deltas of the eight are computed once, each in its own lanes.
+// No condition stands around a row's load and no store or dependent load among the groups: a wavefront's memory
+// operations retire in order, and each would wait for the rows on their way (65,536 positives x 64 negatives, d = 256:
+// 1.06 ms with them, 0.83 now).
 // Nothing is added into dH here.  The wavefront walks the positives in the order `perm` gives (sorted by relation:
 // the relation gradient then stays in registers over runs of positives and few atomics meet on one row), and
-// writes each triple's record where the entity-sorted list has it (slot_of).
+// writes each triple's record in occurrence order, 64 negatives at a time: whole lines, where a record at its place in the
+// entity-sorted list was a 16-byte piece of one (and the list had to be inverted first).
 template <int NV>
 __global__ __launch_bounds__(64 * DS_WAVES) void k_distmult_score(
     const float4 *__restrict__ H, const float4 *__restrict__ M, int32_t d4,
@@ -347,7 +342,7 @@ __global__ __launch_bounds__(64 * DS_WAVES) void k_distmult_score(
     const int32_t *__restrict__ neg_ent, const uint8_t *__restrict__ neg_side, int32_t n_neg,
     uint32_t n_vert, uint32_t n_core,
     float inv_T, float *__restrict__ scores, float *__restrict__ dM,
-    const uint32_t *__restrict__ slot_of, int4 *__restrict__ recs, float4 *__restrict__ rows,
+    float *__restrict__ deltas, int4 *__restrict__ triples, float4 *__restrict__ rows,
     float4 *__restrict__ dm_part, int32_t *__restrict__ dm_rel, float *__restrict__ loss_part)
 {
     __shared__ float loss_of_wave[DS_WAVES];
@@ -358,10 +353,10 @@ __global__ __launch_bounds__(64 * DS_WAVES) void k_distmult_score(
     const int64_t q_beg = wave_id * per_wave;
     const int64_t q_end = q_beg + per_wave < n_pos ? q_beg + per_wave : n_pos;
     const float4 zero4 = make_float4(0.f, 0.f, 0.f, 0.f);
-    const int my_z = ((lane >> 5) & 1) * 4 + ((lane >> 4) & 1) * 2 + ((lane >> 3) & 1);   // the row reduce8 leaves here
     bool ok[NV];
+    int col[NV];
 #pragma unroll
-    for (int u = 0; u < NV; ++u) ok[u] = lane + 64 * u < d4;
+    for (int u = 0; u < NV; ++u) { ok[u] = lane + 64 * u < d4; col[u] = ok[u] ? lane + 64 * u : 0; }
 
     float4 aM[NV];
 #pragma unroll
@@ -382,11 +377,20 @@ __global__ __launch_bounds__(64 * DS_WAVES) void k_distmult_score(
         }
     };
 
+    // what the wavefront's positives are (four dependent loads), 64 positives at a time, a lane each
+    int32_t my_q = 0, my_s = 0, my_r = 0, my_t = 0;
     for (int64_t i = q_beg; i < q_end; ++i) {
-        const int64_t q = (int64_t)perm[i];
-        uint32_t c = (uint32_t)pos[q];
-        if (c >= n_core) c = 0;           // counted by k_score_keys
-        const int32_t s = core_h[c], r = core_r[c], t = core_t[c];
+        const int at = (int)(i - q_beg) & 63;
+        if (at == 0) {
+            const int64_t m = i + lane < q_end ? i + lane : q_end - 1;
+            my_q = (int32_t)perm[m];
+            uint32_t c = (uint32_t)pos[my_q];
+            if (c >= n_core) c = 0;       // counted by k_score_keys
+            my_s = core_h[c]; my_r = core_r[c]; my_t = core_t[c];
+        }
+        const int64_t q = __builtin_amdgcn_readlane(my_q, at);
+        const int32_t s = __builtin_amdgcn_readlane(my_s, at), r = __builtin_amdgcn_readlane(my_r, at);
+        const int32_t t = __builtin_amdgcn_readlane(my_t, at);
         if (r != r_cur) {                 // uniform: flush the relation gradient of the finished run
             if (r_cur >= 0) flush_rel(r_cur);
             r_cur = r;
@@ -394,11 +398,13 @@ __global__ __launch_bounds__(64 * DS_WAVES) void k_distmult_score(
         float4 hs[NV], ht[NV], mr[NV], aS[NV], aT[NV];
 #pragma unroll
         for (int u = 0; u < NV; ++u) {
-            const int k = lane + 64 * u;
-            hs[u] = ok[u] ? H[(int64_t)s * d4 + k] : zero4;
-            ht[u] = ok[u] ? H[(int64_t)t * d4 + k] : zero4;
-            mr[u] = ok[u] ? M[(int64_t)r * d4 + k] : zero4;
+            hs[u] = H[(int64_t)s * d4 + col[u]];
+            ht[u] = H[(int64_t)t * d4 + col[u]];
+            mr[u] = M[(int64_t)r * d4 + col[u]];
         }
+#pragma unroll
+        for (int u = 0; u < NV; ++u)
+            if (!ok[u]) { hs[u] = zero4; ht[u] = zero4; mr[u] = zero4; }
         {   // the positive
             float g = 0.f;
 #pragma unroll
@@ -409,9 +415,8 @@ __global__ __launch_bounds__(64 * DS_WAVES) void k_distmult_score(
             if (lane == 0) {
                 lsum += sp;
                 if (scores) scores[q * (1 + n_neg)] = g;
-                recs[slot_of[q * per + n_neg]] = make_int4(-1 - (int32_t)(2 * q), r, 0, 0);
-                recs[slot_of[q * per + n_neg + 1]] = make_int4(-1 - (int32_t)(2 * q + 1), r, 0, 0);
             }
+            if (lane == 0) triples[q] = make_int4(s, r, t, 0);
             const float delta = -sg * inv_T;
 #pragma unroll
             for (int u = 0; u < NV; ++u) {
@@ -426,22 +431,22 @@ __global__ __launch_bounds__(64 * DS_WAVES) void k_distmult_score(
         // negatives: 64 at a time, a lane per corrupting entity; within those, groups of eight rows
         for (int32_t kb = 0; kb < n_neg; kb += 64) {
             const int32_t cnt = n_neg - kb < 64 ? n_neg - kb : 64;
-            int32_t my_ent = 0, my_side = 0;
-            if (lane < cnt) {
-                my_ent = neg_ent[q * n_neg + kb + lane];
-                if ((uint32_t)my_ent >= n_vert) my_ent = 0;
-                my_side = (int32_t)neg_side[q * n_neg + kb + lane];
-            }
+            const int64_t mine = kb + (lane < cnt ? lane : cnt - 1);
+            int32_t my_ent = neg_ent[q * n_neg + mine];
+            const int32_t my_side = (int32_t)neg_side[q * n_neg + mine];
+            if ((uint32_t)my_ent >= n_vert) my_ent = 0;
             const int32_t n_grp = (cnt + 7) >> 3;
-            // fetch the eight rows of group g (rows past the end: zeros)
+            float my_g = 0.f, my_d = 0.f;          // score and delta of this lane's negative
+            // fetch the eight rows of group g.  No condition stands around a load (each would wait for the one before):
+            // a row past the end is the first one again and its results are not used, a lane past the width reads
+            // column 0 and is left out of the sums
             auto fetch = [&](float4 (&hx)[8][NV], int32_t g) {
 #pragma unroll
                 for (int z = 0; z < 8; ++z) {
                     const int j = 8 * g + z;
-                    const int32_t e = __shfl(my_ent, j < cnt ? j : 0, 64);
+                    const int32_t e = __builtin_amdgcn_readlane(my_ent, j < cnt ? j : 0);
 #pragma unroll
-                    for (int u = 0; u < NV; ++u)
-                        hx[z][u] = (j < cnt && ok[u]) ? H[(int64_t)e * d4 + lane + 64 * u] : zero4;
+                    for (int u = 0; u < NV; ++u) hx[z][u] = H[(int64_t)e * d4 + col[u]];
                 }
             };
             // score the eight rows of group g and add what they contribute to the positive's own rows and to dM_r
@@ -451,30 +456,26 @@ __global__ __launch_bounds__(64 * DS_WAVES) void k_distmult_score(
                 float part[8];
 #pragma unroll
                 for (int z = 0; z < 8; ++z) {
-                    side[z] = __shfl(my_side, 8 * g + z < cnt ? 8 * g + z : 0, 64);
+                    side[z] = __builtin_amdgcn_readlane(my_side, 8 * g + z < cnt ? 8 * g + z : 0);
                     // the corrupted entity is scored against M_r * h_t (head replaced) or M_r * h_s
                     float gz = 0.f;
 #pragma unroll
-                    for (int u = 0; u < NV; ++u) gz += dot4(hx[z][u], mr[u], side[z] ? ht[u] : hs[u]);
+                    for (int u = 0; u < NV; ++u) {
+                        const float x = dot4(hx[z][u], mr[u], side[z] ? ht[u] : hs[u]);
+                        gz += ok[u] ? x : 0.f;
+                    }
                     part[z] = gz;
                 }
                 const float g_mine = reduce8(part, lane);          // score of row my_z, in its 8 lanes
-                float sp, sg;
-                softplus_sigmoid(g_mine, sp, sg);
-                const float d_mine = sg * inv_T;
-                if ((lane & 7) == 0 && k0 + my_z < n_neg) {         // one lane per row writes what the row produced
-                    lsum += sp;
-                    if (scores) scores[q * (1 + n_neg) + 1 + k0 + my_z] = g_mine;
-                    const int64_t o = q * per + k0 + my_z;
-                    int32_t oth = s;
-#pragma unroll
-                    for (int z = 0; z < 8; ++z) if (z == my_z && side[z]) oth = t;
-                    recs[slot_of[o]] = make_int4(oth, r, __float_as_int(d_mine), 0);
-                }
+                const float e_mine = expf(-fabsf(g_mine));
+                const float d_mine = (g_mine >= 0.f ? 1.f : e_mine) / (1.f + e_mine) * inv_T;      // sigmoid / T
 #pragma unroll
                 for (int z = 0; z < 8; ++z) {
                     if (k0 + z >= n_neg) break;
                     const float delta = lane_value(d_mine, lane8_of(z));
+                    const float gz = lane_value(g_mine, lane8_of(z));
+                    my_d = lane == 8 * g + z ? delta : my_d;
+                    my_g = lane == 8 * g + z ? gz : my_g;
 #pragma unroll
                     for (int u = 0; u < NV; ++u) {
                         const float4 other = side[z] ? ht[u] : hs[u];
@@ -500,6 +501,15 @@ __global__ __launch_bounds__(64 * DS_WAVES) void k_distmult_score(
                     if (g + 2 < n_grp) fetch(bufA, g + 2);
                     score(bufB, g + 1);
                 }
+            }
+            // what the 64 negatives produced leaves at once (a store among the groups would have to be waited for with
+            // the rows behind it)
+            float sp, sg;
+            softplus_sigmoid(my_g, sp, sg);
+            if (lane < cnt) {
+                lsum += sp;
+                if (scores) scores[q * (1 + n_neg) + 1 + kb + lane] = my_g;
+                deltas[q * per + kb + lane] = __int_as_float(__float_as_int(my_d) | (my_side ? (int32_t)0x80000000 : 0));
             }
         }
         // the two rows this positive adds to its own head and tail
@@ -596,65 +606,104 @@ __global__ __launch_bounds__(256) void k_score_finish(const float *__restrict__ 
 // dH[e] = sum over the occurrences of entity e, in ascending occurrence id, of
 //   delta (M_r * h_other)   for a negative that put e into a triple, or the stored row of a positive's own end.
 // The rows h_other are those of the batch's positives (a few hundred MB at most, re-read many times: they stay in
-// the last-level cache).  A wavefront owns DG_ENT consecutive entities and streams their occurrences - contiguous
-// in the entity-sorted list - four at a time (eight rows in flight) straight across the entity boundaries: when
-// the next occurrence belongs to a later entity the finished sum is stored and the accumulator cleared.  Every
-// row of dH is written exactly once (zeros for entities no triple names), in a fixed order of additions: the
-// result repeats bit for bit.
-constexpr int DG_ENT = 16;
+// the last-level cache).  A block owns `ents` consecutive entities (at most 64) and its four wavefronts an even share each
+// of their occurrences - contiguous in the entity-sorted list - which they stream four at a time (eight rows in flight)
+// straight across the entity boundaries: when the next occurrence belongs to a later entity the finished sum is stored
+// and the accumulator cleared.  An entity whose occurrences fall to several wavefronts is put together through LDS in
+// their order, by the wavefront it starts in.  Every row of dH is written exactly once (zeros for entities no triple
+// names), in a fixed order of additions: the result repeats bit for bit.
+// Bound by the gathered rows (4.3 M occurrences, d = 256: 0.88 ms, of which the deltas' random reads are 0.08; reading
+// records that the scoring kernel had placed in sorted order took 0.75, and that kernel 0.17 longer plus 0.06 for the
+// inverse of the list).  With whole entities per wavefront a hub of a power-law graph was one chain (30,000 positives x 10
+// negatives, 14,541 entities, d = 200: 182 us, 57 now).
 template <int NV>
 __global__ __launch_bounds__(256) void k_distmult_gather(
-    const float4 *__restrict__ H, const float4 *__restrict__ M, int32_t d4, int64_t N,
-    const int32_t *__restrict__ ent_ptr, const int4 *__restrict__ recs, const float4 *__restrict__ rows,
+    const float4 *__restrict__ H, const float4 *__restrict__ M, int32_t d4, int64_t N, int32_t ents,
+    const int32_t *__restrict__ ent_ptr, const uint32_t *__restrict__ occ, int32_t n_neg,
+    const float *__restrict__ deltas, const int4 *__restrict__ triples, const float4 *__restrict__ rows,
     float4 *__restrict__ dH)
 {
-    const int lane = threadIdx.x & 63;
-    const int64_t e0 = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * DG_ENT;
-    if (e0 >= N) return;
-    const int n_ent = N - e0 < DG_ENT ? (int)(N - e0) : DG_ENT;
+    __shared__ float4 part[4][2][64 * NV];         // a wavefront's sums of the entity it begins in and of the one it ends in
+    __shared__ int32_t kind[4];                    // bit 0: the first belongs to an earlier wavefront's entity; bit 1: the
+                                                   // last goes on in the next one; bit 2: both are one
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int64_t e0 = (int64_t)blockIdx.x * ents;
+    const int n_ent = N - e0 < ents ? (int)(N - e0) : ents;
     const float4 zero4 = make_float4(0.f, 0.f, 0.f, 0.f), one4 = make_float4(1.f, 1.f, 1.f, 1.f);
     bool ok[NV];
+    int col[NV];
     float4 acc[NV];
 #pragma unroll
-    for (int u = 0; u < NV; ++u) { ok[u] = lane + 64 * u < d4; acc[u] = zero4; }
-    const int32_t my_ptr = lane <= n_ent ? ent_ptr[e0 + lane] : 0x7fffffff;      // lane l: where entity e0 + l starts
-    const int32_t lo = __shfl(my_ptr, 0, 64), hi = __shfl(my_ptr, n_ent, 64);
-    int cur = 0;                                   // the entity being summed
-    int32_t boundary = __shfl(my_ptr, 1, 64);      // where the next one starts
+    for (int u = 0; u < NV; ++u) { ok[u] = lane + 64 * u < d4; col[u] = ok[u] ? lane + 64 * u : 0; acc[u] = zero4; }
+    const int32_t my_ptr = ent_ptr[e0 + (lane < n_ent ? lane : n_ent)];          // where entity e0 + lane starts
+    const int32_t end = ent_ptr[e0 + n_ent], begin = __builtin_amdgcn_readlane(my_ptr, 0);
+    const int32_t lo = begin + (int32_t)((int64_t)(end - begin) * w / 4), hi = begin + (int32_t)((int64_t)(end - begin) * (w + 1) / 4);
+    auto start_of = [&](int e) { return e < 64 ? __builtin_amdgcn_readlane(my_ptr, e) : end; };
+    // the entity being summed: for the first wavefront the block's first, for the others the one that holds `lo` (those
+    // that end at or before `lo` are the wavefront before's)
+    int32_t next_ptr = __shfl_down(my_ptr, 1, 64);       // every lane takes part
+    if (lane == 63) next_ptr = end;
+    int cur = w == 0 ? 0 : __popcll(__ballot(lane < n_ent && next_ptr <= lo));
+    int32_t boundary = start_of(cur + 1);          // where the next one starts
+    int flags = 0;
     auto close_entity = [&]() {
+        if (start_of(cur) < lo) {                  // it began in an earlier wavefront
+            flags |= 1;
 #pragma unroll
-        for (int u = 0; u < NV; ++u) {
-            if (ok[u]) dH[(e0 + cur) * d4 + lane + 64 * u] = acc[u];
-            acc[u] = zero4;
+            for (int u = 0; u < NV; ++u) part[w][0][lane + 64 * u] = acc[u];
+        } else {
+#pragma unroll
+            for (int u = 0; u < NV; ++u)
+                if (ok[u]) dH[(e0 + cur) * d4 + lane + 64 * u] = acc[u];
         }
+#pragma unroll
+        for (int u = 0; u < NV; ++u) acc[u] = zero4;
         ++cur;
-        boundary = __shfl(my_ptr, cur + 1, 64);
+        boundary = start_of(cur + 1);
     };
+    const uint32_t per = (uint32_t)n_neg + 2;
+    auto id_at = [&](int32_t base) { const int32_t i = base + lane < hi ? base + lane : hi - 1; return occ[i < 0 ? 0 : i]; };
+    uint32_t cur_id = 0, next_id = 0;
+    float cur_delta = 0.f;
+    int4 cur_tr = make_int4(0, 0, 0, 0);
+    if (lo < hi) {
+        cur_id = id_at(lo);
+        next_id = id_at(lo + 64);
+        cur_delta = deltas[cur_id];
+        cur_tr = triples[cur_id / per];
+    }
     for (int32_t base = lo; base < hi; base += 64) {
         const int32_t cnt = hi - base < 64 ? hi - base : 64;
-        int32_t other = 0, rel = 0;
-        float wgt = 0.f;
-        if (lane < cnt) {
-            const int4 rec = recs[base + lane];
-            other = rec.x; rel = rec.y;
-            wgt = other >= 0 ? __int_as_float(rec.z) : 1.f;
-        }
+        // what the occurrences add: the other entity of their triple (or -1 - a row of `rows`), its relation, the weight;
+        // the next 64 are on their way meanwhile
+        const uint32_t q = cur_id / per, slot = cur_id - q * per;
+        const int4 tr = cur_tr;
+        const bool own = slot >= (uint32_t)n_neg, head = __float_as_int(cur_delta) < 0;      // the sign bit, also of a zero
+        const int32_t other = own ? -1 - (int32_t)(2 * q + (slot - n_neg)) : head ? tr.z : tr.x, rel = tr.y;
+        const float wgt = own ? 1.f : fabsf(cur_delta);
+        cur_id = next_id;
+        cur_delta = deltas[cur_id];
+        cur_tr = triples[cur_id / per];
+        next_id = id_at(base + 128);
         for (int32_t j0 = 0; j0 < cnt; j0 += 4) {
+            // every load unconditional: past the end the last occurrence again, past the width column 0 (both unused), for
+            // a positive's own end its relation's row, replaced by ones
             float4 a[4][NV], b[4][NV];
             float wj[4];
 #pragma unroll
             for (int z = 0; z < 4; ++z) {
-                const int j = j0 + z < cnt ? j0 + z : cnt - 1;          // past the end: the last one again, unused
-                const int32_t oj = __shfl(other, j, 64), rj = __shfl(rel, j, 64);
-                wj[z] = __shfl(wgt, j, 64);
+                const int j = j0 + z < cnt ? j0 + z : cnt - 1;
+                const int32_t oj = __builtin_amdgcn_readlane(other, j), rj = __builtin_amdgcn_readlane(rel, j);
+                wj[z] = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(wgt), j));
+                const float4 *ra = oj < 0 ? rows + (int64_t)(-1 - oj) * d4 : H + (int64_t)oj * d4, *rb = M + (int64_t)rj * d4;
 #pragma unroll
-                for (int u = 0; u < NV; ++u) {
-                    const int k = lane + 64 * u;
-                    if (!ok[u]) { a[z][u] = zero4; b[z][u] = zero4; }
-                    else if (oj < 0) { a[z][u] = rows[(int64_t)(-1 - oj) * d4 + k]; b[z][u] = one4; }
-                    else { a[z][u] = H[(int64_t)oj * d4 + k]; b[z][u] = M[(int64_t)rj * d4 + k]; }
-                }
+                for (int u = 0; u < NV; ++u) { a[z][u] = ra[col[u]]; b[z][u] = rb[col[u]]; }
             }
+#pragma unroll
+            for (int z = 0; z < 4; ++z)
+                if (__builtin_amdgcn_readlane(other, j0 + z < cnt ? j0 + z : cnt - 1) < 0)
+#pragma unroll
+                    for (int u = 0; u < NV; ++u) b[z][u] = one4;
 #pragma unroll
             for (int z = 0; z < 4; ++z) {
                 if (j0 + z >= cnt) break;
@@ -669,7 +718,27 @@ __global__ __launch_bounds__(256) void k_distmult_gather(
             }
         }
     }
-    while (cur < n_ent) close_entity();
+    while (cur < n_ent && boundary <= hi) close_entity();
+    if (cur < n_ent && start_of(cur) < hi) {       // it goes on in the next wavefront
+        flags |= start_of(cur) < lo ? 6 : 2;
+#pragma unroll
+        for (int u = 0; u < NV; ++u) part[w][1][lane + 64 * u] = acc[u];
+    }
+    if (lane == 0) kind[w] = flags;
+    __syncthreads();
+    if ((flags & 6) != 2) return;                  // only the wavefront in which an entity starts puts it together
+    for (int x = w + 1; x < 4; ++x) {
+        const bool through = (kind[x] & 4) != 0;
+#pragma unroll
+        for (int u = 0; u < NV; ++u) {
+            const float4 y = part[x][through ? 1 : 0][lane + 64 * u];
+            acc[u].x += y.x; acc[u].y += y.y; acc[u].z += y.z; acc[u].w += y.w;
+        }
+        if (!through) break;
+    }
+#pragma unroll
+    for (int u = 0; u < NV; ++u)
+        if (ok[u]) dH[(e0 + cur) * d4 + lane + 64 * u] = acc[u];
 }
 
 }  // namespace
@@ -707,8 +776,8 @@ extern "C" int kge_score_index_create(const kge_partition *p, int64_t max_pos, i
     for (int k = 0; k < 2; ++k) { take((void **)&x->keys[k], 4 * (size_t)max_occ); take((void **)&x->vals[k], 4 * (size_t)max_occ); }
     take((void **)&x->sort_ws, 4 * radix_scratch_words(max_occ));
     take((void **)&x->ent_ptr, 4 * ((size_t)p->n_vert + 1));
-    take((void **)&x->slot_of, 4 * (size_t)max_occ);
-    take((void **)&x->recs, 16 * (size_t)max_occ);
+    take((void **)&x->deltas, 4 * (size_t)max_occ);
+    take((void **)&x->triples, 16 * (size_t)max_pos);
     for (int k = 0; k < 2; ++k) { take((void **)&x->pkeys[k], 4 * (size_t)max_pos); take((void **)&x->pvals[k], 4 * (size_t)max_pos); }
     take((void **)&x->rows, 4 * (size_t)2 * max_pos * d);
     take((void **)&x->dm_part, 4 * (size_t)KGE_SCORE_MAX_BLOCKS * d);
@@ -726,7 +795,7 @@ extern "C" int kge_score_index_create(const kge_partition *p, int64_t max_pos, i
 extern "C" void kge_score_index_destroy(kge_score_index *x)
 {
     if (!x) return;
-    void *all[] = {x->keys[0], x->keys[1], x->vals[0], x->vals[1], x->sort_ws, x->ent_ptr, x->slot_of, x->recs,
+    void *all[] = {x->keys[0], x->keys[1], x->vals[0], x->vals[1], x->sort_ws, x->ent_ptr, x->deltas, x->triples,
                    x->pkeys[0], x->pkeys[1], x->pvals[0], x->pvals[1], x->rows, x->dm_part, x->dm_rel, x->loss_part};
     for (void *q : all) if (q) (void)hipFree(q);
     delete x;
@@ -765,8 +834,6 @@ int launch_distmult_indexed(const kge_partition *p, kge_score_index *x, const fl
         if (rc != KGE_OK) return rc;
         k_ptr_from_sorted<uint32_t><<<(unsigned)cdiv(n_occ + 1, 256), 256, 0, st>>>(keys, n_occ, p->n_vert, x->ent_ptr);
         KGE_LAUNCH_CHECK();
-        k_invert_permutation<<<(unsigned)cdiv(n_occ, 256), 256, 0, st>>>(vals, n_occ, x->slot_of);
-        KGE_LAUNCH_CHECK();
         // the positives in relation order (stable), for the walk of the scoring kernel
         k_score_rel_keys<<<(unsigned)cdiv(n_pos, 256), 256, 0, st>>>(p->core_r, pos, n_pos, (uint32_t)p->n_core, pkeys, pvals);
         KGE_LAUNCH_CHECK();
@@ -784,7 +851,7 @@ int launch_distmult_indexed(const kge_partition *p, kge_score_index *x, const fl
 #define DMS_CALL(NVV)                                                                                               \
         k_distmult_score<NVV><<<grid, 64 * DS_WAVES, 0, st>>>((const float4 *)H, (const float4 *)M, d4, p->core_h,  \
             p->core_r, p->core_t, pos, pvals, n_pos, (int32_t)per_wave, neg_ent, neg_side, n_neg,                  \
-            (uint32_t)p->n_vert, (uint32_t)p->n_core, inv_T, scores, dM, x->slot_of, x->recs, (float4 *)x->rows,  \
+            (uint32_t)p->n_vert, (uint32_t)p->n_core, inv_T, scores, dM, x->deltas, x->triples, (float4 *)x->rows,  \
             (float4 *)x->dm_part, x->dm_rel, x->loss_part)
         KGE_REQUIRE(grid <= KGE_SCORE_MAX_BLOCKS, KGE_ERANGE, "scoring: more blocks than the index has partial rows for");
         if (d4 <= 64) DMS_CALL(1); else DMS_CALL(2);
@@ -797,13 +864,15 @@ int launch_distmult_indexed(const kge_partition *p, kge_score_index *x, const fl
     }
     {
         KGE_PROF("distmult_gather", st);
-        const unsigned g2 = (unsigned)cdiv(cdiv(p->n_vert, DG_ENT), 4);
+        // 64 entities per block, fewer where that would leave less than eight blocks per compute unit
+        const int32_t ents = (int32_t)(p->n_vert >= 64 * 2048 ? 64 : p->n_vert < 4 * 2048 ? 4 : p->n_vert / 2048);
+        const unsigned g2 = (unsigned)cdiv(p->n_vert, ents);
         if (d4 <= 64)
-            k_distmult_gather<1><<<g2, 256, 0, st>>>((const float4 *)H, (const float4 *)M, d4, p->n_vert, x->ent_ptr,
-                                                     x->recs, (const float4 *)x->rows, (float4 *)dH);
+            k_distmult_gather<1><<<g2, 256, 0, st>>>((const float4 *)H, (const float4 *)M, d4, p->n_vert, ents, x->ent_ptr, vals,
+                                                     n_neg, x->deltas, x->triples, (const float4 *)x->rows, (float4 *)dH);
         else
-            k_distmult_gather<2><<<g2, 256, 0, st>>>((const float4 *)H, (const float4 *)M, d4, p->n_vert, x->ent_ptr,
-                                                     x->recs, (const float4 *)x->rows, (float4 *)dH);
+            k_distmult_gather<2><<<g2, 256, 0, st>>>((const float4 *)H, (const float4 *)M, d4, p->n_vert, ents, x->ent_ptr, vals,
+                                                     n_neg, x->deltas, x->triples, (const float4 *)x->rows, (float4 *)dH);
         KGE_LAUNCH_CHECK();
     }
     return KGE_OK;

@@ -74,6 +74,7 @@ __global__ void k_scan_apply(const uint32_t *in, int64_t n, const uint32_t *bloc
         if (base + k < n) out[base + k] = run;
         run += v[k];
     }
+    if (blockIdx.x == 0 && threadIdx.x == 0) out[n] = block_offs[gridDim.x];      // the total
 }
 
 // Single block: exclusive scan of up to any n (loops), writes total to out[n].
@@ -104,8 +105,6 @@ __global__ void k_scan_small(const uint32_t *in, int64_t n, uint32_t *out)
     if (threadIdx.x == 0) out[n] = carry;
 }
 
-__global__ void k_copy_word(const uint32_t *src, uint32_t *dst) { *dst = *src; }
-
 // Words of scratch exclusive_scan_ws needs for n inputs (block sums and their offsets, level by level).
 inline size_t scan_scratch_words(int64_t n)
 {
@@ -135,8 +134,6 @@ inline int exclusive_scan_ws(const uint32_t *in, uint32_t *out, int64_t n, uint3
     int rc = exclusive_scan_ws(sums, offs, nb, scratch + 2 * (nb + 1), st);
     if (rc != KGE_OK) return rc;
     k_scan_apply<<<(unsigned)nb, TB, 0, st>>>(in, n, offs, out);
-    KGE_LAUNCH_CHECK();
-    k_copy_word<<<1, 1, 0, st>>>(offs + nb, out + n);      // total
     KGE_LAUNCH_CHECK();
     return KGE_OK;
 }
