@@ -391,6 +391,11 @@ extern "C" int kge_rgcn_backward(const kge_partition *p, const kge_cgraph *cg, c
             float *Self = (float *)(ws + w.off_self);
             const bool need_in = l > 0 || dH0;
             float *dst = l > 0 ? dHbuf[l & 1] : dH0;
+            // everything that is accumulated below
+            const kge_span acc[4] = {{C, sizeof(float) * (size_t)R2 * dd}, {grads[l].da, sizeof(float) * (size_t)R2 * L.n_bases},
+                                     {grads[l].dV, sizeof(float) * (size_t)L.n_bases * dd}, {grads[l].dW0, sizeof(float) * (size_t)dd}};
+            rc = launch_fill_zero_spans(acc, 4, st);
+            if (rc != KGE_OK) return rc;
             if (bf) {
                 if (!g_bf) rc = launch_append_g_bf16(Gl, p->n_vert, L.d_out, 0, dP, st);          // Gbf [N][d_out]
                 if (rc != KGE_OK) return rc;
@@ -429,6 +434,12 @@ extern "C" int kge_rgcn_backward(const kge_partition *p, const kge_cgraph *cg, c
             continue;
         }
         const int64_t bd = (int64_t)L.n_bases * L.d_out;
+        const kge_span acc[4] = {{seg, sizeof(float) * (size_t)p->n_seg * L.n_bases},
+                                 {grads[l].da, sizeof(float) * (size_t)2 * p->n_relations * L.n_bases},
+                                 {grads[l].dV, sizeof(float) * (size_t)bd * L.d_in},
+                                 {grads[l].dW0, sizeof(float) * (size_t)L.d_in * L.d_out}};
+        rc = launch_fill_zero_spans(acc, 4, st);
+        if (rc != KGE_OK) return rc;
         const bool on_cores = bf && gather_transpose_bf16_supported(L.n_bases, L.d_out);      // dP on the matrix cores
         rc = launch_project_first_backward(p, P, bf, Gl, L.a, L.n_bases, L.d_out, seg, part, grads[l].da, on_cores ? nullptr : dP,
                                            bf ? bd + L.d_out : bd, kge_cgraph_layer(cg, l), st);

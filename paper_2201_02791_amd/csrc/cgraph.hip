@@ -70,12 +70,15 @@ __device__ __forceinline__ void block_add4(unsigned long long a, unsigned long l
     }
 }
 
-// counts of one layer: active vertices and edges (over vertices), active runs (over runs)
+// counts of layer blockIdx.y: active vertices and edges (over vertices), active runs (over runs)
 __global__ __launch_bounds__(256) void k_cg_stats(const int32_t *__restrict__ dm_ptr,
                                                   const int32_t *__restrict__ sm_ptr, int64_t N,
                                                   const int32_t *__restrict__ seg_dst, int64_t S,
-                                                  const uint8_t *__restrict__ act, unsigned long long *out)
+                                                  const uint8_t *__restrict__ active, int64_t row,
+                                                  unsigned long long *out)
 {
+    const uint8_t *act = active + blockIdx.y * row;
+    out += 4 * blockIdx.y;
     unsigned long long nv = 0, ne = 0, ns = 0, no = 0;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < N; i += stride)
@@ -139,9 +142,8 @@ extern "C" int kge_compute_graph(const kge_partition *p, kge_cgraph *cg, const i
     hipStream_t st = (hipStream_t)stream;
     const int L = cg->n_layers;
     KGE_PROF("compute_graph", st);
-    int rc = launch_fill_zero(cg->active, (size_t)cg->stride * (L + 1), st);
-    if (rc != KGE_OK) return rc;
-    rc = launch_fill_zero(cg->stats, sizeof(unsigned long long) * 4 * (L + 1), st);
+    const kge_span acc[2] = {{cg->active, (size_t)cg->stride * (L + 1)}, {cg->stats, sizeof(unsigned long long) * 4 * (L + 1)}};
+    int rc = launch_fill_zero_spans(acc, 2, st);
     if (rc != KGE_OK) return rc;
     if (p->n_vert == 0) return KGE_OK;
     const int64_t n_mark = n_pos + n_neg_entries;
@@ -163,11 +165,10 @@ extern "C" int kge_compute_graph(const kge_partition *p, kge_cgraph *cg, const i
     k_cg_expand<<<(unsigned)cdiv(p->n_vert, 4), 256, 0, st>>>(p->dm_ptr, p->dm_src, p->n_vert, cg->active,
                                                              cg->active + (size_t)L * cg->stride);
     KGE_LAUNCH_CHECK();
-    for (int l = 0; l <= L; ++l) {
-        k_cg_stats<<<1024, 256, 0, st>>>(p->dm_ptr, p->sm_ptr, p->n_vert, p->seg_dst, p->n_seg,
-                                         cg->active + (size_t)l * cg->stride, cg->stats + 4 * l);
-        KGE_LAUNCH_CHECK();
-    }
+    const int64_t most = p->n_vert > p->n_seg ? p->n_vert : p->n_seg, want = cdiv(most, 4 * 256);       // four items per thread
+    k_cg_stats<<<dim3((unsigned)(want < 1024 ? want : 1024), (unsigned)(L + 1)), 256, 0, st>>>(
+        p->dm_ptr, p->sm_ptr, p->n_vert, p->seg_dst, p->n_seg, cg->active, cg->stride, cg->stats);
+    KGE_LAUNCH_CHECK();
     return KGE_OK;
 }
 

@@ -62,7 +62,8 @@ struct kge_partition {
     // the runs grouped by destination (order dst, rel): dr_seg = run id, dr_rel = its relation
     int32_t *dr_ptr, *dr_seg, *dr_rel;
     kge_heavy_index hv_dr;
-    // each relation's run range cut into chunks of KGE_REL_CHUNK .. 8 KGE_REL_CHUNK runs (about 2048 chunks in all)
+    // each relation's run range cut into chunks: KGE_REL_CHUNK .. 8 KGE_REL_CHUNK runs (about 2048 chunks in all), in
+    // small graphs fewer runs
     int32_t n_relc;
     int32_t *relc_rel, *relc_beg, *relc_end;
     // and into row tiles of at most KGE_REL_TILE runs
@@ -88,6 +89,7 @@ struct kge_partition {
     uint32_t *bad_ids;
 };
 #define KGE_REL_CHUNK 2048
+#define KGE_REL_CHUNK_DIV 512
 #define KGE_REL_TILE 128
 #define KGE_REL_RANGE 4096
 // vertices per slab of the destination range by which those ranges are ordered
@@ -111,7 +113,7 @@ static inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; 
 // P[N][B*d_out] and Self[N][d_out] = H[N][d_in] * [V_1 .. V_B | W0]
 int launch_project(const float *H, int64_t N, int32_t d_in, int32_t d_out, int32_t B,
                    const float *V, const float *W0, float *P, float *Self, hipStream_t st);
-// dV[B][d_in][d_out] = H^T dP_b ; dW0 = H^T G      (outputs zeroed inside, split over N)
+// dV[B][d_in][d_out] = H^T dP_b ; dW0 = H^T G      (split over N: the outputs come zeroed)
 int launch_weight_grad(const float *H, int64_t N, int32_t d_in, int32_t d_out, int32_t B,
                        const float *dP, const float *G, float *dV, float *dW0, hipStream_t st);
 // dH[N][d_in] = sum_b dP_b V_b^T + G W0^T
@@ -161,7 +163,7 @@ int launch_gather_transpose_bf16(const kge_partition *p, const void *Gbf, int64_
                                  int32_t d, void *dP, int64_t ld, float *partial, const uint8_t *active, hipStream_t st);
 // da[r][b] = sum_{edges e of r} invc_e <P[src_e][b][:], G[dst_e][:]> and, where dP is given, dP (fp32, or bf16 with bf16
 // messages): dP[j][b][:] = sum_{e out of j} a[rel_e][b] invc_e G[dst_e][:], rows ld elements apart.  dP null: bf16 messages
-// only.  seg_scratch [S][B] floats; `partial`: [hv_sm.n_units][B*d] floats
+// only.  seg_scratch [S][B] floats; `partial`: [hv_sm.n_units][B*d] floats.  da and seg_scratch come zeroed
 int launch_project_first_backward(const kge_partition *p, const void *P, int msg_bf16, const float *G, const float *a,
                                   int32_t B, int32_t d, float *seg_scratch, float *partial, float *da, void *dP, int64_t ld,
                                   const uint8_t *active, hipStream_t st);
@@ -190,10 +192,10 @@ int launch_sum_edges_out(const kge_partition *p, const void *dZ, int z_bf16, int
 // Wrel[r] = sum_b a[r][b] V_b ([2R][d_in*d_out] floats)
 int launch_relation_weights(const float *a, int32_t R2, int32_t B, const float *V, int64_t dd, float *Wrel,
                             hipStream_t st);
-// dV[b] = sum_r a[r][b] C[r]   (overwrites dV)
 // the same matrices summed in fp32 and stored as bf16 only: Wb [2R][d_in][d_out] and WbT [2R][d_out][d_in]
 int launch_relation_weights_bf16(const float *a, int32_t R2, int32_t B, const float *V, int32_t d_in, int32_t d_out,
                                  void *Wb, void *WbT, hipStream_t st);
+// dV[b] = sum_r a[r][b] C[r]   (dV comes zeroed)
 int launch_basis_grad_from_relations(const float *a, int32_t R2, int32_t B, const float *C, int64_t dd, float *dV,
                                      hipStream_t st);
 // U[s] = Z[s] Wrel[rel(s)]  and  dZ[s] = G[dst(s)] Wrel[rel(s)]^T   (fp32)
@@ -214,10 +216,10 @@ int launch_apply_relation_weights_t_bf16(const kge_partition *p, const void *Gbf
                                          int32_t d_in, int32_t d_out, void *dZ, hipStream_t st);
 
 // gemm.hip, relation-weight order (coefficient gradient) ---------------------
-// C[r] (d_in x d_out; [2R][d_in*d_out] floats, zeroed inside) = sum_{runs s of relation r} Z[s]^T G[seg_dst[s]]
+// C[r] (d_in x d_out; [2R][d_in*d_out] floats, comes zeroed) = sum_{runs s of relation r} Z[s]^T G[seg_dst[s]]
 int launch_rel_outer(const kge_partition *p, const float *Z, const float *G, int32_t d_in, int32_t d_out,
                      float *C, hipStream_t st);
-// da[r][b] = <C[r], V_b>   (fp32)
+// da[r][b] = <C[r], V_b>   (fp32; da comes zeroed)
 int launch_coeff_contract(const kge_partition *p, const float *C, const float *V, int32_t d_in, int32_t d_out,
                           int32_t B, float *da, hipStream_t st);
 
@@ -239,6 +241,9 @@ int launch_distmult_indexed(const kge_partition *p, kge_score_index *x, const fl
                             const int32_t *pos, int64_t n_pos, const int32_t *neg_ent, const uint8_t *neg_side,
                             int32_t n_neg, float *scores, float *loss, float *dH, float *dM, hipStream_t st);
 int launch_fill_zero(void *ptr, size_t bytes, hipStream_t st);
+// several buffers at once (each a multiple of 4 bytes, 4-byte aligned): one launch
+struct kge_span { void *ptr; size_t bytes; };
+int launch_fill_zero_spans(const kge_span *spans, int n, hipStream_t st);      // n <= 4
 
 // dst = dropout(src) on [n_rows][d] floats (d a multiple of 4), inverted scaling, Philox mask keyed by
 // (seed, step, layer, row, column); src == dst is allowed.  p == 0 copies.

@@ -1033,13 +1033,9 @@ int launch_project_first_backward(const kge_partition *p, const void *P, int msg
                                   int32_t B, int32_t d, float *seg_scratch, float *partial, float *da, void *dP, int64_t ld,
                                   const uint8_t *active, hipStream_t st)
 {
-    const int64_t S = p->n_seg;
-    int rc = launch_fill_zero(da, sizeof(float) * (size_t)2 * p->n_relations * B, st);
-    if (rc != KGE_OK) return rc;
     KGE_REQUIRE(B <= 256 && d <= 256, KGE_EINVAL, "more than 256 bases or a wider row than 256 are not supported");
     if (p->n_vert == 0) return KGE_OK;
-    rc = launch_fill_zero(seg_scratch, sizeof(float) * (size_t)S * B, st);
-    if (rc != KGE_OK) return rc;
+    int rc;
     if (!dP) rc = launch_source_backward<true, false>(p, G, a, P, B, d, dP, ld, partial, seg_scratch, active, st);
     else if (msg_bf16) rc = launch_source_backward<true, true>(p, G, a, P, B, d, dP, ld, partial, seg_scratch, active, st);
     else rc = launch_source_backward<false, true>(p, G, a, P, B, d, dP, ld, partial, seg_scratch, active, st);

@@ -113,13 +113,13 @@ struct WcatX {                  // x-contiguous: row k of [V_1 .. V_B | W_0]
 // ---- outputs: column n's address in row 0 and its row pitch; bind(g) selects the group of a grouped launch
 struct EpiProject {             // columns < B*d_out go to P, the rest to Self
     float *P, *Self; int32_t d_out, bd;
-    __device__ __forceinline__ void bind(int32_t) {}
+    __device__ __forceinline__ void bind(int32_t, bool) {}
     __device__ __forceinline__ float *column(int32_t n, int64_t &ld) const { ld = n < bd ? bd : d_out; return n < bd ? P + n : Self + (n - bd); }
     __device__ __forceinline__ void put(float *q, float v) const { *q = v; }
 };
 struct EpiWeightGrad {          // atomic accumulation of split-K partial tiles
     float *dV, *dW0; int32_t d_in, d_out, B;
-    __device__ __forceinline__ void bind(int32_t) {}
+    __device__ __forceinline__ void bind(int32_t, bool) {}
     __device__ __forceinline__ float *column(int32_t n, int64_t &ld) const
     {
         const int32_t b = n / d_out;
@@ -130,15 +130,15 @@ struct EpiWeightGrad {          // atomic accumulation of split-K partial tiles
 };
 struct EpiRows {                // streamed out: the next kernel reads it once
     float *out; int64_t cols;
-    __device__ __forceinline__ void bind(int32_t) {}
+    __device__ __forceinline__ void bind(int32_t, bool) {}
     __device__ __forceinline__ float *column(int32_t n, int64_t &ld) const { ld = cols; return out + n; }
     __device__ __forceinline__ void put(float *q, float v) const { __builtin_nontemporal_store(v, q); }
 };
-struct EpiRowsAtomic {          // split-K partial tiles; one matrix per group, gstride apart
-    float *out; int64_t cols, gstride;
-    __device__ __forceinline__ void bind(int32_t g) { out += g * gstride; }
+struct EpiRowsAtomic {          // split-K partial tiles; one matrix per group, gstride apart; a group's only part is stored
+    float *out; int64_t cols, gstride; bool sole;
+    __device__ __forceinline__ void bind(int32_t g, bool only) { out += g * gstride; sole = only; }
     __device__ __forceinline__ float *column(int32_t n, int64_t &ld) const { ld = cols; return out + n; }
-    __device__ __forceinline__ void put(float *q, float v) const { unsafeAtomicAdd(q, v); }
+    __device__ __forceinline__ void put(float *q, float v) const { if (sole) *q = v; else unsafeAtomicAdd(q, v); }
 };
 
 // A launch is (row tiles) x (column tiles) x (splits) blocks in one dimension.  Row tile x holds rows x * BM.. or, with
@@ -188,7 +188,12 @@ __global__ __launch_bounds__(GT, 2) void k_gemm(SA A, SB B, EPI epi, int32_t M_,
     const int32_t n0 = tn * BN;
     int64_t kbeg = sp * g.kchunk;
     int64_t kend = (kbeg + g.kchunk < g.K) ? kbeg + g.kchunk : g.K;
-    if (g.g_beg) { kbeg = g.g_beg[sp]; kend = g.g_end[sp]; epi.bind(g.g_id[sp]); }
+    if (g.g_beg) {
+        kbeg = g.g_beg[sp];
+        kend = g.g_end[sp];
+        const int32_t id = g.g_id[sp];
+        epi.bind(id, (sp == 0 || g.g_id[sp - 1] != id) && (sp + 1 == g.splits || g.g_id[sp + 1] != id));
+    }
     if (kbeg >= kend) return;
     const int64_t klast = kbeg + (kend - 1 - kbeg) / BK * BK;         // the last step's first k
 
@@ -418,7 +423,48 @@ __global__ void k_zero4(uint32_t *p, int64_t n)
     for (; i < n; i += stride) p[i] = 0u;
 }
 
+struct ZeroSpans { uint32_t *p[4]; int64_t first[5]; };      // span k: words [first[k], first[k + 1]) of the whole
+
+__global__ __launch_bounds__(256) void k_zero_spans(ZeroSpans s)
+{
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < s.first[4]; i += stride) {
+        const int k = i < s.first[1] ? 0 : i < s.first[2] ? 1 : i < s.first[3] ? 2 : 3;
+        s.p[k][i - s.first[k]] = 0u;
+    }
+}
+
 }  // namespace
+
+// Several small buffers in one launch (a launch and its gap cost 5 us, the fills of a small graph a fraction of that); a
+// big one among them gets a launch of its own with 16-byte stores.
+int launch_fill_zero_spans(const kge_span *spans, int n, hipStream_t st)
+{
+    KGE_REQUIRE(n >= 0 && n <= 4, KGE_EINVAL, "at most four buffers");
+    ZeroSpans z{};
+    int64_t words = 0;
+    for (int k = 0; k < 4; ++k) {
+        z.first[k] = words;
+        if (k >= n || spans[k].bytes == 0) continue;
+        KGE_REQUIRE(((uintptr_t)spans[k].ptr % 4) == 0 && spans[k].bytes % 4 == 0, KGE_EINVAL,
+                    "zero fill needs a 4-byte aligned buffer and size");
+        if (spans[k].bytes > ((size_t)4 << 20)) {
+            int rc = launch_fill_zero(spans[k].ptr, spans[k].bytes, st);
+            if (rc != KGE_OK) return rc;
+            continue;
+        }
+        z.p[k] = (uint32_t *)spans[k].ptr;
+        words += (int64_t)(spans[k].bytes / 4);
+    }
+    z.first[4] = words;
+    if (words == 0) return KGE_OK;
+    KGE_PROF("zero", st);
+    int64_t blocks = cdiv(words, 256);
+    if (blocks > 2048) blocks = 2048;
+    k_zero_spans<<<(unsigned)blocks, 256, 0, st>>>(z);
+    KGE_LAUNCH_CHECK();
+    return KGE_OK;
+}
 
 // Zero `bytes` bytes (a multiple of 4, 4-byte aligned) with a fill kernel; no memset nodes,
 // so callers may capture the step in a HIP graph.
@@ -457,10 +503,6 @@ int launch_project(const float *H, int64_t N, int32_t d_in, int32_t d_out, int32
 int launch_weight_grad(const float *H, int64_t N, int32_t d_in, int32_t d_out, int32_t B,
                        const float *dP, const float *G, float *dV, float *dW0, hipStream_t st)
 {
-    int rc = launch_fill_zero(dV, sizeof(float) * (size_t)B * d_in * d_out, st);
-    if (rc != KGE_OK) return rc;
-    rc = launch_fill_zero(dW0, sizeof(float) * (size_t)d_in * d_out, st);
-    if (rc != KGE_OK) return rc;
     if (N == 0) return KGE_OK;
     int32_t nc = (B + 1) * d_out;
     int64_t tiles = cdiv(d_in, BM) * cdiv(nc, BN);
@@ -492,14 +534,11 @@ int launch_input_grad(const float *dP, const float *G, int64_t N, int32_t d_in,
 int launch_rel_outer(const kge_partition *p, const float *Z, const float *G, int32_t d_in, int32_t d_out,
                      float *C, hipStream_t st)
 {
-    const int64_t R2 = 2 * (int64_t)p->n_relations;
     const int64_t dd = (int64_t)d_in * d_out;
-    int rc = launch_fill_zero(C, sizeof(float) * (size_t)R2 * dd, st);
-    if (rc != KGE_OK) return rc;
     if (p->n_seg == 0 || p->n_relc == 0) return KGE_OK;
     RowsX sa{Z, d_in, nullptr, 0};
     RowsX sb{G, d_out, p->seg_dst, 0};
-    EpiRowsAtomic ep{C, d_out, dd};
+    EpiRowsAtomic ep{C, d_out, dd, false};
     KGE_PROF("rel_outer", st);
     return run_gemm(
         sa, sb, ep, d_in, d_out, GemmGrid{0, 0, p->n_relc, p->n_seg, 0, p->relc_rel, p->relc_beg, p->relc_end}, st);
@@ -510,8 +549,6 @@ int launch_coeff_contract(const kge_partition *p, const float *C, const float *V
 {
     const int64_t R2 = 2 * (int64_t)p->n_relations;
     const int64_t dd = (int64_t)d_in * d_out;
-    int rc = launch_fill_zero(da, sizeof(float) * (size_t)R2 * B, st);
-    if (rc != KGE_OK) return rc;
     if (p->n_seg == 0) return KGE_OK;
     {
         const int64_t tiles = cdiv(R2, BM) * cdiv(B, BN);
@@ -521,7 +558,7 @@ int launch_coeff_contract(const kge_partition *p, const float *C, const float *V
         splits = cdiv(dd, kchunk);
         RowsK sa{C, dd, nullptr, 0};
         RowsK sb{V, dd, nullptr, 0};
-        EpiRowsAtomic ep{da, B, 0};
+        EpiRowsAtomic ep{da, B, 0, false};
         KGE_PROF("coeff_contract", st);
         return run_gemm(sa, sb, ep, R2, B, GemmGrid{0, 0, (int32_t)splits, dd, kchunk}, st);
     }
@@ -650,11 +687,10 @@ int basis_grad_groups(const float *a, int32_t R2, int32_t B, int32_t &b_done, co
 int launch_basis_grad_from_relations(const float *a, int32_t R2, int32_t B, const float *C, int64_t dd, float *dV,
                                      hipStream_t st)
 {
-    int rc = launch_fill_zero(dV, sizeof(float) * (size_t)B * dd, st);
-    if (rc != KGE_OK || R2 == 0 || B == 0) return rc;
+    if (R2 == 0 || B == 0) return KGE_OK;
     KGE_PROF("basis_grad", st);
     int32_t b_done = 0;
-    rc = basis_grad_groups<64>(a, R2, B, b_done, C, dd, dV, st);
+    int rc = basis_grad_groups<64>(a, R2, B, b_done, C, dd, dV, st);
     if (rc == KGE_OK) rc = basis_grad_groups<16>(a, R2, B, b_done, C, dd, dV, st);
     if (rc == KGE_OK) rc = basis_grad_groups<4>(a, R2, B, b_done, C, dd, dV, st);
     if (rc == KGE_OK) rc = basis_grad_groups<1>(a, R2, B, b_done, C, dd, dV, st);

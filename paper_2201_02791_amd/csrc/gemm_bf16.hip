@@ -714,10 +714,6 @@ static int project_gemm(const void *Hbf, int64_t N, int32_t d_in, int32_t d_out,
 int launch_weight_grad_bf16(const void *Hbf, int64_t N, int32_t d_in, int32_t d_out, int32_t B, const void *X,
                             float *dV, float *dW0, hipStream_t st)
 {
-    int rc = launch_fill_zero(dV, sizeof(float) * (size_t)B * d_in * d_out, st);
-    if (rc != KGE_OK) return rc;
-    rc = launch_fill_zero(dW0, sizeof(float) * (size_t)d_in * d_out, st);
-    if (rc != KGE_OK) return rc;
     if (N == 0) return KGE_OK;
     const int32_t nc = (B + 1) * d_out;
     if (rel_outer_bf16_supported(d_in, d_out)) {     // the row-streaming kernel of rel_outer_bf16.hip
@@ -756,9 +752,6 @@ int launch_input_grad_bf16(const void *X, int64_t N, int32_t d_in, int32_t d_out
 int launch_rel_outer_bf16(const kge_partition *p, const void *Zbf, const int32_t *zrow, const void *Gbf, int64_t ldg,
                           int32_t d_in, int32_t d_out, float *C, hipStream_t st)
 {
-    const int64_t R2 = 2 * (int64_t)p->n_relations;
-    int rc = launch_fill_zero(C, sizeof(float) * (size_t)R2 * d_in * d_out, st);
-    if (rc != KGE_OK) return rc;
     if (p->n_seg == 0 || p->n_relc == 0) return KGE_OK;
     if (rel_outer_bf16_supported(d_in, d_out)) {     // the row-streaming kernel of rel_outer_bf16.hip
         KGE_PROF("rel_outer", st);

@@ -531,7 +531,13 @@ int build_impl(const int32_t *h_head, const int32_t *h_rel, const int32_t *h_tai
         // chunk length: about 2048 chunks over all runs (every chunk ends in one atomic accumulation of a
         // whole d_in x d_out tile, so fewer, longer chunks are cheaper as long as the chip stays full)
         int32_t chunk = (int32_t)((S / 2048 + 31) / 32 * 32);
-        if (chunk < KGE_REL_CHUNK) chunk = KGE_REL_CHUNK;
+        // a small graph: about 512 chunks, down to 64 runs each, or a few blocks walk what there is while the chip idles
+        // (fp32 rel_outer: 10 k runs at width 32 52 -> 8 us, 352 k at 200 384 -> 335, 580 k at 128 x 32 183 -> 98; about 256
+        // chunks: 8, 317, 159; 128: 8, 358, 160)
+        int32_t least = (int32_t)((S / KGE_REL_CHUNK_DIV + 31) / 32 * 32);
+        if (least < 64) least = 64;
+        if (least > KGE_REL_CHUNK) least = KGE_REL_CHUNK;
+        if (chunk < least) chunk = least;
         if (chunk > 8 * KGE_REL_CHUNK) chunk = 8 * KGE_REL_CHUNK;
         // and into row tiles of at most KGE_REL_TILE runs (one output tile of the per-relation products)
         for (int64_t r = 0; r < R2; ++r)

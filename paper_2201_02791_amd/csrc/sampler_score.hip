@@ -813,9 +813,8 @@ int launch_distmult_indexed(const kge_partition *p, kge_score_index *x, const fl
                 (long long)x->max_pos, x->max_neg, x->d);
     KGE_REQUIRE(((uintptr_t)H % 16) == 0 && ((uintptr_t)M % 16) == 0 && ((uintptr_t)dH % 16) == 0, KGE_EINVAL,
                 "H, M and dH must be 16-byte aligned");
-    int rc = launch_fill_zero(dM, sizeof(float) * (size_t)p->n_relations * d, st);
-    if (rc != KGE_OK) return rc;
-    rc = launch_fill_zero(loss, sizeof(float), st);
+    const kge_span acc[2] = {{dM, sizeof(float) * (size_t)p->n_relations * d}, {loss, sizeof(float)}};
+    int rc = launch_fill_zero_spans(acc, 2, st);
     if (rc != KGE_OK) return rc;
     if (n_pos == 0 || p->n_vert == 0) return launch_fill_zero(dH, sizeof(float) * (size_t)p->n_vert * d, st);
     const int64_t n_occ = n_pos * ((int64_t)n_neg + 2);
@@ -882,11 +881,9 @@ int launch_distmult(const kge_partition *p, const float *H, const float *M, int3
                     const int32_t *pos, int64_t n_pos, const int32_t *neg_ent, const uint8_t *neg_side,
                     int32_t n_neg, float *scores, float *loss, float *dH, float *dM, hipStream_t st)
 {
-    int rc = launch_fill_zero(dH, sizeof(float) * (size_t)p->n_vert * d, st);
-    if (rc != KGE_OK) return rc;
-    rc = launch_fill_zero(dM, sizeof(float) * (size_t)p->n_relations * d, st);
-    if (rc != KGE_OK) return rc;
-    rc = launch_fill_zero(loss, sizeof(float), st);
+    const kge_span acc[3] = {{dH, sizeof(float) * (size_t)p->n_vert * d}, {dM, sizeof(float) * (size_t)p->n_relations * d},
+                             {loss, sizeof(float)}};
+    int rc = launch_fill_zero_spans(acc, 3, st);
     if (rc != KGE_OK) return rc;
     if (n_pos == 0) return KGE_OK;
     const float inv_T = (float)(1.0 / ((double)n_pos * (1.0 + (double)n_neg)));
