@@ -227,9 +227,12 @@ __global__ __launch_bounds__(64 * PW) void k_eval_pairs(const float *__restrict_
 template <int LPR, int NP>
 __device__ __forceinline__ float row_dot(const float4 *__restrict__ hrow, const float4 (&q4)[NP], int32_t d4, int sub)
 {
+    // no condition stands around the loads (those of several rows would wait for each other): past the width column 0
     float4 h[NP];
 #pragma unroll
-    for (int j = 0; j < NP; ++j) h[j] = sub + j * LPR < d4 ? hrow[sub + j * LPR] : make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int j = 0; j < NP; ++j) h[j] = hrow[sub + j * LPR < d4 ? sub + j * LPR : 0];
+#pragma unroll
+    for (int j = 0; j < NP; ++j) if (sub + j * LPR >= d4) h[j] = make_float4(0.f, 0.f, 0.f, 0.f);
     float s = 0.f;
 #pragma unroll
     for (int j = 0; j < NP; ++j) {
@@ -267,8 +270,8 @@ __global__ __launch_bounds__(256) void k_eval_candidates(const float4 *__restric
 #pragma unroll
         for (int u = 0; u < UN; ++u) {
             const int32_t i = b + u * RPP + grp;
-            e[u] = i < n_cand ? list[i] : -1;
-            if (e[u] == ans) e[u] = -1;
+            e[u] = list[i < n_cand ? i : n_cand - 1];
+            if (i >= n_cand || e[u] == ans) e[u] = -1;
         }
 #pragma unroll
         for (int u = 0; u < UN; ++u) s[u] = row_dot<LPR, NP>(H + (int64_t)(e[u] < 0 ? 0 : e[u]) * d4, q4, d4, sub);

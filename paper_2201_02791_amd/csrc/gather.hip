@@ -175,13 +175,19 @@ __global__ __launch_bounds__(64 * WPB) void k_gather_fwd(
         for (int q0 = 0; q0 < items; q0 += U) {
             float coef[U];
             uint4 raw[U];
+            // Plain sums with several lane groups load no more rows than there are (a vertex with two runs two, not
+            // 16: sum_runs of 5.8 M runs into 2.9 M rows of 128 floats 2.07 -> 1.42 ms); with one group, or several
+            // bases per edge, the slots are nearly always full and the bound costs more (1.42 -> 2.00 ms for 544 k edges
+            // x 10 bases x 200 floats).  Uniform over the wavefront.
+            const int slots = PLAIN && G > 1 ? min(U, items - q0) : U;
 #pragma unroll
             for (int u = 0; u < U; ++u) {
+                if (u >= slots) break;
                 const int el = er * GE + ge;
                 const int b = bi * GB + gb;
                 // a slot past the end repeats the chunk's first edge with coefficient 0, and a lane past the
                 // row's width reads its start: every load is unconditional (no divergent branch around it)
-                const bool ok = (q0 + u < items) && el < cnt && b < B;
+                const bool ok = q0 + u < items && el < cnt && b < B;
                 const int els = ok ? el : 0, bs = ok ? b : 0;
                 const int32_t src = __shfl(my_src, els, 64);
                 const int32_t rel = __shfl(my_rel, els, 64);
@@ -193,6 +199,7 @@ __global__ __launch_bounds__(64 * WPB) void k_gather_fwd(
             }
 #pragma unroll
             for (int u = 0; u < U; ++u) {
+                if (u >= slots) break;
                 float val[VEC];
                 MsgRow<BF16>::unpack(raw[u], val);
 #pragma unroll
@@ -643,23 +650,31 @@ __global__ __launch_bounds__(64 * WPB) void k_run_mean(
     const bool skip = active && !active[seg_dst[rw.row]];     // destination outside the sub-graph: zeros
     if (skip && rw.unit >= 0) return;
     const int len = skip ? 0 : rw.end - rw.beg;
-    for (int e0 = 0; e0 < len; e0 += NG * U) {
-        uint4 x[U];
+    // 64 sources at a time, a lane each, handed out by shuffles; rounds of NG * U rows, the last one as many as there are.
+    // No per-lane condition around a row's load (the loads of a round would wait for each other): a slot past the end
+    // repeats the last row and is replaced by zeros, a lane past the width reads the row's start.  60 M edges into 5.8 M runs
+    // of 128 floats: 5.22 ms with an index and a condition per load, 4.16 now (7.4 TB/s of rows)
+    const int64_t col = kact ? kl * VEC : 0;
+    for (int e0 = 0; e0 < len; e0 += 64) {
+        const int cnt = min(64, len - e0);
+        const int32_t mine = col_src[rw.beg + e0 + min(lane, cnt - 1)];
+        for (int j0 = 0; j0 < cnt; j0 += NG * U) {
+            const int slots = min(U, (cnt - j0 + NG - 1) / NG);          // uniform
+            uint4 x[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int el = e0 + u * NG + g;
-            x[u] = make_uint4(0u, 0u, 0u, 0u);
-            if (el < len && kact) {
-                const int32_t src = col_src[rw.beg + el];
-                x[u] = MsgRow<BF16>::load_raw(H, (int64_t)src * d + kl * VEC);
+            for (int u = 0; u < U; ++u) {
+                const int32_t src = __shfl(mine, min(j0 + u * NG + g, cnt - 1), 64);
+                if (u < slots) x[u] = MsgRow<BF16>::load_raw(H, (int64_t)src * d + col);
             }
-        }
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            float val[VEC];
-            MsgRow<BF16>::unpack(x[u], val);
+            for (int u = 0; u < U; ++u) {
+                if (u >= slots) break;
+                if (j0 + u * NG + g >= cnt) x[u] = make_uint4(0u, 0u, 0u, 0u);
+                float val[VEC];
+                MsgRow<BF16>::unpack(x[u], val);
 #pragma unroll
-            for (int v = 0; v < VEC; ++v) acc[v] += val[v];
+                for (int v = 0; v < VEC; ++v) acc[v] += val[v];
+            }
         }
     }
 #pragma unroll
@@ -738,30 +753,50 @@ __global__ __launch_bounds__(64 * WPB) void k_run_mean_multi(
             else { w[i] = inv_c[sr]; src0[i] = col_src[b]; }
         }
     }
+    // no condition stands around the rows' loads (each would wait for the one before): a run without edges reads row 0 and
+    // drops it, a lane past the width the row's start
+    const int64_t col = kact ? kl * VEC : 0;
     uint4 x0[PER];
 #pragma unroll
-    for (int i = 0; i < PER; ++i) {
-        x0[i] = make_uint4(0u, 0u, 0u, 0u);
-        if (len[i] > 0 && kact) x0[i] = MsgRow<BF16>::load_raw(H, (int64_t)src0[i] * d + kl * VEC);
-    }
+    for (int i = 0; i < PER; ++i) x0[i] = MsgRow<BF16>::load_raw(H, (int64_t)src0[i] * d + col);
+#pragma unroll
+    for (int i = 0; i < PER; ++i) if (len[i] <= 0) x0[i] = make_uint4(0u, 0u, 0u, 0u);
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
         if (len[i] < 0) continue;
         float acc[VEC];
         MsgRow<BF16>::unpack(x0[i], acc);
-        for (int el = 1; el < len[i]; el += 2) {           // the rest of a longer run, two rows at a time
-            const bool two = el + 1 < len[i];
-            uint4 xa = make_uint4(0u, 0u, 0u, 0u), xb = make_uint4(0u, 0u, 0u, 0u);
-            const int32_t sa = col_src[beg[i] + el], sb = two ? col_src[beg[i] + el + 1] : 0;
-            if (kact) {
-                xa = MsgRow<BF16>::load_raw(H, (int64_t)sa * d + kl * VEC);
-                if (two) xb = MsgRow<BF16>::load_raw(H, (int64_t)sb * d + kl * VEC);
-            }
-            float va[VEC], vb[VEC];
-            MsgRow<BF16>::unpack(xa, va);
-            MsgRow<BF16>::unpack(xb, vb);
+        // the rest of a longer run, two rows at a time and, from the fourth edge on, four: the sources of the next rows are
+        // fetched with these, so that a step is one memory round trip
+        const int32_t last = beg[i] + (len[i] > 0 ? len[i] - 1 : 0);
+        int32_t nx[4];
+        if (len[i] > 1) {
 #pragma unroll
-            for (int v = 0; v < VEC; ++v) acc[v] += va[v] + vb[v];
+            for (int u = 0; u < 4; ++u) nx[u] = col_src[min(beg[i] + 1 + u, last)];
+        }
+        for (int el = 1; el < len[i]; el += 4) {
+            uint4 x[4];
+            const bool more = el + 2 < len[i];
+            x[0] = MsgRow<BF16>::load_raw(H, (int64_t)nx[0] * d + col);
+            x[1] = MsgRow<BF16>::load_raw(H, (int64_t)nx[1] * d + col);
+            if (more) {
+                x[2] = MsgRow<BF16>::load_raw(H, (int64_t)nx[2] * d + col);
+                x[3] = MsgRow<BF16>::load_raw(H, (int64_t)nx[3] * d + col);
+#pragma unroll
+                for (int u = 0; u < 4; ++u) nx[u] = col_src[min(beg[i] + el + 4 + u, last)];
+            } else {
+                x[2] = x[3] = make_uint4(0u, 0u, 0u, 0u);
+            }
+#pragma unroll
+            for (int u = 1; u < 4; ++u) if (el + u >= len[i]) x[u] = make_uint4(0u, 0u, 0u, 0u);
+#pragma unroll
+            for (int h = 0; h < 4; h += 2) {
+                float va[VEC], vb[VEC];
+                MsgRow<BF16>::unpack(x[h], va);
+                MsgRow<BF16>::unpack(x[h + 1], vb);
+#pragma unroll
+                for (int v = 0; v < VEC; ++v) acc[v] += va[v] + vb[v];
+            }
         }
         if (!kact) continue;
         const int64_t o = (int64_t)rid[i] * d + kl * VEC;
