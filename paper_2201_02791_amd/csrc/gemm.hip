@@ -150,6 +150,10 @@ struct GemmGrid {
     int64_t K, kchunk;
     const int32_t *g_id, *g_beg, *g_end, *mt_id, *mt_beg, *mt_end;
 };
+__host__ __device__ __forceinline__ bool gemm_by_cols(const GemmGrid &g)
+{
+    return g.splits <= 1 && !g.g_beg && !g.mt_beg && g.tiles_m < 8 && g.tiles_n > g.tiles_m;
+}
 
 // C (+)= A B^T, A (M x K), B (N x K).
 // Steps of 16 k: a step's operands are split into LDS ([part][row][k]) one step ahead of their use, their loads are issued
@@ -177,12 +181,13 @@ __global__ __launch_bounds__(GT, 2) void k_gemm(SA A, SB B, EPI epi, int32_t M_,
     const int w = __builtin_amdgcn_readfirstlane(t >> 6), wm = w >> 1, wn = w & 1;
     // block id -> (row tile, column tile, split).  Workgroup i runs on XCD i % 8: the tiles that read the same rows of
     // a long operand (the column tiles of a row tile; all tiles of a split) run on one XCD one after another, and the
-    // rows come from its L2 all but once.
-    const bool by_split = g.splits > 1 || g.g_beg;
-    const int32_t per = by_split ? g.tiles_m * g.tiles_n : g.tiles_n;
+    // rows come from its L2 all but once.  With fewer row tiles than XCDs the column tiles go round them instead.
+    const bool by_split = g.splits > 1 || g.g_beg, by_cols = gemm_by_cols(g);
+    const int32_t per = by_split ? g.tiles_m * g.tiles_n : by_cols ? g.tiles_m : g.tiles_n;
     const int32_t slot = blockIdx.x / 8, unit = slot / per * 8 + blockIdx.x % 8, in_unit = slot % per;
-    const int32_t tn = in_unit % g.tiles_n, tm = by_split ? in_unit / g.tiles_n : unit, sp = by_split ? unit : 0;
-    if (tm >= g.tiles_m || sp >= g.splits) return;            // padding blocks of the last units
+    const int32_t tn = by_cols ? unit : in_unit % g.tiles_n, sp = by_split ? unit : 0;
+    const int32_t tm = by_split ? in_unit / g.tiles_n : by_cols ? in_unit : unit;
+    if (tm >= g.tiles_m || tn >= g.tiles_n || sp >= g.splits) return;       // padding blocks of the last units
     int64_t m0 = (int64_t)tm * BM, m_end = M_;
     if (g.mt_beg) { m0 = g.mt_beg[tm]; m_end = g.mt_end[tm]; B.bind(g.mt_id[tm]); }
     const int32_t n0 = tn * BN;
@@ -401,7 +406,9 @@ int run_gemm(const SA &sa, const SB &sb, const EPI &ep, int64_t rows, int32_t co
     if (!g.mt_beg) g.tiles_m = (int32_t)cdiv(rows, BM);
     g.tiles_n = (int32_t)cdiv(cols, BN);
     const bool by_split = g.splits > 1 || g.g_beg;
-    const int64_t per = by_split ? (int64_t)g.tiles_m * g.tiles_n : g.tiles_n, units = by_split ? g.splits : g.tiles_m;
+    const bool by_cols = gemm_by_cols(g);
+    const int64_t per = by_split ? (int64_t)g.tiles_m * g.tiles_n : by_cols ? g.tiles_m : g.tiles_n;
+    const int64_t units = by_split ? g.splits : by_cols ? g.tiles_n : g.tiles_m;
     const int64_t blocks = cdiv(units, 8) * 8 * per;
     KGE_REQUIRE(rows <= 0x7fffffffLL && blocks <= 0x7fffffffLL, KGE_ERANGE, "too many tiles for one launch");
     k_gemm<SA, SB, EPI><<<(unsigned)blocks, GT, 0, st>>>(sa, sb, ep, (int32_t)rows, cols, g);
@@ -683,16 +690,28 @@ int basis_grad_groups(const float *a, int32_t R2, int32_t B, int32_t &b_done, co
 }  // namespace
 
 // dV_b = sum_r a[r][b] C[r]   (the chain rule on Wrel[r] = sum_b a[r][b] V_b with dWrel = C)
-// Groups of 64 bases per block, then what is left in groups of 16, 4 and 1.
+// Many bases (a multiple of 4: the operand loads take pairs of them) and columns: a product on the matrix cores, a^T C,
+// that reads C once: 2000 relations x 65,536 columns with 64 bases 188 us, 359 on the vector units (whose multiply-adds
+// bound it), with 20 bases 150, 197; 240 relations 33, 93 and 28, 43.  It needs one and a half tiles of 128 columns per
+// compute unit: at 2000 x 50,176 with 32 bases 145, 154, but at 2000 x 40,000 145, 125.  Otherwise groups of 64, 16, 8,
+// 4, 2 and 1 bases per block (10 bases as 8 + 2: 36 us at 474 x 40,000, 51 as 4 + 4 + 1 + 1).
 int launch_basis_grad_from_relations(const float *a, int32_t R2, int32_t B, const float *C, int64_t dd, float *dV,
                                      hipStream_t st)
 {
     if (R2 == 0 || B == 0) return KGE_OK;
     KGE_PROF("basis_grad", st);
+    if (B >= 20 && B % 4 == 0 && dd >= 384 * BN) {
+        RowsX sa{a, B, nullptr, 0};
+        RowsX sb{C, dd, nullptr, 0};
+        EpiRowsAtomic ep{dV, dd, 0, true};
+        return run_gemm(sa, sb, ep, B, (int32_t)dd, GemmGrid{0, 0, 1, R2, R2}, st);
+    }
     int32_t b_done = 0;
     int rc = basis_grad_groups<64>(a, R2, B, b_done, C, dd, dV, st);
     if (rc == KGE_OK) rc = basis_grad_groups<16>(a, R2, B, b_done, C, dd, dV, st);
+    if (rc == KGE_OK) rc = basis_grad_groups<8>(a, R2, B, b_done, C, dd, dV, st);
     if (rc == KGE_OK) rc = basis_grad_groups<4>(a, R2, B, b_done, C, dd, dV, st);
+    if (rc == KGE_OK) rc = basis_grad_groups<2>(a, R2, B, b_done, C, dd, dV, st);
     if (rc == KGE_OK) rc = basis_grad_groups<1>(a, R2, B, b_done, C, dd, dV, st);
     return rc;
 }

@@ -46,7 +46,8 @@ def model(seed, n, R, di, do, B):
 # widths around the tile edges (16 deep, 32 and 128 wide), one row, one past a tile of rows, a relation of few runs
 @pytest.mark.parametrize("order", [0, 2])
 @pytest.mark.parametrize("n,R,di,do,B", [(1, 1, 4, 4, 1), (129, 1, 16, 128, 2), (300, 7, 20, 132, 3), (257, 2, 128, 36, 2),
-                                         (400, 30, 200, 200, 5), (131, 1, 256, 256, 1)])
+                                         (400, 30, 200, 200, 5), (131, 1, 256, 256, 1), (90, 40, 36, 64, 15),
+                                         (60, 3, 32, 32, 64), (40, 500, 256, 256, 20), (40, 501, 256, 256, 132)])
 def test_tile_edges(n, R, di, do, B, order):
     H0, dH, V, a, W0 = model(n, n, R, di, do, B)
     got, want = layer(n, R, 4 * n, di, do, B, order, H0, dH, V, a, W0)
