@@ -241,15 +241,13 @@ __global__ __launch_bounds__(64 * DM_WAVES) void k_distmult(
 }
 
 // ---------------------------------------------------------------- atomic-free form
-// keys[o] = the entity whose gradient row occurrence o adds to; vals[o] = o
-__global__ void k_score_keys(const int32_t *__restrict__ core_h, const int32_t *__restrict__ core_t,
-                             const int32_t *__restrict__ pos, int64_t n_pos, const int32_t *__restrict__ neg_ent,
-                             int32_t n_neg, uint32_t n_vert, uint32_t n_core, uint32_t *__restrict__ keys,
-                             uint32_t *__restrict__ vals, uint32_t *__restrict__ bad)
+// the entity whose gradient row occurrence o adds to.  An id outside the partition never becomes an address: it is counted
+// and replaced by vertex 0
+__device__ __forceinline__ uint32_t entity_of(int64_t o, const int32_t *__restrict__ core_h, const int32_t *__restrict__ core_t,
+                                              const int32_t *__restrict__ pos, const int32_t *__restrict__ neg_ent,
+                                              int32_t n_neg, uint32_t n_vert, uint32_t n_core, uint32_t *__restrict__ bad)
 {
-    const int64_t o = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int32_t per = n_neg + 2;
-    if (o >= n_pos * per) return;
     const int64_t q = o / per;
     const int32_t slot = (int32_t)(o - q * per);
     uint32_t e;
@@ -260,10 +258,112 @@ __global__ void k_score_keys(const int32_t *__restrict__ core_h, const int32_t *
         if (c >= n_core) { c = 0; if (slot == n_neg) atomicAdd(bad, 1u); }
         e = (uint32_t)(slot == n_neg ? core_h[c] : core_t[c]);
     }
-    // an id outside the partition never becomes an address: it is counted and replaced by vertex 0
     if (e >= n_vert) { e = 0; atomicAdd(bad, 1u); }
-    keys[o] = e;
+    return e;
+}
+
+// keys[o] = the entity whose gradient row occurrence o adds to; vals[o] = o
+__global__ void k_score_keys(const int32_t *__restrict__ core_h, const int32_t *__restrict__ core_t,
+                             const int32_t *__restrict__ pos, int64_t n_pos, const int32_t *__restrict__ neg_ent,
+                             int32_t n_neg, uint32_t n_vert, uint32_t n_core, uint32_t *__restrict__ keys,
+                             uint32_t *__restrict__ vals, uint32_t *__restrict__ bad)
+{
+    const int64_t o = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (o >= n_pos * (n_neg + 2)) return;
+    keys[o] = entity_of(o, core_h, core_t, pos, neg_ent, n_neg, n_vert, n_core, bad);
     vals[o] = (uint32_t)o;
+}
+
+// The whole index of a small batch in one launch: block 0 sorts the occurrences by entity (and looks up where each entity's
+// range starts), block 1 the positives by relation.  A stable sort of (key, position) words in LDS, seven key bits per
+// pass: each wavefront ranks its 256 words among themselves by matching ballots, a scan over (digit, wavefront) places
+// them.  The general path's 15 small launches wait for each other more than they work.  At most 4096 occurrences (four
+// words per thread) and 16,384 vertices (17 look-ups per thread).  3072 occurrences of 1000 entities: 14 us, 47 before.
+constexpr int SMALL_OCC = 4096, SMALL_VERT = 16384, SMALL_POS_BITS = 12;
+__global__ __launch_bounds__(1024) void k_score_index_small(const int32_t *__restrict__ core_h, const int32_t *__restrict__ core_r,
+                                                            const int32_t *__restrict__ core_t,
+                                                            const int32_t *__restrict__ pos, int32_t n_pos,
+                                                            const int32_t *__restrict__ neg_ent, int32_t n_neg, uint32_t n_vert,
+                                                            uint32_t n_core, uint32_t n_rel, uint32_t *__restrict__ vals,
+                                                            int32_t *__restrict__ ent_ptr, uint32_t *__restrict__ pvals,
+                                                            uint32_t *__restrict__ bad)
+{
+    __shared__ uint32_t w[SMALL_OCC], cnt[128 * 16], tot[16];
+    const int t = threadIdx.x, wave = t >> 6, lane = t & 63;
+    const bool by_entity = blockIdx.x == 0;
+    const int n = by_entity ? n_pos * (n_neg + 2) : n_pos;
+    for (int i = t; i < n; i += 1024) {
+        uint32_t key;
+        if (by_entity) {
+            key = entity_of(i, core_h, core_t, pos, neg_ent, n_neg, n_vert, n_core, bad);
+        } else {
+            const uint32_t c = (uint32_t)pos[i];
+            key = (uint32_t)core_r[c < n_core ? c : 0];
+        }
+        w[i] = key << SMALL_POS_BITS | (uint32_t)i;
+    }
+    const uint32_t last = by_entity ? n_vert - 1 : n_rel - 1;
+    const uint64_t below = (1ull << lane) - 1ull;
+    for (int bit = 0; bit < 32 - SMALL_POS_BITS && last >> bit != 0; bit += 7) {
+        cnt[t] = cnt[t + 1024] = 0;
+        __syncthreads();
+        uint32_t word[4], slot[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int i = wave * 256 + r * 64 + lane;
+            word[r] = w[i];                                    // past the end: whatever is there, never placed
+            const uint32_t digit = word[r] >> (SMALL_POS_BITS + bit) & 127u;
+            uint64_t same = __ballot(i < n);
+#pragma unroll
+            for (int k = 0; k < 7; ++k) {
+                const uint64_t ones = __ballot(digit >> k & 1u);
+                same &= digit >> k & 1u ? ones : ~ones;
+            }
+            const uint32_t before = cnt[digit * 16 + wave];
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            slot[r] = before + (uint32_t)__popcll(same & below);
+            if (i < n && (same & below) == 0) cnt[digit * 16 + wave] = before + (uint32_t)__popcll(same);
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+        }
+        __syncthreads();
+        const uint32_t c0 = cnt[2 * t], c1 = cnt[2 * t + 1];
+        uint32_t sum = c0 + c1;
+#pragma unroll
+        for (int k = 1; k < 64; k <<= 1) {
+            const uint32_t up = __shfl_up(sum, k, 64);
+            sum += lane >= k ? up : 0u;
+        }
+        if (lane == 63) tot[wave] = sum;
+        __syncthreads();
+        uint32_t start = sum - c0 - c1;
+        for (int v = 0; v < 16; ++v) start += v < wave ? tot[v] : 0u;
+        cnt[2 * t] = start;
+        cnt[2 * t + 1] = start + c0;
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            if (wave * 256 + r * 64 + lane < n)
+                w[cnt[(word[r] >> (SMALL_POS_BITS + bit) & 127u) * 16 + wave] + slot[r]] = word[r];
+        __syncthreads();
+    }
+    __syncthreads();
+    const uint32_t mask = (1u << SMALL_POS_BITS) - 1u;
+    uint32_t *out = by_entity ? vals : pvals;
+    for (int i = t; i < n; i += 1024) out[i] = w[i] & mask;
+    if (by_entity)
+        for (uint32_t v = t; v <= n_vert; v += 1024) {         // where v's range starts: the first word not below v's
+            const uint32_t key = v << SMALL_POS_BITS;
+            int lo = 0, len = n;
+            while (len > 0) {
+                const int half = len >> 1;
+                const bool up = w[lo + half] < key;
+                lo = up ? lo + half + 1 : lo;
+                len = up ? len - half - 1 : half;
+            }
+            ent_ptr[v] = lo;
+        }
 }
 
 // keys[q] = relation of positive q, vals[q] = q
@@ -824,22 +924,29 @@ int launch_distmult_indexed(const kge_partition *p, kge_score_index *x, const fl
     uint32_t *pkeys = x->pkeys[0], *pkeys_alt = x->pkeys[1], *pvals = x->pvals[0], *pvals_alt = x->pvals[1];
     {
         KGE_PROF("score_index", st);
-        k_score_keys<<<(unsigned)cdiv(n_occ, 256), 256, 0, st>>>(p->core_h, p->core_t, pos, n_pos, neg_ent, n_neg,
-                                                                (uint32_t)p->n_vert, (uint32_t)p->n_core, keys, vals, p->bad_ids);
-        KGE_LAUNCH_CHECK();
-        int bits = 1;
-        while (bits < 32 && ((int64_t)1 << bits) < p->n_vert) ++bits;
-        rc = radix_sort_ws<uint32_t>(&keys, &vals, &keys_alt, &vals_alt, n_occ, bits, x->sort_ws, st);
-        if (rc != KGE_OK) return rc;
-        k_ptr_from_sorted<uint32_t><<<(unsigned)cdiv(n_occ + 1, 256), 256, 0, st>>>(keys, n_occ, p->n_vert, x->ent_ptr);
-        KGE_LAUNCH_CHECK();
-        // the positives in relation order (stable), for the walk of the scoring kernel
-        k_score_rel_keys<<<(unsigned)cdiv(n_pos, 256), 256, 0, st>>>(p->core_r, pos, n_pos, (uint32_t)p->n_core, pkeys, pvals);
-        KGE_LAUNCH_CHECK();
-        int rbits = 1;
-        while (rbits < 32 && ((int64_t)1 << rbits) < p->n_relations) ++rbits;
-        rc = radix_sort_ws<uint32_t>(&pkeys, &pvals, &pkeys_alt, &pvals_alt, n_pos, rbits, x->sort_ws, st);
-        if (rc != KGE_OK) return rc;
+        if (n_occ <= SMALL_OCC && p->n_vert <= SMALL_VERT && p->n_relations < (1 << (32 - SMALL_POS_BITS))) {
+            k_score_index_small<<<2, 1024, 0, st>>>(p->core_h, p->core_r, p->core_t, pos, (int32_t)n_pos, neg_ent, n_neg,
+                                                    (uint32_t)p->n_vert, (uint32_t)p->n_core, (uint32_t)p->n_relations, vals,
+                                                    x->ent_ptr, pvals, p->bad_ids);
+            KGE_LAUNCH_CHECK();
+        } else {
+            k_score_keys<<<(unsigned)cdiv(n_occ, 256), 256, 0, st>>>(p->core_h, p->core_t, pos, n_pos, neg_ent, n_neg,
+                                                                    (uint32_t)p->n_vert, (uint32_t)p->n_core, keys, vals, p->bad_ids);
+            KGE_LAUNCH_CHECK();
+            int bits = 1;
+            while (bits < 32 && ((int64_t)1 << bits) < p->n_vert) ++bits;
+            rc = radix_sort_ws<uint32_t>(&keys, &vals, &keys_alt, &vals_alt, n_occ, bits, x->sort_ws, st);
+            if (rc != KGE_OK) return rc;
+            k_ptr_from_sorted<uint32_t><<<(unsigned)cdiv(n_occ + 1, 256), 256, 0, st>>>(keys, n_occ, p->n_vert, x->ent_ptr);
+            KGE_LAUNCH_CHECK();
+            // the positives in relation order (stable), for the walk of the scoring kernel
+            k_score_rel_keys<<<(unsigned)cdiv(n_pos, 256), 256, 0, st>>>(p->core_r, pos, n_pos, (uint32_t)p->n_core, pkeys, pvals);
+            KGE_LAUNCH_CHECK();
+            int rbits = 1;
+            while (rbits < 32 && ((int64_t)1 << rbits) < p->n_relations) ++rbits;
+            rc = radix_sort_ws<uint32_t>(&pkeys, &pvals, &pkeys_alt, &pvals_alt, n_pos, rbits, x->sort_ws, st);
+            if (rc != KGE_OK) return rc;
+        }
     }
     int64_t per_wave = cdiv(n_pos, 16384);
     if (per_wave < 4) per_wave = n_pos >= 4 * 1024 ? 4 : 1;

@@ -1,6 +1,7 @@
 """The atomic-free scoring call where its gather can go wrong: four, some and 64 entities per block, entities whose
 occurrences fall to several wavefronts of a block (a hub that is the head of half the batch), blocks without any
-occurrence, more than 64 negatives, rows wider than a wavefront's 64 x 4 columns.
+occurrence, more than 64 negatives, rows wider than a wavefront's 64 x 4 columns; batches on both sides of the index
+that one launch builds (4096 occurrences, 16,384 entities).
 
 Tolerance: a row of dH is an fp32 sum of up to 5000 terms: sqrt(5000) * 2^-24 = 4e-6 of the largest element; scores and
 loss 1e-5."""
@@ -12,7 +13,9 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("n,d,n_pos,n_neg,hub", [(50, 4, 3, 0, False), (900, 36, 700, 1, True), (20000, 200, 1500, 10, True),
                                                  (140000, 16, 5000, 3, True), (140001, 256, 3000, 70, False),
-                                                 (300, 300, 40, 65, True), (131072, 8, 20, 1, False)])
+                                                 (300, 300, 40, 65, True), (131072, 8, 20, 1, False),
+                                                 (16384, 8, 1, 0, False), (16384, 8, 128, 30, True), (16385, 8, 64, 30, True),
+                                                 (700, 8, 4096 // 7, 5, True), (700, 8, 1366, 1, False)])
 def test_scoring_against_fp64(n, d, n_pos, n_neg, hub):
     import torch
     from paper_2201_02791_amd import binding as kb
