@@ -21,8 +21,9 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 PEAK_HBM_GBS = 8000.0
-PEAK_F32_MFMA_TFLOPS = 157.3
 PEAK_BF16_MFMA_TFLOPS = 2500.0
+# fp32 products run on the bf16 matrix cores, six products of bf16 parts per term
+PEAK_F32_MFMA_TFLOPS = PEAK_BF16_MFMA_TFLOPS / 6
 # plain vector ALUs: 256 compute units x 4 SIMDs x 32 fp32 FMA lanes per clock x 2 flops x 2.4 GHz
 PEAK_F32_VALU_TFLOPS = 256 * 4 * 32 * 2 * 2.4e9 / 1e12
 # Adam's learning rate per workload.  The paper's 0.01 (Sec. 4) is kept where it trains; at configs[4]
@@ -90,7 +91,8 @@ def kernel_work(name, part, spec, dims, B, ep, n_pos, n_neg, cone=None, order="p
             w = {"flops": 2.0 * R2 * B * di * do, "unit": "alu",
                  "bytes": B * di * do * 4.0 + R2 * di * do * (4.0 if ep == 4 else 2.0 * ep)}
         elif name == "basis_grad":   # the transposed product: C read once, dV written
-            w = {"flops": 2.0 * R2 * B * di * do, "bytes": (R2 + B) * di * do * 4.0, "unit": "alu"}
+            w = {"flops": 2.0 * R2 * B * di * do, "bytes": (R2 + B) * di * do * 4.0, "f32": True,
+                 "unit": "mfma" if B >= 20 and B % 4 == 0 and di * do >= 49152 else "alu"}
         elif name == "coeff_contract":   # da_rb = <C_r, V_b>: C and V read once
             w = {"flops": 2.0 * R2 * di * do * B, "bytes": (R2 + B) * di * do * 4.0, "unit": "mfma", "f32": True}
         elif name == "project":    # H read, P and Self written
@@ -251,7 +253,7 @@ def run_eval(args):
     for name, (tot, calls) in sorted(prof.items(), key=lambda kv: -kv[1][0]):
         log("%-13s %9.3f ms/step  %4.1f launches" % (name, tot / args.steps, calls / args.steps))
     avg_ms = prof[work_name][0] / max(prof[work_name][1], 1)
-    if flops is not None:        # dense contraction on the fp32 matrix cores
+    if flops is not None:        # dense contraction of fp32 numbers on the matrix cores
         roof = {"kernel": work_name, "bound": "mfma", "achieved": flops / (avg_ms * 1e-3) / 1e12,
                 "peak": PEAK_F32_MFMA_TFLOPS, "unit": "TFLOP/s", "traffic": None, "avg_launch_ms": avg_ms}
     else:                        # gathers one entity row per (query, candidate)

@@ -6,7 +6,8 @@
 // Work decomposition.  One wavefront per row (destination, source, or (relation, destination)
 // run).  Rows with >= KGE_HEAVY edges are cut into units of KGE_HEAVY edges, one wavefront
 // each, placed first in the grid; a unit writes a partial sum and a small finishing kernel adds
-// the partials of a row in unit order.  No atomics: results are bit-reproducible.
+// the partials of a row in unit order.  No atomics, bit-reproducible results - but for the coefficient gradient's dot
+// products of k_source_backward.
 //
 // Lane layout.  A row of `d` elements is covered by LPR lanes, each holding VEC consecutive
 // elements (VEC = 4 for fp32, 8 for bf16: one 16-byte load).  The 64 / LPR lane groups of a
