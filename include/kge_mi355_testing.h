@@ -28,6 +28,11 @@ int kge_eval_debug_scores(const float *H, int64_t n_entities, int32_t d, const f
  * thread-safe. */
 void kge_test_set_rel_slab(int32_t vertices, int32_t min_runs);
 
+/* Host only: how the per-query kernel of the evaluation finds its pairs.  A block holds n_queries (1 .. 32) queries with
+ * n_known[i] known answers each, HOST array, laid end to end.  Returns the query whose row the kernel reads for place
+ * `at` (places past the last one come up in the last group of 32) and writes the number of places; -1 on bad arguments. */
+int32_t kge_test_pair_query(const int64_t *n_known, int32_t n_queries, int64_t at, int64_t *n_pairs);
+
 #ifdef __cplusplus
 }
 #endif

@@ -24,7 +24,7 @@ EXPORTED = ["kge_build_partition", "kge_partition_info", "kge_partition_export",
             "kge_optimizer_step_rows", "kge_eval_filter_create", "kge_eval_filter_destroy",
             "kge_eval_workspace_bytes", "kge_eval_rank_all", "kge_eval_rank_candidates", "kge_eval_metrics",
             "kge_eval_debug_scores", "kge_eval_rank_all_static", "kge_cgraph_input_rows", "kge_score_index_create", "kge_score_index_destroy",
-            "kge_partition_bad_ids", "kge_test_set_rel_slab"]
+            "kge_partition_bad_ids", "kge_test_set_rel_slab", "kge_test_pair_query"]
 
 ACT_IDENTITY, ACT_RELU = 0, 1
 ORDER_PROJECT_FIRST, ORDER_RELATION_WEIGHTS = 0, 2
@@ -155,6 +155,15 @@ def set_rel_slab_for_tests(vertices: int, min_runs: int = 0):
     """Test hook: slab size (destinations) and cutting threshold (runs) of the range order that partitions built
     afterwards give the transposed per-run products; (0, 0) restores the library's values."""
     load().kge_test_set_rel_slab(C.c_int32(vertices), C.c_int32(min_runs))
+
+
+def pair_query_for_tests(n_known, at: int):
+    """Test hook: (query whose row the evaluation's per-query kernel reads for place `at` of a block whose queries have
+    n_known known answers each, number of places)."""
+    known = np.ascontiguousarray(n_known, np.int64)
+    n_pairs = C.c_int64()
+    i = load().kge_test_pair_query(known.ctypes.data_as(C.c_void_p), C.c_int32(len(known)), C.c_int64(at), C.byref(n_pairs))
+    return i, n_pairs.value
 
 
 def build_partition(head, rel, tail, n_entities: int, n_relations: int, n_parts: int = 1,

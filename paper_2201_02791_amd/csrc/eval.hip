@@ -154,6 +154,20 @@ struct FilterTables {
     const int64_t *key[2]; const int32_t *val[2]; int64_t n[2]; int64_t N; int32_t R;
 };
 
+constexpr int PQ = 32, PW = 8;             // queries and wavefronts of a block of k_eval_pairs
+
+// The known answers of a block's PQ queries laid end to end, query i's from place ptr[i] on: the query at place `at`.
+// A place past the last one (the rest of the last tile, whose rows are read all the same) has the block's first query: the
+// block may hold fewer than PQ.
+using PairPlace = int32_t;
+__host__ __device__ __forceinline__ int query_at(const PairPlace *ptr, PairPlace at)
+{
+    int i = 0;                             // the last query that starts at or before `at`
+#pragma unroll
+    for (int step = PQ / 2; step > 0; step >>= 1) if (ptr[i + step] <= at) i += step;
+    return at < ptr[PQ] ? i : 0;
+}
+
 // The answers' scores and, among the known answers of each query's (fixed entity, relation), how many others score
 // above / exactly at them.  A block takes PQ queries.  Their answers are one matrix-core tile of 32 pairs; the known
 // answers of all its queries are laid end to end and cut into such tiles, dealt out over the block's wavefronts: most
@@ -161,7 +175,6 @@ struct FilterTables {
 // wavefront's chain.  Bound by the splitting of the pairs' rows.  40,932 queries of the 14,541-entity graph at width 200:
 // 676 us with one wavefront and one tile per query and fp32 steps, 198 now (545 with
 // conditions around the row loads: each then waits for the last).
-constexpr int PQ = 32, PW = 8;             // queries and wavefronts of a block
 __global__ __launch_bounds__(64 * PW) void k_eval_pairs(const float *__restrict__ Q, const float *__restrict__ H,
                                                     int32_t d, int64_t nq, int64_t n_test,
                                                     const int32_t *__restrict__ fixed, const int32_t *__restrict__ rel,
@@ -170,7 +183,8 @@ __global__ __launch_bounds__(64 * PW) void k_eval_pairs(const float *__restrict_
                                                     int32_t *__restrict__ out_eq)
 {
     __shared__ int64_t bound[2 * PQ];
-    __shared__ int32_t ptr[PQ + 1], gt_s[PQ], eq_s[PQ];
+    __shared__ PairPlace ptr[PQ + 1];
+    __shared__ int32_t gt_s[PQ], eq_s[PQ];
     __shared__ float thr[PQ];
     const int t = threadIdx.x, lane = t & 63, w = t >> 6;
     const int64_t q0 = (int64_t)blockIdx.x * PQ;
@@ -193,18 +207,16 @@ __global__ __launch_bounds__(64 * PW) void k_eval_pairs(const float *__restrict_
     }
     __syncthreads();
     if (w == 0) {                                           // where each query's known answers start in the block's row
-        int x = lane < PQ ? (int)(bound[2 * lane + 1] - bound[2 * lane]) : 0;
-        const int own = x;
-        for (int off = 1; off < PQ; off <<= 1) { const int y = __shfl_up(x, off, 64); if (lane >= off) x += y; }
+        PairPlace x = lane < PQ ? (PairPlace)(bound[2 * lane + 1] - bound[2 * lane]) : 0;
+        const PairPlace own = x;
+        for (int off = 1; off < PQ; off <<= 1) { const PairPlace y = __shfl_up(x, off, 64); if (lane >= off) x += y; }
         if (lane < PQ) { ptr[lane] = x - own; if (lane == PQ - 1) ptr[PQ] = x; }
     }
     __syncthreads();
-    const int n_pairs = ptr[PQ];
-    for (int b = w * 32; b < n_pairs; b += PW * 32) {        // bounds are the same in every lane
-        const int at = b + (lane & 31);
-        int i = 0;                                          // the last query that starts at or before `at`
-#pragma unroll
-        for (int step = PQ / 2; step > 0; step >>= 1) if (ptr[i + step] <= at) i += step;
+    const PairPlace n_pairs = ptr[PQ];
+    for (PairPlace b = w * 32; b < n_pairs; b += PW * 32) {  // bounds are the same in every lane
+        const PairPlace at = b + (lane & 31);
+        const int i = query_at(ptr, at);
         int32_t e = -1;
         if (at < n_pairs) {
             e = ft.val[q0 + i >= n_test ? 1 : 0][bound[2 * i] + (at - ptr[i])];
@@ -759,6 +771,15 @@ extern "C" int kge_eval_rank_all_static(const kge_eval_filter *filter, const flo
     if (rc != KGE_OK) return rc;
     return rank_all(filter, H, n_entities, d, M, n_relations, test_h, test_r, test_t, n_test, ptr,
                     (size_t)KGE_EVAL_STATIC_BYTES, higher, equal, nullptr, nullptr, (hipStream_t)stream);
+}
+
+extern "C" int32_t kge_test_pair_query(const int64_t *n_known, int32_t n_queries, int64_t at, int64_t *n_pairs)
+{
+    if (!n_known || !n_pairs || n_queries < 1 || n_queries > PQ) return -1;
+    PairPlace ptr[PQ + 1] = {0};
+    for (int i = 0; i < PQ; ++i) ptr[i + 1] = ptr[i] + (PairPlace)(i < n_queries ? n_known[i] : 0);
+    *n_pairs = ptr[PQ];
+    return query_at(ptr, (PairPlace)at);
 }
 
 extern "C" int kge_eval_debug_scores(const float *H, int64_t n_entities, int32_t d, const float *M, int32_t n_relations,
