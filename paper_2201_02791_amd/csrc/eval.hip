@@ -159,7 +159,7 @@ constexpr int PQ = 32, PW = 8;             // queries and wavefronts of a block 
 // The known answers of a block's PQ queries laid end to end, query i's from place ptr[i] on: the query at place `at`.
 // A place past the last one (the rest of the last tile, whose rows are read all the same) has the block's first query: the
 // block may hold fewer than PQ.
-using PairPlace = int32_t;
+using PairPlace = int64_t;                  // 32 lists of up to 2^31 entities
 __host__ __device__ __forceinline__ int query_at(const PairPlace *ptr, PairPlace at)
 {
     int i = 0;                             // the last query that starts at or before `at`

@@ -24,3 +24,11 @@ def test_every_place_of_a_tile_names_a_query_of_the_block(kb, n_known):
             assert i == owner[at]
         else:                                   # no pair: its score is dropped, but the row is read
             assert 0 <= i < len(n_known), at
+
+
+@pytest.mark.parametrize("n_known", [[70_000_000] * 32, [2**31 - 1, 5], [3, 2**31 - 1, 0, 2**31 - 1]])
+def test_more_places_than_32_bits_count(kb, n_known):
+    starts = np.concatenate([[0], np.cumsum(n_known)])
+    for i, n in enumerate(n_known):
+        for at in (starts[i], starts[i] + n - 1) if n else ():
+            assert kb.pair_query_for_tests(n_known, int(at)) == (i, starts[-1])
