@@ -172,8 +172,9 @@ __host__ __device__ __forceinline__ int query_at(const PairPlace *ptr, PairPlace
 // above / exactly at them.  A block takes PQ queries.  Their answers are one matrix-core tile of 32 pairs; the known
 // answers of all its queries are laid end to end and cut into such tiles, dealt out over the block's wavefronts: most
 // lists hold a handful of entities (a tile of their own would be nearly empty) and a hub's hundreds are not one
-// wavefront's chain.  Bound by the splitting of the pairs' rows.  40,932 queries of the 14,541-entity graph at width 200:
-// 676 us with one wavefront and one tile per query and fp32 steps, 198 now (545 with
+// wavefront's chain.  A block's queries lie a grid apart: neighbours in a test file often share a hub, whose list is as long
+// for each of them.  Bound by the splitting of the pairs' rows.  40,932 queries of the 14,541-entity graph at width 200:
+// 676 us with one wavefront and one tile per query and fp32 steps, 200 now (545 with
 // conditions around the row loads: each then waits for the last).
 __global__ __launch_bounds__(64 * PW) void k_eval_pairs(const float *__restrict__ Q, const float *__restrict__ H,
                                                     int32_t d, int64_t nq, int64_t n_test,
@@ -187,21 +188,24 @@ __global__ __launch_bounds__(64 * PW) void k_eval_pairs(const float *__restrict_
     __shared__ int32_t gt_s[PQ], eq_s[PQ];
     __shared__ float thr[PQ];
     const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-    const int64_t q0 = (int64_t)blockIdx.x * PQ;
-    const int n_here = (int)(nq - q0 < PQ ? nq - q0 : PQ);
+    const int64_t step = gridDim.x;                         // the block's queries: blockIdx.x, and every step-th after it
+    auto query = [&](int i) { return (int64_t)blockIdx.x + i * step; };
+    const int n_here = (int)((nq - 1 - blockIdx.x) / step) + 1;
     if (t < 2 * PQ) {                                       // ends of the queries' ranges in the tables, by wavefront 0
         const int i = t >> 1;
         int64_t pos = 0;
         if (i < n_here) {
-            const int side = q0 + i >= n_test ? 1 : 0;
-            const int64_t base = ((int64_t)fixed[q0 + i] * ft.R + rel[q0 + i]) * ft.N;
+            const int64_t q = query(i);
+            const int side = q >= n_test ? 1 : 0;
+            const int64_t base = ((int64_t)fixed[q] * ft.R + rel[q]) * ft.N;
             pos = lower_bound_i64(ft.key[side], ft.n[side], (t & 1) ? base + ft.N : base);
         }
         bound[t] = pos;
     } else if (w == 1) {                                    // the answers' scores, by wavefront 1
         const int i = lane & 31;
-        const float s = pair_scores(Q + (q0 + (i < n_here ? i : 0)) * d, H, i < n_here ? answer[q0 + i] : -1, d, lane);
-        if (lane < n_here) { thr[lane] = s; s_answer[q0 + lane] = s; }
+        const int64_t q = query(i < n_here ? i : 0);
+        const float s = pair_scores(Q + q * d, H, i < n_here ? answer[q] : -1, d, lane);
+        if (lane < n_here) { thr[lane] = s; s_answer[q] = s; }
     } else if (w == 2 && lane < PQ) {
         gt_s[lane] = 0; eq_s[lane] = 0;
     }
@@ -217,19 +221,20 @@ __global__ __launch_bounds__(64 * PW) void k_eval_pairs(const float *__restrict_
     for (PairPlace b = w * 32; b < n_pairs; b += PW * 32) {  // bounds are the same in every lane
         const PairPlace at = b + (lane & 31);
         const int i = query_at(ptr, at);
+        const int64_t q = query(i);
         int32_t e = -1;
         if (at < n_pairs) {
-            e = ft.val[q0 + i >= n_test ? 1 : 0][bound[2 * i] + (at - ptr[i])];
-            if (e == answer[q0 + i]) e = -1;
+            e = ft.val[q >= n_test ? 1 : 0][bound[2 * i] + (at - ptr[i])];
+            if (e == answer[q]) e = -1;
         }
-        const float s = pair_scores(Q + (q0 + i) * d, H, e, d, lane);
+        const float s = pair_scores(Q + q * d, H, e, d, lane);
         if (lane < 32 && e >= 0) {
             if (s > thr[i]) atomicAdd(gt_s + i, 1);
             if (s == thr[i]) atomicAdd(eq_s + i, 1);
         }
     }
     __syncthreads();
-    if (t < n_here) { out_gt[q0 + t] = gt_s[t]; out_eq[q0 + t] = eq_s[t]; }
+    if (t < n_here) { out_gt[query(t)] = gt_s[t]; out_eq[query(t)] = eq_s[t]; }
 }
 
 // Candidate lists: one wavefront per query, LPR lanes per entity row (LPR * 4 >= min(d, 256) columns at a
@@ -612,6 +617,12 @@ int launch_count(const float *Q, int64_t nq, const float *H, int64_t N, int32_t 
     return launch_count_tiles<2, 1>(Q, nq, H, N, d, s_answer, cnt_gt, cnt_eq, dump, st);
 }
 
+// Queries per block of k_eval_pairs: the most that leave 1024 blocks (four of them fill a compute unit), but no fewer than a
+// block's wavefronts, so that long lists never get fewer wavefronts than queries.  2000 queries, half of them with
+// 50,000 known answers, d = 64: 2.1 ms; one wavefront per query 5.7; always 32 neighbouring queries per block 19.2.  200
+// queries with short lists at d = 200: 32 us, 48 with 32 per block.
+int64_t pair_queries(int64_t nq) { return nq >= 1024 * PQ ? PQ : nq >= 1024 * PW ? nq / 1024 : PW; }
+
 int rank_all(const kge_eval_filter *f, const float *H, int64_t N, int32_t d, const float *M, int32_t R,
              const int32_t *test_h, const int32_t *test_r, const int32_t *test_t, int64_t n_test, void *workspace,
              size_t ws_bytes, int32_t *higher, int32_t *equal, float *dump, float *dump_answer, hipStream_t st)
@@ -646,7 +657,7 @@ int rank_all(const kge_eval_filter *f, const float *H, int64_t N, int32_t d, con
             ft.key[sde] = f ? f->key[sde] : nullptr; ft.val[sde] = f ? f->val[sde] : nullptr; ft.n[sde] = f ? f->n[sde] : 0;
         }
         ft.N = N; ft.R = R;
-        k_eval_pairs<<<(unsigned)cdiv(nq, PQ), 64 * PW, 0, st>>>(Q, H, d, nq, n_test, fixed, rel, answer, ft,
+        k_eval_pairs<<<(unsigned)cdiv(nq, pair_queries(nq)), 64 * PW, 0, st>>>(Q, H, d, nq, n_test, fixed, rel, answer, ft,
                                                            dump_answer ? dump_answer : s, sub_gt, sub_eq);
         KGE_LAUNCH_CHECK();
     }

@@ -194,3 +194,19 @@ def test_empty_inputs_and_errors(kb):
         kb.EvalFilter(np.array([50], np.int32), np.array([0], np.int32), np.array([0], np.int32), 50, 2)
     with pytest.raises(kb.KgeError):          # d not a multiple of 4
         kb.eval_rank_all(dev(H[:, :6].copy()), dev(M[:, :6].copy()), dev(th), dev(tr), dev(tt))
+
+
+@pytest.mark.parametrize("n_test", [5, 4500, 9000, 17000])
+def test_every_number_of_queries_per_block(kb, n_test):
+    """The per-query kernel gives a block 8 to 32 queries by their number, a grid apart; a third of them share a hub."""
+    say("queries per block", n_test)
+    n, R, d = 150, 2, 8
+    H, M = integer_model(31, n, R, d)
+    th, tr, tt = triples(32, n, R, n_test)
+    tt[: n_test // 3] = 7; tr[: n_test // 3] = 0
+    kh, kr, kt = triples(33, n, R, 400)
+    kt[:100] = 7; kr[:100] = 0
+    hi, eq = gpu_rank_all(kb, H, M, (th, tr, tt), (kh, kr, kt), n, R)
+    whi, weq = ev.filtered_counts(H, M, th, tr, tt, (kh, kr, kt))
+    np.testing.assert_array_equal(hi.cpu().numpy(), whi)
+    np.testing.assert_array_equal(eq.cpu().numpy(), weq)
