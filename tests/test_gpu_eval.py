@@ -210,3 +210,9 @@ def test_every_number_of_queries_per_block(kb, n_test):
     whi, weq = ev.filtered_counts(H, M, th, tr, tt, (kh, kr, kt))
     np.testing.assert_array_equal(hi.cpu().numpy(), whi)
     np.testing.assert_array_equal(eq.cpu().numpy(), weq)
+
+
+@pytest.mark.parametrize("d", [32, 64, 128, 256, 260, 512, 516])
+def test_candidate_lists_around_full_widths(kb, d):
+    """Widths that fill a row's lanes (their loads have no condition) and the first ones past them."""
+    test_candidate_lists(kb, 21, d)
