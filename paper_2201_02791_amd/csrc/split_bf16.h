@@ -1,16 +1,19 @@
 // fp32 products on the bf16 matrix cores, for the kernels whose operands are fp32.
 //
-// An fp32 number is the exact sum of three bf16 numbers: its leading 8 significant bits, the next 8 and the last 8
-// (each part is cut off, not rounded, so the subtractions are exact and all parts have the number's sign).  Of the nine
-// products of two such sums the six largest are formed; the three left out are below 2^-24 of the product, less than
-// the rounding of one fp32 addition.  All six accumulate in fp32, 16 terms per v_mfma_f32_32x32x16_bf16, so a sum
-// is rounded 6 times per 16 terms where the fp32 instruction (v_mfma_f32_32x32x2_f32) rounds after every term or two.
+// An fp32 number is the exact sum of three bf16 numbers: it rounded to nearest, what is left rounded to nearest, and what
+// is left then.  What is left has either sign and at most half a unit of the part before: 2^-8 of the number and, after
+// the second part, 2^-17.  Of the nine products of two such sums the six largest are formed; the three left out are below
+// 2^-24 of the product, less than the rounding of one fp32 addition, and of either sign.  (Parts that are cut off instead
+// of rounded leave out up to 7.8 x 2^-24 of it, always towards zero.)  All six accumulate in fp32, 16 terms per
+// v_mfma_f32_32x32x16_bf16, so a sum is rounded 6 times per 16 terms where the fp32 instruction (v_mfma_f32_32x32x2_f32)
+// rounds after every term or two.
 //
 // Why: the fp32 instruction delivers 157 TFLOP/s on this chip and the bf16 one 2.5 PFLOP/s; a sixth of that is 417.
 //
-// What does not survive the split: infinities (inf - inf) and sums that leave the fp32 range on the way.  Both show as a
-// result that is not finite, and the kernels form such results again with the fp32 instruction.  Parts of numbers below
-// 2^-102 can fall under the smallest normal bf16 number; what is lost there is below 2^-126 in magnitude.
+// What does not survive the split: infinities (inf - inf), numbers that round to one (from 3.39e38 on) and sums that leave
+// the fp32 range on the way.  All show as a result that is not finite, and the kernels form such results again with the
+// fp32 instruction.  Conversion and matrix cores keep subnormal bf16 numbers; of a number below 2^-110 the last part can
+// fall under the smallest of them, and at most 2^-134 of it is lost.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -18,21 +21,26 @@
 typedef float split_floatx16 __attribute__((ext_vector_type(16)));
 typedef __bf16 split_bf16x8 __attribute__((ext_vector_type(8)));
 
-// the upper halves of two fp32 words as one word of two bf16 numbers (a first)
-__device__ __forceinline__ uint32_t split_pack(uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x07060302u); }
+typedef __bf16 split_bf16x2 __attribute__((ext_vector_type(2)));
+typedef float split_floatx2 __attribute__((ext_vector_type(2)));
+
+// two numbers rounded to nearest even as one word of two bf16 numbers (a first): v_cvt_pk_bf16_f32
+__device__ __forceinline__ uint32_t split_round(float a, float b)
+{
+    const split_floatx2 v = {a, b};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, split_bf16x2));
+}
 
 struct Split3 { uint32_t w[3]; };      // leading, middle and last parts of two numbers, packed
 
 __device__ __forceinline__ Split3 split_pair(float x, float y)
 {
-    const uint32_t xb = __float_as_uint(x), yb = __float_as_uint(y);
-    const float x1 = x - __uint_as_float(xb & 0xffff0000u), y1 = y - __uint_as_float(yb & 0xffff0000u);
-    const uint32_t x1b = __float_as_uint(x1), y1b = __float_as_uint(y1);
-    const float x2 = x1 - __uint_as_float(x1b & 0xffff0000u), y2 = y1 - __uint_as_float(y1b & 0xffff0000u);
     Split3 s;
-    s.w[0] = split_pack(xb, yb);
-    s.w[1] = split_pack(x1b, y1b);
-    s.w[2] = split_pack(__float_as_uint(x2), __float_as_uint(y2));
+    s.w[0] = split_round(x, y);
+    const float x1 = x - __uint_as_float(s.w[0] << 16), y1 = y - __uint_as_float(s.w[0] & 0xffff0000u);
+    s.w[1] = split_round(x1, y1);
+    const float x2 = x1 - __uint_as_float(s.w[1] << 16), y2 = y1 - __uint_as_float(s.w[1] & 0xffff0000u);
+    s.w[2] = split_round(x2, y2);
     return s;
 }
 
