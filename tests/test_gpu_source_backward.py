@@ -30,3 +30,18 @@ def test_long_edge_lists():
     got, want = layer(n, R, 1500, di, do, B, 0, H0, dH, V, a, W0)
     for k in want:
         assert np.abs(got[k] - want[k]).max() <= 10 * TOL * np.abs(want[k]).max(), k
+
+
+# an infinity in a gradient row: the dot products with it are infinite, also at widths that leave lanes of a row idle
+@pytest.mark.parametrize("do,B,msg", [(8, 2, 0), (12, 2, 0), (40, 3, 0), (72, 3, 0), (132, 2, 0), (200, 10, 0), (256, 3, 0),
+                                      (200, 10, 1), (96, 40, 1), (160, 33, 1)])
+def test_infinite_gradients_stay_infinite(do, B, msg):
+    n, R, di = 40, 3, 16
+    H0, dH, V, a, W0 = model(do, n, R, di, do, B)
+    H0, V = np.abs(H0), np.abs(V)               # P > 0: every term with the infinity has its sign
+    dH[7, 1] = np.inf
+    got, want = layer(n, R, 20 * n, di, do, B, 0, H0, dH, V, a, W0, msg)
+    hit = np.isinf(want["da"])
+    assert hit.any() and not np.isnan(want["da"]).any()
+    np.testing.assert_array_equal(got["da"][hit], want["da"][hit].astype(np.float32))
+    assert np.isfinite(got["da"][~hit]).all()
