@@ -66,6 +66,10 @@ struct kge_partition {
     // small graphs fewer runs
     int32_t n_relc;
     int32_t *relc_rel, *relc_beg, *relc_end;
+    // and into chunks of KGE_REL_CHUNK .. 8 KGE_REL_CHUNK runs, in small graphs about KGE_REL_WIDE_DIV: for a kernel that
+    // adds more than 128 x 128 sums to the relation's matrix at the end of each
+    int32_t n_relw;
+    int32_t *relw_rel, *relw_beg, *relw_end;
     // and into row tiles of at most KGE_REL_TILE runs
     int32_t n_relt;
     int32_t *relt_rel, *relt_beg, *relt_end;
@@ -90,6 +94,7 @@ struct kge_partition {
 };
 #define KGE_REL_CHUNK 2048
 #define KGE_REL_CHUNK_DIV 512
+#define KGE_REL_WIDE_DIV 64
 #define KGE_REL_TILE 128
 #define KGE_REL_RANGE 4096
 // vertices per slab of the destination range by which those ranges are ordered

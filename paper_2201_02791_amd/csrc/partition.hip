@@ -530,15 +530,16 @@ int build_impl(const int32_t *h_head, const int32_t *h_rel, const int32_t *h_tai
         KGE_HIP(hipMemcpy(h_rel_ptr.data(), p->rel_ptr, sizeof(int32_t) * (size_t)(R2 + 1), hipMemcpyDeviceToHost));
         // chunk length: about 2048 chunks over all runs (every chunk ends in one atomic accumulation of a
         // whole d_in x d_out tile, so fewer, longer chunks are cheaper as long as the chip stays full)
-        int32_t chunk = (int32_t)((S / 2048 + 31) / 32 * 32);
+        const int32_t whole = (int32_t)((S / 2048 + 31) / 32 * 32);
         // a small graph: about 512 chunks, down to 64 runs each, or a few blocks walk what there is while the chip idles
         // (fp32 rel_outer: 10 k runs at width 32 52 -> 8 us, 352 k at 200 384 -> 335, 580 k at 128 x 32 183 -> 98; about 256
-        // chunks: 8, 317, 159; 128: 8, 358, 160)
-        int32_t least = (int32_t)((S / KGE_REL_CHUNK_DIV + 31) / 32 * 32);
-        if (least < 64) least = 64;
-        if (least > KGE_REL_CHUNK) least = KGE_REL_CHUNK;
-        if (chunk < least) chunk = least;
-        if (chunk > 8 * KGE_REL_CHUNK) chunk = 8 * KGE_REL_CHUNK;
+        // chunks: 8, 317, 159; 128: 8, 358, 160).  Where a chunk ends in more than 128 x 128 sums (bf16 rel_outer at 256 x 256)
+        // about 64: 40 k runs 57 us in chunks of 2048, 113 in 512 of them, 35 now (128: 46, 32: 41); 400 k runs 97, 141, 99
+        auto chunk_of = [&](int64_t div) {
+            const int32_t least = (int32_t)std::min<int64_t>(KGE_REL_CHUNK, std::max<int64_t>(64, (S / div + 31) / 32 * 32));
+            return std::min(8 * KGE_REL_CHUNK, std::max(whole, least));
+        };
+        const int32_t chunk = chunk_of(KGE_REL_CHUNK_DIV), wide = chunk_of(KGE_REL_WIDE_DIV);
         // and into row tiles of at most KGE_REL_TILE runs (one output tile of the per-relation products)
         for (int64_t r = 0; r < R2; ++r)
             for (int32_t b = h_rel_ptr[r]; b < h_rel_ptr[r + 1]; b += KGE_REL_TILE) {
@@ -584,11 +585,25 @@ int build_impl(const int32_t *h_head, const int32_t *h_rel, const int32_t *h_tai
         };
         // the chunks keep the plain order, relation by relation: cut by slab they made the relation matrices'
         // gradient slower (4.23 against 3.9 ms per launch at 25 M runs)
-        for (int64_t r = 0; r < R2; ++r)
-            for (int32_t b = h_rel_ptr[r]; b < h_rel_ptr[r + 1]; b += chunk) {
-                c_rel.push_back((int32_t)r); c_beg.push_back(b);
-                c_end.push_back(b + chunk < h_rel_ptr[r + 1] ? b + chunk : h_rel_ptr[r + 1]);
+        auto cut = [&](int32_t piece, std::vector<int32_t> &o_rel, std::vector<int32_t> &o_beg, std::vector<int32_t> &o_end) {
+            for (int64_t r = 0; r < R2; ++r)
+                for (int32_t b = h_rel_ptr[r]; b < h_rel_ptr[r + 1]; b += piece) {
+                    o_rel.push_back((int32_t)r); o_beg.push_back(b);
+                    o_end.push_back(b + piece < h_rel_ptr[r + 1] ? b + piece : h_rel_ptr[r + 1]);
+                }
+        };
+        cut(chunk, c_rel, c_beg, c_end);
+        {
+            std::vector<int32_t> w_rel, w_beg, w_end;
+            cut(wide, w_rel, w_beg, w_end);
+            p->n_relw = (int32_t)w_rel.size();
+            TRY(palloc(&p->relw_rel, w_rel.size())); TRY(palloc(&p->relw_beg, w_rel.size())); TRY(palloc(&p->relw_end, w_rel.size()));
+            if (!w_rel.empty()) {
+                KGE_HIP(hipMemcpy(p->relw_rel, w_rel.data(), sizeof(int32_t) * w_rel.size(), hipMemcpyHostToDevice));
+                KGE_HIP(hipMemcpy(p->relw_beg, w_beg.data(), sizeof(int32_t) * w_beg.size(), hipMemcpyHostToDevice));
+                KGE_HIP(hipMemcpy(p->relw_end, w_end.data(), sizeof(int32_t) * w_end.size(), hipMemcpyHostToDevice));
             }
+        }
         {
             std::vector<int32_t> g_rel, g_beg, g_end;
             slab_ordered(KGE_REL_RANGE, g_rel, g_beg, g_end);
@@ -671,7 +686,7 @@ extern "C" void kge_partition_destroy(kge_partition *p)
                     p->hv_sm.hv_row, p->hv_sm.hv_unit_ptr, p->hv_sm.unit_hv,
                     p->hv_seg.hv_row, p->hv_seg.hv_unit_ptr, p->hv_seg.unit_hv,
                     p->dr_ptr, p->dr_seg, p->dr_rel, p->hv_dr.hv_row, p->hv_dr.hv_unit_ptr, p->hv_dr.unit_hv,
-                    p->relc_rel, p->relc_beg, p->relc_end, p->sm_seg, p->relt_rel, p->relt_beg, p->relt_end,
+                    p->relc_rel, p->relc_beg, p->relc_end, p->relw_rel, p->relw_beg, p->relw_end, p->sm_seg, p->relt_rel, p->relt_beg, p->relt_end,
                     p->relr_rel, p->relr_beg, p->relr_end, p->rels_rel, p->rels_beg, p->rels_end, p->seg_zrow, p->mrun,
                     p->bad_ids};
     for (void *q : arrs) if (q) (void)hipFree(q);

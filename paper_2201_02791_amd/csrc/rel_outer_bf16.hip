@@ -260,7 +260,9 @@ int launch_rel_outer_rows_bf16(const kge_partition *p, const void *X, int64_t ld
                                int64_t ldg, int32_t d_in, int32_t d_out, float *C, hipStream_t st)
 {
     if (p->n_relc == 0) return KGE_OK;
-    const OuterArgs a{X, ldx, xidx, G, ldg, p->seg_dst, p->relc_rel, p->relc_beg, p->relc_end, p->n_relc, C, 0, 0, 0, nullptr};
+    const bool wide = d_in * d_out > 128 * 128;
+    const OuterArgs a{X, ldx, xidx, G, ldg, p->seg_dst, wide ? p->relw_rel : p->relc_rel, wide ? p->relw_beg : p->relc_beg,
+                      wide ? p->relw_end : p->relc_end, wide ? p->n_relw : p->n_relc, C, 0, 0, 0, nullptr};
     return launch_any(a, d_in, d_out, st);
 }
 
