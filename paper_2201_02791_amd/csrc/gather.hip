@@ -380,7 +380,10 @@ __global__ __launch_bounds__(64 * WPB) void k_source_backward(
             const float *ar = a + (int64_t)cur_rel * B;
             // a lane past the width has read column 0, and an infinity there times its zero of P would be NaN (a condition
             // around the loads instead: 1 to 2 % slower at all widths)
-            if (4 * LPR != d && !kact) y = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (4 * LPR != d) {
+                asm volatile("");                        // stays a branch: selects for every width are 1 % of the kernel
+                if (!kact) y = make_float4(0.f, 0.f, 0.f, 0.f);
+            }
             float part[NB];
 #pragma unroll
             for (int n = 0; n < NB; ++n) {
