@@ -739,11 +739,21 @@ __global__ __launch_bounds__(256) void k_distmult_gather(
     const int32_t end = ent_ptr[e0 + n_ent], begin = __builtin_amdgcn_readlane(my_ptr, 0);
     const int32_t lo = begin + (int32_t)((int64_t)(end - begin) * w / 4), hi = begin + (int32_t)((int64_t)(end - begin) * (w + 1) / 4);
     auto start_of = [&](int e) { return e < 64 ? __builtin_amdgcn_readlane(my_ptr, e) : end; };
-    // the entity being summed: for the first wavefront the block's first, for the others the one that holds `lo` (those
-    // that end at or before `lo` are the wavefront before's)
     int32_t next_ptr = __shfl_down(my_ptr, 1, 64);       // every lane takes part
     if (lane == 63) next_ptr = end;
-    int cur = w == 0 ? 0 : __popcll(__ballot(lane < n_ent && next_ptr <= lo));
+    // the rows of entities without occurrences are dealt out over the wavefronts whatever the shares, which say nothing
+    // about them: with few occurrences they are all there is to do (1 M entities, 36 k occurrences, d = 128: 128 us when the
+    // wavefront that came past them wrote them, 96 now)
+    const uint64_t named = __ballot(lane < n_ent && next_ptr > my_ptr);
+    for (int e = w; e < n_ent; e += 4)
+        if (!(named >> e & 1))
+#pragma unroll
+            for (int u = 0; u < NV; ++u)
+                if (ok[u]) dH[(e0 + e) * d4 + lane + 64 * u] = zero4;
+    // the entity being summed, at first the one that holds `lo` (those that end at or before `lo` are the wavefront
+    // before's)
+    auto named_from = [&](int e) { return e < 64 && named >> e ? e + __builtin_ctzll(named >> e) : n_ent; };
+    int cur = named_from(__popcll(__ballot(lane < n_ent && next_ptr <= lo)));
     int32_t boundary = start_of(cur + 1);          // where the next one starts
     int flags = 0;
     auto close_entity = [&]() {
@@ -758,7 +768,7 @@ __global__ __launch_bounds__(256) void k_distmult_gather(
         }
 #pragma unroll
         for (int u = 0; u < NV; ++u) acc[u] = zero4;
-        ++cur;
+        cur = named_from(cur + 1);
         boundary = start_of(cur + 1);
     };
     const uint32_t per = (uint32_t)n_neg + 2;
@@ -807,7 +817,7 @@ __global__ __launch_bounds__(256) void k_distmult_gather(
 #pragma unroll
             for (int z = 0; z < 4; ++z) {
                 if (j0 + z >= cnt) break;
-                while (base + j0 + z >= boundary) close_entity();       // uniform: entities without occurrences too
+                if (base + j0 + z >= boundary) close_entity();          // uniform
 #pragma unroll
                 for (int u = 0; u < NV; ++u) {
                     acc[u].x = fmaf(wj[z] * b[z][u].x, a[z][u].x, acc[u].x);
@@ -818,7 +828,7 @@ __global__ __launch_bounds__(256) void k_distmult_gather(
             }
         }
     }
-    while (cur < n_ent && boundary <= hi) close_entity();
+    if (cur < n_ent && boundary <= hi) close_entity();
     if (cur < n_ent && start_of(cur) < hi) {       // it goes on in the next wavefront
         flags |= start_of(cur) < lo ? 6 : 2;
 #pragma unroll
