@@ -762,8 +762,12 @@ int launch_rel_outer_bf16(const kge_partition *p, const void *Zbf, const int32_t
     MatBF Bm{reinterpret_cast<const uint16_t *>(Gbf), p->n_seg, d_out, ldg, p->seg_dst};
     EpiRelOuterAtomic ep{C, d_in, d_out, 0};
     KGE_PROF("rel_outer", st);
-    return launch_gemm<false, EpiRelOuterAtomic>(A, Bm, ep, p->n_seg, 0, tiles_m, tiles_n, p->n_relc, st,
-                                                 p->relc_rel, p->relc_beg, p->relc_end);
+    // more than 256 x 256 sums per chunk: fewer chunks (264 x 512, 40 k runs: 53 us, 188 with the short ones; 350 k runs of
+    // 474 relations 298, 380).  200 x 200 is mixed: 39, 96 and 198, 151
+    const bool wide = d_in * d_out > 256 * 256;
+    return launch_gemm<false, EpiRelOuterAtomic>(A, Bm, ep, p->n_seg, 0, tiles_m, tiles_n, wide ? p->n_relw : p->n_relc, st,
+                                                 wide ? p->relw_rel : p->relc_rel, wide ? p->relw_beg : p->relc_beg,
+                                                 wide ? p->relw_end : p->relc_end);
 }
 
 // Wb[r][k][n] and WbT[r][n][k] = bf16(sum_b a[r][b] V[b][k][n]): Eq. 2 written out for every relation, summed in
