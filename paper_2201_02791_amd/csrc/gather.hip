@@ -15,6 +15,8 @@
 // GE = groups / GB across edges.
 #include "common.h"
 
+#include <type_traits>
+
 namespace {
 
 constexpr int WPB = 4;                 // wavefronts per block
@@ -323,7 +325,7 @@ template <int K, int LPR, int OFF = 1> __device__ __forceinline__ float sums_ove
     }
 }
 
-template <bool BF16, int LPR, int NB, bool DP>
+template <bool BF16, int LPR, int NB, bool DP, bool FULL>
 __global__ __launch_bounds__(64 * WPB) void k_source_backward(
     const int32_t *__restrict__ sm_ptr, const int32_t *__restrict__ sm_dst, const int32_t *__restrict__ sm_rel,
     const float *__restrict__ sm_invc, const int32_t *__restrict__ sm_seg, int64_t N,
@@ -379,11 +381,8 @@ __global__ __launch_bounds__(64 * WPB) void k_source_backward(
         auto flush = [&]() __attribute__((always_inline)) {
             const float *ar = a + (int64_t)cur_rel * B;
             // a lane past the width has read column 0, and an infinity there times its zero of P would be NaN (a condition
-            // around the loads instead: 1 to 2 % slower at all widths)
-            if (4 * LPR != d) {
-                asm volatile("");                        // stays a branch: selects for every width are 1 % of the kernel
-                if (!kact) y = make_float4(0.f, 0.f, 0.f, 0.f);
-            }
+            // around the loads instead: 1 to 2 % slower at all widths).  FULL: there is none
+            if (!FULL && !kact) y = make_float4(0.f, 0.f, 0.f, 0.f);
             float part[NB];
 #pragma unroll
             for (int n = 0; n < NB; ++n) {
@@ -1031,9 +1030,13 @@ static int launch_source_backward_nb(const kge_partition *p, const float *G, con
     const int64_t blocks = cdiv((p->n_vert + hx.n_units) * n_chunks, WPB);
     KGE_REQUIRE(blocks < 0x7fffffffLL, KGE_ERANGE, "grid too large");
     KGE_PROF(DP ? "gather_t" : "coeff_seg", st);
-    k_source_backward<BF16, LPR, NB, DP><<<(unsigned)blocks, 64 * WPB, 0, st>>>(
-        p->sm_ptr, p->sm_dst, p->sm_rel, p->sm_invc, p->sm_seg, p->n_vert, hx.n_units, hx.hv_row, hx.hv_unit_ptr, hx.unit_hv, G, a,
-        P, B, d, n_chunks, dP, ld, partial, seg_scratch, active);
+    auto run = [&](auto full) {
+        k_source_backward<BF16, LPR, NB, DP, decltype(full)::value><<<(unsigned)blocks, 64 * WPB, 0, st>>>(
+            p->sm_ptr, p->sm_dst, p->sm_rel, p->sm_invc, p->sm_seg, p->n_vert, hx.n_units, hx.hv_row, hx.hv_unit_ptr, hx.unit_hv, G, a,
+            P, B, d, n_chunks, dP, ld, partial, seg_scratch, active);
+    };
+    if (d == 4 * LPR) run(std::true_type{});
+    else run(std::false_type{});
     KGE_LAUNCH_CHECK();
     return KGE_OK;
 }
