@@ -297,6 +297,8 @@ __global__ void k_act_backward(const float4 *__restrict__ dH, const float4 *__re
 // relation's rows), after a chunk of 64 edges, so that no atomic stands between the gathered loads.
 // A row is covered by LPR lanes of 4 columns, the 64 / LPR lane groups take NB bases each (16 per wavefront at most).
 // DP = false: the dot products only (dP comes from the matrix-core kernel below).
+// SPREAD: with few bases and narrow rows most lane groups would hold no base; they share a relation's edges instead, all of
+// them with the same NB bases, and their sums meet in a butterfly per relation.
 // Bound by the vector instructions of the groups (most sources have one edge of a relation), the rows coming from the
 // caches.  544 k edges, 10 bases, d = 200, fp32: 361 us, where one kernel per gradient took 728 + 425; 2 M edges, 16 bases,
 // d = 128, bf16 messages: 748 against 1125 + 867.
@@ -325,7 +327,7 @@ template <int K, int LPR, int OFF = 1> __device__ __forceinline__ float sums_ove
     }
 }
 
-template <bool BF16, int LPR, int NB, bool DP, bool FULL>
+template <bool BF16, int LPR, int NB, bool DP, bool SPREAD, bool FULL>
 __global__ __launch_bounds__(64 * WPB) void k_source_backward(
     const int32_t *__restrict__ sm_ptr, const int32_t *__restrict__ sm_dst, const int32_t *__restrict__ sm_rel,
     const float *__restrict__ sm_invc, const int32_t *__restrict__ sm_seg, int64_t N,
@@ -334,7 +336,7 @@ __global__ __launch_bounds__(64 * WPB) void k_source_backward(
     const void *__restrict__ P, int32_t B, int32_t d, int32_t n_chunks, void *__restrict__ dP, int64_t ld,
     float *__restrict__ partial, float *__restrict__ seg_out, const uint8_t *__restrict__ active)
 {
-    constexpr int NG = 64 / LPR, NBT = NG * NB, U = 4;
+    constexpr int NG = 64 / LPR, NBT = SPREAD ? NB : NG * NB, U = 4;
     constexpr int KA = NB == 12 ? 8 : NB, KB = NB == 12 ? 4 : 0;      // dot products reduced together
     __shared__ float dots[WPB][64][NBT];
     __shared__ int32_t dot_seg[WPB][64];
@@ -344,7 +346,7 @@ __global__ __launch_bounds__(64 * WPB) void k_source_backward(
     const int b0 = (int)(wid_all - wid * n_chunks) * NBT;
     const RowWork rw = row_work(wid, sm_ptr, N, n_units, hv_row, hv_unit_ptr, unit_hv);
     if (rw.row < 0) return;                              // whole wavefronts leave; the kernel has no block barrier
-    const int kl = lane % LPR, g = lane / LPR;
+    const int kl = lane % LPR, g = lane / LPR, first_b = SPREAD ? 0 : g * NB;      // of this lane's bases in the chunk
     const bool kact = kl * 4 < d;
     const int col = kact ? kl * 4 : 0;
     const int nbs = B - b0 < NBT ? B - b0 : NBT;         // bases of this chunk
@@ -352,7 +354,7 @@ __global__ __launch_bounds__(64 * WPB) void k_source_backward(
     float pv[NB][4], acc[NB][4];
 #pragma unroll
     for (int n = 0; n < NB; ++n) {
-        const int b = b0 + g * NB + n;
+        const int b = b0 + first_b + n;
         const int64_t o = (rw.row * B + (b < B ? b : B - 1)) * d + col;
         float4 x;
         if (BF16) {
@@ -383,55 +385,98 @@ __global__ __launch_bounds__(64 * WPB) void k_source_backward(
             // a lane past the width has read column 0, and an infinity there times its zero of P would be NaN (a condition
             // around the loads instead: 1 to 2 % slower at all widths).  FULL: there is none
             if (!FULL && !kact) y = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (SPREAD)                                  // the lane groups' shares of the edges
+#pragma unroll
+                for (int off = LPR; off < 64; off <<= 1) {
+                    y.x += __shfl_xor(y.x, off, 64); y.y += __shfl_xor(y.y, off, 64);
+                    y.z += __shfl_xor(y.z, off, 64); y.w += __shfl_xor(y.w, off, 64);
+                }
             float part[NB];
 #pragma unroll
             for (int n = 0; n < NB; ++n) {
                 if (DP) {
                     float c = ar[min(b0 + n, B - 1)];    // scalar loads: every lane group's coefficients, then its own
 #pragma unroll
-                    for (int h = 1; h < NG; ++h) c = g == h ? ar[min(b0 + h * NB + n, B - 1)] : c;
+                    for (int h = 1; h < NG && !SPREAD; ++h) c = g == h ? ar[min(b0 + h * NB + n, B - 1)] : c;
                     acc[n][0] = fmaf(c, y.x, acc[n][0]); acc[n][1] = fmaf(c, y.y, acc[n][1]);
                     acc[n][2] = fmaf(c, y.z, acc[n][2]); acc[n][3] = fmaf(c, y.w, acc[n][3]);
                 }
                 part[n] = fmaf(pv[n][3], y.w, fmaf(pv[n][2], y.z, fmaf(pv[n][1], y.y, pv[n][0] * y.x)));
             }
             const float s = sums_over_lanes<KA, LPR>(part, lane);
-            if (kl < KA) dots[wv][n_grp][g * NB + kl] = s;
+            if (kl < KA && (!SPREAD || g == 0)) dots[wv][n_grp][first_b + kl] = s;
             if constexpr (KB > 0) {
                 const float s2 = sums_over_lanes<KB, LPR>(part + KA, lane);
-                if (kl < KB) dots[wv][n_grp][g * NB + KA + kl] = s2;
+                if (kl < KB) dots[wv][n_grp][first_b + KA + kl] = s2;
             }
             if (lane == 0) dot_seg[wv][n_grp] = cur_seg;
             ++n_grp;
         };
-        float4 nxt[U];
-        auto fetch = [&](int q0) __attribute__((always_inline)) {
+        if constexpr (SPREAD) {
+            const bool live = lane < cnt && my_dst >= 0;
+            const uint64_t lives = __ballot(live);
+            const int32_t before = __shfl_up(my_rel, 1, 64);
+            uint64_t starts = __ballot(lane < cnt && (lane == 0 || my_rel != before));
+            while (starts) {                             // uniform: one relation's edges [s, t) of the chunk
+                const int s = __builtin_ctzll(starts);
+                starts &= starts - 1;
+                const int t = starts ? __builtin_ctzll(starts) : cnt;
+                if (!(lives >> s & (t - s == 64 ? ~0ull : (1ull << (t - s)) - 1ull))) continue;
+                cur_rel = __builtin_amdgcn_readlane(my_rel, s);
+                cur_seg = __builtin_amdgcn_readlane(my_seg, s);
+                y = make_float4(0.f, 0.f, 0.f, 0.f);
+                for (int q0 = s; q0 < t; q0 += NG * U) {
+                    float4 row[U];
+                    float w[U];
+                    bool on[U];
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int32_t dst = __builtin_amdgcn_readlane(my_dst, min(q0 + u, cnt - 1));
-                nxt[u] = *reinterpret_cast<const float4 *>(G + (int64_t)(dst < 0 ? 0 : dst) * d + col);
-            }
-        };
-        fetch(0);
-        for (int q0 = 0; q0 < cnt; q0 += U) {
-            float4 row[U];
+                    for (int u = 0; u < U; ++u) {        // a slot past the end or outside the sub-graph: a row that is dropped
+                        const int el = min(q0 + u * NG + g, t - 1);
+                        const int32_t dst = __shfl(my_dst, el, 64);
+                        on[u] = q0 + u * NG + g < t && dst >= 0 && kact;
+                        w[u] = __shfl(my_w, el, 64);
+                        row[u] = *reinterpret_cast<const float4 *>(G + (int64_t)(dst < 0 ? 0 : dst) * d + col);
+                    }
 #pragma unroll
-            for (int u = 0; u < U; ++u) row[u] = nxt[u];
-            fetch(q0 + U);                               // past the chunk: its last edge again
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int el = q0 + u;
-                if (el >= cnt || __builtin_amdgcn_readlane(my_dst, el) < 0) continue;
-                const int32_t rel = __builtin_amdgcn_readlane(my_rel, el);
-                const float w = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(my_w), el));
-                if (rel != cur_rel) {
-                    if (cur_rel >= 0) flush();
-                    cur_rel = rel;
-                    cur_seg = __builtin_amdgcn_readlane(my_seg, el);
-                    y = make_float4(0.f, 0.f, 0.f, 0.f);
+                    for (int u = 0; u < U; ++u) {
+                        if (!on[u]) row[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+                        y.x = fmaf(w[u], row[u].x, y.x); y.y = fmaf(w[u], row[u].y, y.y);
+                        y.z = fmaf(w[u], row[u].z, y.z); y.w = fmaf(w[u], row[u].w, y.w);
+                    }
                 }
-                y.x = fmaf(w, row[u].x, y.x); y.y = fmaf(w, row[u].y, y.y);
-                y.z = fmaf(w, row[u].z, y.z); y.w = fmaf(w, row[u].w, y.w);
+                flush();
+                cur_rel = -1;
+            }
+        } else {
+            float4 nxt[U];
+            auto fetch = [&](int q0) __attribute__((always_inline)) {
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int32_t dst = __builtin_amdgcn_readlane(my_dst, min(q0 + u, cnt - 1));
+                    nxt[u] = *reinterpret_cast<const float4 *>(G + (int64_t)(dst < 0 ? 0 : dst) * d + col);
+                }
+            };
+            fetch(0);
+            for (int q0 = 0; q0 < cnt; q0 += U) {
+                float4 row[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) row[u] = nxt[u];
+                fetch(q0 + U);                               // past the chunk: its last edge again
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int el = q0 + u;
+                    if (el >= cnt || __builtin_amdgcn_readlane(my_dst, el) < 0) continue;
+                    const int32_t rel = __builtin_amdgcn_readlane(my_rel, el);
+                    const float w = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(my_w), el));
+                    if (rel != cur_rel) {
+                        if (cur_rel >= 0) flush();
+                        cur_rel = rel;
+                        cur_seg = __builtin_amdgcn_readlane(my_seg, el);
+                        y = make_float4(0.f, 0.f, 0.f, 0.f);
+                    }
+                    y.x = fmaf(w, row[u].x, y.x); y.y = fmaf(w, row[u].y, y.y);
+                    y.z = fmaf(w, row[u].z, y.z); y.w = fmaf(w, row[u].w, y.w);
+                }
             }
         }
         if (cur_rel >= 0) flush();
@@ -442,10 +487,10 @@ __global__ __launch_bounds__(64 * WPB) void k_source_backward(
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     }
-    if (!DP || !kact) return;
+    if (!DP || !kact || (SPREAD && g != 0)) return;
 #pragma unroll
     for (int n = 0; n < NB; ++n) {
-        const int b = b0 + g * NB + n;
+        const int b = b0 + first_b + n;
         if (b >= B) continue;
         if (rw.unit >= 0) {
             *reinterpret_cast<float4 *>(partial + ((int64_t)rw.unit * B + b) * d + kl * 4) =
@@ -1021,32 +1066,48 @@ static int launch_gather_t_finish(const kge_partition *p, const float *partial, 
     return KGE_OK;
 }
 
-template <bool BF16, int LPR, int NB, bool DP>
+template <bool BF16, int LPR, int NB, bool DP, bool SPREAD = false>
 static int launch_source_backward_nb(const kge_partition *p, const float *G, const float *a, const void *P, int32_t B, int32_t d,
                                      void *dP, int64_t ld, float *partial, float *seg_scratch, const uint8_t *active, hipStream_t st)
 {
     const kge_heavy_index &hx = p->hv_sm;
-    const int n_chunks = (int)cdiv(B, 64 / LPR * NB);
+    const int n_chunks = (int)cdiv(B, SPREAD ? NB : 64 / LPR * NB);
     const int64_t blocks = cdiv((p->n_vert + hx.n_units) * n_chunks, WPB);
     KGE_REQUIRE(blocks < 0x7fffffffLL, KGE_ERANGE, "grid too large");
     KGE_PROF(DP ? "gather_t" : "coeff_seg", st);
     auto run = [&](auto full) {
-        k_source_backward<BF16, LPR, NB, DP, decltype(full)::value><<<(unsigned)blocks, 64 * WPB, 0, st>>>(
+        k_source_backward<BF16, LPR, NB, DP, SPREAD, decltype(full)::value><<<(unsigned)blocks, 64 * WPB, 0, st>>>(
             p->sm_ptr, p->sm_dst, p->sm_rel, p->sm_invc, p->sm_seg, p->n_vert, hx.n_units, hx.hv_row, hx.hv_unit_ptr, hx.unit_hv, G, a,
             P, B, d, n_chunks, dP, ld, partial, seg_scratch, active);
     };
-    if (d == 4 * LPR) run(std::true_type{});
+    if (SPREAD || d == 4 * LPR) run(std::true_type{});
     else run(std::false_type{});
     KGE_LAUNCH_CHECK();
     return KGE_OK;
 }
 
-// the fewest bases per lane that cover B in one chunk, 16 per wavefront at most; the dot products alone: always those 16
+// the fewest bases per lane that cover B in one chunk, 16 per wavefront at most; the dot products alone: always those 16.
+// At most 4 bases of rows of at most 16 lanes, six edges or more per relation of a source on average: shared edges (2 M
+// edges of 20,000 sources, one relation: d = 16, 2 bases 128 -> 65 us, d = 64, 4 bases 131 -> 74; 6.3 edges per relation:
+// 141 -> 114 and 146 -> 144; 4.2 edges: 152 -> 161 and 160 -> 200).
 template <bool BF16, bool DP>
 static int launch_source_backward(const kge_partition *p, const float *G, const float *a, const void *P, int32_t B, int32_t d,
                                   void *dP, int64_t ld, float *partial, float *seg_scratch, const uint8_t *active, hipStream_t st)
 {
 #define SB_CALL(LPRV, NBV) return launch_source_backward_nb<BF16, LPRV, NBV, DP>(p, G, a, P, B, d, dP, ld, partial, seg_scratch, active, st)
+    if constexpr (DP)
+        if (d <= 64 && B <= 4 && p->n_edge >= 6 * p->n_seg) {      // lane groups without a basis, and edges to share
+#define SB_SPREAD(LPRV, NBV) return launch_source_backward_nb<BF16, LPRV, NBV, DP, true>(p, G, a, P, B, d, dP, ld, partial, seg_scratch, active, st)
+            if (d > 32) {
+                if (B == 1) SB_SPREAD(16, 1);
+                if (B == 2) SB_SPREAD(16, 2);
+                SB_SPREAD(16, 4);
+            }
+            if (B == 1) SB_SPREAD(8, 1);
+            if (B == 2) SB_SPREAD(8, 2);
+            SB_SPREAD(8, 4);
+#undef SB_SPREAD
+        }
     if (d > 128) {
         if constexpr (DP) {
             if (B <= 2) SB_CALL(64, 2);

@@ -45,3 +45,38 @@ def test_infinite_gradients_stay_infinite(do, B, msg):
     assert hit.any() and not np.isnan(want["da"]).any()
     np.testing.assert_array_equal(got["da"][hit], want["da"][hit].astype(np.float32))
     assert np.isfinite(got["da"][~hit]).all()
+
+
+# few bases, narrow rows and many edges per relation of a source: the lane groups share the edges (every width / base-count
+# class of that form; 200 or 600 edges per source, the latter in units of 256), an infinity among them as above
+@pytest.mark.parametrize("msg", [0, 1])
+@pytest.mark.parametrize("n,do,B", [(30, 8, 1), (10, 16, 2), (30, 24, 3), (10, 32, 4), (30, 40, 1), (10, 56, 2), (30, 64, 4), (1, 8, 2)])
+def test_edges_shared_by_lane_groups(n, do, B, msg):
+    R, di = 2, 16
+    H0, dH, V, a, W0 = model(do + B, n, R, di, do, B)
+    m = 100 * n if n == 30 else 600 * n
+    got, want = layer(n, R, m, di, do, B, 0, H0, dH, V, a, W0, msg)
+    for k in want:
+        tol = 2e-2 if msg else 10 * TOL
+        assert np.abs(got[k] - want[k]).max() <= tol * np.abs(want[k]).max(), k
+    if n > 1:
+        dH[n // 2, 1] = np.inf
+        got, want = layer(n, R, m, di, do, B, 0, np.abs(H0), dH, np.abs(V), a, W0, msg)
+        hit = np.isinf(want["da"])
+        assert hit.any()
+        np.testing.assert_array_equal(got["da"][hit], want["da"][hit].astype(np.float32))
+
+
+@pytest.mark.parametrize("d,B", [(16, 2), (36, 3), (64, 1)])
+def test_shared_edges_on_a_batch_s_sub_graph(orc, d, B):
+    """One positive: of the 100 edges per relation of a source, the last layer takes those into two vertices."""
+    from paper_2201_02791_amd import synth
+    from gpu_util import assert_step_close, gpu_step, oracle_step
+    n, R, m = 60, 2, 6000
+    spec = synth.scaled(synth.WORKLOADS[0], name="dense", seed=3, n_entities=n, n_relations=R, n_triples=m, d=d, n_bases=B,
+                        n_pos=1, n_neg=0, n_parts=1, part_id=0, acts=[0, 0])
+    rng = np.random.default_rng(d)
+    head, rel, tail = (rng.integers(0, k, m).astype(np.int32) for k in (n, R, n))
+    gp, ts, params, pos = gpu_step(spec, head, rel, tail, cone=True)
+    op, res = oracle_step(orc, spec, head, rel, tail, params, pos)
+    assert_step_close(ts, res, 1e-5, 1e-4, batch_rows=orc.batch_vertices(op, pos, res["neg_ent"]))
