@@ -690,9 +690,9 @@ int basis_grad_groups(const float *a, int32_t R2, int32_t B, int32_t &b_done, co
 }  // namespace
 
 // dV_b = sum_r a[r][b] C[r]   (the chain rule on Wrel[r] = sum_b a[r][b] V_b with dWrel = C)
-// Many bases (a multiple of 4: the operand loads take pairs of them) and columns: a product on the matrix cores, a^T C,
-// that reads C once: 2000 relations x 65,536 columns with 64 bases 188 us, 359 on the vector units (whose multiply-adds
-// bound it), with 20 bases 150, 197; 240 relations 33, 93 and 28, 43 (in a
+// Many bases (multiples of 4 were measured; the operand loads take pairs of them, which have to be aligned as such) and
+// columns: a product on the matrix cores, a^T C, that reads C once: 2000 relations x 65,536 columns with 64 bases 188 us,
+// 359 on the vector units (whose multiply-adds bound it), with 20 bases 150, 197; 240 relations 33, 93 and 28, 43 (in a
 // layer of 25 M runs, where C comes from memory: 64 bases 268, 445).  It needs one and a half tiles of 128 columns per
 // compute unit: at 2000 x 50,176 with 32 bases 145, 154, but at 2000 x 40,000 145, 125.  Otherwise groups of 64, 16, 8,
 // 4, 2 and 1 bases per block (10 bases as 8 + 2: 36 us at 474 x 40,000, 51 as 4 + 4 + 1 + 1).
@@ -701,7 +701,7 @@ int launch_basis_grad_from_relations(const float *a, int32_t R2, int32_t B, cons
 {
     if (R2 == 0 || B == 0) return KGE_OK;
     KGE_PROF("basis_grad", st);
-    if (B >= 20 && B % 4 == 0 && dd >= 384 * BN) {
+    if (B >= 20 && B % 4 == 0 && dd >= 384 * BN && ((uintptr_t)a % 8) == 0) {
         RowsX sa{a, B, nullptr, 0};
         RowsX sb{C, dd, nullptr, 0};
         EpiRowsAtomic ep{dV, dd, 0, true};

@@ -14,7 +14,7 @@ pytestmark = pytest.mark.gpu
 TOL = 4e-6
 
 
-def layer(n, R, m, di, do, B, order, H0, dH, V, a, W0, msg=0):
+def layer(n, R, m, di, do, B, order, H0, dH, V, a, W0, msg=0, a_at=0):
     import torch
     from paper_2201_02791_amd import binding as kb
     rng = np.random.default_rng(n + di)
@@ -23,7 +23,8 @@ def layer(n, R, m, di, do, B, order, H0, dH, V, a, W0, msg=0):
     rel = rng.integers(0, R, m).astype(np.int32)
     part, opart = kb.build_partition(head, rel, tail, n, R), orc.build_partition(head, rel, tail, n, R)
     t = lambda x: torch.from_numpy(np.ascontiguousarray(x)).cuda()  # noqa: E731
-    lay = [dict(V=t(V), a=t(a), W0=t(W0), act=kb.ACT_IDENTITY, order=order)]
+    coeff = torch.empty(a.size + a_at, device="cuda")[a_at:].view(a.shape).copy_(t(a))
+    lay = [dict(V=t(V), a=coeff, W0=t(W0), act=kb.ACT_IDENTITY, order=order)]
     ws = torch.zeros(kb.workspace_bytes(part, lay, msg), dtype=torch.uint8, device="cuda")
     H, G, out, dH0 = t(H0), t(dH), torch.empty(n, do, device="cuda"), torch.empty(n, di, device="cuda")
     grads = [{k: torch.empty_like(lay[0][k[1:]]) for k in ("dV", "da", "dW0")}]
@@ -55,9 +56,19 @@ def test_tile_edges(n, R, di, do, B, order):
         assert np.abs(got[k] - want[k]).max() <= TOL * np.abs(want[k]).max(), k
 
 
+# the coefficients may lie at any multiple of 4 bytes; the basis gradient's product reads them in pairs
+@pytest.mark.parametrize("a_at", [1, 2, 3])
+def test_coefficients_at_any_float(a_at):
+    n, R, di, do, B = 40, 60, 256, 256, 20
+    H0, dH, V, a, W0 = model(n, n, R, di, do, B)
+    got, want = layer(n, R, 4 * n, di, do, B, 2, H0, dH, V, a, W0, a_at=a_at)
+    for k in want:
+        assert np.abs(got[k] - want[k]).max() <= TOL * np.abs(want[k]).max(), k
+
+
 # the parts of an infinity or a NaN are no use: such results come from fp32 products, and no other result changes
 @pytest.mark.parametrize("order", [0, 2])
-@pytest.mark.parametrize("bad", [np.inf, -np.inf, np.nan, 1.5e38])
+@pytest.mark.parametrize("bad", [np.inf, -np.inf, np.nan, 1.5e38, 3.4e38])
 def test_values_that_do_not_split(bad, order):
     n, R, di, do = 200, 2, 36, 132
     H0, dH, V, a, W0 = model(3, n, R, di, do, 1)
