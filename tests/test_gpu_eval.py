@@ -216,3 +216,40 @@ def test_every_number_of_queries_per_block(kb, n_test):
 def test_candidate_lists_around_full_widths(kb, d):
     """Widths that fill a row's lanes (their loads have no condition) and the first ones past them."""
     test_candidate_lists(kb, 21, d)
+
+
+@pytest.mark.parametrize("d,bad", [(100, False), (200, False), (36, True), (200, True)])
+def test_large_tiles(kb, d, bad):
+    """Enough queries and entities for the 256 x 256 tiles: several steps per tile, a width that ends inside a step, tiles
+    that end inside the last entities, and an infinite column entry, whose scores are formed again.  As for small
+    tiles: the two kernels' bits agree, all scores match fp64, the filtered counts lie in the margin's bracket."""
+    say("large tiles", d, bad)
+    import torch
+    n, R, n_test = 20001, 3, 520
+    H, M = real_model(41, n, R, d)
+    th, tr, tt = triples(42, n, R, n_test)
+    kh, kr, kt = triples(43, n, R, 30000)
+    kh[:3000] = 7; kr[:3000] = 0                      # a hub; a tenth of the queries ask for it
+    th[:104] = 7; tr[:104] = 0
+    if bad:
+        H[77, 3] = np.inf
+        th[5], tt[6] = 77, 77                          # as the fixed entity and as the answer
+        kt[10] = 77
+    scores, ans = kb.eval_debug_scores(dev(H), dev(M), dev(th), dev(tr), dev(tt))
+    fixed, rel, true, side = ev.queries_of(th, tr, tt)
+    picked = scores[torch.arange(2 * n_test, device="cuda"), dev(true)]
+    assert torch.equal(picked.view(torch.int32), ans.view(torch.int32))
+    H64, M64 = torch.from_numpy(H).double().cuda(), torch.from_numpy(M).double().cuda()
+    want = (H64[dev(fixed)] * M64[dev(rel)]) @ H64.T
+    fin = torch.isfinite(want)
+    assert bool(fin.all()) != bad and not bool(torch.isnan(want).any())
+    assert torch.equal(scores[~fin].double(), want[~fin])
+    smax = float(want[fin].abs().max())
+    assert float((scores.double() - want)[fin].abs().max()) <= 1e-6 * smax
+    hi, eq = gpu_rank_all(kb, H, M, (th, tr, tt), (kh, kr, kt), n, R)
+    lo, up = ev.filtered_counts(H, M, th, tr, tt, (kh, kr, kt), tol=1e-6 * smax)
+    hi, eq = hi.cpu().numpy(), eq.cpu().numpy()
+    assert (lo <= hi).all() and (hi + eq <= up).all()
+    closed = lo == up
+    assert closed.mean() > 0.9
+    np.testing.assert_array_equal(hi[closed], lo[closed])
