@@ -289,7 +289,7 @@ int kge_sample_negatives(const kge_partition *p, const int32_t *pos_core_idx, in
  *            differ from run to run.
  *     else : the atomic-free form.  The rows every scored triple adds into dH (one per negative, to the
  *            corrupting entity; two per positive, to its head and tail) are sorted by entity with a stable
- *            radix sort inside the call, the triples are scored, and one wavefront per entity adds up its rows
+ *            radix sort inside the call, the triples are scored, and each entity's rows are added up
  *            in the order of the batch: every row of dH is written once and the result repeats bit for bit.
  *            H, M and dH must then be 16-byte aligned.
  *   In both forms an id outside [0, n_core) / [0, N) is replaced by 0 and counted (kge_partition_bad_ids).

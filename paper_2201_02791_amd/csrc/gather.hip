@@ -648,14 +648,12 @@ __global__ __launch_bounds__(256) void k_gather_t_bf16(
 template <bool BF16>
 __global__ void k_gather_t_finish(int32_t n_hv, const int32_t *__restrict__ hv_row,
                                   const int32_t *__restrict__ hv_unit_ptr, const float *__restrict__ partial,
-                                  int32_t bd, void *__restrict__ dP, int64_t ld,
-                                  const uint8_t *__restrict__ row_active)
+                                  int32_t bd, void *__restrict__ dP, int64_t ld)
 {
     const int bd4 = bd >> 2;
     const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (idx >= (int64_t)n_hv * bd4) return;
     const int32_t h = (int32_t)(idx / bd4);
-    if (row_active && !row_active[hv_row[h]]) return;
     const int k4 = (int)(idx - (int64_t)h * bd4) * 4;
     float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
     for (int32_t u = hv_unit_ptr[h]; u < hv_unit_ptr[h + 1]; ++u) {
@@ -1051,8 +1049,7 @@ int launch_act_backward(const float *dHout, const float *Hout, int act, int64_t 
     return KGE_OK;
 }
 
-// A CSR view whose rows each sum coefficient-weighted rows of another matrix:
-//   out[row][b][:] = sum_{q in row} a[rel[q]][b] * w[q] * X[idx[q]][:]       (w = 1 if null)
+// rows of dP whose edges were cut into units: their partial sums added up
 static int launch_gather_t_finish(const kge_partition *p, const float *partial, int32_t bd, void *dP, int64_t ld, bool bf16,
                                   hipStream_t st)
 {
@@ -1060,8 +1057,8 @@ static int launch_gather_t_finish(const kge_partition *p, const float *partial, 
     if (hx.n_hv == 0) return KGE_OK;
     KGE_PROF("gather_t_fin", st);
     const int64_t n = (int64_t)hx.n_hv * (bd / 4);
-    if (bf16) k_gather_t_finish<true><<<(unsigned)cdiv(n, 256), 256, 0, st>>>(hx.n_hv, hx.hv_row, hx.hv_unit_ptr, partial, bd, dP, ld, nullptr);
-    else k_gather_t_finish<false><<<(unsigned)cdiv(n, 256), 256, 0, st>>>(hx.n_hv, hx.hv_row, hx.hv_unit_ptr, partial, bd, dP, ld, nullptr);
+    if (bf16) k_gather_t_finish<true><<<(unsigned)cdiv(n, 256), 256, 0, st>>>(hx.n_hv, hx.hv_row, hx.hv_unit_ptr, partial, bd, dP, ld);
+    else k_gather_t_finish<false><<<(unsigned)cdiv(n, 256), 256, 0, st>>>(hx.n_hv, hx.hv_row, hx.hv_unit_ptr, partial, bd, dP, ld);
     KGE_LAUNCH_CHECK();
     return KGE_OK;
 }

@@ -912,7 +912,7 @@ extern "C" void kge_score_index_destroy(kge_score_index *x)
 }
 
 // The atomic-free form: sort the batch's occurrences by entity (stable, so ties keep occurrence order), score
-// every triple, then let one wavefront per entity add up its rows.
+// every triple, then add up each entity's rows in that order (k_distmult_gather).
 int launch_distmult_indexed(const kge_partition *p, kge_score_index *x, const float *H, const float *M, int32_t d,
                             const int32_t *pos, int64_t n_pos, const int32_t *neg_ent, const uint8_t *neg_side,
                             int32_t n_neg, float *scores, float *loss, float *dH, float *dM, hipStream_t st)
