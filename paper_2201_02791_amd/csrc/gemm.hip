@@ -170,7 +170,7 @@ __host__ __device__ __forceinline__ bool gemm_by_cols(const GemmGrid &g)
 // What bounds it: with rows of 128 floats the bytes moved (60 M edges, 5.8 M runs: a layer's six products take 7.0 ms at
 // about 4 TB/s; with fp32 matrix-core steps they took 8.6); with wider rows what a wavefront issues around the
 // matrix-core steps (splitting, addresses, the sums' moves: 9 vector instructions for each, where up to 6 would hide).
-// 352 k runs of 474 relations at width 200, microseconds with fp32 steps / now: rel_outer 570 / 380, apply_rel 427 /
+// 352 k runs of 474 relations at width 200, microseconds with fp32 steps / now: rel_outer 570 / 335, apply_rel 427 /
 // 319, apply_rel_t 406 / 270; against fp64 the gradients are off by 3e-7 there, 5e-7 before.
 template <class SA, class SB, class EPI>
 __global__ __launch_bounds__(GT, 2) void k_gemm(SA A, SB B, EPI epi, int32_t M_, int32_t N_, GemmGrid g)
