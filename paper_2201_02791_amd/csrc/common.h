@@ -62,6 +62,7 @@ struct kge_partition {
     // the runs grouped by destination (order dst, rel): dr_seg = run id, dr_rel = its relation
     int32_t *dr_ptr, *dr_seg, *dr_rel;
     kge_heavy_index hv_dr;
+    int32_t *run_lists;      // holds the five lists that follow
     // each relation's run range cut into chunks: KGE_REL_CHUNK .. 8 KGE_REL_CHUNK runs (about 2048 chunks in all), in
     // small graphs fewer runs
     int32_t n_relc;
