@@ -243,20 +243,30 @@ __global__ __launch_bounds__(64 * PW) void k_eval_pairs(const float *__restrict_
 // row's lanes), the answer's score included, so equal rows give equal scores.
 //
 // A lane past the row's width loads nothing: the first-level cache hands out 64 bytes per cycle, lanes that only repeat
-// a column included (3000 queries x 200 candidates at d = 200: 134 us, 99 without them).  But the rows of a round are
-// loaded under one condition, not under one each: every load would wait for the one before.
+// a column included (3000 queries x 200 candidates at d = 200: 134 us, 98 without them).  Rows of a part of the
+// wavefront's lanes stand under one condition per round (d = 36: 26.4 us, 29.0 under one each); a row of all 64, and an
+// index of its list, under its own (150,000 entities, 5000 queries x 500 at d = 200: 305 us, 323 under one per round, 310
+// with the indices under one each and the rows under one; d = 132: 240, 248, 246).
 template <int LPR, int NP, int UN, bool FULL>
 __device__ __forceinline__ void row_dots(const float4 *__restrict__ H, const int32_t (&e)[UN], const float4 (&q4)[NP], int32_t d4,
                                          int sub, float (&s)[UN])
 {
     float4 h[NP][UN];
+    if constexpr (!FULL && LPR == 64) {
 #pragma unroll
-    for (int j = 0; j < NP; ++j) {
+        for (int u = 0; u < UN; ++u)
 #pragma unroll
-        for (int u = 0; u < UN; ++u) h[j][u] = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (FULL || sub + j * LPR < d4)
+            for (int j = 0; j < NP; ++j)
+                h[j][u] = sub + j * LPR < d4 ? H[(int64_t)(e[u] < 0 ? 0 : e[u]) * d4 + sub + j * LPR] : make_float4(0.f, 0.f, 0.f, 0.f);
+    } else {
 #pragma unroll
-            for (int u = 0; u < UN; ++u) h[j][u] = H[(int64_t)(e[u] < 0 ? 0 : e[u]) * d4 + sub + j * LPR];
+        for (int j = 0; j < NP; ++j) {
+#pragma unroll
+            for (int u = 0; u < UN; ++u) h[j][u] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (FULL || sub + j * LPR < d4)
+#pragma unroll
+                for (int u = 0; u < UN; ++u) h[j][u] = H[(int64_t)(e[u] < 0 ? 0 : e[u]) * d4 + sub + j * LPR];
+        }
     }
 #pragma unroll
     for (int u = 0; u < UN; ++u) {
@@ -301,7 +311,8 @@ __global__ __launch_bounds__(256) void k_eval_candidates(const float4 *__restric
 #pragma unroll
         for (int u = 0; u < UN; ++u) {
             const int32_t i = b + u * RPP + grp;
-            e[u] = list[i < n_cand ? i : n_cand - 1];
+            if constexpr (!FULL && LPR == 64) e[u] = i < n_cand ? list[i] : -1;
+            else e[u] = list[i < n_cand ? i : n_cand - 1];
             if (i >= n_cand || e[u] == ans) e[u] = -1;
         }
         row_dots<LPR, NP, UN, FULL>(H, e, q4, d4, sub, s);
