@@ -353,7 +353,7 @@ int kge_optimizer_step_rows(const kge_opt *opt, float *param, const float *grad,
  *   and must have been built for the same n_entities / n_relations.  higher, equal: DEVICE int32
  *   [2 n_test], tail queries first, then head queries.  workspace: DEVICE, 256-byte aligned, at least
  *   kge_eval_workspace_bytes(2 n_test, d) bytes.  Scores are an (2 n_test x d) by (d x n_entities)
- *   product on the fp32 matrix cores that is compared and counted tile by tile, never stored.
+ *   product of fp32 accuracy on the matrix cores that is compared and counted tile by tile, never stored.
  * kge_eval_rank_candidates: every query brings its own list cand[q][0..n_cand) (DEVICE int32; the
  *   setting of the large citation graph, which ships a fixed number of negative targets per test edge);
  *   fixed, rel, answer: DEVICE int32 [n_queries]; an entry equal to the answer is skipped.

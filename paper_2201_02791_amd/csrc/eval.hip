@@ -6,17 +6,19 @@
 // (queries x entities) matrix is never stored: k_eval_count computes it tile by tile on the matrix cores and
 // keeps, per query, only how many entries lie above / exactly at the answer's score.
 // What the filtered setting removes - the known answers of the same (f, r), from none to thousands per query - is
-// scored again by k_eval_pairs and subtracted.  Both kernels build a score from the same sequence of steps (fp32
-// numbers split into three bf16 parts, split_bf16.h; k ascending, 16 k per step, six products per step, fp32
-// accumulator starting at zero; a score that is not finite from v_mfma_f32_32x32x2_f32 steps, two k each), so a pair
-// gets the same bits in both and the subtraction is exact.
+// scored again by k_eval_pairs and subtracted.  Both kernels build a score from the same sequence of steps (k ascending,
+// 16 k per step, fp32 accumulator starting at zero; a step is three products of two fp16 parts, split_f16.h, or, where
+// k_eval_range finds numbers that do not allow that, six products of three bf16 parts, split_bf16.h, and then a score that
+// is not finite comes from v_mfma_f32_32x32x2_f32 steps, two k each), so a pair gets the same bits in both and the
+// subtraction is exact.
 // The same per-query kernel ranks against explicit candidate lists.
 #include "common.h"
-#include "split_bf16.h"
+#include "split_f16.h"
 
 #include <algorithm>
 #include <cmath>
 #include <mutex>
+#include <type_traits>
 #include <vector>
 
 // Scratch of kge_eval_rank_all_static: device memory that lives in the library's code object, one copy
@@ -36,15 +38,24 @@ struct kge_eval_filter {
 
 namespace {
 
+// What k_eval_range found: the largest number of H and of Q and the smallest of their rows' largest numbers (rows of zeros
+// aside), as the bits of their absolute values.  From that, whether scores are formed from two fp16 parts, and the powers of
+// two that bring the largest numbers to 2^14 .. 2^15.  Below 80 columns three bf16 parts are the more accurate (relative
+// error at 64: 1.12e-7 against 1.15e-7, at 128 1.66e-7 against 1.44e-7); a row more than 14 binades below the largest one
+// would lose its second parts to fp16's smallest numbers; with both exponents within 24 no score or threshold can leave
+// fp32's normal range on the way; infinities and NaN lie above every exponent that is let through.
+struct EvalRange { uint32_t max_h, min_h, max_q, min_q; };
+
 // tail queries of all test triples first, then the head queries; their query vectors Q[q][:] = H[fixed][:] * M[rel][:]
 // (one thread per 4 columns) and cleared counters
 __global__ void k_eval_queries(const int32_t *__restrict__ th, const int32_t *__restrict__ tr,
                                const int32_t *__restrict__ tt, int64_t n_test, const float4 *__restrict__ H,
                                const float4 *__restrict__ M, int32_t d4, int32_t *__restrict__ fixed,
                                int32_t *__restrict__ rel, int32_t *__restrict__ answer, float4 *__restrict__ Q,
-                               unsigned *__restrict__ cnt_gt, unsigned *__restrict__ cnt_eq)
+                               unsigned *__restrict__ cnt_gt, EvalRange *__restrict__ range)
 {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t == 0) *range = EvalRange{0u, 0x7f800000u, 0u, 0x7f800000u};
     if (t >= 2 * n_test * d4) return;
     const int64_t i = t / d4;
     const int32_t c = (int32_t)(t - i * d4);
@@ -58,7 +69,6 @@ __global__ void k_eval_queries(const int32_t *__restrict__ th, const int32_t *__
         rel[i] = r;
         answer[i] = head_query ? th[j] : tt[j];
         cnt_gt[i] = 0u;
-        cnt_eq[i] = 0u;
     }
 }
 
@@ -85,15 +95,30 @@ __device__ __forceinline__ Row8 row_of(const float *__restrict__ row, int32_t k,
     r.y = *reinterpret_cast<const float4 *>(row + (k + 4 < d ? k + 4 : d - 4));
     return r;
 }
-struct Parts8 { uint4 p[3]; };
-__device__ __forceinline__ Parts8 parts_of(const Row8 &r, float sx, float sy)
+template <int NP> struct Parts8 { uint4 p[NP]; };
+template <int NP>
+__device__ __forceinline__ Parts8<NP> parts_of(const Row8 &r, float sx, float sy)
 {
-    const Split3 a = split_pair(r.x.x * sx, r.x.y * sx), b = split_pair(r.x.z * sx, r.x.w * sx);
-    const Split3 c = split_pair(r.y.x * sy, r.y.y * sy), e = split_pair(r.y.z * sy, r.y.w * sy);
-    Parts8 q;
+    const auto a = split_parts<NP>(r.x.x * sx, r.x.y * sx), b = split_parts<NP>(r.x.z * sx, r.x.w * sx);
+    const auto c = split_parts<NP>(r.y.x * sy, r.y.y * sy), e = split_parts<NP>(r.y.z * sy, r.y.w * sy);
+    Parts8<NP> q;
 #pragma unroll
-    for (int p = 0; p < 3; ++p) q.p[p] = make_uint4(a.w[p], b.w[p], c.w[p], e.w[p]);
+    for (int p = 0; p < NP; ++p) q.p[p] = make_uint4(a.w[p], b.w[p], c.w[p], e.w[p]);
     return q;
+}
+
+constexpr int HALF_FROM = 80;
+struct EvalScale { bool half; float h, q, inv; };
+__device__ __forceinline__ EvalScale eval_scale(const EvalRange *__restrict__ range)
+{
+    EvalScale c = {false, 1.f, 1.f, 1.f};
+    if (!range) return c;
+    const EvalRange r = *range;
+    const int eh = (int)(r.max_h >> 23) - 127, eq = (int)(r.max_q >> 23) - 127;
+    c.half = abs(eh) <= 24 && abs(eq) <= 24 && (int)(r.min_h >> 23) - 127 >= eh - 14 && (int)(r.min_q >> 23) - 127 >= eq - 14;
+    auto two_to = [](int e) { return __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((e + 127) << 23)); };
+    if (c.half) { c.h = two_to(14 - eh); c.q = two_to(14 - eq); c.inv = two_to(eh + eq - 28); }
+    return c;
 }
 
 // Scores of 32 (query, entity) pairs: lane l and lane l + 32 name pair l (qrow its query vector, ent its entity; ent < 0:
@@ -108,8 +133,10 @@ __device__ __forceinline__ float diagonal(const split_floatx16 &acc, int lane)
     for (int u = 1; u < 16; ++u) s = v == u ? acc[u] : s;
     return __shfl(s, c + 32 * ((c >> 2) & 1), 64);
 }
+// NP parts per number; sh, sq: scales of entities and queries (the score comes times their product)
+template <int NP>
 __device__ __forceinline__ float pair_scores(const float *__restrict__ qrow, const float *__restrict__ H,
-                                             int32_t ent, int32_t d, int lane)
+                                             int32_t ent, int32_t d, int lane, float sh, float sq)
 {
     split_floatx16 acc;
 #pragma unroll
@@ -121,15 +148,15 @@ __device__ __forceinline__ float pair_scores(const float *__restrict__ qrow, con
     Row8 q1 = row_of(qrow, 16 + 8 * half, d), h1 = row_of(hb, 16 + 8 * half, d);
     for (int32_t k0 = 0; k0 < d; k0 += 16) {
         const int32_t k = k0 + 8 * half;
-        const Parts8 q = parts_of(q0, 1.f, 1.f), h = parts_of(h0, k < d ? 1.f : 0.f, k + 4 < d ? 1.f : 0.f);
+        const Parts8<NP> q = parts_of<NP>(q0, sq, sq), h = parts_of<NP>(h0, k < d ? sh : 0.f, k + 4 < d ? sh : 0.f);
         q0 = q1; h0 = h1;
         q1 = row_of(qrow, k + 32, d);
         h1 = row_of(hb, k + 32, d);
 #pragma unroll
-        for (int p = 0; p < SPLIT_TERMS; ++p) acc = split_mfma(q.p[split_pb(p)], h.p[split_pa(p)], acc);
+        for (int p = 0; p < split_terms<NP>(); ++p) acc = split_product<NP>(q.p[split_b<NP>(p)], h.p[split_a<NP>(p)], acc);
     }
     float s = diagonal(acc, lane);
-    if (__any(ent >= 0 && split_not_finite(s))) {
+    if (NP == 3 && __any(ent >= 0 && split_not_finite(s))) {
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[v] = 0.f;
         for (int32_t k0 = 0; k0 < d; k0 += 2)
@@ -173,15 +200,16 @@ __host__ __device__ __forceinline__ int query_at(const PairPlace *ptr, PairPlace
 // answers of all its queries are laid end to end and cut into such tiles, dealt out over the block's wavefronts: most
 // lists hold a handful of entities (a tile of their own would be nearly empty) and a hub's hundreds are not one
 // wavefront's chain.  A block's queries lie a grid apart: neighbours in a test file often share a hub, whose list is as long
-// for each of them.  Bound by the splitting of the pairs' rows.  40,932 queries of the 14,541-entity graph at width 200:
-// 676 us with one wavefront and one tile per query and fp32 steps, 200 now (545 with
-// conditions around the row loads: each then waits for the last).
+// for each of them.  Bound by the gathered rows (a load touches 32 of them).  40,932 queries of the 14,541-entity graph at
+// width 200: 676 us with one wavefront and one tile per query and fp32 steps, 187 with three bf16 parts, 180 with two
+// fp16 parts (545 with conditions around the row loads: each then waits for the last).
 __global__ __launch_bounds__(64 * PW) void k_eval_pairs(const float *__restrict__ Q, const float *__restrict__ H,
                                                     int32_t d, int64_t nq, int64_t n_test,
                                                     const int32_t *__restrict__ fixed, const int32_t *__restrict__ rel,
                                                     const int32_t *__restrict__ answer, FilterTables ft,
+                                                    const EvalRange *__restrict__ range,
                                                     float *__restrict__ s_answer, int32_t *__restrict__ out_gt,
-                                                    int32_t *__restrict__ out_eq)
+                                                    unsigned *__restrict__ cnt_eq)
 {
     __shared__ int64_t bound[2 * PQ];
     __shared__ PairPlace ptr[PQ + 1];
@@ -191,6 +219,10 @@ __global__ __launch_bounds__(64 * PW) void k_eval_pairs(const float *__restrict_
     const int64_t step = gridDim.x;                         // the block's queries: blockIdx.x, and every step-th after it
     auto query = [&](int i) { return (int64_t)blockIdx.x + i * step; };
     const int n_here = (int)((nq - 1 - blockIdx.x) / step) + 1;
+    const EvalScale sc = eval_scale(range);
+    auto scores = [&](const float *qrow, int32_t ent) __attribute__((always_inline)) {
+        return sc.half ? pair_scores<2>(qrow, H, ent, d, lane, sc.h, sc.q) * sc.inv : pair_scores<3>(qrow, H, ent, d, lane, 1.f, 1.f);
+    };
     if (t < 2 * PQ) {                                       // ends of the queries' ranges in the tables, by wavefront 0
         const int i = t >> 1;
         int64_t pos = 0;
@@ -204,7 +236,7 @@ __global__ __launch_bounds__(64 * PW) void k_eval_pairs(const float *__restrict_
     } else if (w == 1) {                                    // the answers' scores, by wavefront 1
         const int i = lane & 31;
         const int64_t q = query(i < n_here ? i : 0);
-        const float s = pair_scores(Q + q * d, H, i < n_here ? answer[q] : -1, d, lane);
+        const float s = scores(Q + q * d, i < n_here ? answer[q] : -1);
         if (lane < n_here) { thr[lane] = s; s_answer[q] = s; }
     } else if (w == 2 && lane < PQ) {
         gt_s[lane] = 0; eq_s[lane] = 0;
@@ -227,14 +259,14 @@ __global__ __launch_bounds__(64 * PW) void k_eval_pairs(const float *__restrict_
             e = ft.val[q >= n_test ? 1 : 0][bound[2 * i] + (at - ptr[i])];
             if (e == answer[q]) e = -1;
         }
-        const float s = pair_scores(Q + q * d, H, e, d, lane);
+        const float s = scores(Q + q * d, e);
         if (lane < 32 && e >= 0) {
             if (s > thr[i]) atomicAdd(gt_s + i, 1);
             if (s == thr[i]) atomicAdd(eq_s + i, 1);
         }
     }
     __syncthreads();
-    if (t < n_here) { out_gt[query(t)] = gt_s[t]; out_eq[query(t)] = eq_s[t]; }
+    if (t < n_here) { out_gt[query(t)] = gt_s[t]; cnt_eq[query(t)] = 0u - (unsigned)eq_s[t]; }
 }
 
 // Candidate lists: one wavefront per query, LPR lanes per entity row (LPR * 4 >= min(d, 256) columns at a
@@ -332,22 +364,23 @@ __global__ __launch_bounds__(256) void k_eval_candidates(const float4 *__restric
 // is the accumulator's column, so a lane has one threshold and one pair of counts per 32 queries, kept in registers over
 // all tiles.  16-deep steps: a step's rows are split into LDS ([part][row][k], two buffers) one step ahead, their loads
 // issued one step before that, one barrier per step, also from one tile to the next.
-// Bound by the matrix cores (six bf16 products per term; every split row is used by 256 rows of the other side, so the
-// splitting hides behind them).  20,000 queries x 1 M entities at width 256: 49-51 ms (205 TFLOP/s, 1.2 PFLOP/s of
-// bf16 products: what a library's bf16 product of random 8192 x 8192 matrices reaches here); with fp32 steps 88.6 ms.
+// Bound by the matrix cores, which run at 1.7 GHz under this load and are 61 % busy; the rest goes to the barrier of a step
+// and to what no product covers.  20,000 queries x 1 M entities at width 256, NP = 2: 27.6 ms (371 TFLOP/s, 1.1 PFLOP/s of
+// fp16 products); NP = 3, six products per term: 49 (208); fp32 steps: 88.6.  40,932 x 14,541 at width 200: 0.83 ms, 1.34
+// with NP = 3.
 constexpr int ELP = 48;                       // bytes per LDS row: 16 bf16 and 16 of padding (an odd multiple of 16)
 
-template <int WI, int WJ, bool DUMP>
-__global__ __launch_bounds__(512, 2) void k_eval_count(const float *__restrict__ Q, int64_t nq,
-                                                    const float *__restrict__ H, int64_t N, int32_t d,
-                                                    const float *__restrict__ s_answer, int32_t tiles_per_block,
-                                                    int32_t n_col_tiles, int32_t n_row_tiles, int32_t n_col_chunks,
-                                                    unsigned *__restrict__ cnt_gt,
-                                                    unsigned *__restrict__ cnt_eq, float *__restrict__ dump)
+
+template <int WI, int WJ, bool DUMP, int NP>
+__device__ __forceinline__ void count_tiles(unsigned char *lds, const EvalScale sc, const float *__restrict__ Q, int64_t nq,
+                                            const float *__restrict__ H, int64_t N, int32_t d,
+                                            const float *__restrict__ s_answer, int32_t tiles_per_block,
+                                            int32_t n_col_tiles, int32_t n_row_tiles, int32_t n_col_chunks,
+                                            unsigned *__restrict__ cnt_gt, unsigned *__restrict__ cnt_eq,
+                                            float *__restrict__ dump)
 {
     constexpr int EM = 64 * WI, QN = 128 * WJ, NA = EM / 128, NB = QN / 128;
-    constexpr int PA = EM * ELP, PB = QN * ELP, BUF = 3 * (PA + PB);       // bytes of a part of either operand, of a buffer
-    __shared__ __attribute__((aligned(16))) unsigned char lds[2 * BUF];
+    constexpr int PA = EM * ELP, PB = QN * ELP, BUF = NP * (PA + PB);      // bytes of a part of either operand, of a buffer
     const int t = threadIdx.x, lane = t & 63, half = lane >> 5;
     const int w = __builtin_amdgcn_readfirstlane(t >> 6), we = w >> 2, wq = w & 3;
     // block id -> (query tile, chunk of entity tiles).  Workgroup i runs on XCD i % 8, each with its own L2.
@@ -370,6 +403,7 @@ __global__ __launch_bounds__(512, 2) void k_eval_count(const float *__restrict__
     const int r_ld = t >> 2, k_ld = (t & 3) * 4;
     const float *qb = Q + q0 * d;
     const uint32_t q_last = (uint32_t)(nq - 1 - q0 < QN - 1 ? nq - 1 - q0 : QN - 1);
+    const float sq = NP == 2 ? sc.q : 1.f;
     float4 ra[NA], rb[NB];
     int32_t lt = ct_beg, lk = 0, sk = 0;                    // tile and k of the next load, k of the next staging
     auto load = [&]() __attribute__((always_inline)) {
@@ -386,30 +420,37 @@ __global__ __launch_bounds__(512, 2) void k_eval_count(const float *__restrict__
         lk += 16;
         if (lk >= d) { lk = 0; if (lt + 1 < ct_end) ++lt; }
     };
-    auto stage = [&](unsigned char *L) __attribute__((always_inline)) {
-        const float on = sk + k_ld < d ? 1.f : 0.f;
+    // the two operands' rows of the next staging; entities' k past the width are zeroed
+    auto stage_a = [&](unsigned char *L) __attribute__((always_inline)) {
+        const float on = sk + k_ld < d ? sc.h : 0.f;
         unsigned char *at = L + r_ld * ELP + k_ld * 2;
 #pragma unroll
         for (int ps = 0; ps < NA; ++ps) {
-            const Split3 x = split_pair(ra[ps].x * on, ra[ps].y * on), y = split_pair(ra[ps].z * on, ra[ps].w * on);
+            const auto x = split_parts<NP>(ra[ps].x * on, ra[ps].y * on), y = split_parts<NP>(ra[ps].z * on, ra[ps].w * on);
 #pragma unroll
-            for (int p = 0; p < 3; ++p) *reinterpret_cast<uint2 *>(at + p * PA + ps * 128 * ELP) = make_uint2(x.w[p], y.w[p]);
-        }
-#pragma unroll
-        for (int ps = 0; ps < NB; ++ps) {
-            const Split3 x = split_pair(rb[ps].x, rb[ps].y), y = split_pair(rb[ps].z, rb[ps].w);
-#pragma unroll
-            for (int p = 0; p < 3; ++p) *reinterpret_cast<uint2 *>(at + 3 * PA + p * PB + ps * 128 * ELP) = make_uint2(x.w[p], y.w[p]);
+            for (int p = 0; p < NP; ++p) *reinterpret_cast<uint2 *>(at + p * PA + ps * 128 * ELP) = make_uint2(x.w[p], y.w[p]);
         }
         sk = sk + 16 < d ? sk + 16 : 0;
     };
+    auto stage_b = [&](unsigned char *L) __attribute__((always_inline)) {
+        unsigned char *at = L + r_ld * ELP + k_ld * 2;
+#pragma unroll
+        for (int ps = 0; ps < NB; ++ps) {
+            const auto x = split_parts<NP>(rb[ps].x * sq, rb[ps].y * sq), y = split_parts<NP>(rb[ps].z * sq, rb[ps].w * sq);
+#pragma unroll
+            for (int p = 0; p < NP; ++p) *reinterpret_cast<uint2 *>(at + NP * PA + p * PB + ps * 128 * ELP) = make_uint2(x.w[p], y.w[p]);
+        }
+    };
+    auto stage = [&](unsigned char *L) __attribute__((always_inline)) { stage_a(L); stage_b(L); };
 
     float thr[WJ];
     unsigned gt[WJ], eq[WJ];
 #pragma unroll
     for (int j = 0; j < WJ; ++j) {
         const int64_t q = q0 + (wq * WJ + j) * 32 + (lane & 31);
-        thr[j] = q < nq ? s_answer[q] : INFINITY;
+        // two parts: scores come times a power of two, and so does what they are compared with (no bit is lost either way:
+        // a sum of fp16 products is no smaller than 2^-48, and the powers are limited)
+        thr[j] = q < nq ? s_answer[q] * (NP == 2 ? sc.h * sc.q : 1.f) : INFINITY;
         gt[j] = eq[j] = 0u;
     }
     split_floatx16 acc[WI][WJ];
@@ -425,63 +466,99 @@ __global__ __launch_bounds__(512, 2) void k_eval_count(const float *__restrict__
     // of 32, query l % 32 of 32
     auto count = [&](int32_t ct) __attribute__((always_inline)) {
         const int64_t e0 = (int64_t)ct * EM + we * WI * 32;
-        float most = 0.f;          // v_maximum3_f32: two scores per instruction, a NaN stays
-#pragma unroll
-        for (int i = 0; i < WI; ++i)
-#pragma unroll
-            for (int j = 0; j < WJ; ++j)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) most = __builtin_elementwise_maximum(most, __builtin_fabsf(acc[i][j][v]));
-        if (__any(split_not_finite(most))) {          // an infinity, a NaN or an overflow among the terms: such scores again, in fp32
+        if constexpr (NP == 3) {
+            float most = 0.f;          // v_maximum3_f32: two scores per instruction, a NaN stays
 #pragma unroll
             for (int i = 0; i < WI; ++i)
 #pragma unroll
-                for (int j = 0; j < WJ; ++j) {
-                    split_floatx16 f;
+                for (int j = 0; j < WJ; ++j)
 #pragma unroll
-                    for (int v = 0; v < 16; ++v) f[v] = 0.f;
-                    const int64_t e = e0 + i * 32 + (lane & 31), q = q0 + (wq * WJ + j) * 32 + (lane & 31);
-                    const float *hp = H + (e < N ? e : N - 1) * d, *qr = Q + (q < nq ? q : nq - 1) * d;
-                    for (int32_t k = half; k < d; k += 2) f = __builtin_amdgcn_mfma_f32_32x32x2f32(hp[k], qr[k], f, 0, 0, 0);
+                    for (int v = 0; v < 16; ++v) most = __builtin_elementwise_maximum(most, __builtin_fabsf(acc[i][j][v]));
+            if (__any(split_not_finite(most))) {          // an infinity, a NaN or an overflow among the terms: such scores again, in fp32
 #pragma unroll
-                    for (int v = 0; v < 16; ++v) if (split_not_finite(acc[i][j][v])) acc[i][j][v] = f[v];
-                }
-        }
-        const int32_t left = N - e0 < (int64_t)WI * 32 ? (int32_t)(N - e0) : WI * 32;      // entities of this wavefront's part
+                for (int i = 0; i < WI; ++i)
 #pragma unroll
-        for (int i = 0; i < WI; ++i)
+                    for (int j = 0; j < WJ; ++j) {
+                        split_floatx16 f;
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int row = i * 32 + 8 * (v >> 2) + 4 * half + (v & 3);
-                const bool in = left == WI * 32 || row < left;
+                        for (int v = 0; v < 16; ++v) f[v] = 0.f;
+                        const int64_t e = e0 + i * 32 + (lane & 31), q = q0 + (wq * WJ + j) * 32 + (lane & 31);
+                        const float *hp = H + (e < N ? e : N - 1) * d, *qr = Q + (q < nq ? q : nq - 1) * d;
+                        for (int32_t k = half; k < d; k += 2) f = __builtin_amdgcn_mfma_f32_32x32x2f32(hp[k], qr[k], f, 0, 0, 0);
 #pragma unroll
-                for (int j = 0; j < WJ; ++j) {
-                    gt[j] += in && acc[i][j][v] > thr[j] ? 1u : 0u;
-                    eq[j] += in && acc[i][j][v] == thr[j] ? 1u : 0u;
-                    if (DUMP) {
-                        const int64_t q = q0 + (wq * WJ + j) * 32 + (lane & 31);
-                        if (in && q < nq) dump[q * N + e0 + row] = acc[i][j][v];
+                        for (int v = 0; v < 16; ++v) if (split_not_finite(acc[i][j][v])) acc[i][j][v] = f[v];
                     }
+            }
+        }
+        int32_t left = N - e0 < (int64_t)WI * 32 ? (int32_t)(N - e0) : WI * 32;            // entities of this wavefront's part
+        if (NP == 2 && !DUMP && left == WI * 32) {
+            // thr - s has its sign bit where s lies above (a difference of fp32 numbers is zero only if they are equal): the
+            // signs are shifted into a word and counted 32 at a time, 2 instructions per score where a compare and an add
+            // with carry wait for each other.  An equal score (a difference of +0 bits) is rare: one minimum over all.
+            uint32_t least = 0xffffffffu;
+#pragma unroll
+            for (int j = 0; j < WJ; ++j)
+#pragma unroll
+                for (int i2 = 0; i2 < WI; i2 += 2) {
+                    uint32_t above = 0u;
+#pragma unroll
+                    for (int v = 0; v < 32; v += 2) {
+                        const uint32_t u = __float_as_uint(thr[j] - acc[i2 + v / 16][j][v % 16]);
+                        const uint32_t x = __float_as_uint(thr[j] - acc[i2 + v / 16][j][v % 16 + 1]);
+                        above = __builtin_amdgcn_alignbit(__builtin_amdgcn_alignbit(above, u, 31), x, 31);
+                        asm("v_min3_u32 %0, %0, %1, %2" : "+v"(least) : "v"(u), "v"(x));      // one chain: a tree keeps them all
+                    }
+                    gt[j] += __popc(above);
+                    asm volatile("" : "+v"(gt[j]));       // counted here, not behind the branch below
+                }
+            if (__any(least == 0u)) {
+#pragma unroll
+                for (int j = 0; j < WJ; ++j) {
+                    float x = thr[j];
+                    asm volatile("" : "+v"(x));           // keeps the comparisons in this branch
+#pragma unroll
+                    for (int i = 0; i < WI; ++i)
+#pragma unroll
+                        for (int v = 0; v < 16; ++v) eq[j] += acc[i][j][v] == x ? 1u : 0u;
                 }
             }
-        clear();
+        } else {
+            asm volatile("" : "+s"(left));        // keeps the rows' conditions in this branch
+#pragma unroll
+            for (int i = 0; i < WI; ++i)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const int row = i * 32 + 8 * (v >> 2) + 4 * half + (v & 3);
+                    const bool in = row < left;
+#pragma unroll
+                    for (int j = 0; j < WJ; ++j) {
+                        gt[j] += in && acc[i][j][v] > thr[j] ? 1u : 0u;
+                        eq[j] += in && acc[i][j][v] == thr[j] ? 1u : 0u;
+                        if (DUMP) {
+                            const int64_t q = q0 + (wq * WJ + j) * 32 + (lane & 31);
+                            if (in && q < nq) dump[q * N + e0 + row] = acc[i][j][v] * (NP == 2 ? sc.inv : 1.f);
+                        }
+                    }
+                }
+        }
+        if (NP == 3) clear();
     };
 
-    if (ct_beg < ct_end) {
+    if (NP == 3 && ct_beg < ct_end) {
         load();
         stage(lds);
         load();
         clear();
         __syncthreads();
-        const int off_a = (we * WI * 32 + (lane & 31)) * ELP + half * 16, off_b = 3 * PA + (wq * WJ * 32 + (lane & 31)) * ELP + half * 16;
+        const int off_a = (we * WI * 32 + (lane & 31)) * ELP + half * 16, off_b = NP * PA + (wq * WJ * 32 + (lane & 31)) * ELP + half * 16;
         int32_t ct = ct_beg, kc = 0;
         int cur = 0;
         while (true) {
             const unsigned char *L = lds + cur;
             cur ^= BUF;
-            uint4 a[WI][3], b[WJ][3];
+            uint4 a[WI][NP], b[WJ][NP];
 #pragma unroll
-            for (int p = 0; p < 3; ++p) {
+            for (int p = 0; p < NP; ++p) {
 #pragma unroll
                 for (int i = 0; i < WI; ++i) a[i][p] = *reinterpret_cast<const uint4 *>(L + off_a + p * PA + i * 32 * ELP);
 #pragma unroll
@@ -490,11 +567,11 @@ __global__ __launch_bounds__(512, 2) void k_eval_count(const float *__restrict__
             stage(lds + cur);
             load();
 #pragma unroll
-            for (int p = 0; p < SPLIT_TERMS; ++p)
+            for (int p = 0; p < split_terms<NP>(); ++p)
 #pragma unroll
                 for (int i = 0; i < WI; ++i)
 #pragma unroll
-                    for (int j = 0; j < WJ; ++j) acc[i][j] = split_mfma(a[i][split_pa(p)], b[j][split_pb(p)], acc[i][j]);
+                    for (int j = 0; j < WJ; ++j) acc[i][j] = split_product<NP>(a[i][split_a<NP>(p)], b[j][split_b<NP>(p)], acc[i][j]);
             kc += 16;
             if (kc >= d) {
                 count(ct);
@@ -502,6 +579,70 @@ __global__ __launch_bounds__(512, 2) void k_eval_count(const float *__restrict__
                 if (++ct == ct_end) break;
             }
             __syncthreads();
+        }
+    }
+    if (NP == 2 && ct_beg < ct_end) {
+        // Three buffers: while a step is multiplied, the one after next is split into LDS and the next one's operands are
+        // read into the registers that the step no longer needs, so that no product waits for LDS.  The barrier stands
+        // where the writes before it are long done and the reads behind it are needed eight products later.  A step's
+        // three rounds of products are spread among the other instructions by hand (mix): clustered, they and the
+        // splitting take turns, because all wavefronts keep the same step.
+        const int off_a = (we * WI * 32 + (lane & 31)) * ELP + half * 16, off_b = NP * PA + (wq * WJ * 32 + (lane & 31)) * ELP + half * 16;
+        uint4 ah[WI], al[WI], bh[WJ], bl[WJ];
+        auto read_a = [&](const unsigned char *L, int p, uint4 (&x)[WI]) __attribute__((always_inline)) {
+#pragma unroll
+            for (int i = 0; i < WI; ++i) x[i] = *reinterpret_cast<const uint4 *>(L + off_a + p * PA + i * 32 * ELP);
+        };
+        auto read_b = [&](const unsigned char *L, int p, uint4 (&x)[WJ]) __attribute__((always_inline)) {
+#pragma unroll
+            for (int j = 0; j < WJ; ++j) x[j] = *reinterpret_cast<const uint4 *>(L + off_b + p * PB + j * 32 * ELP);
+        };
+        const split_floatx16 zero = {};
+        auto multiply = [&](const uint4 (&x)[WI], const uint4 (&y)[WJ], auto fresh) __attribute__((always_inline)) {
+#pragma unroll
+            for (int i = 0; i < WI; ++i)
+#pragma unroll
+                for (int j = 0; j < WJ; ++j) acc[i][j] = split_product<2>(x[i], y[j], decltype(fresh)::value ? zero : acc[i][j]);
+        };
+        auto mix = [&](auto valu) __attribute__((always_inline)) {
+#pragma unroll
+            for (int m = 0; m < WI * WJ; ++m) {
+                __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);                      // one product
+                __builtin_amdgcn_sched_group_barrier(0x2, decltype(valu)::value, 0);  // vector instructions
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        int nxt = BUF, after = 2 * BUF;
+        auto step = [&](auto fresh) __attribute__((always_inline)) {
+            const std::false_type more{};
+            stage_a(lds + after);
+            multiply(al, bh, fresh);
+            mix(std::integral_constant<int, 4>{});
+            read_a(lds + nxt, 1, al);
+            stage_b(lds + after);
+            multiply(ah, bh, more);
+            mix(std::integral_constant<int, 4>{});
+            __syncthreads();
+            read_b(lds + nxt, 0, bh);
+            load();
+            multiply(ah, bl, more);
+            mix(std::integral_constant<int, 3>{});
+            read_a(lds + nxt, 0, ah);
+            read_b(lds + nxt, 1, bl);
+            nxt = after;
+            after = after == 2 * BUF ? 0 : after + BUF;
+        };
+        load();
+        stage(lds);
+        load();
+        stage(lds + BUF);
+        load();
+        __syncthreads();
+        read_a(lds, 1, al); read_b(lds, 0, bh); read_a(lds, 0, ah); read_b(lds, 1, bl);
+        for (int32_t ct = ct_beg; ct < ct_end; ++ct) {
+            step(std::true_type{});
+            for (int32_t kc = 16; kc < d; kc += 16) step(std::false_type{});
+            count(ct);
         }
     }
 #pragma unroll
@@ -516,63 +657,145 @@ __global__ __launch_bounds__(512, 2) void k_eval_count(const float *__restrict__
     }
 }
 
-// higher = above - above among the filtered; equal = equal - equal among the filtered - the answer itself
+template <int WI, int WJ, bool DUMP>
+__global__ __launch_bounds__(512, 2) void k_eval_count(const EvalRange *__restrict__ range, const float *__restrict__ Q,
+                                                    int64_t nq, const float *__restrict__ H, int64_t N, int32_t d,
+                                                    const float *__restrict__ s_answer, int32_t tiles_per_block,
+                                                    int32_t n_col_tiles, int32_t n_row_tiles, int32_t n_col_chunks,
+                                                    unsigned *__restrict__ cnt_gt,
+                                                    unsigned *__restrict__ cnt_eq, float *__restrict__ dump)
+{
+    // two buffers of three parts or three of two
+    __shared__ __attribute__((aligned(16))) unsigned char lds[6 * (64 * WI + 128 * WJ) * ELP];
+    const EvalScale sc = eval_scale(range);
+    if (sc.half)
+        count_tiles<WI, WJ, DUMP, 2>(lds, sc, Q, nq, H, N, d, s_answer, tiles_per_block, n_col_tiles, n_row_tiles, n_col_chunks,
+                                     cnt_gt, cnt_eq, dump);
+    else
+        count_tiles<WI, WJ, DUMP, 3>(lds, sc, Q, nq, H, N, d, s_answer, tiles_per_block, n_col_tiles, n_row_tiles, n_col_chunks,
+                                     cnt_gt, cnt_eq, dump);
+}
+
+// Largest numbers of H and of Q and the smallest of their rows' largest numbers (rows of zeros aside; EvalRange), as the bits
+// of the absolute values: ordered as the numbers are, infinities above them and NaN above those.  A wavefront takes four
+// rows at a time; blocks [0, h_blocks) walk H, the rest Q.  `out` comes initialised.  Bound by reading H: 1 M x 256, 177 us
+// (5.8 TB/s); 14,541 and 40,932 rows of 200: 28 us, mostly latency.
+__global__ __launch_bounds__(256) void k_eval_range(const uint4 *__restrict__ H, int64_t N, const uint4 *__restrict__ Q, int64_t nq,
+                                                    int32_t d4, int32_t h_blocks, EvalRange *__restrict__ out)
+{
+    __shared__ uint32_t red[2][4];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const bool is_h = (int)blockIdx.x < h_blocks;
+    const uint4 *X = is_h ? H : Q;
+    const int64_t n = is_h ? N : nq;
+    const int64_t first = (is_h ? blockIdx.x : blockIdx.x - h_blocks) * (int64_t)4 + w, step = (is_h ? h_blocks : gridDim.x - h_blocks) * (int64_t)4;
+    uint32_t most = 0u, least = 0x7f800000u;
+    for (int64_t r0 = first * 4; r0 < n; r0 += step * 4) {
+        uint32_t m[4] = {0u, 0u, 0u, 0u};
+        for (int32_t c = lane; c < d4; c += 64) {
+            uint4 x[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) x[u] = X[(r0 + u < n ? r0 + u : n - 1) * d4 + c];
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                m[u] = max(m[u], max(max(x[u].x & 0x7fffffffu, x[u].y & 0x7fffffffu), max(x[u].z & 0x7fffffffu, x[u].w & 0x7fffffffu)));
+        }
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1)
+#pragma unroll
+            for (int u = 0; u < 4; ++u) m[u] = max(m[u], (uint32_t)__shfl_xor((int)m[u], off, 64));
+#pragma unroll
+        for (int u = 0; u < 4; ++u) { most = max(most, m[u]); if (m[u]) least = min(least, m[u]); }
+    }
+    if (lane == 0) { red[0][w] = most; red[1][w] = least; }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int i = 1; i < 4; ++i) { most = max(most, red[0][i]); least = min(least, red[1][i]); }
+        // most blocks change neither word: a look first keeps them off the one address (1900 blocks that all add: 47 us instead of 28)
+        uint32_t *hi = is_h ? &out->max_h : &out->max_q, *lo = is_h ? &out->min_h : &out->min_q;
+        if (most > __hip_atomic_load(hi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(hi, most);
+        if (least < __hip_atomic_load(lo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMin(lo, least);
+    }
+}
+
+// higher = above - above among the filtered; equal = equal - equal among the filtered (where the counter started) - the
+// answer itself
 __global__ void k_eval_finish(const unsigned *__restrict__ cnt_gt, const unsigned *__restrict__ cnt_eq,
-                              const int32_t *__restrict__ sub_gt, const int32_t *__restrict__ sub_eq, int64_t nq,
+                              const int32_t *__restrict__ sub_gt, int64_t nq,
                               int32_t *__restrict__ higher, int32_t *__restrict__ equal)
 {
     const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (q >= nq) return;
-    const int64_t g = (int64_t)cnt_gt[q] - sub_gt[q], e = (int64_t)cnt_eq[q] - sub_eq[q] - 1;
+    const int64_t g = (int64_t)cnt_gt[q] - sub_gt[q], e = (int64_t)(int32_t)cnt_eq[q] - 1;
     higher[q] = (int32_t)(g > 0 ? g : 0);
     equal[q] = (int32_t)(e > 0 ? e : 0);
 }
 
 struct Ks { int32_t k[8]; int32_t n; };
 
-// one block: sums of 1 / rank and of [rank <= k] in double, fixed order.  16 wavefronts with 4 queries of a thread in
-// flight: the walk over the counts is a chain of memory round trips otherwise.
+// One block: the sum of 1 / rank in double, in a fixed order, and the numbers of ranks up to each k.  Bound by one compute
+// unit's instructions and a few memory round trips: 8 queries of a thread in flight, ranks doubled so that they are whole
+// numbers, the reciprocal from v_rcp_f64 and two Newton steps (within a unit in the last place; the full division takes
+// twice the instructions).  40,932 queries: 22 us, 32 with divisions, conditions per k and 4 in flight.
 __global__ __launch_bounds__(1024) void k_eval_metrics(const int32_t *__restrict__ higher,
                                                        const int32_t *__restrict__ equal, int64_t nq, Ks ks,
                                                        double *__restrict__ out)
 {
-    __shared__ double red[16][9];
+    constexpr int UN = 8;
+    __shared__ double red[16];
+    __shared__ uint32_t hits[16][8];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    double s[9];
+    double s = 0.0;
+    uint32_t n[8], k2[8];                                   // 2 k; a k below 1, or none: no rank is that small
 #pragma unroll
-    for (int j = 0; j < 9; ++j) s[j] = 0.0;
-    for (int64_t q0 = threadIdx.x; q0 < nq; q0 += 4096) {
-        int32_t h[4], e[4];
+    for (int j = 0; j < 8; ++j) { n[j] = 0u; k2[j] = j < ks.n && ks.k[j] > 0 ? 2u * (uint32_t)ks.k[j] : 0u; }
+    for (int64_t q0 = threadIdx.x; q0 < nq; q0 += UN * 1024) {
+        int32_t h[UN], e[UN];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int64_t q = q0 + u * 1024;
-            h[u] = q < nq ? higher[q] : -1;
-            e[u] = q < nq ? equal[q] : 0;
+        for (int u = 0; u < UN; ++u) {
+            const int64_t q = q0 + u * 1024 < nq ? q0 + u * 1024 : nq - 1;
+            h[u] = higher[q];
+            e[u] = equal[q];
+        }
+        uint32_t c2[UN];                                    // twice the rank; past the last query: above every 2 k
+#pragma unroll
+        for (int u = 0; u < UN; ++u) {
+            const bool in = q0 + u * 1024 < nq;
+            const int64_t r2 = 2 + 2 * (int64_t)h[u] + e[u];
+            c2[u] = !in || r2 > 0xffffffffll ? 0xffffffffu : r2 < 1 ? 1u : (uint32_t)r2;
+            const double r = (double)r2;
+            double x = __builtin_amdgcn_rcp(r);
+            x = __builtin_fma(__builtin_fma(-r, x, 1.0), x, x);
+            x = __builtin_fma(__builtin_fma(-r, x, 1.0), x, x);
+            if (r2 <= 0) x = 1.0 / r;                       // no counts of a ranking
+            s += in ? x : 0.0;
         }
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            if (q0 + u * 1024 >= nq) break;
-            const double r = 1.0 + (double)h[u] + 0.5 * (double)e[u];
-            s[0] += 1.0 / r;
+        for (int j = 0; j < 8; ++j)
+            if (j < ks.n)
 #pragma unroll
-            for (int j = 0; j < 8; ++j) s[1 + j] += j < ks.n && r <= (double)ks.k[j] ? 1.0 : 0.0;
-        }
+                for (int u = 0; u < UN; ++u) n[j] += c2[u] <= k2[j] ? 1u : 0u;
     }
+    s *= 2.0;
+    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+    if (lane == 0) red[w] = s;
 #pragma unroll
-    for (int j = 0; j < 9; ++j) {
-        for (int off = 32; off > 0; off >>= 1) s[j] += __shfl_xor(s[j], off, 64);
-        if (lane == 0) red[w][j] = s[j];
+    for (int j = 0; j < 8; ++j) {
+        for (int off = 32; off > 0; off >>= 1) n[j] += __shfl_xor(n[j], off, 64);
+        if (lane == 0) hits[w][j] = n[j];
     }
     __syncthreads();
-    if ((int)threadIdx.x <= ks.n) {
+    const int t = (int)threadIdx.x;
+    if (t <= ks.n) {
         double x = 0.0;
-        for (int i = 0; i < 16; ++i) x += red[i][threadIdx.x];
-        out[threadIdx.x] = nq > 0 ? x / (double)nq : 0.0;
+        if (t == 0) for (int i = 0; i < 16; ++i) x += red[i];
+        else for (int i = 0; i < 16; ++i) x += (double)hits[i][t - 1];
+        out[t] = nq > 0 ? x / (double)nq : 0.0;
     }
 }
 
 struct EvalWs {
-    size_t off_fixed, off_rel, off_answer, off_Q, off_s, off_sub_gt, off_sub_eq, off_cnt_gt, off_cnt_eq, total;
+    size_t off_fixed, off_rel, off_answer, off_Q, off_s, off_sub_gt, off_range, off_cnt_gt, off_cnt_eq, total;
 };
 
 EvalWs eval_layout(int64_t nq, int32_t d)
@@ -583,7 +806,7 @@ EvalWs eval_layout(int64_t nq, int32_t d)
     auto take = [&](size_t bytes) { size_t o = cur; cur = align_up(cur + bytes, 256); return o; };
     w.off_fixed = take(n * 4); w.off_rel = take(n * 4); w.off_answer = take(n * 4);
     w.off_Q = take(n * (size_t)d * 4); w.off_s = take(n * 4);
-    w.off_sub_gt = take(n * 4); w.off_sub_eq = take(n * 4);
+    w.off_sub_gt = take(n * 4); w.off_range = take(n * 4);      // 16 bytes are used
     w.off_cnt_gt = take(n * 4); w.off_cnt_eq = take(n * 4);
     w.total = cur;
     return w;
@@ -608,7 +831,7 @@ int check_ws(void *workspace, size_t ws_bytes, int64_t nq, int32_t d, EvalWs *w)
 }
 
 template <int WI, int WJ>
-int launch_count_tiles(const float *Q, int64_t nq, const float *H, int64_t N, int32_t d, const float *s_answer,
+int launch_count_tiles(const EvalRange *range, const float *Q, int64_t nq, const float *H, int64_t N, int32_t d, const float *s_answer,
                        unsigned *cnt_gt, unsigned *cnt_eq, float *dump, hipStream_t st)
 {
     const int64_t row_tiles = cdiv(nq, 128 * WJ), col_tiles = cdiv(N, 64 * WI);
@@ -623,22 +846,22 @@ int launch_count_tiles(const float *Q, int64_t nq, const float *H, int64_t N, in
     const int64_t blocks = cdiv(patches, 8) * 8 * 32;        // whole rounds of 8 patches, 32 blocks each
     KGE_REQUIRE(blocks <= 0x7FFFFFFFll, KGE_ERANGE, "evaluation grid too large");
     if (dump)
-        k_eval_count<WI, WJ, true><<<(unsigned)blocks, 512, 0, st>>>(Q, nq, H, N, d, s_answer, (int32_t)tpb, (int32_t)col_tiles,
+        k_eval_count<WI, WJ, true><<<(unsigned)blocks, 512, 0, st>>>(range, Q, nq, H, N, d, s_answer, (int32_t)tpb, (int32_t)col_tiles,
                                                                     (int32_t)row_tiles, (int32_t)col_chunks, cnt_gt, cnt_eq, dump);
     else
-        k_eval_count<WI, WJ, false><<<(unsigned)blocks, 512, 0, st>>>(Q, nq, H, N, d, s_answer, (int32_t)tpb, (int32_t)col_tiles,
+        k_eval_count<WI, WJ, false><<<(unsigned)blocks, 512, 0, st>>>(range, Q, nq, H, N, d, s_answer, (int32_t)tpb, (int32_t)col_tiles,
                                                                      (int32_t)row_tiles, (int32_t)col_chunks, cnt_gt, cnt_eq, nullptr);
     KGE_LAUNCH_CHECK();
     return KGE_OK;
 }
 
-int launch_count(const float *Q, int64_t nq, const float *H, int64_t N, int32_t d, const float *s_answer,
+int launch_count(const EvalRange *range, const float *Q, int64_t nq, const float *H, int64_t N, int32_t d, const float *s_answer,
                  unsigned *cnt_gt, unsigned *cnt_eq, float *dump, hipStream_t st)
 {
     // 256 x 256 tiles halve the splitting per product; with fewer of them than compute units (256) most of the chip
     // would wait for them, and 128 x 128 tiles spread the work
-    if (cdiv(nq, 256) * cdiv(N, 256) >= 256) return launch_count_tiles<4, 2>(Q, nq, H, N, d, s_answer, cnt_gt, cnt_eq, dump, st);
-    return launch_count_tiles<2, 1>(Q, nq, H, N, d, s_answer, cnt_gt, cnt_eq, dump, st);
+    if (cdiv(nq, 256) * cdiv(N, 256) >= 256) return launch_count_tiles<4, 2>(range, Q, nq, H, N, d, s_answer, cnt_gt, cnt_eq, dump, st);
+    return launch_count_tiles<2, 1>(range, Q, nq, H, N, d, s_answer, cnt_gt, cnt_eq, dump, st);
 }
 
 // Queries per block of k_eval_pairs: the most that leave 1024 blocks (four of them fill a compute unit), but no fewer than a
@@ -665,14 +888,21 @@ int rank_all(const kge_eval_filter *f, const float *H, int64_t N, int32_t d, con
     char *ws = (char *)workspace;
     int32_t *fixed = (int32_t *)(ws + w.off_fixed), *rel = (int32_t *)(ws + w.off_rel), *answer = (int32_t *)(ws + w.off_answer);
     float *Q = (float *)(ws + w.off_Q), *s = (float *)(ws + w.off_s);
-    int32_t *sub_gt = (int32_t *)(ws + w.off_sub_gt), *sub_eq = (int32_t *)(ws + w.off_sub_eq);
+    int32_t *sub_gt = (int32_t *)(ws + w.off_sub_gt);
+    EvalRange *range = (EvalRange *)(ws + w.off_range);
+    const EvalRange *half_range = d >= HALF_FROM ? range : nullptr;      // narrower: three bf16 parts without a look
     unsigned *cnt_gt = (unsigned *)(ws + w.off_cnt_gt), *cnt_eq = (unsigned *)(ws + w.off_cnt_eq);
     {
         KGE_PROF("eval_queries", st);
         k_eval_queries<<<(unsigned)cdiv(nq * (d / 4), 256), 256, 0, st>>>(test_h, test_r, test_t, n_test, (const float4 *)H,
                                                                          (const float4 *)M, d / 4, fixed, rel, answer,
-                                                                         (float4 *)Q, cnt_gt, cnt_eq);
+                                                                         (float4 *)Q, cnt_gt, range);
         KGE_LAUNCH_CHECK();
+        if (d >= HALF_FROM) {
+            const int32_t h_blocks = (int32_t)std::min<int64_t>(cdiv(N, 32), 1024), q_blocks = (int32_t)std::min<int64_t>(cdiv(nq, 32), 512);
+            k_eval_range<<<h_blocks + q_blocks, 256, 0, st>>>((const uint4 *)H, N, (const uint4 *)Q, nq, d / 4, h_blocks, range);
+            KGE_LAUNCH_CHECK();
+        }
     }
     {
         KGE_PROF("eval_pairs", st);
@@ -682,16 +912,16 @@ int rank_all(const kge_eval_filter *f, const float *H, int64_t N, int32_t d, con
         }
         ft.N = N; ft.R = R;
         k_eval_pairs<<<(unsigned)cdiv(nq, pair_queries(nq)), 64 * PW, 0, st>>>(Q, H, d, nq, n_test, fixed, rel, answer, ft,
-                                                           dump_answer ? dump_answer : s, sub_gt, sub_eq);
+                                                           half_range, dump_answer ? dump_answer : s, sub_gt, cnt_eq);
         KGE_LAUNCH_CHECK();
     }
     {
         KGE_PROF("eval_count", st);
-        rc = launch_count(Q, nq, H, N, d, dump_answer ? dump_answer : s, cnt_gt, cnt_eq, dump, st);
+        rc = launch_count(half_range, Q, nq, H, N, d, dump_answer ? dump_answer : s, cnt_gt, cnt_eq, dump, st);
         if (rc != KGE_OK) return rc;
     }
     if (higher && equal) {
-        k_eval_finish<<<(unsigned)cdiv(nq, 256), 256, 0, st>>>(cnt_gt, cnt_eq, sub_gt, sub_eq, nq, higher, equal);
+        k_eval_finish<<<(unsigned)cdiv(nq, 256), 256, 0, st>>>(cnt_gt, cnt_eq, sub_gt, nq, higher, equal);
         KGE_LAUNCH_CHECK();
     }
     return KGE_OK;

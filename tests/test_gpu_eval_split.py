@@ -1,0 +1,109 @@
+"""The evaluation's scores from two fp16 parts per number, and where three bf16 parts take their place: widths around the
+change, rows of very different size, numbers near fp16's and fp32's limits, ragged tiles.  Against 64 bits.
+
+Bound on a score: every term q_k h_k is known to 2^-21 of itself (each factor keeps 23 of its 24 bits or more, 2^-23 each,
+and the product of the two second parts is left out, 2^-22), and every addition into the accumulator (six per 16 terms at
+most) rounds at 2^-23 of a partial sum, which is at most S = sum |q_k h_k|.  Columns of a row that are tiny against the row's largest
+add up to 2^-25 of the scaled sizes, 2^-39 of the largest numbers' product per term."""
+import sys
+
+import numpy as np
+import pytest
+
+from oracle import eval_oracle as ev
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def kb():
+    import torch
+    assert torch.cuda.is_available(), "these tests need the MI355X"
+    from paper_2201_02791_amd import binding
+    binding.load()
+    return binding
+
+
+def check(kb, H, M, n, R, n_test, seed):
+    import torch
+    rng = np.random.default_rng(seed)
+    th, tr, tt = (rng.integers(0, hi, n_test).astype(np.int32) for hi in (n, R, n))
+    th[:3], tt[:3] = n - 1, 0
+    dev = lambda x: torch.from_numpy(np.ascontiguousarray(x)).cuda()  # noqa: E731
+    scores, ans = kb.eval_debug_scores(dev(H), dev(M), dev(th), dev(tr), dev(tt))
+    fixed, rel, true, _ = ev.queries_of(th, tr, tt)
+    picked = scores[torch.arange(2 * n_test, device="cuda"), dev(true)]
+    assert torch.equal(picked.view(torch.int32), ans.view(torch.int32))       # the two kernels agree on a pair's bits
+    Q = dev(H[fixed] * M[rel]).double()                                         # the query vectors are fp32 products
+    H64 = dev(H).double()
+    want, size = Q @ H64.T, Q.abs() @ H64.abs().T
+    d = H.shape[1]
+    tiny = d * 2.0 ** -39 * float(Q.abs().max()) * float(H64.abs().max())
+    bound = (2.0 ** -21 + 6 * -(-d // 16) * 2.0 ** -23) * size + tiny
+    assert bool(((scores.double() - want).abs() <= bound).all())
+    # counts are those of the scores themselves
+    hi, eq = kb.eval_rank_all(dev(H), dev(M), dev(th), dev(tr), dev(tt))
+    others = torch.ones_like(scores, dtype=torch.bool)
+    others[torch.arange(2 * n_test, device="cuda"), dev(true)] = False
+    assert torch.equal(hi.long(), ((scores > ans[:, None]) & others).sum(1))
+    assert torch.equal(eq.long(), ((scores == ans[:, None]) & others).sum(1))
+
+
+def model(n, R, d, seed):
+    rng = np.random.default_rng(seed)
+    H, M = rng.normal(size=(n, d)).astype(np.float32), rng.normal(size=(R, d)).astype(np.float32)
+    H[n // 2] = H[n // 3]                               # equal scores, and a row of zeros
+    H[1] = 0.0
+    return H, M
+
+
+@pytest.mark.parametrize("n,n_test", [(700, 90), (17001, 520)])       # 128 x 128 and 256 x 256 tiles, ragged both ways
+@pytest.mark.parametrize("d", [76, 80, 84, 200, 1024])
+def test_widths(kb, n, n_test, d):
+    print("[case] widths", n, n_test, d, file=sys.stderr, flush=True)
+    H, M = model(n, 3, d, 51)
+    check(kb, H, M, n, 3, n_test, 52)
+
+
+@pytest.mark.parametrize("what,scale", [("row", 2.0 ** -13), ("row", 2.0 ** -16), ("row", 2.0 ** -40), ("column", 2.0 ** -30),
+                                        ("all", 2.0 ** -23), ("all", 2.0 ** -26), ("all", 2.0 ** 23), ("all", 2.0 ** 30),
+                                        ("relation", 2.0 ** -20)])
+def test_sizes(kb, what, scale):
+    """Rows, columns, relations and whole tensors far from the rest in size."""
+    print("[case] sizes", what, scale, file=sys.stderr, flush=True)
+    n, R, d = 700, 3, 128
+    H, M = model(n, R, d, 53)
+    if what == "row": H[n - 1] *= scale; H[5] *= scale
+    elif what == "column": H[:, 7] *= scale
+    elif what == "all": H *= scale
+    else: M[1] *= scale
+    check(kb, H, M, n, R, 90, 54)
+
+
+def test_whole_numbers_are_exact(kb):
+    print("[case] whole numbers", file=sys.stderr, flush=True)
+    import torch
+    n, R, d, n_test = 5000, 2, 96, 300
+    rng = np.random.default_rng(55)
+    H = rng.integers(-9, 10, (n, d)).astype(np.float32); M = rng.integers(-3, 4, (R, d)).astype(np.float32)
+    th, tr, tt = (rng.integers(0, hi, n_test).astype(np.int32) for hi in (n, R, n))
+    dev = lambda x: torch.from_numpy(np.ascontiguousarray(x)).cuda()  # noqa: E731
+    hi, eq = kb.eval_rank_all(dev(H), dev(M), dev(th), dev(tr), dev(tt))
+    whi, weq = ev.filtered_counts(H, M, th, tr, tt)
+    assert weq.max() > 0
+    np.testing.assert_array_equal(hi.cpu().numpy(), whi)
+    np.testing.assert_array_equal(eq.cpu().numpy(), weq)
+
+
+def test_counts_of_many_queries(kb):
+    """Mean reciprocal rank and shares of ranks up to k from given counts, extreme ones among them."""
+    print("[case] metrics", file=sys.stderr, flush=True)
+    import torch
+    rng = np.random.default_rng(56)
+    for n in (1, 1023, 8193, 30000):
+        hi, eq = rng.integers(0, 40, n).astype(np.int32), rng.integers(0, 4, n).astype(np.int32)
+        hi[: n // 9], eq[0] = 2**31 - 1, 2**31 - 1
+        ks = (1, 3, 10, 2**31 - 1)
+        got = kb.eval_metrics(torch.from_numpy(hi).cuda(), torch.from_numpy(eq).cuda(), ks).cpu().numpy()
+        rank = 1.0 + hi.astype(np.float64) + 0.5 * eq
+        np.testing.assert_allclose(got, [np.mean(1.0 / rank)] + [np.mean(rank <= k) for k in ks], rtol=1e-12)
