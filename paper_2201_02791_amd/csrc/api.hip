@@ -124,7 +124,7 @@ void layout(const kge_partition *p, const kge_layer *layers, int32_t n_layers, i
     w->off_P.assign(n_layers, 0); w->off_H.resize(n_layers); w->off_Z.assign(n_layers, 0);
     w->off_Wrel.assign(n_layers, 0); w->off_Wrb.assign(n_layers, 0); w->off_WrbT.assign(n_layers, 0);
     size_t max_u = 0;
-    size_t max_c = 0, max_zd = 0;
+    size_t max_c = 0, max_zd = 0, max_rel_rows = 0;
     w->off_Hbf.assign(n_layers, 0); w->off_Wbf.assign(n_layers, 0); w->off_WbfT.assign(n_layers, 0);
     w->off_Hd.assign(n_layers, 0);
     for (int l = 0; l < n_layers; ++l) {
@@ -148,6 +148,8 @@ void layout(const kge_partition *p, const kge_layer *layers, int32_t n_layers, i
             if ((size_t)L.d_in > max_dout) max_dout = L.d_in;      // Self also holds the self-loop part of dH
         } else {
             w->off_P[l] = cur; cur = align_up(cur + N * L.n_bases * L.d_out * ep, 256);
+            if (gather_by_relation(p, L.n_bases, L.d_out, bf) && (size_t)p->n_sgrp * L.d_out * 4 > max_rel_rows)
+                max_rel_rows = (size_t)p->n_sgrp * L.d_out * 4;
         }
         w->off_H[l] = cur; cur = align_up(cur + N * L.d_out * 4, 256);
         if (L.dropout > 0.0f) { w->off_Hd[l] = cur; cur = align_up(cur + N * L.d_in * 4, 256); }
@@ -168,7 +170,9 @@ void layout(const kge_partition *p, const kge_layer *layers, int32_t n_layers, i
     w->off_self = cur; cur = align_up(cur + N * max_dout * 4, 256);
     w->off_G = cur; cur = align_up(cur + N * max_dout * 4, 256);
     // dP; bf16 workloads append G behind it so that X = [dP | G] is one bf16 matrix
-    w->off_dP = cur; cur = align_up(cur + (bf ? N * max_nc * 2 : N * max_bd * ep), 256);
+    // the forward pass keeps its rows per (source, relation) there
+    const size_t dp_bytes = bf ? N * max_nc * 2 : N * max_bd * ep;
+    w->off_dP = cur; cur = align_up(cur + (dp_bytes > max_rel_rows ? dp_bytes : max_rel_rows), 256);
     w->off_dHa = cur; cur = align_up(cur + N * max_din * 4, 256);
     w->off_dHb = cur; cur = align_up(cur + N * max_din * 4, 256);
     w->off_seg = cur; cur = align_up(cur + (size_t)p->n_seg * max_B * 4, 256);
@@ -328,7 +332,8 @@ extern "C" int kge_rgcn_forward(const kge_partition *p, const kge_cgraph *cg, co
         }
         if (rc != KGE_OK) return rc;
         rc = launch_gather_forward(p, P, bf, L.a, L.n_bases, L.d_out, Self, L.act, out1, out2, part,
-                                   kge_cgraph_layer(cg, l), st);
+                                   (float *)(ws + w.off_dP), kge_cgraph_layer(cg, l), kge_cgraph_layer(cg, l - 1),
+                                   kge_cgraph_edge_count(cg, l), st);
         if (rc != KGE_OK) return rc;
         Hin = Hl;
     }

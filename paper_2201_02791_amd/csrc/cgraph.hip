@@ -206,6 +206,11 @@ extern "C" int kge_cgraph_export(const kge_cgraph *cg, uint8_t *host_active, int
     return KGE_OK;
 }
 
+const unsigned long long *kge_cgraph_edge_count(const kge_cgraph *cg, int32_t layer)
+{
+    return cg ? cg->stats + 4 * layer + 1 : nullptr;
+}
+
 const uint8_t *kge_cgraph_layer(const kge_cgraph *cg, int32_t layer)
 {
     if (!cg) return nullptr;

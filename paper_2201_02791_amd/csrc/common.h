@@ -34,6 +34,7 @@ void kge_set_error(const char *fmt, ...);
 // small finishing kernel sums in unit order (deterministic).  Power-law graphs put a large share
 // of all edges into such rows.
 #define KGE_HEAVY 256
+#define KGE_HEAVY_GROUPS 64       // the same for a source's (source, relation) groups
 struct kge_heavy_index {
     int32_t n_hv, n_units;
     int32_t *hv_row;        // [n_hv]    row id of each heavy row, ascending
@@ -57,6 +58,11 @@ struct kge_partition {
     int32_t *sm_ptr, *sm_dst, *sm_rel;
     float *sm_invc;
     int32_t *sm_seg;    // [E] run id of each edge in source-major order
+    // the source-major edges grouped by relation inside a source: one group per (source, relation) pair that occurs
+    int64_t n_sgrp;
+    int32_t *sg_ptr, *sg_rel;        // [N+1] first group of each source, [n_sgrp] relation (one allocation)
+    int32_t *dm_grp;                 // [E] group of each edge in destination-major order (behind sm_seg)
+    kge_heavy_index hv_sg;           // sources of KGE_HEAVY_GROUPS groups or more
     int32_t *rel_ptr;   // [2R+1] run range per relation
     kge_heavy_index hv_dm, hv_sm, hv_seg;   // heavy destinations, sources, runs
     // the runs grouped by destination (order dst, rel): dr_seg = run id, dr_rel = its relation
@@ -147,10 +153,13 @@ int launch_input_grad_bf16(const void *X, int64_t N, int32_t d_in, int32_t d_out
 // computational sub-graph for this layer.  Rows outside it are written as zeros (forward) and
 // edges into them are skipped (backward: their upstream gradient is zero).
 // out[i] = act( sum_{e into i} invc_e sum_b a[rel_e][b] P[src_e][b][:] + Self[i] ); out2 optional copy
-// `partial`: [hv_dm.n_units][d] floats of scratch
+// `partial`: [hv_dm.n_units][d] floats of scratch.  Where gather_by_relation(), `rel_rows` is scratch of [n_sgrp][d] floats;
+// with a sub-graph also src_active (the vertices the layer reads) and n_active_edges (DEVICE: edges into `active`)
+bool gather_by_relation(const kge_partition *p, int32_t B, int32_t d, int msg_bf16);
 int launch_gather_forward(const kge_partition *p, const void *P, int msg_bf16, const float *a,
                           int32_t B, int32_t d, const float *Self, int act, float *out, float *out2,
-                          float *partial, const uint8_t *active, hipStream_t st);
+                          float *partial, float *rel_rows, const uint8_t *active, const uint8_t *src_active,
+                          const unsigned long long *n_active_edges, hipStream_t st);
 // G = dHout * act'(Hout) (ReLU: Hout > 0)
 int launch_act_backward(const float *dHout, const float *Hout, int act, int64_t n, float *G,
                         hipStream_t st);
@@ -177,6 +186,8 @@ int launch_project_first_backward(const kge_partition *p, const void *P, int msg
 // cgraph.hip: per-batch computational sub-graph ------------------------------
 // flag row of layer `layer` (device pointer; -1: the first layer's input rows the batch reads), or null when cg is null
 const uint8_t *kge_cgraph_layer(const kge_cgraph *cg, int32_t layer);
+// DEVICE count of the message edges into that layer's active vertices, or null when cg is null
+const unsigned long long *kge_cgraph_edge_count(const kge_cgraph *cg, int32_t layer);
 int kge_cgraph_check(const kge_partition *p, const kge_cgraph *cg, int32_t n_layers);
 
 // gather.hip, run means (relation-weight order) -----------------------------

@@ -70,15 +70,15 @@ struct RowWork {
 __device__ __forceinline__ RowWork row_work(int64_t wid, const int32_t *__restrict__ ptr, int64_t n_rows,
                                             int32_t n_units, const int32_t *__restrict__ hv_row,
                                             const int32_t *__restrict__ hv_unit_ptr,
-                                            const int32_t *__restrict__ unit_hv)
+                                            const int32_t *__restrict__ unit_hv, int32_t heavy = KGE_HEAVY)
 {
     RowWork w;
     if (wid < n_units) {
         const int32_t h = unit_hv[wid];
         w.row = hv_row[h];
         w.unit = (int32_t)wid;
-        w.beg = ptr[w.row] + (int32_t)(wid - hv_unit_ptr[h]) * KGE_HEAVY;
-        w.end = min(w.beg + KGE_HEAVY, ptr[w.row + 1]);
+        w.beg = ptr[w.row] + (int32_t)(wid - hv_unit_ptr[h]) * heavy;
+        w.end = min(w.beg + heavy, ptr[w.row + 1]);
         return w;
     }
     w.row = wid - n_units;
@@ -86,9 +86,17 @@ __device__ __forceinline__ RowWork row_work(int64_t wid, const int32_t *__restri
     if (w.row >= n_rows) { w.row = -1; w.beg = w.end = 0; return w; }
     w.beg = ptr[w.row];
     w.end = ptr[w.row + 1];
-    if (w.end - w.beg >= KGE_HEAVY) w.row = -1;
+    if (w.end - w.beg >= heavy) w.row = -1;
     return w;
 }
+
+// A sub-graph's size is known on the device only: of two forms of a sum that are both launched, one runs if the sub-graph has
+// more than `at` edges and the other if not.  count null: always.
+struct EdgeGate {
+    const unsigned long long *count;
+    unsigned long long at;
+    __device__ __forceinline__ bool shut(bool above) const { return count && (*count > at) != above; }
+};
 
 // ------------------------------------------------------------------ forward
 //   out[i][:] = act( sum_e invc_e sum_b a[rel_e][b] P[src_e][b][:] + Self[i][:] )
@@ -102,8 +110,9 @@ __global__ __launch_bounds__(64 * WPB) void k_gather_fwd(
     const int32_t *__restrict__ unit_hv,
     const void *__restrict__ P, const float *__restrict__ a, int32_t B, int32_t d, int32_t gb_count,
     const float *__restrict__ Self, int act, float *__restrict__ out, float *__restrict__ out2,
-    uint16_t *__restrict__ outbf, float *__restrict__ partial, const uint8_t *__restrict__ active)
+    uint16_t *__restrict__ outbf, float *__restrict__ partial, const uint8_t *__restrict__ active, EdgeGate gate)
 {
+    if (gate.shut(PLAIN)) return;
     // outbf (optional): a bf16 copy of the output rows (the next layer's bf16 input, written here instead of by a
     // conversion pass over `out`)
     constexpr int VEC = MsgRow<BF16>::VEC;
@@ -233,6 +242,85 @@ __global__ __launch_bounds__(64 * WPB) void k_gather_fwd(
             *reinterpret_cast<float4 *>(out + o + v4) = r;
             if (out2) *reinterpret_cast<float4 *>(out2 + o + v4) = r;
             if (outbf) *reinterpret_cast<uint2 *>(outbf + o + v4) = make_uint2(pack_bf16x2(r.x, r.y), pack_bf16x2(r.z, r.w));
+        }
+    }
+}
+
+// The rows that the edges of one (source, relation) pair share:
+//   Q[g][:] = sum_b a[rel_g][b] P[src_g][b][:]        (fp32, [n_sgrp][d])
+// for every group g of the source-major view, after which the forward sum over edges gathers one row per edge instead of B.
+// One wavefront per source (per 64 groups of one with more); a row is covered by LPR lanes, the 64 / LPR lane groups take
+// different groups, U each at a time.  A lane holds the coefficients of one of the 64 groups and hands them out (a scalar
+// where a wavefront has one lane group, else by a shuffle), so that no memory round trip stands between the groups.  The
+// source's P rows and the coefficients stay in registers if it has at most NB bases, else they pass NB at a time per round.
+// Bound by writing Q and by the latency of a source's chain.  544 k edges, 355 k groups, 10 bases of 200 floats: 87 us and
+// the gather of one row per edge 94, where gathering ten took 723; 2 M edges, 1.16 M groups, 16 bases of 128 bf16: 209 + 190,
+// 1036.  (The loop over the bases has to be unrolled in full: with P indexed in scratch memory 185 and 596 us.)
+template <bool BF16, int LPR, int NB>
+__global__ __launch_bounds__(64 * WPB) void k_relation_rows(
+    const int32_t *__restrict__ sg_ptr, const int32_t *__restrict__ sg_rel, int64_t N,
+    int32_t n_units, const int32_t *__restrict__ hv_row, const int32_t *__restrict__ hv_unit_ptr,
+    const int32_t *__restrict__ unit_hv, const void *__restrict__ P, const float *__restrict__ a, int32_t B, int32_t d,
+    float *__restrict__ Q, const uint8_t *__restrict__ active, EdgeGate gate)
+{
+    if (gate.shut(true)) return;
+    constexpr int VEC = MsgRow<BF16>::VEC, NG = 64 / LPR, U = NG > 1 ? 4 : 8;
+    const int lane = threadIdx.x & 63;
+    const RowWork rw = row_work((int64_t)blockIdx.x * WPB + (threadIdx.x >> 6), sg_ptr, N, n_units, hv_row, hv_unit_ptr, unit_hv,
+                                KGE_HEAVY_GROUPS);
+    if (rw.row < 0) return;                              // whole wavefronts leave
+    if (active && !active[rw.row]) return;               // no active destination has an edge from here
+    const int kl = lane % LPR, g = lane / LPR;
+    const bool kact = kl * VEC < d;
+    const int64_t col = kact ? kl * VEC : 0;
+    const int64_t prow = rw.row * B;
+    uint4 p[NB];
+    float c[NB];                                         // of the lane's group
+    auto fetch = [&](int b0) __attribute__((always_inline)) {
+#pragma unroll
+        for (int n = 0; n < NB; ++n) p[n] = MsgRow<BF16>::load_raw(P, (prow + min(b0 + n, B - 1)) * d + col);
+    };
+    if (B <= NB) fetch(0);
+    for (int32_t g0 = rw.beg; g0 < rw.end; g0 += 64) {
+        const int cnt = min(64, rw.end - g0);
+        const float *ar = a + (int64_t)sg_rel[g0 + min(lane, cnt - 1)] * B;
+        auto coefs = [&](int b0) __attribute__((always_inline)) {
+#pragma unroll
+            for (int n = 0; n < NB; ++n) c[n] = ar[min(b0 + n, B - 1)];
+        };
+        if (B <= NB) coefs(0);
+        for (int q0 = 0; q0 < cnt; q0 += NG * U) {
+            float acc[U][VEC];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int v = 0; v < VEC; ++v) acc[u][v] = 0.f;
+            for (int b0 = 0; b0 < B; b0 += NB) {
+                if (B > NB) { fetch(b0); coefs(b0); }
+#pragma unroll
+                for (int n = 0; n < NB; ++n)
+                    if (b0 + n < B) {                    // uniform
+                        float val[VEC];
+                        MsgRow<BF16>::unpack(p[n], val);
+#pragma unroll
+                        for (int u = 0; u < U; ++u) {    // a slot past the last group: sums that nothing stores
+                            float x;
+                            if constexpr (NG > 1) x = __shfl(c[n], (q0 + u * NG + g) & 63, 64);
+                            else x = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(c[n]), (q0 + u) & 63));
+#pragma unroll
+                            for (int v = 0; v < VEC; ++v) acc[u][v] = fmaf(x, val[v], acc[u][v]);
+                        }
+                    }
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int q = q0 + u * NG + g;
+                if (q >= cnt || !kact) continue;
+                float *o = Q + (int64_t)(g0 + q) * d + col;
+#pragma unroll
+                for (int v4 = 0; v4 < VEC; v4 += 4)
+                    *reinterpret_cast<float4 *>(o + v4) = make_float4(acc[u][v4], acc[u][v4 + 1], acc[u][v4 + 2], acc[u][v4 + 3]);
+            }
         }
     }
 }
@@ -958,9 +1046,79 @@ int largest_pow2_dividing(int x, int cap) { int p = 1; while (p * 2 <= cap && x 
     default: { constexpr int L = 64; CALL; } break;                                     \
     }
 
+// out[i] = act( sum_{q in row i of the view} w_q X[idx_q][:] + Self[i] ),  X rows of d elements (fp32 or bf16)
+static int launch_row_sum(const int32_t *ptr, const int32_t *idx, const float *w, int64_t n_rows,
+                          const kge_heavy_index &hx, const char *name, const void *X, int x_bf16, int32_t d,
+                          const float *Self, int act, float *out, float *out2, uint16_t *outbf, float *partial,
+                          const uint8_t *active, hipStream_t st, EdgeGate gate = {nullptr, 0}, bool finish = true)
+{
+    if (n_rows == 0) return KGE_OK;
+    const int vec = x_bf16 ? 8 : 4;
+    const int lpr = pow2_at_least((d + vec - 1) / vec);
+    KGE_REQUIRE(lpr <= 64, KGE_EINVAL, "feature width %d too large for the aggregation kernel", d);
+    const unsigned grid = (unsigned)cdiv(n_rows + hx.n_units, WPB);
+    {
+        KGE_PROF(name, st);
+#define RS_ARGS ptr, idx, nullptr, w, n_rows, hx.n_units, hx.hv_row, hx.hv_unit_ptr, hx.unit_hv, X, nullptr, 1, d, 1, \
+                Self, act, out, out2, outbf, partial, active, gate
+        if (x_bf16) { DISPATCH_LPR(lpr, (k_gather_fwd<true, L, true><<<grid, 64 * WPB, 0, st>>>(RS_ARGS))); }
+        else { DISPATCH_LPR(lpr, (k_gather_fwd<false, L, true><<<grid, 64 * WPB, 0, st>>>(RS_ARGS))); }
+#undef RS_ARGS
+    }
+    KGE_LAUNCH_CHECK();
+    if (finish && hx.n_hv > 0) {
+        KGE_PROF("gather_fwd_fin", st);
+        const int64_t n = (int64_t)hx.n_hv * (d / 4);
+        k_gather_fwd_finish<<<(unsigned)cdiv(n, 256), 256, 0, st>>>(hx.n_hv, hx.hv_row, hx.hv_unit_ptr, partial, d,
+                                                                   Self, act, out, out2, outbf, active);
+        KGE_LAUNCH_CHECK();
+    }
+    return KGE_OK;
+}
+
+// Bytes: the form with a row per (source, relation) reads P once, writes and reads fp32 rows of the groups and gathers one
+// fp32 row per edge; the other one gathers B rows per edge.  What has to be saved pays for the launches (about 5 us each at
+// the rate of the gathers): one more, and two where both forms are launched and a sub-graph's size decides.
+// Whole forward passes, us, a row per pair / B rows per edge: 14,541 entities x 272,115 triples, d = 64: 3 bases 70 / 81, 4
+// bases 73 / 100; d = 200: 3 bases 193 / 257; one relation, 1 M triples, d = 128, 2 bases 274 / 302; 50,021 entities x
+// 1 M triples, 128 bf16: 6 bases 457 / 477, 8 bases 458 / 593.
+static double relation_rows_fixed(const kge_partition *p, int32_t B, int32_t d, int msg_bf16)
+{
+    return d * ((double)p->n_vert * B * (msg_bf16 ? 2 : 4) + 8.0 * (double)p->n_sgrp);
+}
+static double relation_rows_per_edge(int32_t B, int32_t d, int msg_bf16) { return (double)d * (B * (msg_bf16 ? 2 : 4) - 4); }
+static bool relation_rows_pay(const kge_partition *p, int32_t B, int32_t d, int msg_bf16, double least)
+{
+    return p->n_edge * relation_rows_per_edge(B, d, msg_bf16) > relation_rows_fixed(p, B, d, msg_bf16) + least;
+}
+constexpr double ONE_LAUNCH = 3.2e7;
+bool gather_by_relation(const kge_partition *p, int32_t B, int32_t d, int msg_bf16)
+{
+    return relation_rows_pay(p, B, d, msg_bf16, ONE_LAUNCH);
+}
+
+template <bool BF16>
+static int launch_relation_rows(const kge_partition *p, const void *P, const float *a, int32_t B, int32_t d, float *Q,
+                                const uint8_t *src_active, EdgeGate gate, hipStream_t st)
+{
+    const kge_heavy_index &hx = p->hv_sg;
+    const int lpr = pow2_at_least((d + MsgRow<BF16>::VEC - 1) / MsgRow<BF16>::VEC);
+    const unsigned grid = (unsigned)cdiv(p->n_vert + hx.n_units, WPB);
+    KGE_PROF("gather_rows", st);
+#define RR_ARGS p->sg_ptr, p->sg_rel, p->n_vert, hx.n_units, hx.hv_row, hx.hv_unit_ptr, hx.unit_hv, P, a, B, d, Q, src_active, gate
+    if (B <= 4) { DISPATCH_LPR(lpr, (k_relation_rows<BF16, L, 4><<<grid, 64 * WPB, 0, st>>>(RR_ARGS))); }
+    else if (B <= 8) { DISPATCH_LPR(lpr, (k_relation_rows<BF16, L, 8><<<grid, 64 * WPB, 0, st>>>(RR_ARGS))); }
+    else if (B <= 12) { DISPATCH_LPR(lpr, (k_relation_rows<BF16, L, 12><<<grid, 64 * WPB, 0, st>>>(RR_ARGS))); }
+    else { DISPATCH_LPR(lpr, (k_relation_rows<BF16, L, 16><<<grid, 64 * WPB, 0, st>>>(RR_ARGS))); }
+#undef RR_ARGS
+    KGE_LAUNCH_CHECK();
+    return KGE_OK;
+}
+
 int launch_gather_forward(const kge_partition *p, const void *P, int msg_bf16, const float *a,
                           int32_t B, int32_t d, const float *Self, int act, float *out, float *out2,
-                          float *partial, const uint8_t *active, hipStream_t st)
+                          float *partial, float *rel_rows, const uint8_t *active, const uint8_t *src_active,
+                          const unsigned long long *n_active_edges, hipStream_t st)
 {
     const int64_t N = p->n_vert;
     if (N == 0) return KGE_OK;
@@ -969,11 +1127,22 @@ int launch_gather_forward(const kge_partition *p, const void *P, int msg_bf16, c
     KGE_REQUIRE(lpr <= 64, KGE_EINVAL, "feature width %d too large for the aggregation kernel", d);
     const int gbc = largest_pow2_dividing(B, 64 / lpr);
     const kge_heavy_index &hx = p->hv_dm;
+    EdgeGate gate = {nullptr, 0};
+    if (relation_rows_pay(p, B, d, msg_bf16, active ? 4 * ONE_LAUNCH : ONE_LAUNCH)) {
+        // with a sub-graph: only if it has the edges that pay for all groups' rows
+        if (active) gate = {n_active_edges, (unsigned long long)(relation_rows_fixed(p, B, d, msg_bf16) / relation_rows_per_edge(B, d, msg_bf16))};
+        int rc = msg_bf16 ? launch_relation_rows<true>(p, P, a, B, d, rel_rows, src_active, gate, st)
+                          : launch_relation_rows<false>(p, P, a, B, d, rel_rows, src_active, gate, st);
+        if (rc != KGE_OK) return rc;
+        rc = launch_row_sum(p->dm_ptr, p->dm_grp, p->dm_invc, N, hx, "gather_fwd", rel_rows, 0, d, Self, act, out, out2, nullptr,
+                            partial, active, st, gate, !gate.count);
+        if (rc != KGE_OK || !gate.count) return rc;
+    }
     const unsigned grid = (unsigned)cdiv(N + hx.n_units, WPB);
     {
         KGE_PROF("gather_fwd", st);
 #define GF_ARGS p->dm_ptr, p->dm_src, p->dm_rel, p->dm_invc, N, hx.n_units, hx.hv_row, hx.hv_unit_ptr, hx.unit_hv, \
-                P, a, B, d, gbc, Self, act, out, out2, nullptr, partial, active
+                P, a, B, d, gbc, Self, act, out, out2, nullptr, partial, active, gate
         if (msg_bf16) { DISPATCH_LPR(lpr, (k_gather_fwd<true, L, false><<<grid, 64 * WPB, 0, st>>>(GF_ARGS))); }
         else { DISPATCH_LPR(lpr, (k_gather_fwd<false, L, false><<<grid, 64 * WPB, 0, st>>>(GF_ARGS))); }
 #undef GF_ARGS
@@ -984,36 +1153,6 @@ int launch_gather_forward(const kge_partition *p, const void *P, int msg_bf16, c
         const int64_t n = (int64_t)hx.n_hv * (d / 4);
         k_gather_fwd_finish<<<(unsigned)cdiv(n, 256), 256, 0, st>>>(hx.n_hv, hx.hv_row, hx.hv_unit_ptr, partial, d,
                                                                    Self, act, out, out2, nullptr, active);
-        KGE_LAUNCH_CHECK();
-    }
-    return KGE_OK;
-}
-
-// out[i] = act( sum_{q in row i of the view} w_q X[idx_q][:] + Self[i] ),  X rows of d elements (fp32 or bf16)
-static int launch_row_sum(const int32_t *ptr, const int32_t *idx, const float *w, int64_t n_rows,
-                          const kge_heavy_index &hx, const char *name, const void *X, int x_bf16, int32_t d,
-                          const float *Self, int act, float *out, float *out2, uint16_t *outbf, float *partial,
-                          const uint8_t *active, hipStream_t st)
-{
-    if (n_rows == 0) return KGE_OK;
-    const int vec = x_bf16 ? 8 : 4;
-    const int lpr = pow2_at_least((d + vec - 1) / vec);
-    KGE_REQUIRE(lpr <= 64, KGE_EINVAL, "feature width %d too large for the aggregation kernel", d);
-    const unsigned grid = (unsigned)cdiv(n_rows + hx.n_units, WPB);
-    {
-        KGE_PROF(name, st);
-#define RS_ARGS ptr, idx, nullptr, w, n_rows, hx.n_units, hx.hv_row, hx.hv_unit_ptr, hx.unit_hv, X, nullptr, 1, d, 1, \
-                Self, act, out, out2, outbf, partial, active
-        if (x_bf16) { DISPATCH_LPR(lpr, (k_gather_fwd<true, L, true><<<grid, 64 * WPB, 0, st>>>(RS_ARGS))); }
-        else { DISPATCH_LPR(lpr, (k_gather_fwd<false, L, true><<<grid, 64 * WPB, 0, st>>>(RS_ARGS))); }
-#undef RS_ARGS
-    }
-    KGE_LAUNCH_CHECK();
-    if (hx.n_hv > 0) {
-        KGE_PROF("gather_fwd_fin", st);
-        const int64_t n = (int64_t)hx.n_hv * (d / 4);
-        k_gather_fwd_finish<<<(unsigned)cdiv(n, 256), 256, 0, st>>>(hx.n_hv, hx.hv_row, hx.hv_unit_ptr, partial, d,
-                                                                   Self, act, out, out2, outbf, active);
         KGE_LAUNCH_CHECK();
     }
     return KGE_OK;

@@ -218,6 +218,32 @@ __global__ void k_view_emit(const uint32_t *pos_sorted, int64_t E, const uint64_
     if (o_seg) o_seg[q] = (int32_t)edge_seg[e];
 }
 
+// first edges of the (source, relation) groups of the source-major view
+__global__ void k_group_flag(const uint32_t *src, const int32_t *rel, int64_t E, uint32_t *flag)
+{
+    int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (q >= E) return;
+    flag[q] = q == 0 || src[q] != src[q - 1] || rel[q] != rel[q - 1] ? 1u : 0u;
+}
+
+// relation of every group and, by position in the canonical order, every edge's group
+__global__ void k_group_emit(const uint32_t *pos_sorted, const int32_t *rel, int64_t E, const uint32_t *flag,
+                             const uint32_t *before, int32_t *sg_rel, uint32_t *group_of)
+{
+    int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (q >= E) return;
+    const uint32_t g = before[q] + flag[q] - 1u;
+    if (flag[q]) sg_rel[g] = rel[q];
+    group_of[pos_sorted[q]] = g;
+}
+
+// out[i] = table[idx[i]]
+__global__ void k_pick(const uint32_t *table, const uint32_t *idx, int64_t n, int32_t *out)
+{
+    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) out[i] = (int32_t)table[idx[i]];
+}
+
 // keys[s] = destination of run s, vals[s] = s
 __global__ void k_run_keys(const int32_t *seg_dst, int64_t S, uint32_t *k, uint32_t *v)
 {
@@ -244,15 +270,15 @@ __global__ void k_max_degree(const int32_t *ptr, int64_t nv, int32_t *out)
     atomicMax(out, ptr[v + 1] - ptr[v]);
 }
 
-// Heavy-row index: rows with at least KGE_HEAVY edges, cut into units of KGE_HEAVY edges.
-__global__ void k_heavy_flag(const int32_t *ptr, int64_t n_rows, uint32_t *flag, uint32_t *units)
+// Heavy-row index: rows with at least `heavy` edges, cut into units of as many.
+__global__ void k_heavy_flag(const int32_t *ptr, int64_t n_rows, int32_t heavy, uint32_t *flag, uint32_t *units)
 {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n_rows) return;
     int32_t deg = ptr[i + 1] - ptr[i];
-    uint32_t f = deg >= KGE_HEAVY ? 1u : 0u;
+    uint32_t f = deg >= heavy ? 1u : 0u;
     flag[i] = f;
-    units[i] = f ? (uint32_t)((deg + KGE_HEAVY - 1) / KGE_HEAVY) : 0u;
+    units[i] = f ? (uint32_t)((deg + heavy - 1) / heavy) : 0u;
 }
 
 __global__ void k_heavy_emit(int64_t n_rows, const uint32_t *flag, const uint32_t *hpos,
@@ -306,13 +332,13 @@ template <typename T> int palloc(T **out, size_t count)
 #define TRY(x) do { int rc__ = (x); if (rc__ != KGE_OK) return rc__; } while (0)
 inline unsigned grid_for(int64_t n) { return (unsigned)(n > 0 ? cdiv(n, TB) : 1); }
 
-int build_heavy_index(const int32_t *ptr, int64_t n_rows, kge_heavy_index *hx, hipStream_t st)
+int build_heavy_index(const int32_t *ptr, int64_t n_rows, kge_heavy_index *hx, hipStream_t st, int32_t heavy = KGE_HEAVY)
 {
     TempBufs tmp;
     uint32_t *flag, *units, *hpos, *upos;
     TRY(tmp.alloc(&flag, n_rows)); TRY(tmp.alloc(&units, n_rows));
     TRY(tmp.alloc(&hpos, (size_t)n_rows + 1)); TRY(tmp.alloc(&upos, (size_t)n_rows + 1));
-    if (n_rows > 0) { k_heavy_flag<<<grid_for(n_rows), TB, 0, st>>>(ptr, n_rows, flag, units); KGE_LAUNCH_CHECK(); }
+    if (n_rows > 0) { k_heavy_flag<<<grid_for(n_rows), TB, 0, st>>>(ptr, n_rows, heavy, flag, units); KGE_LAUNCH_CHECK(); }
     TRY(exclusive_scan(flag, hpos, n_rows, st));
     TRY(exclusive_scan(units, upos, n_rows, st));
     uint32_t nh = 0, nu = 0;
@@ -480,14 +506,16 @@ int build_impl(const int32_t *h_head, const int32_t *h_rel, const int32_t *h_tai
     // --- destination-major and source-major views: stable sorts of edge positions
     TRY(palloc(&p->dm_ptr, N + 1)); TRY(palloc(&p->dm_src, E)); TRY(palloc(&p->dm_rel, E)); TRY(palloc(&p->dm_invc, E));
     TRY(palloc(&p->sm_ptr, N + 1)); TRY(palloc(&p->sm_dst, E)); TRY(palloc(&p->sm_rel, E)); TRY(palloc(&p->sm_invc, E));
-    TRY(palloc(&p->sm_seg, E));
-    uint32_t *k2, *k2_alt, *v2, *v2_alt;
-    TRY(tmp.alloc(&k2, E)); TRY(tmp.alloc(&k2_alt, E)); TRY(tmp.alloc(&v2, E)); TRY(tmp.alloc(&v2_alt, E));
+    TRY(palloc(&p->sm_seg, 2 * (size_t)E));
+    p->dm_grp = p->sm_seg + E;
+    uint32_t *gflag = sflag, *gbefore = spos, *group_of = vals;      // the runs are emitted: their scratch is free
+    uint32_t *k2, *k2_alt = eflag, *v2, *v2_alt = vals_alt;          // the edges are emitted and sorted
+    TRY(tmp.alloc(&k2, E)); TRY(tmp.alloc(&v2, E));
     int32_t *maxdeg;
     TRY(tmp.alloc(&maxdeg, 2));
     KGE_HIP(hipMemsetAsync(maxdeg, 0, 2 * sizeof(int32_t), st));
     const uint64_t vmask = (1ull << vbits) - 1ull;
-    for (int view = 0; view < 2; ++view) {
+    for (int view = 1; view >= 0; --view) {                // by source first: its groups index the other view's edges
         const int key_shift = view == 0 ? vbits : 0;       // sort by dst (view 0) or src (view 1)
         const int other_shift = view == 0 ? 0 : vbits;
         int32_t *ptr = view == 0 ? p->dm_ptr : p->sm_ptr;
@@ -504,9 +532,29 @@ int build_impl(const int32_t *h_head, const int32_t *h_rel, const int32_t *h_tai
         k_ptr_from_sorted<uint32_t><<<grid_for(E + 1), TB, 0, st>>>(k2, E, N, ptr);
         KGE_LAUNCH_CHECK();
         if (N > 0) { k_max_degree<<<grid_for(N), TB, 0, st>>>(ptr, N, maxdeg + view); KGE_LAUNCH_CHECK(); }
+        if (view == 1) {
+            if (E > 0) { k_group_flag<<<grid_for(E), TB, 0, st>>>(k2, p->sm_rel, E, gflag); KGE_LAUNCH_CHECK(); }
+            TRY(exclusive_scan(gflag, gbefore, E, st));
+            uint32_t n_groups = 0;
+            KGE_HIP(hipMemcpy(&n_groups, gbefore + E, sizeof(uint32_t), hipMemcpyDeviceToHost));
+            p->n_sgrp = n_groups;
+            TRY(palloc(&p->sg_ptr, (size_t)N + 1 + n_groups));
+            p->sg_rel = p->sg_ptr + N + 1;
+            if (E > 0) {
+                k_group_emit<<<grid_for(E), TB, 0, st>>>(v2, p->sm_rel, E, gflag, gbefore, p->sg_rel, group_of);
+                KGE_LAUNCH_CHECK();
+            }
+            // a source's first group: the groups that start before its first edge
+            k_pick<<<grid_for(N + 1), TB, 0, st>>>(gbefore, reinterpret_cast<const uint32_t *>(p->sm_ptr), N + 1, p->sg_ptr);
+            KGE_LAUNCH_CHECK();
+        } else if (E > 0) {
+            k_pick<<<grid_for(E), TB, 0, st>>>(group_of, v2, E, p->dm_grp);
+            KGE_LAUNCH_CHECK();
+        }
     }
     TRY(build_heavy_index(p->dm_ptr, N, &p->hv_dm, st));
     TRY(build_heavy_index(p->sm_ptr, N, &p->hv_sm, st));
+    TRY(build_heavy_index(p->sg_ptr, N, &p->hv_sg, st, KGE_HEAVY_GROUPS));
     TRY(build_heavy_index(p->seg_ptr, S, &p->hv_seg, st));
 
     // --- the runs grouped by destination: a stable sort of run ids by destination keeps the
@@ -651,6 +699,7 @@ extern "C" void kge_partition_destroy(kge_partition *p)
                     p->hv_seg.hv_row, p->hv_seg.hv_unit_ptr, p->hv_seg.unit_hv,
                     p->dr_ptr, p->dr_seg, p->dr_rel, p->hv_dr.hv_row, p->hv_dr.hv_unit_ptr, p->hv_dr.unit_hv,
                     p->run_lists, p->sm_seg, p->seg_zrow, p->mrun,
+                    p->sg_ptr, p->hv_sg.hv_row, p->hv_sg.hv_unit_ptr, p->hv_sg.unit_hv,
                     p->bad_ids};
     for (void *q : arrs) if (q) (void)hipFree(q);
     delete p;

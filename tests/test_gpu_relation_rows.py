@@ -1,0 +1,89 @@
+"""Forward pass of the project-first order with one combined row per (source, relation) pair: every width / base-count class
+of its kernel, sources with none, a few, more than 64 and more than 256 relations, on the whole partition and on sub-graphs
+above and below the size at which it runs.  Against the oracle; tolerances as for the other kernels of that order (fp32
+sums of at most a few hundred terms 1e-5 of the largest element, bf16 messages 2e-2)."""
+import numpy as np
+import pytest
+
+from paper_2201_02791_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+def graph(seed, n, R, m, hub_relations=0):
+    rng = np.random.default_rng(seed)
+    head, rel, tail = (rng.integers(0, k, m).astype(np.int32) for k in (n, R, n))
+    rel = (rel.astype(np.int64) * rel // R).astype(np.int32)        # some relations more often
+    if hub_relations:                                               # one source with an edge of every relation
+        head[:hub_relations], rel[:hub_relations] = 5, np.arange(hub_relations)
+    return head, rel, tail
+
+
+def forward_case(orc, n, R, m, d, B, msg, hub=0, seed=0, cone=False, n_pos=64, acts=(1, 0)):
+    from gpu_util import gpu_step, oracle_step
+    spec = synth.scaled(synth.WORKLOADS[0], name="groups", seed=seed, n_entities=n, n_relations=R, n_triples=m, d=d, n_bases=B,
+                        n_pos=n_pos, n_neg=1, n_parts=1, part_id=0, acts=list(acts), msg_dtype=msg)
+    head, rel, tail = graph(seed + 1, n, R, m, hub)
+    gp, ts, params, pos = gpu_step(spec, head, rel, tail, cone=cone)
+    op, res = oracle_step(orc, spec, head, rel, tail, params, pos)
+    return gp, ts, op, res, pos
+
+
+def saved_bytes(gp, B, d, ep):
+    """Bytes per row of an edge and of the rest, as the dispatch counts them (groups counted from the exported arrays)."""
+    rel, ptr = gp.export("sm_rel"), gp.export("sm_ptr")
+    src = np.repeat(np.arange(gp.n_vert), np.diff(ptr))
+    groups = 1 + int(((src[1:] != src[:-1]) | (rel[1:] != rel[:-1])).sum())
+    return d * (gp.n_edge * (B * ep - 4.0) - gp.n_vert * B * ep - 8.0 * groups), groups
+
+
+# identity activations: a ReLU decision within rounding would move whole terms
+@pytest.mark.parametrize("msg,d,B", [("f32", 8, 16), ("f32", 16, 9), ("f32", 32, 12), ("f32", 36, 5), ("f32", 64, 8),
+                                     ("f32", 100, 3), ("f32", 128, 17), ("f32", 200, 10), ("f32", 256, 4), ("f32", 256, 33),
+                                     ("bf16", 16, 24), ("bf16", 32, 16), ("bf16", 64, 12), ("bf16", 128, 16), ("bf16", 136, 5),
+                                     ("bf16", 200, 8), ("bf16", 256, 64)])
+def test_every_class_of_shapes(orc, msg, d, B):
+    n, R = 900, 300
+    m = 90000 if d < 64 or B < 8 else 30000
+    gp, ts, op, res, pos = forward_case(orc, n, R, m, d, B, msg, hub=R, seed=d + B, acts=(0, 0))
+    saved, groups = saved_bytes(gp, B, d, 2 if msg == "bf16" else 4)
+    assert saved > 4e7 or d < 64 or B < 8          # the rule takes it (the others lie on either side)
+    tol = 2e-2 if msg == "bf16" else 1e-5
+    got = ts.H_out.cpu().numpy()
+    assert np.abs(got - res["Hs"][-1]).max() <= tol * np.abs(res["Hs"][-1]).max()
+
+
+@pytest.mark.parametrize("n_pos", [2, 60000])
+@pytest.mark.parametrize("d,B", [(64, 10), (200, 6)])
+def test_sub_graphs_of_either_size(orc, d, B, n_pos):
+    """Two positives: the last layer takes few edges and gathers the bases' rows, the first one most of them; many: both
+    take the combined rows.  The rows of the batch equal the oracle's."""
+    n, R, m = 6000, 20, 90000
+    gp, ts, op, res, pos = forward_case(orc, n, R, m, d, B, "f32", seed=7, cone=True, n_pos=n_pos, acts=(0, 0))
+    saved, _ = saved_bytes(gp, B, d, 4)
+    assert saved > 1.3e8
+    rows = orc.batch_vertices(op, pos, res["neg_ent"])
+    want = res["Hs"][-1][rows]
+    assert np.abs(ts.H_out.cpu().numpy()[rows] - want).max() <= 1e-5 * np.abs(want).max()
+    for l in range(2):
+        for k in ("dV", "da", "dW0"):
+            w = res["grads"][l][k]
+            assert np.abs(ts.grads[l][k].cpu().numpy() - w).max() <= 1e-4 * np.abs(w).max(), (l, k)
+
+
+def test_an_edge_less_partition_and_sources_without_edges(orc):
+    """Vertices that no edge leaves have no group; a second step on the same buffers gives the same bits."""
+    n, R, m, d, B = 5000, 4, 60000, 128, 8
+    from gpu_util import gpu_step, oracle_step
+    import torch
+    spec = synth.scaled(synth.WORKLOADS[0], name="groups", seed=3, n_entities=n, n_relations=R, n_triples=m, d=d, n_bases=B,
+                        n_pos=64, n_neg=1, n_parts=4, part_id=1, acts=[0, 0])
+    head, rel, tail = graph(4, n, R, m)
+    gp, ts, params, pos = gpu_step(spec, head, rel, tail)
+    op, res = oracle_step(orc, spec, head, rel, tail, params, pos)
+    assert saved_bytes(gp, B, d, 4)[0] > 4e7
+    first = ts.H_out.clone()
+    assert np.abs(first.cpu().numpy() - res["Hs"][-1]).max() <= 1e-5 * np.abs(res["Hs"][-1]).max()
+    ts.run(spec.neg_mode, 1, 1)
+    torch.cuda.synchronize()
+    assert torch.equal(ts.H_out, first)
