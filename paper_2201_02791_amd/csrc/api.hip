@@ -170,12 +170,12 @@ void layout(const kge_partition *p, const kge_layer *layers, int32_t n_layers, i
     w->off_self = cur; cur = align_up(cur + N * max_dout * 4, 256);
     w->off_G = cur; cur = align_up(cur + N * max_dout * 4, 256);
     // dP; bf16 workloads append G behind it so that X = [dP | G] is one bf16 matrix
-    // the forward pass keeps its rows per (source, relation) there
-    const size_t dp_bytes = bf ? N * max_nc * 2 : N * max_bd * ep;
-    w->off_dP = cur; cur = align_up(cur + (dp_bytes > max_rel_rows ? dp_bytes : max_rel_rows), 256);
+    w->off_dP = cur; cur = align_up(cur + (bf ? N * max_nc * 2 : N * max_bd * ep), 256);
     w->off_dHa = cur; cur = align_up(cur + N * max_din * 4, 256);
     w->off_dHb = cur; cur = align_up(cur + N * max_din * 4, 256);
     w->off_seg = cur; cur = align_up(cur + (size_t)p->n_seg * max_B * 4, 256);
+    // from dP to here nothing lives in the forward pass, which keeps its rows per (source, relation) there
+    if (cur < w->off_dP + max_rel_rows) cur = align_up(w->off_dP + max_rel_rows, 256);
     // partial results of the units of heavy rows; the three users never overlap in time
     size_t part = (size_t)p->hv_dm.n_units * max_dout;
     if ((size_t)p->hv_sm.n_units * max_bd > part) part = (size_t)p->hv_sm.n_units * max_bd;

@@ -384,12 +384,12 @@ __global__ void k_act_backward(const float4 *__restrict__ dH, const float4 *__re
 // (atomically: another source's group may use the same row; runs are sorted by relation and k_coeff_reduce adds up a
 // relation's rows), after a chunk of 64 edges, so that no atomic stands between the gathered loads.
 // A row is covered by LPR lanes of 4 columns, the 64 / LPR lane groups take NB bases each (16 per wavefront at most).
-// DP = false: the dot products only (dP comes from the matrix-core kernel below).
+// DP = false: the dot products only (dP comes from k_gather_t_bf16).
 // SPREAD: with few bases and narrow rows most lane groups would hold no base; they share a relation's edges instead, all of
 // them with the same NB bases, and their sums meet in a butterfly per relation.
 // Bound by the vector instructions of the groups (most sources have one edge of a relation), the rows coming from the
-// caches.  544 k edges, 10 bases, d = 200, fp32: 361 us, where one kernel per gradient took 728 + 425; 2 M edges, 16 bases,
-// d = 128, bf16 messages: 748 against 1125 + 867.
+// caches: 544 k edges, 4 bases, d = 200, fp32: 149 us; for more bases the matrix-core form below takes over (10 bases 365
+// against 203 us).
 template <int OFF> __device__ __forceinline__ float lane_xor(float x)
 {
     if constexpr (OFF == 1) return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0xb1, 0xf, 0xf, true));
@@ -425,7 +425,6 @@ __global__ __launch_bounds__(64 * WPB) void k_source_backward(
     float *__restrict__ partial, float *__restrict__ seg_out, const uint8_t *__restrict__ active)
 {
     constexpr int NG = 64 / LPR, NBT = SPREAD ? NB : NG * NB, U = 4;
-    constexpr int KA = NB == 12 ? 8 : NB, KB = NB == 12 ? 4 : 0;      // dot products reduced together
     __shared__ float dots[WPB][64][NBT];
     __shared__ int32_t dot_seg[WPB][64];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
@@ -491,12 +490,8 @@ __global__ __launch_bounds__(64 * WPB) void k_source_backward(
                 }
                 part[n] = fmaf(pv[n][3], y.w, fmaf(pv[n][2], y.z, fmaf(pv[n][1], y.y, pv[n][0] * y.x)));
             }
-            const float s = sums_over_lanes<KA, LPR>(part, lane);
-            if (kl < KA && (!SPREAD || g == 0)) dots[wv][n_grp][first_b + kl] = s;
-            if constexpr (KB > 0) {
-                const float s2 = sums_over_lanes<KB, LPR>(part + KA, lane);
-                if (kl < KB) dots[wv][n_grp][first_b + KA + kl] = s2;
-            }
+            const float s = sums_over_lanes<NB, LPR>(part, lane);
+            if (kl < NB && (!SPREAD || g == 0)) dots[wv][n_grp][first_b + kl] = s;
             if (lane == 0) dot_seg[wv][n_grp] = cur_seg;
             ++n_grp;
         };
@@ -597,6 +592,184 @@ __global__ __launch_bounds__(64 * WPB) void k_source_backward(
     }
 }
 
+// The same on the fp32 matrix cores (v_mfma_f32_16x16x4_f32), for several bases.  A wavefront takes a source (or a unit of a
+// heavy one) and 16 bases.  It adds up the rows y of up to 16 (source, relation) groups as above, but leaves them in LDS,
+// [group][column], and then forms
+//   dots[group][base] = Y P^T        (16 x W)(W x 16): both operands 16 bytes per lane, P[j] in registers for the whole source
+//   dP[base][column] += A Y          (16 x 16)(16 x W): A[base][group] = a[rel][base], Y read by columns
+// so that a product and a sum over lanes per group, base and column turn into 8 W / 16 matrix-core instructions per 16 groups,
+// and the dots leave as 64-byte rows of atomics straight from the accumulators.  All fp32, as before.
+// The lane groups of a narrow row take consecutive edges of a pass each; a group of edges cut by that, or by a unit, has two
+// rows.  Unused rows and the columns past the width are zeros (an infinity times a zero would be NaN).
+// W = 16 NBLK >= d columns.  A block is one wavefront (its LDS is what limits their number), 8 rows of G in flight per lane.
+// Bound by the latency of a source's chain at two wavefronts per SIMD: 544 k edges, 355 k groups, 10 bases, d = 200, fp32: 203
+// us, 365 on the vector units; 2 M edges, 16 bases, d = 128, bf16 messages: 442, 754.  (Four wavefronts per block and 4 rows in
+// flight 407 and 542; three wavefronts per SIMD by fewer registers 330 and 560.)
+typedef float sb_f32x4 __attribute__((ext_vector_type(4)));
+
+template <bool BF16, int NBLK, bool DP>
+__global__ __launch_bounds__(64, 2) void k_source_cores(
+    const int32_t *__restrict__ sm_ptr, const int32_t *__restrict__ sm_dst, const int32_t *__restrict__ sm_rel,
+    const float *__restrict__ sm_invc, const int32_t *__restrict__ sm_seg, int64_t N,
+    int32_t n_units, const int32_t *__restrict__ hv_row, const int32_t *__restrict__ hv_unit_ptr,
+    const int32_t *__restrict__ unit_hv, const float *__restrict__ G, const float *__restrict__ a,
+    const void *__restrict__ P, int32_t B, int32_t d, int32_t n_chunks, void *__restrict__ dP, int64_t ld,
+    float *__restrict__ partial, float *__restrict__ seg_out, const uint8_t *__restrict__ active)
+{
+    constexpr int W = 16 * NBLK, LPR = W > 128 ? 64 : W > 64 ? 32 : 16, NG = 64 / LPR;
+    constexpr int RPG = NG == 4 ? 4 : 8, SUB = NG * RPG;              // edges per lane group and per pass (16 at most)
+    constexpr int PITCH = W + 4;                                      // 4 rows apart: 16 banks; one: an odd number of 16 bytes
+    __shared__ __attribute__((aligned(16))) float Y[16 * PITCH];
+    __shared__ __attribute__((aligned(16))) int32_t slot_rel[16], slot_seg[16];
+    const int lane = threadIdx.x;
+    const int64_t wid = (int64_t)blockIdx.x / n_chunks;
+    const int b0 = (int)((int64_t)blockIdx.x - wid * n_chunks) * 16;
+    const RowWork rw = row_work(wid, sm_ptr, N, n_units, hv_row, hv_unit_ptr, unit_hv);
+    if (rw.row < 0) return;                              // a block is one wavefront
+    const int kl = lane % LPR, g = lane / LPR;           // of the row phase: column quad, lane group
+    const int l16 = lane & 15, l4 = lane >> 4;           // of the products
+    const bool kact = kl * 4 < d;
+    const int col = kact ? kl * 4 : 0;
+
+    float p[NBLK][4];                                    // P[row][b0 + l16][16 t + 4 l4 ..]
+    sb_f32x4 acc[NBLK];
+    {
+        const int64_t prow = (rw.row * B + min(b0 + l16, B - 1)) * d;
+#pragma unroll
+        for (int t = 0; t < NBLK; ++t) {
+            const int c = 16 * t + 4 * l4;
+            const int64_t o = prow + (c < d ? c : 0);
+            float4 x;
+            if (BF16) {
+                const uint2 r = *reinterpret_cast<const uint2 *>(reinterpret_cast<const uint16_t *>(P) + o);
+                x = make_float4(__uint_as_float(r.x << 16), __uint_as_float(r.x & 0xffff0000u),
+                                __uint_as_float(r.y << 16), __uint_as_float(r.y & 0xffff0000u));
+            } else {
+                x = *reinterpret_cast<const float4 *>(reinterpret_cast<const float *>(P) + o);
+            }
+            p[t][0] = c < d ? x.x : 0.f; p[t][1] = c < d ? x.y : 0.f; p[t][2] = c < d ? x.z : 0.f; p[t][3] = c < d ? x.w : 0.f;
+            acc[t] = sb_f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+    }
+    auto zero_rows = [&](int from) __attribute__((always_inline)) {
+        for (int r = from + g; r < 16; r += NG)
+            if (kl * 4 < W) *reinterpret_cast<float4 *>(Y + r * PITCH + kl * 4) = make_float4(0.f, 0.f, 0.f, 0.f);
+    };
+    zero_rows(0);                                        // the columns past the width stay zeros from here on
+    int used = 0;                                        // rows of Y in use; uniform
+    auto flush = [&]() __attribute__((always_inline)) {
+        zero_rows(used);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        const int4 rel4 = *reinterpret_cast<const int4 *>(&slot_rel[4 * l4]), seg4 = *reinterpret_cast<const int4 *>(&slot_seg[4 * l4]);
+        const int32_t rel[4] = {rel4.x, rel4.y, rel4.z, rel4.w}, seg[4] = {seg4.x, seg4.y, seg4.z, seg4.w};
+        float c[4];
+        if (DP)
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                const float x = a[(int64_t)(4 * l4 + s < used ? rel[s] : 0) * B + min(b0 + l16, B - 1)];
+                c[s] = 4 * l4 + s < used ? x : 0.f;
+            }
+        sb_f32x4 dot0 = {0.f, 0.f, 0.f, 0.f}, dot1 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int t = 0; t < NBLK; ++t) {
+            const float4 y = *reinterpret_cast<const float4 *>(Y + l16 * PITCH + 16 * t + 4 * l4);
+            dot0 = __builtin_amdgcn_mfma_f32_16x16x4f32(y.x, p[t][0], dot0, 0, 0, 0);
+            dot1 = __builtin_amdgcn_mfma_f32_16x16x4f32(y.y, p[t][1], dot1, 0, 0, 0);
+            dot0 = __builtin_amdgcn_mfma_f32_16x16x4f32(y.z, p[t][2], dot0, 0, 0, 0);
+            dot1 = __builtin_amdgcn_mfma_f32_16x16x4f32(y.w, p[t][3], dot1, 0, 0, 0);
+        }
+        if (DP)
+#pragma unroll
+            for (int t = 0; t < NBLK; ++t)
+#pragma unroll
+                for (int s = 0; s < 4; ++s)              // groups 4 k + s of the four lane quarters k
+                    acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(c[s], Y[(4 * l4 + s) * PITCH + 16 * t + l16], acc[t], 0, 0, 0);
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            if (4 * l4 + v < used && b0 + l16 < B) unsafeAtomicAdd(seg_out + (int64_t)seg[v] * B + b0 + l16, dot0[v] + dot1[v]);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        used = 0;
+    };
+
+    for (int32_t e0 = rw.beg; e0 < rw.end; e0 += 64) {
+        int cnt = min(64, rw.end - e0);
+        const int mine = e0 + min(lane, cnt - 1);
+        int32_t my_dst = sm_dst[mine], my_rel = sm_rel[mine], my_seg = sm_seg[mine];
+        float my_w = sm_invc[mine];
+        if (active) {                                    // edges into the sub-graph only, moved together
+            const bool live = lane < cnt && active[my_dst];
+            const uint64_t lives = __ballot(live);
+            cnt = __popcll(lives);
+            if (cnt == 0) continue;
+            const int before = __popcll(lives & ((1ull << lane) - 1ull));
+            const int to = (live ? before : cnt + lane - before) * 4;         // the others fill the rest
+            my_dst = __builtin_amdgcn_ds_permute(to, my_dst);
+            my_rel = __builtin_amdgcn_ds_permute(to, my_rel);
+            my_seg = __builtin_amdgcn_ds_permute(to, my_seg);
+            my_w = __int_as_float(__builtin_amdgcn_ds_permute(to, __float_as_int(my_w)));
+        }
+        const int32_t prev_rel = __shfl_up(my_rel, 1, 64);
+        float4 row[RPG];
+        auto fetch = [&](int e) __attribute__((always_inline)) {     // edge e of the page; past its end the last one again
+            int32_t dst;
+            if constexpr (NG == 1) dst = __builtin_amdgcn_readlane(my_dst, min(e, cnt - 1));
+            else dst = __shfl(my_dst, min(e, cnt - 1), 64);
+            return *reinterpret_cast<const float4 *>(G + (int64_t)dst * d + col);
+        };
+#pragma unroll
+        for (int u = 0; u < RPG; ++u) row[u] = fetch(g * RPG + u);
+        for (int q0 = 0; q0 < cnt; q0 += SUB) {
+            const int end = min(q0 + SUB, cnt);
+            const bool in = lane >= q0 && lane < end;
+            const uint64_t starts = __ballot(in && ((lane - q0) % RPG == 0 || my_rel != prev_rel));
+            const int n_new = __popcll(starts);
+            if (used + n_new > 16) flush();
+            const int slot = used + __popcll(starts & ((2ull << lane) - 1ull)) - 1;
+            const bool first = starts >> lane & 1, last = lane + 1 == end || (lane < 63 && (starts >> (lane + 1) & 1));
+            if (in && first) { slot_rel[slot] = my_rel; slot_seg[slot] = my_seg; }
+            const int info = slot | (first ? 32 : 0) | (last ? 64 : 0);
+            float4 y = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+            for (int u = 0; u < RPG; ++u) {
+                const int e = q0 + g * RPG + u;
+                int f;
+                float w;
+                if constexpr (NG == 1) {
+                    f = __builtin_amdgcn_readlane(info, min(e, 63));
+                    w = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(my_w), min(e, 63)));
+                } else {
+                    f = __shfl(info, min(e, 63), 64);
+                    w = __shfl(my_w, min(e, 63), 64);
+                }
+                if (f & 32) y = make_float4(0.f, 0.f, 0.f, 0.f);
+                y.x = fmaf(w, row[u].x, y.x); y.y = fmaf(w, row[u].y, y.y);
+                y.z = fmaf(w, row[u].z, y.z); y.w = fmaf(w, row[u].w, y.w);
+                row[u] = fetch(e + SUB);
+                if ((f & 64) && e < end && kact) *reinterpret_cast<float4 *>(Y + (f & 15) * PITCH + kl * 4) = y;
+            }
+            used += n_new;
+        }
+    }
+    if (used) flush();
+    if (!DP) return;
+    // the sums through LDS, so that a lane stores four consecutive columns
+#pragma unroll
+    for (int t = 0; t < NBLK; ++t)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) Y[(4 * l4 + v) * PITCH + 16 * t + l16] = acc[t][v];
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    if (!kact) return;
+    for (int m = g; m < 16 && b0 + m < B; m += NG) {
+        const float4 x = *reinterpret_cast<const float4 *>(Y + m * PITCH + kl * 4);
+        if (rw.unit >= 0) {
+            *reinterpret_cast<float4 *>(partial + ((int64_t)rw.unit * B + b0 + m) * d + kl * 4) = x;
+        } else {
+            const int64_t o = (int64_t)rw.row * ld + (int64_t)(b0 + m) * d + kl * 4;
+            if (BF16) *reinterpret_cast<uint2 *>(reinterpret_cast<uint16_t *>(dP) + o) = make_uint2(pack_bf16x2(x.x, x.y), pack_bf16x2(x.z, x.w));
+            else *reinterpret_cast<float4 *>(reinterpret_cast<float *>(dP) + o) = x;
+        }
+    }
+}
 
 // dP with bf16 messages and many bases, a small dense product per source, on v_mfma_f32_32x32x16_bf16:
 //   dP[j] (B x d, bf16) = W^T (B x deg) * Gg (deg x d),  W[e][b] = a[rel_e][b] invc_e (rounded to bf16),  Gg[e] = Gbf[dst_e].
@@ -1189,10 +1362,9 @@ int launch_act_backward(const float *dHout, const float *Hout, int act, int64_t 
 }
 
 // rows of dP whose edges were cut into units: their partial sums added up
-static int launch_gather_t_finish(const kge_partition *p, const float *partial, int32_t bd, void *dP, int64_t ld, bool bf16,
+static int launch_gather_t_finish(const kge_heavy_index &hx, const float *partial, int32_t bd, void *dP, int64_t ld, bool bf16,
                                   hipStream_t st)
 {
-    const kge_heavy_index &hx = p->hv_sm;
     if (hx.n_hv == 0) return KGE_OK;
     KGE_PROF("gather_t_fin", st);
     const int64_t n = (int64_t)hx.n_hv * (bd / 4);
@@ -1222,7 +1394,24 @@ static int launch_source_backward_nb(const kge_partition *p, const float *G, con
     return KGE_OK;
 }
 
-// the fewest bases per lane that cover B in one chunk, 16 per wavefront at most; the dot products alone: always those 16.
+template <bool BF16, int NBLK, bool DP>
+static int launch_source_cores(const kge_partition *p, const float *G, const float *a, const void *P, int32_t B, int32_t d,
+                               void *dP, int64_t ld, float *partial, float *seg_scratch, const uint8_t *active, hipStream_t st)
+{
+    const kge_heavy_index &hx = p->hv_sm;
+    const int n_chunks = (int)cdiv(B, 16);
+    const int64_t blocks = (p->n_vert + hx.n_units) * n_chunks;
+    KGE_REQUIRE(blocks < 0x7fffffffLL, KGE_ERANGE, "grid too large");
+    KGE_PROF(DP ? "gather_t" : "coeff_seg", st);
+    k_source_cores<BF16, NBLK, DP><<<(unsigned)blocks, 64, 0, st>>>(
+        p->sm_ptr, p->sm_dst, p->sm_rel, p->sm_invc, p->sm_seg, p->n_vert, hx.n_units, hx.hv_row, hx.hv_unit_ptr, hx.unit_hv, G, a,
+        P, B, d, n_chunks, dP, ld, partial, seg_scratch, active);
+    KGE_LAUNCH_CHECK();
+    return KGE_OK;
+}
+
+// The vector form: the fewest bases per lane that cover B in one chunk, 16 per wavefront at most; the dot products alone (at 32
+// columns, beyond them the matrix cores): always those 16.
 // At most 4 bases of rows of at most 16 lanes, six edges or more per relation of a source on average: shared edges (2 M
 // edges of 20,000 sources, one relation: d = 16, 2 bases 128 -> 65 us, d = 64, 4 bases 131 -> 74; 6.3 edges per relation:
 // 141 -> 114 and 146 -> 144; 4.2 edges: 152 -> 161 and 160 -> 200).
@@ -1244,29 +1433,39 @@ static int launch_source_backward(const kge_partition *p, const float *G, const 
             SB_SPREAD(8, 4);
 #undef SB_SPREAD
         }
-    if (d > 128) {
-        if constexpr (DP) {
+    // The matrix cores' tiles are 16 groups x 16 bases: from 9 bases on they are well enough filled (whole backward passes, us,
+    // cores / not: 14,541 entities x 272,115 triples, d = 200, 10 bases 315 / 470, d = 256, 9 bases 398 / 466, d = 128, 9 bases
+    // 228 / 338; 50,000 entities with 8 groups each, d = 128, 10 bases 392 / 425).  With fewer bases where sources have enough
+    // relations: up to 64 columns 6 on average (d = 64, 1 to 8 bases 115 / 144 to 153 / 190; 4 groups each: 424 / 387 at 5
+    // bases), up to 208 columns 16 and 5 bases (d = 200, 5 bases 296 / 359, 4 bases 308 / 269; d = 128, 6 bases 209 / 222,
+    // with 8 groups each 329 / 267; d = 256, 8 bases 394 / 383)
+    const int64_t per_source = p->n_sgrp / (p->n_vert > 0 ? p->n_vert : 1);
+    const bool cores = d > 32 && (B >= 9 || (d <= 64 ? per_source >= 6 : d <= 208 && B >= 5 && per_source >= 16));
+#define SB_CORES(NBLKV) return launch_source_cores<BF16, NBLKV, DP>(p, G, a, P, B, d, dP, ld, partial, seg_scratch, active, st)
+    if (cores) {
+        if (d <= 64) SB_CORES(4);
+        if (d <= 128) SB_CORES(8);
+        if (d <= 208) SB_CORES(13);
+        SB_CORES(16);
+    }
+#undef SB_CORES
+    if constexpr (DP) {                                  // 8 bases at most beyond 32 columns
+        if (d > 128) {
             if (B <= 2) SB_CALL(64, 2);
             if (B <= 4) SB_CALL(64, 4);
-            if (B <= 8) SB_CALL(64, 8);
-            if (B <= 12) SB_CALL(64, 12);
+            SB_CALL(64, 8);
         }
-        SB_CALL(64, 16);
-    } else if (d > 64) {
-        if constexpr (DP) {
+        if (d > 64) {
             if (B <= 2) SB_CALL(32, 1);
             if (B <= 4) SB_CALL(32, 2);
-            if (B <= 8) SB_CALL(32, 4);
+            SB_CALL(32, 4);
         }
-        SB_CALL(32, 8);
-    } else if (d > 32) {
-        if constexpr (DP) {
+        if (d > 32) {
             if (B <= 4) SB_CALL(16, 1);
-            if (B <= 8) SB_CALL(16, 2);
+            SB_CALL(16, 2);
         }
-        SB_CALL(16, 4);
+        if (B <= 8) SB_CALL(8, 1);
     }
-    if constexpr (DP) if (B <= 8) SB_CALL(8, 1);
     SB_CALL(8, 2);
 #undef SB_CALL
 }
@@ -1281,7 +1480,7 @@ int launch_project_first_backward(const kge_partition *p, const void *P, int msg
     if (!dP) rc = launch_source_backward<true, false>(p, G, a, P, B, d, dP, ld, partial, seg_scratch, active, st);
     else if (msg_bf16) rc = launch_source_backward<true, true>(p, G, a, P, B, d, dP, ld, partial, seg_scratch, active, st);
     else rc = launch_source_backward<false, true>(p, G, a, P, B, d, dP, ld, partial, seg_scratch, active, st);
-    if (rc == KGE_OK && dP) rc = launch_gather_t_finish(p, partial, B * d, dP, ld, msg_bf16 != 0, st);
+    if (rc == KGE_OK && dP) rc = launch_gather_t_finish(p->hv_sm, partial, B * d, dP, ld, msg_bf16 != 0, st);
     if (rc != KGE_OK || p->n_relc == 0) return rc;
     KGE_PROF("coeff_reduce", st);
     if (B % 4 == 0) k_coeff_reduce<4><<<(unsigned)p->n_relc, 256, 0, st>>>(p->relc_rel, p->relc_beg, p->relc_end, seg_scratch, B,
@@ -1315,7 +1514,7 @@ int launch_gather_transpose_bf16(const kge_partition *p, const void *Gbf, int64_
                                                          n_cchunks, reinterpret_cast<uint16_t *>(dP), ld, partial, active);
         KGE_LAUNCH_CHECK();
     }
-    return launch_gather_t_finish(p, partial, B * d, dP, ld, true, st);
+    return launch_gather_t_finish(p->hv_sm, partial, B * d, dP, ld, true, st);
 }
 
 // Z[s][:] = invc_s * sum_{j in run s} H[j][:]; H and Z fp32, or both bf16; `partial`: [hv_seg.n_units][d] floats
