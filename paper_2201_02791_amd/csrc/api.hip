@@ -77,6 +77,8 @@ struct WsLayout {
     // relation-weight layers: W_r fp32 [2R][d_in*d_out] and, for bf16 workloads, its bf16 copies in both
     // orientations; U / dZ [S][max(d_in, d_out)] (shared)
     std::vector<size_t> off_Wrel, off_Wrb, off_WrbT;
+    // fp32: the matrices (W_0 last) split for the products with rows, per orientation, and their exponents
+    std::vector<size_t> off_Wpf, off_Wpb, off_Wpi;
     size_t off_U = 0;
     std::vector<size_t> off_Hd;         // layers with dropout: the input as the layer reads it, fp32 [N][d_in]
     size_t off_self = 0, off_G = 0, off_dP = 0, off_dHa = 0, off_dHb = 0, off_seg = 0, off_part = 0, total = 0;
@@ -123,6 +125,7 @@ void layout(const kge_partition *p, const kge_layer *layers, int32_t n_layers, i
     size_t max_nc = 0;
     w->off_P.assign(n_layers, 0); w->off_H.resize(n_layers); w->off_Z.assign(n_layers, 0);
     w->off_Wrel.assign(n_layers, 0); w->off_Wrb.assign(n_layers, 0); w->off_WrbT.assign(n_layers, 0);
+    w->off_Wpf.assign(n_layers, 0); w->off_Wpb.assign(n_layers, 0); w->off_Wpi.assign(n_layers, 0);
     size_t max_u = 0;
     size_t max_c = 0, max_zd = 0, max_rel_rows = 0;
     w->off_Hbf.assign(n_layers, 0); w->off_Wbf.assign(n_layers, 0); w->off_WbfT.assign(n_layers, 0);
@@ -137,6 +140,10 @@ void layout(const kge_partition *p, const kge_layer *layers, int32_t n_layers, i
             w->off_Z[l] = cur; cur = align_up(cur + (size_t)p->n_seg * L.d_in * ep, 256);
             if (!bf) {
                 w->off_Wrel[l] = cur; cur = align_up(cur + R2 * dd * 4, 256);
+                const bool pf = row_products_pay(p, L.d_in, L.d_out), pb = row_products_pay(p, L.d_out, L.d_in);
+                w->off_Wpf[l] = cur; if (pf) cur = align_up(cur + (R2 + 1) * row_products_bytes(L.d_in, L.d_out), 256);
+                w->off_Wpb[l] = cur; if (pb) cur = align_up(cur + (R2 + 1) * row_products_bytes(L.d_out, L.d_in), 256);
+                w->off_Wpi[l] = cur; if (pf || pb) cur = align_up(cur + (R2 + 1) * 4, 256);
             } else {
                 w->off_Wrb[l] = cur; cur = align_up(cur + R2 * dd * 2, 256);
                 w->off_WrbT[l] = cur; cur = align_up(cur + R2 * dd * 2, 256);
@@ -306,9 +313,17 @@ extern "C" int kge_rgcn_forward(const kge_partition *p, const kge_cgraph *cg, co
             } else {
                 rc = launch_run_mean(p, Hin, L.d_in, Z, 0, part, act_l, 0, st);
                 if (rc != KGE_OK) return rc;
-                rc = launch_apply_relation_weights(p, (const float *)Z, Wrel, L.d_in, L.d_out, (float *)U, st);
+                const bool pf = row_products_pay(p, L.d_in, L.d_out), pb = row_products_pay(p, L.d_out, L.d_in);
+                int32_t *info = (int32_t *)(ws + w.off_Wpi[l]);
+                char *Wpf = ws + w.off_Wpf[l];
+                if (pf || pb)
+                    rc = launch_pack_products(Wrel, L.W0, R2, L.d_in, L.d_out, pf ? Wpf : nullptr, pb ? ws + w.off_Wpb[l] : nullptr, info, st);
                 if (rc != KGE_OK) return rc;
-                rc = launch_project(Hin, p->n_vert, L.d_in, L.d_out, 0, L.V, L.W0, nullptr, Self, st);
+                if (pf) rc = launch_apply_relation_products(p, (const float *)Z, nullptr, L.d_in, L.d_out, Wpf, info, Wrel, false, (float *)U, st);
+                else rc = launch_apply_relation_weights(p, (const float *)Z, Wrel, L.d_in, L.d_out, (float *)U, st);
+                if (rc != KGE_OK) return rc;
+                if (pf) rc = launch_self_products(Hin, p->n_vert, L.d_in, L.d_out, Wpf + R2 * row_products_bytes(L.d_in, L.d_out), info + R2, L.W0, false, Self, st);
+                else rc = launch_project(Hin, p->n_vert, L.d_in, L.d_out, 0, L.V, L.W0, nullptr, Self, st);
             }
             if (rc != KGE_OK) return rc;
             // the next layer's bf16 input is written by this layer's sums when that layer reads this output as
@@ -422,10 +437,18 @@ extern "C" int kge_rgcn_backward(const kge_partition *p, const kge_cgraph *cg, c
                     if (rc != KGE_OK) return rc;
                     rc = launch_apply_relation_weights_t_bf16(p, dP, L.d_out, ws + w.off_Wrb[l], L.d_in, L.d_out, dZ, st);
                 } else {
-                    rc = launch_input_grad(nullptr, Gl, p->n_vert, L.d_in, L.d_out, 0, L.V, L.W0, Self, st);
-                    if (rc != KGE_OK) return rc;
-                    rc = launch_apply_relation_weights_t(p, Gl, (const float *)(ws + w.off_Wrel[l]), L.d_in, L.d_out,
-                                                         (float *)dZ, st);
+                    const float *Wrel = (const float *)(ws + w.off_Wrel[l]);
+                    const char *Wpb = ws + w.off_Wpb[l];
+                    const int32_t *info = (const int32_t *)(ws + w.off_Wpi[l]);
+                    if (row_products_pay(p, L.d_out, L.d_in)) {
+                        rc = launch_self_products(Gl, p->n_vert, L.d_out, L.d_in, Wpb + R2 * row_products_bytes(L.d_out, L.d_in), info + R2, L.W0, true, Self, st);
+                        if (rc != KGE_OK) return rc;
+                        rc = launch_apply_relation_products(p, Gl, p->seg_dst, L.d_out, L.d_in, Wpb, info, Wrel, true, (float *)dZ, st);
+                    } else {
+                        rc = launch_input_grad(nullptr, Gl, p->n_vert, L.d_in, L.d_out, 0, L.V, L.W0, Self, st);
+                        if (rc != KGE_OK) return rc;
+                        rc = launch_apply_relation_weights_t(p, Gl, Wrel, L.d_in, L.d_out, (float *)dZ, st);
+                    }
                 }
                 if (rc != KGE_OK) return rc;
                 rc = launch_sum_edges_out(p, dZ, bf, L.d_in, Self, dst, part, kge_cgraph_layer(cg, l - 1), st);

@@ -232,6 +232,18 @@ int launch_apply_relation_weights_bf16(const kge_partition *p, const void *Zbf, 
 int launch_apply_relation_weights_t_bf16(const kge_partition *p, const void *Gbf, int64_t ldg, const void *Wb,
                                          int32_t d_in, int32_t d_out, void *dZ, hipStream_t st);
 
+// row_products.hip, relation-weight order, fp32 messages: the same two products and those with W_0 (K terms, N columns; the
+// transposed ones contract over d_out) from matrices split once: `fwd` and `back` hold 2R + 1 operands of row_products_bytes(
+// d_in, d_out) and (d_out, d_in) bytes, info [2R + 1] their exponents, W_0 last.  fwd or back may be null
+bool row_products_pay(const kge_partition *p, int32_t K, int32_t N);
+size_t row_products_bytes(int32_t K, int32_t N);
+int launch_pack_products(const float *Wrel, const float *W0, int32_t R2, int32_t d_in, int32_t d_out, void *fwd, void *back,
+                         int32_t *info, hipStream_t st);
+int launch_apply_relation_products(const kge_partition *p, const float *rows, const int32_t *ridx, int32_t K, int32_t N, const void *pack,
+                                   const int32_t *info, const float *Wrel, bool transposed, float *out, hipStream_t st);
+int launch_self_products(const float *rows, int64_t n_rows, int32_t K, int32_t N, const void *pack, const int32_t *info, const float *W0,
+                         bool transposed, float *out, hipStream_t st);
+
 // gemm.hip, relation-weight order (coefficient gradient) ---------------------
 // C[r] (d_in x d_out; [2R][d_in*d_out] floats, comes zeroed) = sum_{runs s of relation r} Z[s]^T G[seg_dst[s]]
 int launch_rel_outer(const kge_partition *p, const float *Z, const float *G, int32_t d_in, int32_t d_out,

@@ -9,7 +9,8 @@
 // What the three products save is rounding: a sum is rounded 3 times per 16 terms instead of 6.  Relative error (2-norm) of
 // dot products of K normally distributed terms against 64 bits, in 10^-7, three products / six / the fp32 instruction:
 // K = 16: 0.85 / 0.36 / 0.75;  64: 1.15 / 1.12 / 1.44;  128: 1.44 / 1.66 / 2.03;  256: 1.90 / 2.40 / 2.86;  1024: 3.6 /
-// 4.9 / 5.7.  So it takes sums of 80 terms and more.
+// 4.9 / 5.7.  So three products serve sums of 80 terms and more.  (With the fourth, and the products of second parts in sums of
+// their own, 16 terms come to 0.76, which is what two parts of 11 bits leave: row_products.hip.)
 //
 // Infinities and NaN do not survive the split either, and numbers near fp32's limits cannot be scaled: operands that hold
 // such are the caller's to send to the other split.  Conversion and matrix cores keep subnormal fp16 numbers.

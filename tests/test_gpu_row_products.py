@@ -1,0 +1,74 @@
+"""fp32 layers of 100 to 160 columns in the relation-weight order, whose products with rows run on the fp16 matrix cores: edges
+of the classes of widths, tiles that end inside their rows, rows and matrices of very different size, operands that are not
+finite.  Tolerance of ordinary operands as in the split-product tests (4e-6 of the largest element)."""
+import numpy as np
+import pytest
+
+from test_gpu_split_products import TOL, layer, model
+
+pytestmark = pytest.mark.gpu
+
+
+def run(n, R, di, do, B, change=None):
+    H0, dH, V, a, W0 = model(n + di, n, R, di, do, B)
+    if change:
+        change(H0, dH, V, a, W0)
+    return layer(n, R, 8 * n, di, do, B, 2, H0, dH, V, a, W0)
+
+
+@pytest.mark.parametrize("n,R", [(130, 1), (257, 2), (1500, 3)])
+@pytest.mark.parametrize("di,do", [(100, 4), (112, 32), (116, 36), (128, 128), (132, 64), (160, 100), (4, 128), (96, 112)])
+def test_widths(n, R, di, do):
+    got, want = run(n, R, di, do, 2)
+    for k in want:
+        assert np.abs(got[k] - want[k]).max() <= TOL * np.abs(want[k]).max(), k
+
+
+def close_by_rows(got, want, tol):
+    """Every row against its own size."""
+    size = np.abs(want).max(axis=1)
+    assert (np.abs(got - want).max(axis=1) <= tol * size + 1e-37).all()
+
+
+@pytest.mark.parametrize("exponent", [-60, -20, 20, 60])
+def test_every_input_row_at_its_own_size(exponent):
+    """No edge joins the scaled vertices to others' rows: W_r is zero, so an output row is its vertex's own product."""
+    n, scaled = 600, slice(100, 200)
+
+    def change(H0, dH, V, a, W0):
+        H0[scaled] *= np.float32(2.0 ** exponent); dH[scaled] *= np.float32(2.0 ** exponent)
+        a[:] = 0
+    got, want = run(n, 1, 128, 128, 1, change)
+    close_by_rows(got["out"], want["out"], 8e-6)
+    close_by_rows(got["dH0"], want["dH0"], 8e-6)
+
+
+@pytest.mark.parametrize("what", ["column", "row", "matrix", "huge"])
+def test_matrices_that_are_not_split(what):
+    """A column or row far below the rest, or entries near the ends of the range: plain fp32 products."""
+    def change(H0, dH, V, a, W0):
+        if what == "column": W0[:, 5] *= np.float32(2.0 ** -40)
+        elif what == "row": W0[7] *= np.float32(2.0 ** -30)
+        elif what == "matrix": W0 *= np.float32(2.0 ** -110)
+        else: W0 *= np.float32(2.0 ** 105)
+    got, want = run(300, 1, 112, 104, 2, change)
+    for k in ("out", "dH0"):
+        assert np.abs(got[k] - want[k]).max() <= 2 * TOL * np.abs(want[k]).max(), k
+    if what == "column":                          # the column's own sums: only the self-loop's part is tiny, the runs' is not
+        assert np.abs(got["out"][:, 5] - want["out"][:, 5]).max() <= 2 * TOL * np.abs(want["out"][:, 5]).max()
+
+
+@pytest.mark.parametrize("bad", [np.inf, np.nan])
+@pytest.mark.parametrize("where", ["H0", "dH", "W0", "V"])
+def test_numbers_that_are_not_finite(bad, where):
+    """They reach exactly the results that they reach in the oracle, and the others stay as they are."""
+    def change(H0, dH, V, a, W0):
+        a[:] = np.abs(a) + np.float32(0.1)
+        dict(H0=H0, dH=dH, W0=W0, V=V[0])[where][3, 2] = bad
+    got, want = run(200, 1, 128, 112, 2, change)
+    for k in ("out", "dH0"):
+        finite = np.isfinite(want[k])
+        assert np.array_equal(np.isfinite(got[k]), finite), k
+        if finite.any():
+            scale = np.abs(want[k][finite]).max()
+            assert np.abs(got[k][finite] - want[k][finite]).max() <= 2 * TOL * scale, k
