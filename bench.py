@@ -24,6 +24,8 @@ PEAK_HBM_GBS = 8000.0
 PEAK_BF16_MFMA_TFLOPS = 2500.0
 # fp32 products run on the bf16 matrix cores, six products of bf16 parts per term
 PEAK_F32_MFMA_TFLOPS = PEAK_BF16_MFMA_TFLOPS / 6
+# the evaluation's scores from 80 columns on: three products of fp16 parts per term, at the same rate
+PEAK_EVAL_MFMA_TFLOPS = PEAK_BF16_MFMA_TFLOPS / 3
 # plain vector ALUs: 256 compute units x 4 SIMDs x 32 fp32 FMA lanes per clock x 2 flops x 2.4 GHz
 PEAK_F32_VALU_TFLOPS = 256 * 4 * 32 * 2 * 2.4e9 / 1e12
 # Adam's learning rate per workload.  The paper's 0.01 (Sec. 4) is kept where it trains; at configs[4]
@@ -34,13 +36,24 @@ DEFAULT_LR = {4: 1e-3}
 
 
 def kernel_work(name, part, spec, dims, B, ep, n_pos, n_neg, cone=None, order="project", single_runs=0,
-                n_input_rows=None, dropout=0.0):
+                n_input_rows=None, dropout=0.0, pairs=0, layers=None):
     """Algorithmic work of ONE launch of a kernel: what the method itself must move or compute in this
     formulation, as the mean over the layers that launch it.  Returns a dict with "bytes" and / or "flops"
     (a contraction has both and the caller reports whichever ceiling takes longer at its peak), "unit"
     ("mfma" matrix cores, "alu" vector ALUs) for the flops, and "f32" when an fp32 contraction runs inside a
     bf16-message workload.  dims: [(d_in, d_out)] per layer; cone: None, or per layer the counts (active
-    vertices, edges into them, runs into them, edges out of them) of the batch's computational sub-graph."""
+    vertices, edges into them, runs into them, edges out of them) of the batch's computational sub-graph; pairs: the
+    (source, relation) pairs whose combined rows the forward sums read, 0 where they read the projections; layers: the
+    layers that launch the kernel, by default all that have such work."""
+    several = {"fwd_products": ("apply_rel", "project"), "outer_products": ("rel_outer", "weight_grad"),
+               "bwd_products": ("rel_outer", "weight_grad", "apply_rel_t", "input_grad")}
+    if name in several:        # several products of a layer in one launch: their work together
+        total = {"unit": "mfma"}
+        for one in several[name]:
+            w = kernel_work(one, part, spec, dims, B, ep, n_pos, n_neg, cone, order, single_runs, n_input_rows, dropout, pairs, layers)
+            for key in ("bytes", "flops"):
+                total[key] = total.get(key, 0.0) + w.get(key, 0.0)
+        return total
     N, E, S = float(part.n_vert), float(part.n_edge), float(part.n_seg)
     R2 = 2.0 * part.n_relations
     L = len(dims)
@@ -53,10 +66,16 @@ def kernel_work(name, part, spec, dims, B, ep, n_pos, n_neg, cone=None, order="p
     Bg = 0 if order == "relation" else B      # relation-weight order: only the self-loop term W_0 goes through the dense GEMMs
     per_layer = []
     for l, (di, do) in enumerate(dims):
+        if layers is not None and l not in layers:
+            continue
         nv, ne, ns = (N, E, S) if cone is None else (float(cone[l][0]), float(cone[l][1]), float(cone[l][2]))
         inactive = cone is not None
         w = None
-        if name == "gather_fwd":   # per edge: P row + (src, rel, 1/c); per vertex: ptr (+ flag) + Self read + output write
+        if name == "gather_rows":   # per vertex: ptr + P row; per (source, relation) pair: its id, its row written
+            w = {"bytes": N * (4.0 + B * do * ep) + pairs * (4.0 + 4.0 * do) + R2 * B * 4.0}
+        elif name == "gather_fwd" and pairs:   # per edge: its pair's row + (pair, 1/c); per vertex: ptr (+ flag) + Self read + output write
+            w = {"bytes": ne * (4.0 * do + 12.0) + N * ((5.0 if inactive else 4.0) + 4.0 * do) + nv * 4.0 * do}
+        elif name == "gather_fwd":   # per edge: P row + (src, rel, 1/c); per vertex: ptr (+ flag) + Self read + output write
             w = {"bytes": ne * (B * do * ep + 12.0) + N * ((5.0 if inactive else 4.0) + 4.0 * do) + nv * 4.0 * do + R2 * B * 4.0}
         elif name == "coeff_seg":  # the dot products alone, by source: per edge G row + (dst, rel, 1/c, run); per vertex ptr + P row; S x B sums
             w = {"bytes": ne * 4.0 * do + E * (17.0 if inactive else 16.0) + N * (4.0 + B * do * ep) + S * B * 8.0}
@@ -255,7 +274,8 @@ def run_eval(args):
     avg_ms = prof[work_name][0] / max(prof[work_name][1], 1)
     if flops is not None:        # dense contraction of fp32 numbers on the matrix cores
         roof = {"kernel": work_name, "bound": "mfma", "achieved": flops / (avg_ms * 1e-3) / 1e12,
-                "peak": PEAK_F32_MFMA_TFLOPS, "unit": "TFLOP/s", "traffic": None, "avg_launch_ms": avg_ms}
+                "peak": PEAK_EVAL_MFMA_TFLOPS if d >= 80 else PEAK_F32_MFMA_TFLOPS, "unit": "TFLOP/s", "traffic": None,
+                "avg_launch_ms": avg_ms}
     else:                        # gathers one entity row per (query, candidate)
         nbytes = nq * (1000 + 1) * (d * 4.0 + 4.0)
         roof = {"kernel": work_name, "bound": "hbm", "achieved": nbytes / (avg_ms * 1e-3) / 1e9, "peak": PEAK_HBM_GBS,
@@ -392,6 +412,10 @@ def run_workload(graphs, cfg, order="relation", whole=False, dropout=0.0, steps=
     ep = 2 if spec.msg_dtype == "bf16" else 4
     dims = [(spec.d_in or spec.d, spec.d)] + [(spec.d, spec.d)] * (spec.n_layers - 1)
     kernels = {}
+    pairs = 0
+    if "gather_rows" in prof:
+        rel_of_edge = np.repeat(part.export("seg_rel").astype(np.int64), np.diff(part.export("seg_ptr")))
+        pairs = len(np.unique(part.export("col_src").astype(np.int64) * (2 * part.n_relations) + rel_of_edge))
     if "distmult_gather" in prof:
         # the atomic-free scoring call is three steps (sort the batch's rows by entity, score, sum per entity):
         # its algorithmic bytes are those of the whole call, so the three are reported as one entry
@@ -405,8 +429,14 @@ def run_workload(graphs, cfg, order="relation", whole=False, dropout=0.0, steps=
     for name, (tot_ms, calls) in prof.items():
         avg_ms = tot_ms / max(calls, 1)
         rec = {"ms_per_step": tot_ms / steps, "launches_per_step": calls / steps, "avg_ms": avg_ms}
+        # fp32, relation-weight order: the products of some layers share launches, those of the first ones may not
+        at, n = None, max(calls // steps, 1)
+        if name in ("fwd_products", "bwd_products"):
+            at = range(len(dims))[-n:]
+        elif name == "outer_products" or (name in ("apply_rel", "project") and "fwd_products" in prof):
+            at = range(len(dims))[:n]
         roof = roof_of(kernel_work(name, part, spec, dims, spec.n_bases, ep, n_pos, n_neg, cone, order, single_runs,
-                                   n_input_rows, dropout), avg_ms, ep)
+                                   n_input_rows, dropout, pairs, at), avg_ms, ep)
         if roof:
             rec.update(roof)
             if roof["frac"] > 1.0:

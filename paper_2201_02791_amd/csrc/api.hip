@@ -319,11 +319,10 @@ extern "C" int kge_rgcn_forward(const kge_partition *p, const kge_cgraph *cg, co
                 if (pf || pb)
                     rc = launch_pack_products(Wrel, L.W0, R2, L.d_in, L.d_out, pf ? Wpf : nullptr, pb ? ws + w.off_Wpb[l] : nullptr, info, st);
                 if (rc != KGE_OK) return rc;
-                if (pf) rc = launch_apply_relation_products(p, (const float *)Z, nullptr, L.d_in, L.d_out, Wpf, info, Wrel, false, (float *)U, st);
-                else rc = launch_apply_relation_weights(p, (const float *)Z, Wrel, L.d_in, L.d_out, (float *)U, st);
+                if (!pf) rc = launch_forward_products(p, (const float *)Z, Wrel, Hin, L.W0, L.d_in, L.d_out, (float *)U, Self, st);
+                else rc = launch_apply_relation_products(p, (const float *)Z, nullptr, L.d_in, L.d_out, Wpf, info, Wrel, false, (float *)U, st);
                 if (rc != KGE_OK) return rc;
                 if (pf) rc = launch_self_products(Hin, p->n_vert, L.d_in, L.d_out, Wpf + R2 * row_products_bytes(L.d_in, L.d_out), info + R2, L.W0, false, Self, st);
-                else rc = launch_project(Hin, p->n_vert, L.d_in, L.d_out, 0, L.V, L.W0, nullptr, Self, st);
             }
             if (rc != KGE_OK) return rc;
             // the next layer's bf16 input is written by this layer's sums when that layer reads this output as
@@ -410,6 +409,8 @@ extern "C" int kge_rgcn_backward(const kge_partition *p, const kge_cgraph *cg, c
             void *dZ = ws + w.off_U;
             float *Self = (float *)(ws + w.off_self);
             const bool need_in = l > 0 || dH0;
+            const float *Wrel = (const float *)(ws + w.off_Wrel[l]);
+            const bool pb = !bf && row_products_pay(p, L.d_out, L.d_in);    // dZ and Self from the packed matrices
             float *dst = l > 0 ? dHbuf[l & 1] : dH0;
             // everything that is accumulated below
             const kge_span acc[4] = {{C, sizeof(float) * (size_t)R2 * dd}, {grads[l].da, sizeof(float) * (size_t)R2 * L.n_bases},
@@ -421,7 +422,8 @@ extern "C" int kge_rgcn_backward(const kge_partition *p, const kge_cgraph *cg, c
                 if (rc != KGE_OK) return rc;
                 rc = launch_rel_outer_bf16(p, p->seg_zrow ? ws + w.off_Hbf[l] : Z, p->seg_zrow, dP, L.d_out, L.d_in, L.d_out, C, st);
             } else {
-                rc = launch_rel_outer(p, (const float *)Z, Gl, L.d_in, L.d_out, C, st);
+                rc = launch_backward_products(p, (const float *)Z, Gl, Wrel, Hprev, L.W0, L.d_in, L.d_out, C, grads[l].dW0,
+                                              need_in && !pb ? (float *)dZ : nullptr, Self, st);
             }
             if (rc != KGE_OK) return rc;
             rc = launch_coeff_contract(p, C, L.V, L.d_in, L.d_out, L.n_bases, grads[l].da, st);
@@ -429,26 +431,18 @@ extern "C" int kge_rgcn_backward(const kge_partition *p, const kge_cgraph *cg, c
             rc = launch_basis_grad_from_relations(L.a, R2, L.n_bases, C, dd, grads[l].dV, st);
             if (rc != KGE_OK) return rc;
             if (bf) rc = launch_weight_grad_bf16(ws + w.off_Hbf[l], p->n_vert, L.d_in, L.d_out, 0, dP, grads[l].dV, grads[l].dW0, st);
-            else rc = launch_weight_grad(Hprev, p->n_vert, L.d_in, L.d_out, 0, nullptr, Gl, grads[l].dV, grads[l].dW0, st);
             if (rc != KGE_OK) return rc;
             if (need_in) {
                 if (bf) {
                     rc = launch_input_grad_bf16(dP, p->n_vert, L.d_in, L.d_out, 0, ws + w.off_Wbf[l], Self, st);
                     if (rc != KGE_OK) return rc;
                     rc = launch_apply_relation_weights_t_bf16(p, dP, L.d_out, ws + w.off_Wrb[l], L.d_in, L.d_out, dZ, st);
-                } else {
-                    const float *Wrel = (const float *)(ws + w.off_Wrel[l]);
+                } else if (pb) {
                     const char *Wpb = ws + w.off_Wpb[l];
                     const int32_t *info = (const int32_t *)(ws + w.off_Wpi[l]);
-                    if (row_products_pay(p, L.d_out, L.d_in)) {
-                        rc = launch_self_products(Gl, p->n_vert, L.d_out, L.d_in, Wpb + R2 * row_products_bytes(L.d_out, L.d_in), info + R2, L.W0, true, Self, st);
-                        if (rc != KGE_OK) return rc;
-                        rc = launch_apply_relation_products(p, Gl, p->seg_dst, L.d_out, L.d_in, Wpb, info, Wrel, true, (float *)dZ, st);
-                    } else {
-                        rc = launch_input_grad(nullptr, Gl, p->n_vert, L.d_in, L.d_out, 0, L.V, L.W0, Self, st);
-                        if (rc != KGE_OK) return rc;
-                        rc = launch_apply_relation_weights_t(p, Gl, Wrel, L.d_in, L.d_out, (float *)dZ, st);
-                    }
+                    rc = launch_self_products(Gl, p->n_vert, L.d_out, L.d_in, Wpb + R2 * row_products_bytes(L.d_out, L.d_in), info + R2, L.W0, true, Self, st);
+                    if (rc != KGE_OK) return rc;
+                    rc = launch_apply_relation_products(p, Gl, p->seg_dst, L.d_out, L.d_in, Wpb, info, Wrel, true, (float *)dZ, st);
                 }
                 if (rc != KGE_OK) return rc;
                 rc = launch_sum_edges_out(p, dZ, bf, L.d_in, Self, dst, part, kge_cgraph_layer(cg, l - 1), st);

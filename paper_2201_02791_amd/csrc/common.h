@@ -215,12 +215,7 @@ int launch_relation_weights_bf16(const float *a, int32_t R2, int32_t B, const fl
 // dV[b] = sum_r a[r][b] C[r]   (dV comes zeroed)
 int launch_basis_grad_from_relations(const float *a, int32_t R2, int32_t B, const float *C, int64_t dd, float *dV,
                                      hipStream_t st);
-// U[s] = Z[s] Wrel[rel(s)]  and  dZ[s] = G[dst(s)] Wrel[rel(s)]^T   (fp32)
-int launch_apply_relation_weights(const kge_partition *p, const float *Z, const float *Wrel, int32_t d_in,
-                                  int32_t d_out, float *U, hipStream_t st);
-int launch_apply_relation_weights_t(const kge_partition *p, const float *G, const float *Wrel, int32_t d_in,
-                                    int32_t d_out, float *dZ, hipStream_t st);
-// the same two products from bf16 operands, bf16 results; Gbf rows are ldg elements apart.  zrow (may be
+// U[s] = Z[s] Wrel[rel(s)]  and  dZ[s] = G[dst(s)] Wrel[rel(s)]^T  from bf16 operands, bf16 results; Gbf rows are ldg elements apart.  zrow (may be
 // NULL): Zbf is then the matrix [X; Z] and run s reads its row zrow[s]
 bool rel_rows_bf16_supported(int32_t K, int32_t N);
 int launch_rel_rows_bf16(const kge_partition *p, const void *A, int64_t lda, const int32_t *aidx, const void *Wk,
@@ -232,6 +227,12 @@ int launch_apply_relation_weights_bf16(const kge_partition *p, const void *Zbf, 
 int launch_apply_relation_weights_t_bf16(const kge_partition *p, const void *Gbf, int64_t ldg, const void *Wb,
                                          int32_t d_in, int32_t d_out, void *dZ, hipStream_t st);
 
+// fp32: a layer's products that do not depend on one another in one launch.  U[s] = Z[s] Wrel[rel(s)] and Self = H W_0;
+// C (below) and dW0, both accumulated, and if dZ is given dZ[s] = G[dst(s)] Wrel[rel(s)]^T and Self = G W_0^T
+int launch_forward_products(const kge_partition *p, const float *Z, const float *Wrel, const float *H, const float *W0, int32_t d_in,
+                            int32_t d_out, float *U, float *Self, hipStream_t st);
+int launch_backward_products(const kge_partition *p, const float *Z, const float *G, const float *Wrel, const float *H, const float *W0,
+                             int32_t d_in, int32_t d_out, float *C, float *dW0, float *dZ, float *Self, hipStream_t st);
 // row_products.hip, relation-weight order, fp32 messages: the same two products and those with W_0 (K terms, N columns; the
 // transposed ones contract over d_out) from matrices split once: `fwd` and `back` hold 2R + 1 operands of row_products_bytes(
 // d_in, d_out) and (d_out, d_in) bytes, info [2R + 1] their exponents, W_0 last.  fwd or back may be null
@@ -245,9 +246,7 @@ int launch_self_products(const float *rows, int64_t n_rows, int32_t K, int32_t N
                          bool transposed, float *out, hipStream_t st);
 
 // gemm.hip, relation-weight order (coefficient gradient) ---------------------
-// C[r] (d_in x d_out; [2R][d_in*d_out] floats, comes zeroed) = sum_{runs s of relation r} Z[s]^T G[seg_dst[s]]
-int launch_rel_outer(const kge_partition *p, const float *Z, const float *G, int32_t d_in, int32_t d_out,
-                     float *C, hipStream_t st);
+// C[r] (d_in x d_out; [2R][d_in*d_out] floats, comes zeroed) = sum_{runs s of relation r} Z[s]^T G[seg_dst[s]]: with launch_backward_products
 // da[r][b] = <C[r], V_b>   (fp32; da comes zeroed)
 int launch_coeff_contract(const kge_partition *p, const float *C, const float *V, int32_t d_in, int32_t d_out,
                           int32_t B, float *da, hipStream_t st);

@@ -172,11 +172,12 @@ __host__ __device__ __forceinline__ bool gemm_by_cols(const GemmGrid &g)
 // matrix-core steps (splitting, addresses, the sums' moves: 9 vector instructions for each, where up to 6 would hide).
 // 352 k runs of 474 relations at width 200, microseconds with fp32 steps / now: rel_outer 570 / 335, apply_rel 427 /
 // 319, apply_rel_t 406 / 270; against fp64 the gradients are off by 3e-7 there, 5e-7 before.
-template <class SA, class SB, class EPI>
-__global__ __launch_bounds__(GT, 2) void k_gemm(SA A, SB B, EPI epi, int32_t M_, int32_t N_, GemmGrid g)
-{
-    __shared__ __attribute__((aligned(16))) unsigned char lds[2][6 * PLANE];      // [buffer][A's parts, B's parts]
+struct GemmLds { unsigned char buf[2][6 * PLANE]; };                              // [buffer][A's parts, B's parts]
 
+template <class SA, class SB, class EPI>
+__device__ __forceinline__ void gemm_tile(GemmLds &shared, uint32_t block, SA A, SB B, EPI epi, int32_t M_, int32_t N_, const GemmGrid &g)
+{
+    auto &lds = shared.buf;
     const int t = threadIdx.x, lane = t & 63, half = lane >> 5;
     const int w = __builtin_amdgcn_readfirstlane(t >> 6), wm = w >> 1, wn = w & 1;
     // block id -> (row tile, column tile, split).  Workgroup i runs on XCD i % 8: the tiles that read the same rows of
@@ -184,7 +185,7 @@ __global__ __launch_bounds__(GT, 2) void k_gemm(SA A, SB B, EPI epi, int32_t M_,
     // rows come from its L2 all but once.  With fewer row tiles than XCDs the column tiles go round them instead.
     const bool by_split = g.splits > 1 || g.g_beg, by_cols = gemm_by_cols(g);
     const int32_t per = by_split ? g.tiles_m * g.tiles_n : by_cols ? g.tiles_m : g.tiles_n;
-    const int32_t slot = blockIdx.x / 8, unit = slot / per * 8 + blockIdx.x % 8, in_unit = slot % per;
+    const int32_t slot = block / 8, unit = slot / per * 8 + block % 8, in_unit = slot % per;
     const int32_t tn = by_cols ? unit : in_unit % g.tiles_n, sp = by_split ? unit : 0;
     const int32_t tm = by_split ? in_unit / g.tiles_n : by_cols ? in_unit : unit;
     if (tm >= g.tiles_m || tn >= g.tiles_n || sp >= g.splits) return;       // padding blocks of the last units
@@ -399,9 +400,20 @@ __global__ __launch_bounds__(GT, 2) void k_gemm(SA A, SB B, EPI epi, int32_t M_,
         }
 }
 
-// row tiles x column tiles x splits of a launch, numbered as k_gemm reads them
 template <class SA, class SB, class EPI>
-int run_gemm(const SA &sa, const SB &sb, const EPI &ep, int64_t rows, int32_t cols, GemmGrid g, hipStream_t st)
+__global__ __launch_bounds__(GT, 2) void k_gemm(SA A, SB B, EPI epi, int32_t M_, int32_t N_, GemmGrid g)
+{
+    __shared__ __attribute__((aligned(16))) GemmLds lds;
+    gemm_tile(lds, blockIdx.x, A, B, epi, M_, N_, g);
+}
+
+// a product and its blocks: row tiles x column tiles x splits, numbered as gemm_tile reads them (a multiple of 8, so that
+// several products behind one another keep their tiles on the XCDs that the numbers name)
+template <class SA, class SB, class EPI>
+struct GemmJob { SA a; SB b; EPI e; int32_t M, N; GemmGrid g; uint32_t blocks; };
+
+template <class SA, class SB, class EPI>
+int gemm_job(const SA &sa, const SB &sb, const EPI &ep, int64_t rows, int32_t cols, GemmGrid g, GemmJob<SA, SB, EPI> *job)
 {
     if (!g.mt_beg) g.tiles_m = (int32_t)cdiv(rows, BM);
     g.tiles_n = (int32_t)cdiv(cols, BN);
@@ -409,9 +421,53 @@ int run_gemm(const SA &sa, const SB &sb, const EPI &ep, int64_t rows, int32_t co
     const bool by_cols = gemm_by_cols(g);
     const int64_t per = by_split ? (int64_t)g.tiles_m * g.tiles_n : by_cols ? g.tiles_m : g.tiles_n;
     const int64_t units = by_split ? g.splits : by_cols ? g.tiles_n : g.tiles_m;
-    const int64_t blocks = cdiv(units, 8) * 8 * per;
+    const int64_t blocks = g.splits == 0 ? 0 : cdiv(units, 8) * 8 * per;     // no splits: nothing to sum, as in a graph without edges
     KGE_REQUIRE(rows <= 0x7fffffffLL && blocks <= 0x7fffffffLL, KGE_ERANGE, "too many tiles for one launch");
-    k_gemm<SA, SB, EPI><<<(unsigned)blocks, GT, 0, st>>>(sa, sb, ep, (int32_t)rows, cols, g);
+    *job = GemmJob<SA, SB, EPI>{sa, sb, ep, (int32_t)rows, cols, g, (uint32_t)blocks};
+    return KGE_OK;
+}
+
+template <class SA, class SB, class EPI>
+int run_job(const GemmJob<SA, SB, EPI> &j, hipStream_t st)
+{
+    k_gemm<SA, SB, EPI><<<j.blocks, GT, 0, st>>>(j.a, j.b, j.e, j.M, j.N, j.g);
+    KGE_LAUNCH_CHECK();
+    return KGE_OK;
+}
+
+template <class SA, class SB, class EPI>
+int run_gemm(const SA &sa, const SB &sb, const EPI &ep, int64_t rows, int32_t cols, GemmGrid g, hipStream_t st)
+{
+    GemmJob<SA, SB, EPI> job;
+    int rc = gemm_job(sa, sb, ep, rows, cols, g, &job);
+    return rc != KGE_OK ? rc : run_job(job, st);
+}
+
+// Several products that do not depend on one another in one launch, one behind the other: the blocks of the next start as
+// those of the one before run out.  In a small graph each product fills a part of the chip for the 7 to 10 us that its few
+// steps take, most of them latency; in a large one the last wave of a launch leaves compute units idle.  Microseconds of a
+// training step's layers with a launch for each product / with two launches in all: 1000 vertices, 10 relations, 5000 edges,
+// width 32: 197 / 146; 14541 vertices, 237 relations, 272 k edges, width 200: 3194 / 3015, width 64: 1132 / 1038; 40000, 200
+// relations, width 256: 5025 / 4806; one layer over 200 k vertices, 2 relations, 2 M edges, width 64: 1097 / 1024; 100 k, 237
+// relations, 1 M edges, width 200: 4484 / 4422; 300 k, 1000 relations, 3 M edges, width 64: 3464 / 3356.  No size tried lost.
+template <class... JOBS>
+__global__ __launch_bounds__(GT, 2) void k_gemm_jobs(JOBS... jobs)
+{
+    __shared__ __attribute__((aligned(16))) GemmLds lds;
+    uint32_t block = blockIdx.x;
+    auto one = [&](const auto &j) __attribute__((always_inline)) {
+        if (block >= j.blocks) { block -= j.blocks; return false; }
+        gemm_tile(lds, block, j.a, j.b, j.e, j.M, j.N, j.g);
+        return true;
+    };
+    (void)(one(jobs) || ...);
+}
+template <class... JOBS> int run_jobs(hipStream_t st, const JOBS &...jobs)
+{
+    const int64_t blocks = (int64_t(0) + ... + jobs.blocks);
+    if (blocks == 0) return KGE_OK;
+    KGE_REQUIRE(blocks <= 0x7fffffffLL, KGE_ERANGE, "too many tiles for one launch");
+    k_gemm_jobs<JOBS...><<<(uint32_t)blocks, GT, 0, st>>>(jobs...);
     KGE_LAUNCH_CHECK();
     return KGE_OK;
 }
@@ -496,21 +552,23 @@ int launch_fill_zero(void *ptr, size_t bytes, hipStream_t st)
     return KGE_OK;
 }
 
-int launch_project(const float *H, int64_t N, int32_t d_in, int32_t d_out, int32_t B, const float *V,
-                   const float *W0, float *P, float *Self, hipStream_t st)
-{
-    if (N == 0) return KGE_OK;
-    RowsK sa{H, d_in, nullptr, 0};
-    WcatX sb{V, W0, d_in, d_out, B};
-    KGE_PROF("project", st);
-    EpiProject ep{P, Self, d_out, B * d_out};
-    return run_gemm(sa, sb, ep, N, (B + 1) * d_out, GemmGrid{0, 0, 1, d_in, d_in}, st);
-}
+namespace {
+using ProjectJob = GemmJob<RowsK, WcatX, EpiProject>;
+using WeightGradJob = GemmJob<RowsX, XcatX, EpiWeightGrad>;
+using InputGradJob = GemmJob<XcatK, WcatK, EpiRows>;
+using RelOuterJob = GemmJob<RowsX, RowsX, EpiRowsAtomic>;
+using ApplyJob = GemmJob<RowsK, RowsX, EpiRows>;
+using ApplyTJob = GemmJob<RowsK, RowsK, EpiRows>;
 
-int launch_weight_grad(const float *H, int64_t N, int32_t d_in, int32_t d_out, int32_t B,
-                       const float *dP, const float *G, float *dV, float *dW0, hipStream_t st)
+int project_job(const float *H, int64_t N, int32_t d_in, int32_t d_out, int32_t B, const float *V, const float *W0, float *P,
+                float *Self, ProjectJob *job)
 {
-    if (N == 0) return KGE_OK;
+    return gemm_job(RowsK{H, d_in, nullptr, 0}, WcatX{V, W0, d_in, d_out, B}, EpiProject{P, Self, d_out, B * d_out}, N,
+                    (B + 1) * d_out, GemmGrid{0, 0, 1, d_in, d_in}, job);
+}
+int weight_grad_job(const float *H, int64_t N, int32_t d_in, int32_t d_out, int32_t B, const float *dP, const float *G, float *dV,
+                    float *dW0, WeightGradJob *job)
+{
     int32_t nc = (B + 1) * d_out;
     int64_t tiles = cdiv(d_in, BM) * cdiv(nc, BN);
     // split the N-long contraction so that roughly 2048 blocks are in flight
@@ -518,11 +576,56 @@ int launch_weight_grad(const float *H, int64_t N, int32_t d_in, int32_t d_out, i
     int64_t kchunk = cdiv(cdiv(N, splits), BK) * BK;
     if (kchunk < 4 * BK) kchunk = 4 * BK;
     splits = cdiv(N, kchunk);
-    RowsX sa{H, d_in, nullptr, 0};
-    XcatX sb{dP, G, d_out, B * d_out};
-    EpiWeightGrad ep{dV, dW0, d_in, d_out, B};
+    return gemm_job(RowsX{H, d_in, nullptr, 0}, XcatX{dP, G, d_out, B * d_out}, EpiWeightGrad{dV, dW0, d_in, d_out, B}, d_in, nc,
+                    GemmGrid{0, 0, (int32_t)splits, N, kchunk}, job);
+}
+int input_grad_job(const float *dP, const float *G, int64_t N, int32_t d_in, int32_t d_out, int32_t B, const float *V, const float *W0,
+                   float *dH, InputGradJob *job)
+{
+    int32_t nc = (B + 1) * d_out;
+    return gemm_job(XcatK{dP, G, d_out, B * d_out}, WcatK{V, W0, d_in, d_out, B}, EpiRows{dH, d_in}, N, d_in,
+                    GemmGrid{0, 0, 1, nc, nc}, job);
+}
+int rel_outer_job(const kge_partition *p, const float *Z, const float *G, int32_t d_in, int32_t d_out, float *C, RelOuterJob *job)
+{
+    return gemm_job(RowsX{Z, d_in, nullptr, 0}, RowsX{G, d_out, p->seg_dst, 0}, EpiRowsAtomic{C, d_out, (int64_t)d_in * d_out, false},
+                    d_in, d_out, GemmGrid{0, 0, p->n_relc, p->n_seg, 0, p->relc_rel, p->relc_beg, p->relc_end}, job);
+}
+// the row tiles of the per-run products: <= 128 consecutive runs of one relation each
+GemmGrid rel_tiles(const kge_partition *p, int32_t K)
+{
+    return GemmGrid{p->n_relt, 0, 1, K, K, nullptr, nullptr, nullptr, p->relt_rel, p->relt_beg, p->relt_end};
+}
+int apply_job(const kge_partition *p, const float *Z, const float *Wrel, int32_t d_in, int32_t d_out, float *U, ApplyJob *job)
+{
+    return gemm_job(RowsK{Z, d_in, nullptr, 0}, RowsX{Wrel, d_out, nullptr, (int64_t)d_in * d_out}, EpiRows{U, d_out}, p->n_seg, d_out,
+                    rel_tiles(p, d_in), job);
+}
+int apply_t_job(const kge_partition *p, const float *G, const float *Wrel, int32_t d_in, int32_t d_out, float *dZ, ApplyTJob *job)
+{
+    return gemm_job(RowsK{G, d_out, p->seg_dst, 0}, RowsK{Wrel, d_out, nullptr, (int64_t)d_in * d_out}, EpiRows{dZ, d_in}, p->n_seg, d_in,
+                    rel_tiles(p, d_out), job);
+}
+}  // namespace
+
+int launch_project(const float *H, int64_t N, int32_t d_in, int32_t d_out, int32_t B, const float *V,
+                   const float *W0, float *P, float *Self, hipStream_t st)
+{
+    if (N == 0) return KGE_OK;
+    KGE_PROF("project", st);
+    ProjectJob job;
+    int rc = project_job(H, N, d_in, d_out, B, V, W0, P, Self, &job);
+    return rc != KGE_OK ? rc : run_job(job, st);
+}
+
+int launch_weight_grad(const float *H, int64_t N, int32_t d_in, int32_t d_out, int32_t B,
+                       const float *dP, const float *G, float *dV, float *dW0, hipStream_t st)
+{
+    if (N == 0) return KGE_OK;
     KGE_PROF("weight_grad", st);
-    return run_gemm(sa, sb, ep, d_in, nc, GemmGrid{0, 0, (int32_t)splits, N, kchunk}, st);
+    WeightGradJob job;
+    int rc = weight_grad_job(H, N, d_in, d_out, B, dP, G, dV, dW0, &job);
+    return rc != KGE_OK ? rc : run_job(job, st);
 }
 
 int launch_input_grad(const float *dP, const float *G, int64_t N, int32_t d_in,
@@ -530,25 +633,10 @@ int launch_input_grad(const float *dP, const float *G, int64_t N, int32_t d_in,
                       hipStream_t st)
 {
     if (N == 0) return KGE_OK;
-    int32_t nc = (B + 1) * d_out;
-    XcatK sa{dP, G, d_out, B * d_out};
-    WcatK sb{V, W0, d_in, d_out, B};
-    EpiRows ep{dH, d_in};
     KGE_PROF("input_grad", st);
-    return run_gemm(sa, sb, ep, N, d_in, GemmGrid{0, 0, 1, nc, nc}, st);
-}
-
-int launch_rel_outer(const kge_partition *p, const float *Z, const float *G, int32_t d_in, int32_t d_out,
-                     float *C, hipStream_t st)
-{
-    const int64_t dd = (int64_t)d_in * d_out;
-    if (p->n_seg == 0 || p->n_relc == 0) return KGE_OK;
-    RowsX sa{Z, d_in, nullptr, 0};
-    RowsX sb{G, d_out, p->seg_dst, 0};
-    EpiRowsAtomic ep{C, d_out, dd, false};
-    KGE_PROF("rel_outer", st);
-    return run_gemm(
-        sa, sb, ep, d_in, d_out, GemmGrid{0, 0, p->n_relc, p->n_seg, 0, p->relc_rel, p->relc_beg, p->relc_end}, st);
+    InputGradJob job;
+    int rc = input_grad_job(dP, G, N, d_in, d_out, B, V, W0, dH, &job);
+    return rc != KGE_OK ? rc : run_job(job, st);
 }
 
 int launch_coeff_contract(const kge_partition *p, const float *C, const float *V, int32_t d_in, int32_t d_out,
@@ -717,32 +805,33 @@ int launch_basis_grad_from_relations(const float *a, int32_t R2, int32_t B, cons
     return rc;
 }
 
-// the row tiles of the per-run products: <= 128 consecutive runs of one relation each
-static GemmGrid rel_tiles(const kge_partition *p, int32_t K)
+// ---- a layer's products that do not depend on one another, in one launch
+// U[s] = Z[s] Wrel[rel(s)] (one row tile per relation and <= 128 runs) and Self = H W_0
+int launch_forward_products(const kge_partition *p, const float *Z, const float *Wrel, const float *H, const float *W0, int32_t d_in,
+                            int32_t d_out, float *U, float *Self, hipStream_t st)
 {
-    return GemmGrid{p->n_relt, 0, 1, K, K, nullptr, nullptr, nullptr, p->relt_rel, p->relt_beg, p->relt_end};
+    KGE_PROF("fwd_products", st);
+    ApplyJob apply;
+    ProjectJob self;
+    int rc = apply_job(p, Z, Wrel, d_in, d_out, U, &apply);
+    if (rc == KGE_OK) rc = project_job(H, p->n_vert, d_in, d_out, 0, W0, W0, nullptr, Self, &self);
+    return rc != KGE_OK ? rc : run_jobs(st, apply, self);
 }
 
-// U[s] = Z[s] Wrel[rel(s)]   (S x d_in) -> (S x d_out), one row tile per (relation, <= 128 runs)
-int launch_apply_relation_weights(const kge_partition *p, const float *Z, const float *Wrel, int32_t d_in,
-                                  int32_t d_out, float *U, hipStream_t st)
+// C_r += sum of its runs' Z[s]^T G[dst(s)] and dW_0 += H^T G; with dZ also dZ[s] = G[dst(s)] Wrel[rel(s)]^T and Self = G W_0^T
+int launch_backward_products(const kge_partition *p, const float *Z, const float *G, const float *Wrel, const float *H, const float *W0,
+                             int32_t d_in, int32_t d_out, float *C, float *dW0, float *dZ, float *Self, hipStream_t st)
 {
-    if (p->n_relt == 0) return KGE_OK;
-    RowsK sa{Z, d_in, nullptr, 0};
-    RowsX sb{Wrel, d_out, nullptr, (int64_t)d_in * d_out};
-    EpiRows ep{U, d_out};
-    KGE_PROF("apply_rel", st);
-    return run_gemm(sa, sb, ep, p->n_seg, d_out, rel_tiles(p, d_in), st);
-}
-
-// dZ[s] = G[dst(s)] Wrel[rel(s)]^T   (S x d_out) -> (S x d_in)
-int launch_apply_relation_weights_t(const kge_partition *p, const float *G, const float *Wrel, int32_t d_in,
-                                    int32_t d_out, float *dZ, hipStream_t st)
-{
-    if (p->n_relt == 0) return KGE_OK;
-    RowsK sa{G, d_out, p->seg_dst, 0};
-    RowsK sb{Wrel, d_out, nullptr, (int64_t)d_in * d_out};
-    EpiRows ep{dZ, d_in};
-    KGE_PROF("apply_rel_t", st);
-    return run_gemm(sa, sb, ep, p->n_seg, d_in, rel_tiles(p, d_out), st);
+    KGE_PROF(dZ ? "bwd_products" : "outer_products", st);
+    RelOuterJob outer;
+    WeightGradJob weight;
+    int rc = rel_outer_job(p, Z, G, d_in, d_out, C, &outer);
+    if (rc == KGE_OK) rc = weight_grad_job(H, p->n_vert, d_in, d_out, 0, nullptr, G, nullptr, dW0, &weight);
+    if (rc != KGE_OK) return rc;
+    if (!dZ) return run_jobs(st, outer, weight);
+    ApplyTJob apply;
+    InputGradJob self;
+    rc = apply_t_job(p, G, Wrel, d_in, d_out, dZ, &apply);
+    if (rc == KGE_OK) rc = input_grad_job(nullptr, G, p->n_vert, d_in, d_out, 0, W0, W0, Self, &self);
+    return rc != KGE_OK ? rc : run_jobs(st, outer, weight, apply, self);
 }
