@@ -112,7 +112,6 @@ struct EvalScale { bool half; float h, q, inv; };
 __device__ __forceinline__ EvalScale eval_scale(const EvalRange *__restrict__ range)
 {
     EvalScale c = {false, 1.f, 1.f, 1.f};
-    if (!range) return c;
     const EvalRange r = *range;
     const int eh = (int)(r.max_h >> 23) - 127, eq = (int)(r.max_q >> 23) - 127;
     c.half = abs(eh) <= 24 && abs(eq) <= 24 && (int)(r.min_h >> 23) - 127 >= eh - 14 && (int)(r.min_q >> 23) - 127 >= eq - 14;
@@ -202,7 +201,9 @@ __host__ __device__ __forceinline__ int query_at(const PairPlace *ptr, PairPlace
 // wavefront's chain.  A block's queries lie a grid apart: neighbours in a test file often share a hub, whose list is as long
 // for each of them.  Bound by the gathered rows (a load touches 32 of them).  40,932 queries of the 14,541-entity graph at
 // width 200: 676 us with one wavefront and one tile per query and fp32 steps, 187 with three bf16 parts, 180 with two
-// fp16 parts (545 with conditions around the row loads: each then waits for the last).
+// fp16 parts (545 with conditions around the row loads: each then waits for the last).  HALF = false: three bf16 parts only, for
+// the narrow rows; both forms in one kernel take 94 registers and leave two blocks per compute unit, this one 78 and three.
+template <bool HALF>
 __global__ __launch_bounds__(64 * PW) void k_eval_pairs(const float *__restrict__ Q, const float *__restrict__ H,
                                                     int32_t d, int64_t nq, int64_t n_test,
                                                     const int32_t *__restrict__ fixed, const int32_t *__restrict__ rel,
@@ -219,9 +220,11 @@ __global__ __launch_bounds__(64 * PW) void k_eval_pairs(const float *__restrict_
     const int64_t step = gridDim.x;                         // the block's queries: blockIdx.x, and every step-th after it
     auto query = [&](int i) { return (int64_t)blockIdx.x + i * step; };
     const int n_here = (int)((nq - 1 - blockIdx.x) / step) + 1;
-    const EvalScale sc = eval_scale(range);
+    const EvalScale sc = HALF ? eval_scale(range) : EvalScale{false, 1.f, 1.f, 1.f};
     auto scores = [&](const float *qrow, int32_t ent) __attribute__((always_inline)) {
-        return sc.half ? pair_scores<2>(qrow, H, ent, d, lane, sc.h, sc.q) * sc.inv : pair_scores<3>(qrow, H, ent, d, lane, 1.f, 1.f);
+        if constexpr (HALF)
+            if (sc.half) return pair_scores<2>(qrow, H, ent, d, lane, sc.h, sc.q) * sc.inv;
+        return pair_scores<3>(qrow, H, ent, d, lane, 1.f, 1.f);
     };
     if (t < 2 * PQ) {                                       // ends of the queries' ranges in the tables, by wavefront 0
         const int i = t >> 1;
@@ -657,7 +660,8 @@ __device__ __forceinline__ void count_tiles(unsigned char *lds, const EvalScale 
     }
 }
 
-template <int WI, int WJ, bool DUMP>
+// HALF = false: three bf16 parts only (narrow rows)
+template <int WI, int WJ, bool DUMP, bool HALF>
 __global__ __launch_bounds__(512, 2) void k_eval_count(const EvalRange *__restrict__ range, const float *__restrict__ Q,
                                                     int64_t nq, const float *__restrict__ H, int64_t N, int32_t d,
                                                     const float *__restrict__ s_answer, int32_t tiles_per_block,
@@ -667,13 +671,15 @@ __global__ __launch_bounds__(512, 2) void k_eval_count(const EvalRange *__restri
 {
     // two buffers of three parts or three of two
     __shared__ __attribute__((aligned(16))) unsigned char lds[6 * (64 * WI + 128 * WJ) * ELP];
-    const EvalScale sc = eval_scale(range);
-    if (sc.half)
-        count_tiles<WI, WJ, DUMP, 2>(lds, sc, Q, nq, H, N, d, s_answer, tiles_per_block, n_col_tiles, n_row_tiles, n_col_chunks,
-                                     cnt_gt, cnt_eq, dump);
-    else
-        count_tiles<WI, WJ, DUMP, 3>(lds, sc, Q, nq, H, N, d, s_answer, tiles_per_block, n_col_tiles, n_row_tiles, n_col_chunks,
-                                     cnt_gt, cnt_eq, dump);
+    const EvalScale sc = HALF ? eval_scale(range) : EvalScale{false, 1.f, 1.f, 1.f};
+    if constexpr (HALF)
+        if (sc.half) {
+            count_tiles<WI, WJ, DUMP, 2>(lds, sc, Q, nq, H, N, d, s_answer, tiles_per_block, n_col_tiles, n_row_tiles, n_col_chunks,
+                                         cnt_gt, cnt_eq, dump);
+            return;
+        }
+    count_tiles<WI, WJ, DUMP, 3>(lds, sc, Q, nq, H, N, d, s_answer, tiles_per_block, n_col_tiles, n_row_tiles, n_col_chunks,
+                                 cnt_gt, cnt_eq, dump);
 }
 
 // Largest numbers of H and of Q and the smallest of their rows' largest numbers (rows of zeros aside; EvalRange), as the bits
@@ -845,12 +851,13 @@ int launch_count_tiles(const EvalRange *range, const float *Q, int64_t nq, const
     const int64_t patches = cdiv(row_tiles, 8) * cdiv(col_chunks, 4);
     const int64_t blocks = cdiv(patches, 8) * 8 * 32;        // whole rounds of 8 patches, 32 blocks each
     KGE_REQUIRE(blocks <= 0x7FFFFFFFll, KGE_ERANGE, "evaluation grid too large");
-    if (dump)
-        k_eval_count<WI, WJ, true><<<(unsigned)blocks, 512, 0, st>>>(range, Q, nq, H, N, d, s_answer, (int32_t)tpb, (int32_t)col_tiles,
-                                                                    (int32_t)row_tiles, (int32_t)col_chunks, cnt_gt, cnt_eq, dump);
-    else
-        k_eval_count<WI, WJ, false><<<(unsigned)blocks, 512, 0, st>>>(range, Q, nq, H, N, d, s_answer, (int32_t)tpb, (int32_t)col_tiles,
-                                                                     (int32_t)row_tiles, (int32_t)col_chunks, cnt_gt, cnt_eq, nullptr);
+#define EC_CALL(DUMPV, HALFV)                                                                                             \
+    k_eval_count<WI, WJ, DUMPV, HALFV><<<(unsigned)blocks, 512, 0, st>>>(range, Q, nq, H, N, d, s_answer, (int32_t)tpb,  \
+                                                                        (int32_t)col_tiles, (int32_t)row_tiles,         \
+                                                                        (int32_t)col_chunks, cnt_gt, cnt_eq, dump)
+    if (range) { if (dump) EC_CALL(true, true); else EC_CALL(false, true); }
+    else { if (dump) EC_CALL(true, false); else EC_CALL(false, false); }
+#undef EC_CALL
     KGE_LAUNCH_CHECK();
     return KGE_OK;
 }
@@ -911,8 +918,8 @@ int rank_all(const kge_eval_filter *f, const float *H, int64_t N, int32_t d, con
             ft.key[sde] = f ? f->key[sde] : nullptr; ft.val[sde] = f ? f->val[sde] : nullptr; ft.n[sde] = f ? f->n[sde] : 0;
         }
         ft.N = N; ft.R = R;
-        k_eval_pairs<<<(unsigned)cdiv(nq, pair_queries(nq)), 64 * PW, 0, st>>>(Q, H, d, nq, n_test, fixed, rel, answer, ft,
-                                                           half_range, dump_answer ? dump_answer : s, sub_gt, cnt_eq);
+        (half_range ? k_eval_pairs<true> : k_eval_pairs<false>)<<<(unsigned)cdiv(nq, pair_queries(nq)), 64 * PW, 0, st>>>(
+            Q, H, d, nq, n_test, fixed, rel, answer, ft, half_range, dump_answer ? dump_answer : s, sub_gt, cnt_eq);
         KGE_LAUNCH_CHECK();
     }
     {
