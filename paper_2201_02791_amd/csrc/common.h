@@ -116,7 +116,7 @@ struct KgeProfScope {
 };
 #define KGE_PROF(name, st) KgeProfScope prof_scope__(name, st)
 
-static inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
+static constexpr int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 static inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 // ---- kernels' host launchers (implemented in the .hip files) ----

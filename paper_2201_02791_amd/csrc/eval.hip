@@ -7,10 +7,9 @@
 // keeps, per query, only how many entries lie above / exactly at the answer's score.
 // What the filtered setting removes - the known answers of the same (f, r), from none to thousands per query - is
 // scored again by k_eval_pairs and subtracted.  Both kernels build a score from the same sequence of steps (k ascending,
-// 16 k per step, fp32 accumulator starting at zero; a step is three products of two fp16 parts, split_f16.h, or, where
-// k_eval_range finds numbers that do not allow that, six products of three bf16 parts, split_bf16.h, and then a score that
-// is not finite comes from v_mfma_f32_32x32x2_f32 steps, two k each), so a pair gets the same bits in both and the
-// subtraction is exact.
+// 16 k per step, fp32 accumulator starting at zero; a step is three products of two fp16 parts, split_f16.h, or, for queries
+// whose numbers do not allow that, six products of three bf16 parts, split_bf16.h, and then a score that is not finite comes
+// from v_mfma_f32_32x32x2_f32 steps, two k each), so a pair gets the same bits in both and the subtraction is exact.
 // The same per-query kernel ranks against explicit candidate lists.
 #include "common.h"
 #include "split_f16.h"
@@ -38,13 +37,9 @@ struct kge_eval_filter {
 
 namespace {
 
-// What k_eval_range found: the largest number of H and of Q and the smallest of their rows' largest numbers (rows of zeros
-// aside), as the bits of their absolute values.  From that, whether scores are formed from two fp16 parts, and the powers of
-// two that bring the largest numbers to 2^14 .. 2^15.  Below 80 columns three bf16 parts are the more accurate (relative
-// error at 64: 1.12e-7 against 1.15e-7, at 128 1.66e-7 against 1.44e-7); a row more than 14 binades below the largest one
-// would lose its second parts to fp16's smallest numbers; with both exponents within 24 no score or threshold can leave
-// fp32's normal range on the way; infinities and NaN lie above every exponent that is let through.
-struct EvalRange { uint32_t max_h, min_h, max_q, min_q; };
+// What k_eval_range found of H and of Q, numbers as the bits of their absolute values: the largest ones and the smallest one of
+// H that is not zero, less one.  n_three: the queries that k_eval_pairs found to need three parts.
+struct EvalRange { uint32_t max_h, least_h, max_q, n_three; };
 
 // tail queries of all test triples first, then the head queries; their query vectors Q[q][:] = H[fixed][:] * M[rel][:]
 // (one thread per 4 columns) and cleared counters
@@ -55,7 +50,7 @@ __global__ void k_eval_queries(const int32_t *__restrict__ th, const int32_t *__
                                unsigned *__restrict__ cnt_gt, EvalRange *__restrict__ range)
 {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t == 0) *range = EvalRange{0u, 0x7f800000u, 0u, 0x7f800000u};
+    if (t == 0) *range = EvalRange{0u, 0xffffffffu, 0u, 0u};
     if (t >= 2 * n_test * d4) return;
     const int64_t i = t / d4;
     const int32_t c = (int32_t)(t - i * d4);
@@ -86,7 +81,7 @@ __global__ void k_eval_qvec(const float4 *__restrict__ H, const float4 *__restri
 }
 
 // 8 consecutive k of a row from k (past the width: the row's last ones; no condition stands around the loads, so that
-// they can be in flight together), and their three parts, scaled by 0 or 1
+// they can be in flight together), and their parts, scaled by sx and sy
 struct Row8 { float4 x, y; };
 __device__ __forceinline__ Row8 row_of(const float *__restrict__ row, int32_t k, int32_t d)
 {
@@ -107,18 +102,49 @@ __device__ __forceinline__ Parts8<NP> parts_of(const Row8 &r, float sx, float sy
     return q;
 }
 
+// Whether scores are formed from two fp16 parts, and the powers of two that bring the largest numbers of H and of Q to
+// 2^14 .. 2^15.  Below 80 columns three bf16 parts are the more accurate (relative error at 64: 1.12e-7 against 1.15e-7, at 128
+// 1.66e-7 against 1.44e-7).  With both exponents within 24 no score or threshold can leave fp32's normal range on the way;
+// infinities and NaN lie above every exponent that is let through.
 constexpr int HALF_FROM = 80;
-struct EvalScale { bool half; float h, q, inv; };
+struct EvalScale { bool half = false, h_loses = false; float h = 1.f, q = 1.f, inv = 1.f; uint32_t q_small = 0u; };
 __device__ __forceinline__ EvalScale eval_scale(const EvalRange *__restrict__ range)
 {
-    EvalScale c = {false, 1.f, 1.f, 1.f};
-    const EvalRange r = *range;
-    const int eh = (int)(r.max_h >> 23) - 127, eq = (int)(r.max_q >> 23) - 127;
-    c.half = abs(eh) <= 24 && abs(eq) <= 24 && (int)(r.min_h >> 23) - 127 >= eh - 14 && (int)(r.min_q >> 23) - 127 >= eq - 14;
+    EvalScale c;
+    const int eh = (int)(range->max_h >> 23) - 127, eq = (int)(range->max_q >> 23) - 127;
+    c.half = abs(eh) <= 24 && abs(eq) <= 24;
     auto two_to = [](int e) { return __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((e + 127) << 23)); };
-    if (c.half) { c.h = two_to(14 - eh); c.q = two_to(14 - eq); c.inv = two_to(eh + eq - 28); }
+    if (c.half) {
+        c.h = two_to(14 - eh); c.q = two_to(14 - eq); c.inv = two_to(eh + eq - 28);
+        c.h_loses = range->least_h + 1u < (uint32_t)(eh + 111) << 23;       // LossBound
+        c.q_small = (uint32_t)(eq + 111) << 23;
+    }
     return c;
 }
+
+// Numbers that scale to less than 2^-2 lose bits to fp16's smallest numbers, 2^-25 each at most, so a score may be off by
+//   2^-25 (sum_k |q_k| where h_k loses bits + sum_k |h_k| where q_k does),   |h_k| < 2^15.
+// That is nothing where the columns that make up a score are of the largest ones' size, and all of it where they are far
+// below: a column of H that is large where every relation is zero, rows of very different size.  A query takes two parts if
+// twice that bound (the answer's score has its own) is at most 2^-25 of sum_k |q_k h_k| over its answer's row, half of
+// what rounding each of the answer's terms to fp32 may move; else all its scores are formed from three parts.  Scores far
+// from the answer's may still have lost bits: they lie on the same side of it.  In ordinary embeddings no query needs three
+// parts, and finding that out costs nothing that can be measured: 20,000 queries x 1 M entities, d = 256, 28.6 ms with and
+// without; 40,932 x 14,541, d = 200, 1005 and 1001 us.
+struct LossBound {
+    float q_sum = 0.f, terms = 0.f;
+    int32_t q_small = 0;
+    __device__ __forceinline__ void add(float q, float h, const EvalScale &sc)
+    {
+        q_sum += __builtin_fabsf(q * sc.q);
+        terms += __builtin_fabsf((q * sc.q) * (h * sc.h));
+        q_small += (__float_as_uint(q) & 0x7fffffffu) - 1u < sc.q_small - 1u ? 1 : 0;       // not zero
+    }
+    __device__ __forceinline__ bool too_large(const EvalScale &sc) const        // 1.01: the sums' own rounding
+    {
+        return terms < 2.02f * ((sc.h_loses ? q_sum : 0.f) + 32768.f * (float)q_small);
+    }
+};
 
 // Scores of 32 (query, entity) pairs: lane l and lane l + 32 name pair l (qrow its query vector, ent its entity; ent < 0:
 // no pair, any score).  Row l of the matrix-core tile is the pair's query and column l its entity, so the scores lie on the
@@ -206,9 +232,9 @@ __host__ __device__ __forceinline__ int query_at(const PairPlace *ptr, PairPlace
 template <bool HALF>
 __global__ __launch_bounds__(64 * PW) void k_eval_pairs(const float *__restrict__ Q, const float *__restrict__ H,
                                                     int32_t d, int64_t nq, int64_t n_test,
-                                                    const int32_t *__restrict__ fixed, const int32_t *__restrict__ rel,
+                                                    int32_t *fixed, const int32_t *__restrict__ rel,
                                                     const int32_t *__restrict__ answer, FilterTables ft,
-                                                    const EvalRange *__restrict__ range,
+                                                    EvalRange *range,
                                                     float *__restrict__ s_answer, int32_t *__restrict__ out_gt,
                                                     unsigned *__restrict__ cnt_eq)
 {
@@ -216,14 +242,23 @@ __global__ __launch_bounds__(64 * PW) void k_eval_pairs(const float *__restrict_
     __shared__ PairPlace ptr[PQ + 1];
     __shared__ int32_t gt_s[PQ], eq_s[PQ];
     __shared__ float thr[PQ];
+    __shared__ bool three[PQ];                              // the query needs three parts
     const int t = threadIdx.x, lane = t & 63, w = t >> 6;
     const int64_t step = gridDim.x;                         // the block's queries: blockIdx.x, and every step-th after it
     auto query = [&](int i) { return (int64_t)blockIdx.x + i * step; };
     const int n_here = (int)((nq - 1 - blockIdx.x) / step) + 1;
-    const EvalScale sc = HALF ? eval_scale(range) : EvalScale{false, 1.f, 1.f, 1.f};
-    auto scores = [&](const float *qrow, int32_t ent) __attribute__((always_inline)) {
+    EvalScale sc;
+    if constexpr (HALF) sc = eval_scale(range);
+    auto scores = [&](const float *qrow, int32_t ent, bool by_three) __attribute__((always_inline)) {
         if constexpr (HALF)
-            if (sc.half) return pair_scores<2>(qrow, H, ent, d, lane, sc.h, sc.q) * sc.inv;
+            if (sc.half) {
+                float s = pair_scores<2>(qrow, H, ent, d, lane, sc.h, sc.q) * sc.inv;
+                if (__any(by_three)) {
+                    const float x = pair_scores<3>(qrow, H, ent, d, lane, 1.f, 1.f);
+                    if (by_three) s = x;
+                }
+                return s;
+            }
         return pair_scores<3>(qrow, H, ent, d, lane, 1.f, 1.f);
     };
     if (t < 2 * PQ) {                                       // ends of the queries' ranges in the tables, by wavefront 0
@@ -239,12 +274,39 @@ __global__ __launch_bounds__(64 * PW) void k_eval_pairs(const float *__restrict_
     } else if (w == 1) {                                    // the answers' scores, by wavefront 1
         const int i = lane & 31;
         const int64_t q = query(i < n_here ? i : 0);
-        const float s = scores(Q + q * d, i < n_here ? answer[q] : -1);
+        const float s = scores(Q + q * d, i < n_here ? answer[q] : -1, false);
         if (lane < n_here) { thr[lane] = s; s_answer[q] = s; }
-    } else if (w == 2 && lane < PQ) {
-        gt_s[lane] = 0; eq_s[lane] = 0;
+    } else {
+        if (w == 2 && lane < PQ) { gt_s[lane] = 0; eq_s[lane] = 0; }
+        if (HALF && sc.half)                                // which queries need three parts, by the others
+            for (int i = w - 2; i < n_here; i += PW - 2) {
+                const int64_t q = query(i);
+                const float4 *qr = reinterpret_cast<const float4 *>(Q + q * d), *hr = reinterpret_cast<const float4 *>(H + (int64_t)answer[q] * d);
+                LossBound b;
+                for (int32_t c = lane; c < d / 4; c += 64) {
+                    const float4 x = qr[c], y = hr[c];
+                    b.add(x.x, y.x, sc); b.add(x.y, y.y, sc); b.add(x.z, y.z, sc); b.add(x.w, y.w, sc);
+                }
+                for (int off = 32; off > 0; off >>= 1) {
+                    b.q_sum += __shfl_xor(b.q_sum, off, 64); b.terms += __shfl_xor(b.terms, off, 64); b.q_small += __shfl_xor(b.q_small, off, 64);
+                }
+                if (lane == 0) three[i] = b.too_large(sc);
+            }
     }
     __syncthreads();
+    if (HALF && sc.half && w == 1) {
+        const int i = lane & 31;
+        const int64_t q = query(i < n_here ? i : 0);
+        const bool by_three = i < n_here && three[i];
+        if (__any(by_three)) {
+            const float s = pair_scores<3>(Q + q * d, H, by_three ? answer[q] : -1, d, lane, 1.f, 1.f);
+            if (lane < n_here && by_three) { thr[lane] = s; s_answer[q] = s; }
+            const int n = __popcll(__ballot(lane < n_here && by_three));
+            if (lane == 0) atomicAdd(&range->n_three, (uint32_t)n);
+        }
+        // k_eval_count finds it where the query's entity was, which only this block reads and wavefront 0 has read
+        if (lane < n_here) fixed[q] = by_three ? 1 : 0;
+    }
     if (w == 0) {                                           // where each query's known answers start in the block's row
         PairPlace x = lane < PQ ? (PairPlace)(bound[2 * lane + 1] - bound[2 * lane]) : 0;
         const PairPlace own = x;
@@ -262,7 +324,7 @@ __global__ __launch_bounds__(64 * PW) void k_eval_pairs(const float *__restrict_
             e = ft.val[q >= n_test ? 1 : 0][bound[2 * i] + (at - ptr[i])];
             if (e == answer[q]) e = -1;
         }
-        const float s = scores(Q + q * d, e);
+        const float s = scores(Q + q * d, e, HALF && sc.half && e >= 0 && three[i]);
         if (lane < 32 && e >= 0) {
             if (s > thr[i]) atomicAdd(gt_s + i, 1);
             if (s == thr[i]) atomicAdd(eq_s + i, 1);
@@ -374,11 +436,41 @@ __global__ __launch_bounds__(256) void k_eval_candidates(const float4 *__restric
 constexpr int ELP = 48;                       // bytes per LDS row: 16 bf16 and 16 of padding (an odd multiple of 16)
 
 
-template <int WI, int WJ, bool DUMP, int NP>
-__device__ __forceinline__ void count_tiles(unsigned char *lds, const EvalScale sc, const float *__restrict__ Q, int64_t nq,
+// Blocks of a count over row_tiles x col_tiles tiles: about 2048 (8 rounds of one per compute unit) when there is that much
+// work, the chunk count a multiple of the patch width when it exceeds it
+struct CountGrid { int32_t tiles_per_block, col_tiles, row_tiles, col_chunks; int64_t blocks; };
+__host__ __device__ inline CountGrid count_grid(int64_t row_tiles, int64_t col_tiles)
+{
+    int64_t col_chunks = cdiv(2048, row_tiles);
+    if (col_chunks > 4) col_chunks = cdiv(col_chunks, 4) * 4;
+    if (col_chunks > col_tiles) col_chunks = col_tiles;
+    const int64_t tpb = cdiv(col_tiles, col_chunks);
+    col_chunks = cdiv(col_tiles, tpb);
+    const int64_t patches = cdiv(row_tiles, 8) * cdiv(col_chunks, 4);
+    return CountGrid{(int32_t)tpb, (int32_t)col_tiles, (int32_t)row_tiles, (int32_t)col_chunks, cdiv(patches, 8) * 8 * 32};     // whole rounds of 8 patches, 32 blocks each
+}
+
+// block id -> (query tile, chunk of entity tiles); false: a padding block of the edge patches.  Workgroup i runs on XCD i % 8,
+// each with its own L2.  The (query tile, chunk) space is cut into 8 x 4 patches; a patch goes to one XCD and is what that XCD
+// runs at a time (32 blocks), so its L2 holds 8 query tiles, re-read at every entity tile, and 4 streams of entity tiles, each
+// shared by 8 blocks.
+__device__ __forceinline__ bool count_place(const CountGrid &g, int64_t block, int64_t &row_tile, int64_t &chunk)
+{
+    const int64_t slot = block / 8, xcd = block % 8;
+    const int64_t patch = (slot / 32) * 8 + xcd;
+    const int r32 = (int)(slot % 32);
+    const int64_t patches_r = (g.row_tiles + 7) / 8;
+    row_tile = (patch % patches_r) * 8 + r32 % 8;
+    chunk = (patch / patches_r) * 4 + r32 / 8;
+    return row_tile < g.row_tiles && chunk < g.col_chunks;
+}
+
+// The block's queries are those from q0 on, or, with `ids`, those named there.  three (NP = 2): queries that three parts rank
+template <int WI, int WJ, bool DUMP, int NP, bool IDS>
+__device__ __forceinline__ void count_tiles(unsigned char *lds, const EvalScale sc, int64_t row_tile, int64_t chunk,
+                                            const int32_t *ids, const int32_t *__restrict__ three, const float *__restrict__ Q, int64_t nq,
                                             const float *__restrict__ H, int64_t N, int32_t d,
-                                            const float *__restrict__ s_answer, int32_t tiles_per_block,
-                                            int32_t n_col_tiles, int32_t n_row_tiles, int32_t n_col_chunks,
+                                            const float *__restrict__ s_answer, int32_t tiles_per_block, int32_t n_col_tiles,
                                             unsigned *__restrict__ cnt_gt, unsigned *__restrict__ cnt_eq,
                                             float *__restrict__ dump)
 {
@@ -386,17 +478,6 @@ __device__ __forceinline__ void count_tiles(unsigned char *lds, const EvalScale 
     constexpr int PA = EM * ELP, PB = QN * ELP, BUF = NP * (PA + PB);      // bytes of a part of either operand, of a buffer
     const int t = threadIdx.x, lane = t & 63, half = lane >> 5;
     const int w = __builtin_amdgcn_readfirstlane(t >> 6), we = w >> 2, wq = w & 3;
-    // block id -> (query tile, chunk of entity tiles).  Workgroup i runs on XCD i % 8, each with its own L2.
-    // The (query tile, chunk) space is cut into 8 x 4 patches; a patch goes to one XCD and is what that XCD
-    // runs at a time (32 blocks), so its L2 holds 8 query tiles, re-read at every entity tile, and 4 streams
-    // of entity tiles, each shared by 8 blocks.
-    const int64_t slot = blockIdx.x / 8, xcd = blockIdx.x % 8;
-    const int64_t patch = (slot / 32) * 8 + xcd;
-    const int r32 = (int)(slot % 32);
-    const int64_t patches_r = (n_row_tiles + 7) / 8;
-    const int64_t row_tile = (patch % patches_r) * 8 + r32 % 8;
-    const int64_t chunk = (patch / patches_r) * 4 + r32 / 8;
-    if (row_tile >= n_row_tiles || chunk >= n_col_chunks) return;      // padding blocks of the edge patches
     const int64_t q0 = row_tile * QN;
     const int32_t ct_beg = (int32_t)chunk * tiles_per_block;
     const int32_t ct_end = ct_beg + tiles_per_block < n_col_tiles ? ct_beg + tiles_per_block : n_col_tiles;
@@ -404,9 +485,13 @@ __device__ __forceinline__ void count_tiles(unsigned char *lds, const EvalScale 
     // rows r_ld + 128 * pass of either operand, 4 consecutive k; rows and k past the end repeat the last ones (such
     // rows are not counted, such k are zeroed in the entities)
     const int r_ld = t >> 2, k_ld = (t & 3) * 4;
-    const float *qb = Q + q0 * d;
+    const float *qb = Q + (IDS ? 0 : q0 * d);
     const uint32_t q_last = (uint32_t)(nq - 1 - q0 < QN - 1 ? nq - 1 - q0 : QN - 1);
     const float sq = NP == 2 ? sc.q : 1.f;
+    auto query = [&](int c) __attribute__((always_inline)) { return IDS ? (int64_t)ids[c] : q0 + c; };     // column c of the tile
+    int32_t id_ld[NB];
+#pragma unroll
+    for (int ps = 0; ps < NB; ++ps) id_ld[ps] = IDS ? ids[min((uint32_t)(r_ld + ps * 128), q_last)] : 0;
     float4 ra[NA], rb[NB];
     int32_t lt = ct_beg, lk = 0, sk = 0;                    // tile and k of the next load, k of the next staging
     auto load = [&]() __attribute__((always_inline)) {
@@ -419,7 +504,8 @@ __device__ __forceinline__ void count_tiles(unsigned char *lds, const EvalScale 
             ra[ps] = *reinterpret_cast<const float4 *>(hb + (min((uint32_t)(r_ld + ps * 128), e_last) * (uint32_t)d + k));
 #pragma unroll
         for (int ps = 0; ps < NB; ++ps)
-            rb[ps] = *reinterpret_cast<const float4 *>(qb + (min((uint32_t)(r_ld + ps * 128), q_last) * (uint32_t)d + k));
+            if constexpr (IDS) rb[ps] = *reinterpret_cast<const float4 *>(qb + (int64_t)id_ld[ps] * d + k);
+            else rb[ps] = *reinterpret_cast<const float4 *>(qb + (min((uint32_t)(r_ld + ps * 128), q_last) * (uint32_t)d + k));
         lk += 16;
         if (lk >= d) { lk = 0; if (lt + 1 < ct_end) ++lt; }
     };
@@ -450,11 +536,17 @@ __device__ __forceinline__ void count_tiles(unsigned char *lds, const EvalScale 
     unsigned gt[WJ], eq[WJ];
 #pragma unroll
     for (int j = 0; j < WJ; ++j) {
-        const int64_t q = q0 + (wq * WJ + j) * 32 + (lane & 31);
+        const int c = (wq * WJ + j) * 32 + (lane & 31);
         // two parts: scores come times a power of two, and so does what they are compared with (no bit is lost either way:
-        // a sum of fp16 products is no smaller than 2^-48, and the powers are limited)
-        thr[j] = q < nq ? s_answer[q] * (NP == 2 ? sc.h * sc.q : 1.f) : INFINITY;
+        // a sum of fp16 products is no smaller than 2^-48, and the powers are limited); nothing is above or at infinity
+        thr[j] = q0 + c < nq && !(NP == 2 && three[q0 + c]) ? s_answer[query(c)] * (NP == 2 ? sc.h * sc.q : 1.f) : INFINITY;
         gt[j] = eq[j] = 0u;
+    }
+    if constexpr (NP == 2) {
+        bool any = false;
+#pragma unroll
+        for (int j = 0; j < WJ; ++j) any |= thr[j] != INFINITY;
+        if (!__syncthreads_or(any)) return;
     }
     split_floatx16 acc[WI][WJ];
     auto clear = [&]() __attribute__((always_inline)) {
@@ -485,8 +577,8 @@ __device__ __forceinline__ void count_tiles(unsigned char *lds, const EvalScale 
                         split_floatx16 f;
 #pragma unroll
                         for (int v = 0; v < 16; ++v) f[v] = 0.f;
-                        const int64_t e = e0 + i * 32 + (lane & 31), q = q0 + (wq * WJ + j) * 32 + (lane & 31);
-                        const float *hp = H + (e < N ? e : N - 1) * d, *qr = Q + (q < nq ? q : nq - 1) * d;
+                        const int64_t e = e0 + i * 32 + (lane & 31);
+                        const float *hp = H + (e < N ? e : N - 1) * d, *qr = Q + query(min((wq * WJ + j) * 32 + (lane & 31), (int)q_last)) * d;
                         for (int32_t k = half; k < d; k += 2) f = __builtin_amdgcn_mfma_f32_32x32x2f32(hp[k], qr[k], f, 0, 0, 0);
 #pragma unroll
                         for (int v = 0; v < 16; ++v) if (split_not_finite(acc[i][j][v])) acc[i][j][v] = f[v];
@@ -538,8 +630,9 @@ __device__ __forceinline__ void count_tiles(unsigned char *lds, const EvalScale 
                         gt[j] += in && acc[i][j][v] > thr[j] ? 1u : 0u;
                         eq[j] += in && acc[i][j][v] == thr[j] ? 1u : 0u;
                         if (DUMP) {
-                            const int64_t q = q0 + (wq * WJ + j) * 32 + (lane & 31);
-                            if (in && q < nq) dump[q * N + e0 + row] = acc[i][j][v] * (NP == 2 ? sc.inv : 1.f);
+                            const int c = (wq * WJ + j) * 32 + (lane & 31);
+                            if (in && q0 + c < nq && !(NP == 2 && thr[j] == INFINITY))
+                                dump[query(c) * N + e0 + row] = acc[i][j][v] * (NP == 2 ? sc.inv : 1.f);
                         }
                     }
                 }
@@ -652,75 +745,118 @@ __device__ __forceinline__ void count_tiles(unsigned char *lds, const EvalScale 
     for (int j = 0; j < WJ; ++j) {
         gt[j] += __shfl_xor(gt[j], 32, 64);
         eq[j] += __shfl_xor(eq[j], 32, 64);
-        const int64_t q = q0 + (wq * WJ + j) * 32 + (lane & 31);
-        if (lane < 32 && q < nq) {
-            if (gt[j]) atomicAdd(cnt_gt + q, gt[j]);
-            if (eq[j]) atomicAdd(cnt_eq + q, eq[j]);
+        const int c = (wq * WJ + j) * 32 + (lane & 31);
+        if (lane < 32 && q0 + c < nq) {
+            if (gt[j]) atomicAdd(cnt_gt + query(c), gt[j]);
+            if (eq[j]) atomicAdd(cnt_eq + query(c), eq[j]);
         }
     }
 }
 
-// HALF = false: three bf16 parts only (narrow rows)
+// Numbers first .. first + QN - 1 of the queries that `three` marks, or of all of them, into ids (past the last one: any query)
+template <int QN>
+__device__ __forceinline__ void pick_queries(const int32_t *__restrict__ three, int64_t nq, bool marked, int64_t first, int32_t *ids)
+{
+    __shared__ int32_t before[8];
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+    if (!marked) {
+        for (int i = t; i < QN; i += 512) ids[i] = (int32_t)(first + i < nq ? first + i : nq - 1);
+        __syncthreads();
+        return;
+    }
+    for (int i = t; i < QN; i += 512) ids[i] = 0;
+    const int64_t per = cdiv(nq, 512), beg = t * per < nq ? t * per : nq, end = beg + per < nq ? beg + per : nq;
+    int32_t n = 0;
+    for (int64_t q = beg; q < end; ++q) n += three[q] ? 1 : 0;
+    int32_t x = n;
+    for (int off = 1; off < 64; off <<= 1) { const int32_t y = __shfl_up(x, off, 64); if (lane >= off) x += y; }
+    if (lane == 63) before[w] = x;
+    __syncthreads();
+    int64_t at = x - n - first;
+    for (int i = 0; i < w; ++i) at += before[i];
+    for (int64_t q = beg; q < end; ++q)
+        if (three[q]) { if (at >= 0 && at < QN) ids[at] = (int32_t)q; ++at; }
+    __syncthreads();
+}
+
+// HALF: blocks [0, g.blocks) rank all queries by two parts; those that need three are left to the rest of the grid, which
+// walks its own, smaller space of tiles.  Where no query can take two parts, the first blocks rank all of them by three.
+// HALF = false: three parts (narrow rows).
 template <int WI, int WJ, bool DUMP, bool HALF>
-__global__ __launch_bounds__(512, 2) void k_eval_count(const EvalRange *__restrict__ range, const float *__restrict__ Q,
+__global__ __launch_bounds__(512, 2) void k_eval_count(const EvalRange *__restrict__ range, const int32_t *__restrict__ three,
+                                                    const float *__restrict__ Q,
                                                     int64_t nq, const float *__restrict__ H, int64_t N, int32_t d,
-                                                    const float *__restrict__ s_answer, int32_t tiles_per_block,
-                                                    int32_t n_col_tiles, int32_t n_row_tiles, int32_t n_col_chunks,
+                                                    const float *__restrict__ s_answer, CountGrid g,
                                                     unsigned *__restrict__ cnt_gt,
                                                     unsigned *__restrict__ cnt_eq, float *__restrict__ dump)
 {
     // two buffers of three parts or three of two
     __shared__ __attribute__((aligned(16))) unsigned char lds[6 * (64 * WI + 128 * WJ) * ELP];
-    const EvalScale sc = HALF ? eval_scale(range) : EvalScale{false, 1.f, 1.f, 1.f};
-    if constexpr (HALF)
-        if (sc.half) {
-            count_tiles<WI, WJ, DUMP, 2>(lds, sc, Q, nq, H, N, d, s_answer, tiles_per_block, n_col_tiles, n_row_tiles, n_col_chunks,
-                                         cnt_gt, cnt_eq, dump);
+    int64_t row_tile, chunk;
+    if constexpr (!HALF) {
+        if (count_place(g, blockIdx.x, row_tile, chunk))
+            count_tiles<WI, WJ, DUMP, 3, false>(lds, EvalScale{}, row_tile, chunk, nullptr, nullptr, Q, nq, H, N, d, s_answer,
+                                                g.tiles_per_block, g.col_tiles, cnt_gt, cnt_eq, dump);
+    } else {
+        __shared__ int32_t ids[128 * WJ];
+        const EvalScale sc = eval_scale(range);
+        const bool rest = blockIdx.x >= g.blocks;
+        if (sc.half && !rest) {
+            if (count_place(g, blockIdx.x, row_tile, chunk))
+                count_tiles<WI, WJ, DUMP, 2, false>(lds, sc, row_tile, chunk, nullptr, three, Q, nq, H, N, d, s_answer,
+                                                    g.tiles_per_block, g.col_tiles, cnt_gt, cnt_eq, dump);
             return;
         }
-    count_tiles<WI, WJ, DUMP, 3>(lds, sc, Q, nq, H, N, d, s_answer, tiles_per_block, n_col_tiles, n_row_tiles, n_col_chunks,
-                                 cnt_gt, cnt_eq, dump);
+        const int64_t n = sc.half ? range->n_three : nq;
+        if (sc.half != rest || n == 0) return;
+        const CountGrid own = rest ? count_grid(cdiv(n, 128 * WJ), g.col_tiles) : g;
+        const int64_t first = rest ? blockIdx.x - g.blocks : blockIdx.x, step = rest ? gridDim.x - g.blocks : own.blocks;
+        for (int64_t block = first; block < own.blocks; block += step) {
+            if (!count_place(own, block, row_tile, chunk)) continue;
+            __syncthreads();                              // the block before has read its operands
+            pick_queries<128 * WJ>(three, nq, rest, row_tile * (128 * WJ), ids);
+            count_tiles<WI, WJ, DUMP, 3, true>(lds, EvalScale{}, row_tile, chunk, ids, nullptr, Q, n, H, N, d, s_answer,
+                                               own.tiles_per_block, own.col_tiles, cnt_gt, cnt_eq, dump);
+        }
+    }
 }
 
-// Largest numbers of H and of Q and the smallest of their rows' largest numbers (rows of zeros aside; EvalRange), as the bits
-// of the absolute values: ordered as the numbers are, infinities above them and NaN above those.  A wavefront takes four
-// rows at a time; blocks [0, h_blocks) walk H, the rest Q.  `out` comes initialised.  Bound by reading H: 1 M x 256, 177 us
-// (5.8 TB/s); 14,541 and 40,932 rows of 200: 28 us, mostly latency.
-__global__ __launch_bounds__(256) void k_eval_range(const uint4 *__restrict__ H, int64_t N, const uint4 *__restrict__ Q, int64_t nq,
-                                                    int32_t d4, int32_t h_blocks, EvalRange *__restrict__ out)
+// EvalRange of H (blocks [0, h_blocks)) and of Q (the rest), as bits of absolute values: ordered as the numbers are, infinities
+// above them and NaN above those.  n4: pieces of 4 numbers.  `out` comes initialised.
+__global__ __launch_bounds__(256) void k_eval_range(const uint4 *__restrict__ H, int64_t h_n4, const uint4 *__restrict__ Q, int64_t q_n4,
+                                                    int32_t h_blocks, EvalRange *__restrict__ out)
 {
     __shared__ uint32_t red[2][4];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const bool is_h = (int)blockIdx.x < h_blocks;
     const uint4 *X = is_h ? H : Q;
-    const int64_t n = is_h ? N : nq;
-    const int64_t first = (is_h ? blockIdx.x : blockIdx.x - h_blocks) * (int64_t)4 + w, step = (is_h ? h_blocks : gridDim.x - h_blocks) * (int64_t)4;
-    uint32_t most = 0u, least = 0x7f800000u;
-    for (int64_t r0 = first * 4; r0 < n; r0 += step * 4) {
-        uint32_t m[4] = {0u, 0u, 0u, 0u};
-        for (int32_t c = lane; c < d4; c += 64) {
-            uint4 x[4];
+    const int64_t n = is_h ? h_n4 : q_n4;
+    const int64_t first = (is_h ? blockIdx.x : blockIdx.x - h_blocks) * (int64_t)1024, step = (is_h ? h_blocks : gridDim.x - h_blocks) * (int64_t)1024;
+    uint32_t most = 0u, least = 0xffffffffu;
+    for (int64_t c0 = first; c0 < n; c0 += step) {
+        uint4 x[4];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) x[u] = X[(r0 + u < n ? r0 + u : n - 1) * d4 + c];
+        for (int u = 0; u < 4; ++u) { const int64_t c = c0 + u * 256 + threadIdx.x; x[u] = X[c < n ? c : n - 1]; }
 #pragma unroll
-            for (int u = 0; u < 4; ++u)
-                m[u] = max(m[u], max(max(x[u].x & 0x7fffffffu, x[u].y & 0x7fffffffu), max(x[u].z & 0x7fffffffu, x[u].w & 0x7fffffffu)));
+        for (int u = 0; u < 4; ++u) {
+            const uint32_t y[4] = {x[u].x & 0x7fffffffu, x[u].y & 0x7fffffffu, x[u].z & 0x7fffffffu, x[u].w & 0x7fffffffu};
+            most = max(most, max(max(y[0], y[1]), max(y[2], y[3])));
+            least = min(least, min(min(y[0] - 1u, y[1] - 1u), min(y[2] - 1u, y[3] - 1u)));      // a zero: the largest there is
         }
+    }
 #pragma unroll
-        for (int off = 32; off > 0; off >>= 1)
-#pragma unroll
-            for (int u = 0; u < 4; ++u) m[u] = max(m[u], (uint32_t)__shfl_xor((int)m[u], off, 64));
-#pragma unroll
-        for (int u = 0; u < 4; ++u) { most = max(most, m[u]); if (m[u]) least = min(least, m[u]); }
+    for (int off = 32; off > 0; off >>= 1) {
+        most = max(most, (uint32_t)__shfl_xor((int)most, off, 64));
+        least = min(least, (uint32_t)__shfl_xor((int)least, off, 64));
     }
     if (lane == 0) { red[0][w] = most; red[1][w] = least; }
     __syncthreads();
     if (threadIdx.x == 0) {
         for (int i = 1; i < 4; ++i) { most = max(most, red[0][i]); least = min(least, red[1][i]); }
         // most blocks change neither word: a look first keeps them off the one address (1900 blocks that all add: 47 us instead of 28)
-        uint32_t *hi = is_h ? &out->max_h : &out->max_q, *lo = is_h ? &out->min_h : &out->min_q;
+        uint32_t *hi = is_h ? &out->max_h : &out->max_q;
         if (most > __hip_atomic_load(hi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(hi, most);
-        if (least < __hip_atomic_load(lo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMin(lo, least);
+        if (is_h && least < __hip_atomic_load(&out->least_h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMin(&out->least_h, least);
     }
 }
 
@@ -837,24 +973,14 @@ int check_ws(void *workspace, size_t ws_bytes, int64_t nq, int32_t d, EvalWs *w)
 }
 
 template <int WI, int WJ>
-int launch_count_tiles(const EvalRange *range, const float *Q, int64_t nq, const float *H, int64_t N, int32_t d, const float *s_answer,
-                       unsigned *cnt_gt, unsigned *cnt_eq, float *dump, hipStream_t st)
+int launch_count_tiles(const EvalRange *range, const int32_t *three, const float *Q, int64_t nq, const float *H, int64_t N, int32_t d,
+                       const float *s_answer, unsigned *cnt_gt, unsigned *cnt_eq, float *dump, hipStream_t st)
 {
-    const int64_t row_tiles = cdiv(nq, 128 * WJ), col_tiles = cdiv(N, 64 * WI);
-    // about 2048 blocks (8 rounds of one per compute unit) when there is that much work, the chunk count a multiple
-    // of the patch width when it exceeds it
-    int64_t col_chunks = cdiv(2048, row_tiles);
-    if (col_chunks > 4) col_chunks = cdiv(col_chunks, 4) * 4;
-    if (col_chunks > col_tiles) col_chunks = col_tiles;
-    const int64_t tpb = cdiv(col_tiles, col_chunks);
-    col_chunks = cdiv(col_tiles, tpb);
-    const int64_t patches = cdiv(row_tiles, 8) * cdiv(col_chunks, 4);
-    const int64_t blocks = cdiv(patches, 8) * 8 * 32;        // whole rounds of 8 patches, 32 blocks each
+    const CountGrid g = count_grid(cdiv(nq, 128 * WJ), cdiv(N, 64 * WI));
+    const int64_t blocks = g.blocks + (range ? 256 : 0);     // one per compute unit for queries that need three parts
     KGE_REQUIRE(blocks <= 0x7FFFFFFFll, KGE_ERANGE, "evaluation grid too large");
 #define EC_CALL(DUMPV, HALFV)                                                                                             \
-    k_eval_count<WI, WJ, DUMPV, HALFV><<<(unsigned)blocks, 512, 0, st>>>(range, Q, nq, H, N, d, s_answer, (int32_t)tpb,  \
-                                                                        (int32_t)col_tiles, (int32_t)row_tiles,         \
-                                                                        (int32_t)col_chunks, cnt_gt, cnt_eq, dump)
+    k_eval_count<WI, WJ, DUMPV, HALFV><<<(unsigned)blocks, 512, 0, st>>>(range, three, Q, nq, H, N, d, s_answer, g, cnt_gt, cnt_eq, dump)
     if (range) { if (dump) EC_CALL(true, true); else EC_CALL(false, true); }
     else { if (dump) EC_CALL(true, false); else EC_CALL(false, false); }
 #undef EC_CALL
@@ -862,13 +988,13 @@ int launch_count_tiles(const EvalRange *range, const float *Q, int64_t nq, const
     return KGE_OK;
 }
 
-int launch_count(const EvalRange *range, const float *Q, int64_t nq, const float *H, int64_t N, int32_t d, const float *s_answer,
+int launch_count(const EvalRange *range, const int32_t *three, const float *Q, int64_t nq, const float *H, int64_t N, int32_t d, const float *s_answer,
                  unsigned *cnt_gt, unsigned *cnt_eq, float *dump, hipStream_t st)
 {
     // 256 x 256 tiles halve the splitting per product; with fewer of them than compute units (256) most of the chip
     // would wait for them, and 128 x 128 tiles spread the work
-    if (cdiv(nq, 256) * cdiv(N, 256) >= 256) return launch_count_tiles<4, 2>(range, Q, nq, H, N, d, s_answer, cnt_gt, cnt_eq, dump, st);
-    return launch_count_tiles<2, 1>(range, Q, nq, H, N, d, s_answer, cnt_gt, cnt_eq, dump, st);
+    if (cdiv(nq, 256) * cdiv(N, 256) >= 256) return launch_count_tiles<4, 2>(range, three, Q, nq, H, N, d, s_answer, cnt_gt, cnt_eq, dump, st);
+    return launch_count_tiles<2, 1>(range, three, Q, nq, H, N, d, s_answer, cnt_gt, cnt_eq, dump, st);
 }
 
 // Queries per block of k_eval_pairs: the most that leave 1024 blocks (four of them fill a compute unit), but no fewer than a
@@ -897,7 +1023,7 @@ int rank_all(const kge_eval_filter *f, const float *H, int64_t N, int32_t d, con
     float *Q = (float *)(ws + w.off_Q), *s = (float *)(ws + w.off_s);
     int32_t *sub_gt = (int32_t *)(ws + w.off_sub_gt);
     EvalRange *range = (EvalRange *)(ws + w.off_range);
-    const EvalRange *half_range = d >= HALF_FROM ? range : nullptr;      // narrower: three bf16 parts without a look
+    EvalRange *half_range = d >= HALF_FROM ? range : nullptr;      // narrower: three bf16 parts without a look
     unsigned *cnt_gt = (unsigned *)(ws + w.off_cnt_gt), *cnt_eq = (unsigned *)(ws + w.off_cnt_eq);
     {
         KGE_PROF("eval_queries", st);
@@ -906,8 +1032,9 @@ int rank_all(const kge_eval_filter *f, const float *H, int64_t N, int32_t d, con
                                                                          (float4 *)Q, cnt_gt, range);
         KGE_LAUNCH_CHECK();
         if (d >= HALF_FROM) {
-            const int32_t h_blocks = (int32_t)std::min<int64_t>(cdiv(N, 32), 1024), q_blocks = (int32_t)std::min<int64_t>(cdiv(nq, 32), 512);
-            k_eval_range<<<h_blocks + q_blocks, 256, 0, st>>>((const uint4 *)H, N, (const uint4 *)Q, nq, d / 4, h_blocks, range);
+            const int64_t h_n4 = N * (d / 4), q_n4 = nq * (d / 4);
+            const int32_t h_blocks = (int32_t)std::min<int64_t>(cdiv(h_n4, 1024), 1024), q_blocks = (int32_t)std::min<int64_t>(cdiv(q_n4, 1024), 512);
+            k_eval_range<<<h_blocks + q_blocks, 256, 0, st>>>((const uint4 *)H, h_n4, (const uint4 *)Q, q_n4, h_blocks, range);
             KGE_LAUNCH_CHECK();
         }
     }
@@ -924,7 +1051,7 @@ int rank_all(const kge_eval_filter *f, const float *H, int64_t N, int32_t d, con
     }
     {
         KGE_PROF("eval_count", st);
-        rc = launch_count(half_range, Q, nq, H, N, d, dump_answer ? dump_answer : s, cnt_gt, cnt_eq, dump, st);
+        rc = launch_count(half_range, fixed, Q, nq, H, N, d, dump_answer ? dump_answer : s, cnt_gt, cnt_eq, dump, st);
         if (rc != KGE_OK) return rc;
     }
     if (higher && equal) {

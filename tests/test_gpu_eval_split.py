@@ -80,6 +80,69 @@ def test_sizes(kb, what, scale):
     check(kb, H, M, n, R, 90, 54)
 
 
+def far_apart(what, gap, n, R, d):
+    """Models whose scores rest, for some queries or all, on numbers 2^gap below the largest ones."""
+    rng = np.random.default_rng(57)
+    H, M = rng.normal(size=(n, d)).astype(np.float32), rng.normal(size=(R, d)).astype(np.float32)
+    low = np.float32(2.0 ** -gap)
+    if what in ("column", "relations"):                  # a column of H above the rest, which all or one of the relations do not read
+        H *= np.float32(2.0 ** -20)
+        H[:, 5] /= low
+        M[slice(None) if what == "column" else 0, 5] = 0.0
+    elif what == "tiny":                                 # ... or read by next to nothing
+        H *= np.float32(2.0 ** -20)
+        H[:, 5] /= low
+        M[:, 5] *= low * low
+    elif what == "kinds":                                # two kinds of rows, and relations that read the columns of either
+        H[0::2, : d // 2] *= low
+        H[1::2, d // 2:] *= low
+        M[0, : d // 2] = 0.0
+        M[1, d // 2:] = 0.0
+    elif what == "sizes":                                # rows and relations of many sizes, one of zeros
+        H *= (2.0 ** (-gap * (np.arange(n) % 5) / 4)).astype(np.float32)[:, None]
+        M[1] *= low
+        H[n // 2] = 0.0
+    return H, M
+
+
+@pytest.mark.parametrize("n,n_test", [(700, 90), (17001, 520)])
+@pytest.mark.parametrize("what,gap", [("column", 20), ("column", 24), ("column", 30), ("relations", 26), ("tiny", 24), ("kinds", 20),
+                                      ("kinds", 40), ("sizes", 14), ("sizes", 30)])
+def test_scores_far_below_the_largest_numbers(kb, what, gap, n, n_test):
+    """A score is as accurate as its own terms allow, and as accurate as the answer's where that is larger: the sides of the
+    answer's score are what is counted.  2^-20 of the terms' sizes: an fp32 sum of 100 terms has rounding errors of 2^-24 of
+    its partial sums, some 50 of random sign."""
+    import torch
+    print("[case] far apart", what, gap, n, n_test, file=sys.stderr, flush=True)
+    R, d = 3, 100
+    H, M = far_apart(what, gap, n, R, d)
+    rng = np.random.default_rng(58)
+    th, tr, tt = (rng.integers(0, hi, n_test).astype(np.int32) for hi in (n, R, n))
+    th[:3], tt[:3] = n - 1, n // 2
+    dev = lambda x: torch.from_numpy(np.ascontiguousarray(x)).cuda()  # noqa: E731
+    scores, ans = kb.eval_debug_scores(dev(H), dev(M), dev(th), dev(tr), dev(tt))
+    fixed, rel, true, _ = ev.queries_of(th, tr, tt)
+    rows = torch.arange(2 * n_test, device="cuda")
+    assert torch.equal(scores[rows, dev(true)].view(torch.int32), ans.view(torch.int32))
+    Q = dev(H[fixed] * M[rel]).double()
+    H64 = dev(H).double()
+    want, size = Q @ H64.T, Q.abs() @ H64.abs().T
+    assert bool(((scores.double() - want).abs() <= 2.0 ** -20 * (size + size[rows, dev(true)][:, None])).all())
+    known = [np.concatenate([x, rng.integers(0, hi, 4000)]).astype(np.int32) for x, hi in ((th, n), (tr, R), (tt, n))]
+    hi, eq = kb.eval_rank_all(dev(H), dev(M), dev(th), dev(tr), dev(tt), kb.EvalFilter(*known, n, R))
+    gone = np.zeros((2 * n_test, n), bool)               # what the filter removes, and the answer itself
+    tails, heads = {}, {}
+    for h, r, t in zip(*known):
+        tails.setdefault((h, r), []).append(t)
+        heads.setdefault((t, r), []).append(h)
+    for i in range(2 * n_test):
+        gone[i, (tails if i < n_test else heads).get((fixed[i], rel[i]), [])] = True
+        gone[i, true[i]] = True
+    left = ~dev(gone)
+    assert torch.equal(hi.long(), ((scores > ans[:, None]) & left).sum(1))
+    assert torch.equal(eq.long(), ((scores == ans[:, None]) & left).sum(1))
+
+
 def test_whole_numbers_are_exact(kb):
     print("[case] whole numbers", file=sys.stderr, flush=True)
     import torch
