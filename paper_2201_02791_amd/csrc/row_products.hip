@@ -9,6 +9,9 @@
 // sums of their own: a sum of K terms is then rounded K / 16 times where it matters.  A row is scaled by its own power of two,
 // found when the block has the whole row in registers; a matrix by one of its own, found when k_pack_products splits it once
 // for all row tiles, into the order in which a wavefront loads it.
+// Second parts are kept 2^11 times as large, as large as the first ones, so that a number keeps both down to 2^-27 of the largest
+// of its row or matrix.  One that is smaller still, and not zero, enters as a NaN: a sum may rest on such numbers alone (where the
+// large ones meet zeros), and all sums that it reaches come from fp32 products, as those do that are not finite.
 #include "common.h"
 #include "split_f16.h"
 
@@ -20,6 +23,26 @@ constexpr int RT = 128;                       // rows of a tile (KGE_REL_TILE)
 static_assert(RT == KGE_REL_TILE, "the partition's row tiles");
 constexpr int NOT_OK = INT32_MIN;             // k_pack_products' exponent of a matrix that cannot be split
 
+// Two parts of numbers below 2^15, the second one times 2^11; not zero, the numbers are at least SMALLEST: from there down the
+// second part is below fp16's ordinary numbers
+constexpr float SMALLEST = 1.220703125e-4f;    // 2^-13
+__device__ __forceinline__ Split2 split_large(float x, float y)
+{
+    const split_floatx2 v = {x, y};
+    const split_halfx2 a = __builtin_convertvector(v, split_halfx2);
+    const split_floatx2 left = {__builtin_fmaf((float)a.x, -1.f, x) * 2048.f, __builtin_fmaf((float)a.y, -1.f, y) * 2048.f};
+    Split2 s;
+    s.w[0] = __builtin_bit_cast(uint32_t, a);
+    s.w[1] = __builtin_bit_cast(uint32_t, __builtin_convertvector(left, split_halfx2));
+    return s;
+}
+// second parts at their own size (what is lost of them here enters a product with another second part only)
+__device__ __forceinline__ uint4 at_own_size(uint4 x)
+{
+    const _Float16 f = (_Float16)4.8828125e-4f;
+    return __builtin_bit_cast(uint4, __builtin_bit_cast(split_halfx8, x) * split_halfx8{f, f, f, f, f, f, f, f});
+}
+
 // steps of 16 terms that a contraction is padded to: one kernel per class
 constexpr int step_class(int32_t K) { return K <= 112 ? 7 : K <= 128 ? 8 : 10; }
 
@@ -27,48 +50,34 @@ constexpr int step_class(int32_t K) { return K <= 112 ? 7 : K <= 128 ? 8 : 10; }
 // `back` over its columns n.  Operand block (c, s, part): 32 columns of the result from 32 c, terms 16 s .. 16 s + 15,
 // 16 bytes per lane: column 32 c + l % 32, terms 16 s + 8 (l / 32) ..; zeros past either end.  Numbers are scaled so that the
 // largest lies in 2^14 .. 2^15; info = the exponent by which a product with it is to be scaled back, or NOT_OK: a number
-// that is not finite, a largest one outside 2^-100 .. 2^100, or a row or column whose largest is more than 12 binades below
-// it (its second parts would fall under fp16's smallest numbers), zeros aside.
+// that is not finite, or a largest one outside 2^-100 .. 2^100.
 // One block of 16 wavefronts per matrix, the last group being W0.  Bound by the latency of its two passes: 10 to 18 us for
 // three matrices of 128 x 32 and 128 x 128 (70 and 80 with a thread per column and 4 rows in flight).
 __global__ __launch_bounds__(1024) void k_pack_products(const float *__restrict__ W, const float *__restrict__ W0, int32_t groups,
                                                         int32_t K, int32_t N, uint4 *__restrict__ fwd, uint4 *__restrict__ back,
                                                         int32_t ks_f, int32_t ks_b, int32_t *__restrict__ info)
 {
-    __shared__ uint32_t cmax[256];
-    __shared__ uint32_t most_s, least_s;
+    __shared__ uint32_t most_s;
     const int t = threadIdx.x, lane = t & 63, w = t >> 6, g = blockIdx.x;
     const float *M = g == groups - 1 ? W0 : W + (int64_t)g * K * N;
-    if (t < 256) cmax[t] = 0u;
-    if (t == 0) { most_s = 0u; least_s = 0x7f800000u; }
+    if (t == 0) most_s = 0u;
     __syncthreads();
     const int col = lane * 4 < N ? lane * 4 : N - 4;         // N is a multiple of 4; lanes past the width repeat its end
-    uint32_t cm[4] = {0u, 0u, 0u, 0u}, rm = 0u, rl = 0x7f800000u;
+    uint32_t most = 0u;
     for (int k0 = w; k0 < K; k0 += 16 * 8) {                 // a wavefront takes every 16th row, 8 in flight
         uint4 v[8];
 #pragma unroll
         for (int u = 0; u < 8; ++u) v[u] = *reinterpret_cast<const uint4 *>(M + (int64_t)min(k0 + 16 * u, K - 1) * N + col);
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const uint32_t x[4] = {v[u].x & 0x7fffffffu, v[u].y & 0x7fffffffu, v[u].z & 0x7fffffffu, v[u].w & 0x7fffffffu};
-#pragma unroll
-            for (int j = 0; j < 4; ++j) cm[j] = max(cm[j], x[j]);
-            uint32_t m = max(max(x[0], x[1]), max(x[2], x[3]));
-#pragma unroll
-            for (int off = 32; off > 0; off >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, off, 64));
-            rm = max(rm, m);
-            if (m) rl = min(rl, m);
-        }
+        for (int u = 0; u < 8; ++u)
+            most = max(most, max(max(v[u].x & 0x7fffffffu, v[u].y & 0x7fffffffu), max(v[u].z & 0x7fffffffu, v[u].w & 0x7fffffffu)));
     }
 #pragma unroll
-    for (int j = 0; j < 4; ++j) atomicMax(&cmax[col + j], cm[j]);
-    if (lane == 0) { atomicMax(&most_s, rm); atomicMin(&least_s, rl); }
-    __syncthreads();
-    if (t < N && cmax[t]) atomicMin(&least_s, cmax[t]);
+    for (int off = 32; off > 0; off >>= 1) most = max(most, (uint32_t)__shfl_xor((int)most, off, 64));
+    if (lane == 0) atomicMax(&most_s, most);
     __syncthreads();
     const int e = (int)(most_s >> 23) - 127;
-    const bool zero = most_s == 0u;
-    const bool ok = zero || (abs(e) <= 100 && (int)(least_s >> 23) - 127 >= e - 12);
+    const bool zero = most_s == 0u, ok = zero || abs(e) <= 100;
     if (t == 0) info[g] = !ok ? NOT_OK : zero ? 0 : e - 14;
     if (!ok) return;
     const float scale = zero ? 1.f : __uint_as_float((uint32_t)(127 + 14 - e) << 23);
@@ -86,9 +95,10 @@ __global__ __launch_bounds__(1024) void k_pack_products(const float *__restrict_
             for (int j = 0; j < 8; ++j) {
                 const int kk = min(k + j, rows - 1), cc = min(rc, cols - 1);
                 const float y = which ? M[(int64_t)cc * N + kk] : M[(int64_t)kk * N + cc];
-                x[j] = k + j < rows && rc < cols ? y * scale : 0.f;
+                x[j] = y != 0.f && __builtin_fabsf(y * scale) < SMALLEST ? __builtin_nanf("") : y * scale;
+                x[j] = k + j < rows && rc < cols ? x[j] : 0.f;
             }
-            const Split2 p0 = split_pair_f16(x[0], x[1]), p1 = split_pair_f16(x[2], x[3]), p2 = split_pair_f16(x[4], x[5]), p3 = split_pair_f16(x[6], x[7]);
+            const Split2 p0 = split_large(x[0], x[1]), p1 = split_large(x[2], x[3]), p2 = split_large(x[4], x[5]), p3 = split_large(x[6], x[7]);
             out[(int64_t)b * 128 + lane] = make_uint4(p0.w[0], p1.w[0], p2.w[0], p3.w[0]);
             out[(int64_t)b * 128 + 64 + lane] = make_uint4(p0.w[1], p1.w[1], p2.w[1], p3.w[1]);
         }
@@ -144,21 +154,27 @@ __global__ __launch_bounds__(512, 2) void k_row_products(const float *__restrict
 #pragma unroll
         for (int ps = 0; ps < 2; ++ps) {
             const int row = (t >> 3) + 64 * ps;
-            uint32_t m = 0u;
+            uint32_t m = 0u, least = 0xffffffffu;        // least: of twice the bits, less one: the smallest number that is not zero
             auto bits = [](float x) { return __float_as_uint(x) & 0x7fffffffu; };
+            auto low = [](float x) { return (__float_as_uint(x) << 1) - 1u; };
 #pragma unroll
-            for (int i = 0; i < NI; ++i) m = max(m, max(max(bits(ra[ps][i].x), bits(ra[ps][i].y)), max(bits(ra[ps][i].z), bits(ra[ps][i].w))));
+            for (int i = 0; i < NI; ++i) {
+                m = max(m, max(max(bits(ra[ps][i].x), bits(ra[ps][i].y)), max(bits(ra[ps][i].z), bits(ra[ps][i].w))));
+                least = min(least, min(min(low(ra[ps][i].x), low(ra[ps][i].y)), min(low(ra[ps][i].z), low(ra[ps][i].w))));
+            }
 #pragma unroll
             for (int off = 1; off < 8; off <<= 1) m = max(m, (uint32_t)__shfl_xor((int)m, off, 64));
             // an infinity or a NaN: any scale, its results are formed again
             const int e = min(max((int)(m >> 23), 27), 254);
-            const float scale = __uint_as_float((uint32_t)(268 - e) << 23);        // 2^(14 - (e - 127))
+            // 2^(14 - (e - 127)), or NaN if one of the lane's numbers would scale to less than SMALLEST (2^(e - 154) before)
+            const uint32_t smallest = e > 27 ? (uint32_t)(e - 27) << 23 : 0x00400000u;
+            const float scale = least < 2u * smallest - 1u ? __builtin_nanf("") : __uint_as_float((uint32_t)(268 - e) << 23);
             if ((t & 7) == 0) row_exp[row] = e - 141;
 #pragma unroll
             for (int i = 0; i < NI; ++i) {
                 const int c = 8 * i + (t & 7);
                 const float s = c < k4 ? scale : 0.f;
-                const Split2 lo = split_pair_f16(ra[ps][i].x * s, ra[ps][i].y * s), hi = split_pair_f16(ra[ps][i].z * s, ra[ps][i].w * s);
+                const Split2 lo = split_large(ra[ps][i].x * s, ra[ps][i].y * s), hi = split_large(ra[ps][i].z * s, ra[ps][i].w * s);
                 if (c >= KS * 4) continue;
 #pragma unroll
                 for (int p = 0; p < 2; ++p) *reinterpret_cast<uint2 *>(lds + p * PLANE + row * PITCH + c * 8) = make_uint2(lo.w[p], hi.w[p]);
@@ -192,7 +208,7 @@ __global__ __launch_bounds__(512, 2) void k_row_products(const float *__restrict
             const bool again = info[g] == NOT_OK;        // nothing was packed: all of it in fp32
             const int32_t w_exp = again ? 0 : info[g];
             const unsigned char *a = lds + (wm * RB * 32 + (lane & 31)) * PITCH + half * 16;
-            split_floatx16 acc[RB], low[RB];             // products of the first parts; those with a second part
+            split_floatx16 acc[RB], low[RB];             // products of the first parts; 2^11 times those with a second part
 #pragma unroll
             for (int i = 0; i < RB; ++i)
 #pragma unroll
@@ -206,7 +222,7 @@ __global__ __launch_bounds__(512, 2) void k_row_products(const float *__restrict
                     ah[i] = *reinterpret_cast<const uint4 *>(a + i * 32 * PITCH + s * 32);
                 }
 #pragma unroll
-                for (int i = 0; i < RB; ++i) low[i] = split_product<2>(al[i], bl[s], low[i]);
+                for (int i = 0; i < RB; ++i) low[i] = split_product<2>(at_own_size(al[i]), bl[s], low[i]);
 #pragma unroll
                 for (int i = 0; i < RB; ++i) low[i] = split_product<2>(al[i], bh[s], low[i]);
 #pragma unroll
@@ -226,7 +242,7 @@ __global__ __launch_bounds__(512, 2) void k_row_products(const float *__restrict
                     const int ex[4] = {e.x, e.y, e.z, e.w};
 #pragma unroll
                     for (int v = 0; v < 4; ++v) {
-                        acc[i][4 * q + v] = __builtin_amdgcn_ldexpf(acc[i][4 * q + v] + low[i][4 * q + v], ex[v] + w_exp);
+                        acc[i][4 * q + v] = __builtin_amdgcn_ldexpf(__builtin_fmaf(low[i][4 * q + v], 4.8828125e-4f, acc[i][4 * q + v]), ex[v] + w_exp);
                         odd |= split_not_finite(acc[i][4 * q + v]);
                     }
                 }

@@ -43,6 +43,34 @@ def test_every_input_row_at_its_own_size(exponent):
     close_by_rows(got["dH0"], want["dH0"], 8e-6)
 
 
+@pytest.mark.parametrize("gap", [24, 30, 70])
+@pytest.mark.parametrize("what", ["rows", "entries", "one number"])
+def test_sums_that_rest_on_small_numbers(what, gap):
+    """Large numbers that meet zeros do not cost the small ones beside them any bits: every column of the results against its own
+    size.  Random rounding errors of an fp32 sum of 128 terms, the largest of some thousand: 4e-6 of its largest element."""
+    n, d, half, big = 600, 128, 64, np.float32(2.0 ** gap)
+    columns = slice(0, half)
+
+    def change(H0, dH, V, a, W0):
+        if what == "rows":                             # a column of the rows is large where the matrices' first half is zero
+            H0[:, 70] *= big; dH[:, 70] *= big
+            for W in (V[0], V[1], W0):
+                W[70, columns] = 0; W[columns, 70] = 0
+        elif what == "entries":                        # an entry of every row and column is large, where the rows are zero
+            H0[:, half:] = 0; dH[:, half:] = 0
+            for W in (V[0], V[1], W0):
+                W[np.arange(d), (np.arange(d) + half) % d] *= big
+        else:                                          # a row of its own has one number that matters, far below the others
+            H0[5::7, 70:] *= big; dH[5::7, 70:] *= big
+            H0[5::7, :69] = 0; dH[5::7, :69] = 0
+            for W in (V[0], V[1], W0):
+                W[70:, columns] = 0; W[columns, 70:] = 0
+    got, want = run(n, 1, d, d, 2, change)
+    for k in ("out", "dH0"):
+        size = np.abs(want[k][:, columns]).max(axis=0)
+        assert (np.abs(got[k] - want[k])[:, columns].max(axis=0) <= TOL * size).all(), k
+
+
 @pytest.mark.parametrize("what", ["column", "row", "matrix", "huge"])
 def test_matrices_that_are_not_split(what):
     """A column or row far below the rest, or entries near the ends of the range: plain fp32 products."""
