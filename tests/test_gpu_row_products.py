@@ -4,22 +4,35 @@ finite.  Tolerance of ordinary operands as in the split-product tests (4e-6 of t
 import numpy as np
 import pytest
 
+from oracle import oracle as orc
 from test_gpu_split_products import TOL, layer, model
 
 pytestmark = pytest.mark.gpu
 
 
-def run(n, R, di, do, B, change=None):
+def takes(n, R, di, do):
+    """The rule that takes the forward products and the transposed ones to these kernels, from the graph that `layer` draws."""
+    rng = np.random.default_rng(n + di)
+    head, tail = rng.integers(0, n, 8 * n).astype(np.int32), rng.integers(0, n, 8 * n).astype(np.int32)
+    head[:n] = np.arange(n)
+    runs = orc.build_partition(head, rng.integers(0, R, 8 * n).astype(np.int32), tail, n, R)["n_seg"] >= 256 * 2 * R
+    return runs and 100 <= di <= 160 and do <= 128, runs and 100 <= do <= 160 and di <= 128
+
+
+def run(n, R, di, do, B, change=None, reach=True):
+    if reach:
+        assert any(takes(n, R, di, do)), "the graph is too small for these kernels"
     H0, dH, V, a, W0 = model(n + di, n, R, di, do, B)
     if change:
         change(H0, dH, V, a, W0)
     return layer(n, R, 8 * n, di, do, B, 2, H0, dH, V, a, W0)
 
 
-@pytest.mark.parametrize("n,R", [(130, 1), (257, 2), (1500, 3)])
+@pytest.mark.parametrize("n,R", [(130, 1), (257, 2), (261, 1), (613, 2), (1500, 3)])       # the first two stay with the tiled product
 @pytest.mark.parametrize("di,do", [(100, 4), (112, 32), (116, 36), (128, 128), (132, 64), (160, 100), (4, 128), (96, 112)])
 def test_widths(n, R, di, do):
-    got, want = run(n, R, di, do, 2)
+    assert any(takes(n, R, di, do)) == (n > 257)
+    got, want = run(n, R, di, do, 2, reach=False)
     for k in want:
         assert np.abs(got[k] - want[k]).max() <= TOL * np.abs(want[k]).max(), k
 
@@ -71,10 +84,13 @@ def test_sums_that_rest_on_small_numbers(what, gap):
         assert (np.abs(got[k] - want[k])[:, columns].max(axis=0) <= TOL * size).all(), k
 
 
+@pytest.mark.parametrize("alone", [False, True])
 @pytest.mark.parametrize("what", ["column", "row", "matrix", "huge"])
-def test_matrices_that_are_not_split(what):
-    """A column or row far below the rest, or entries near the ends of the range: plain fp32 products."""
+def test_matrices_that_are_not_split(what, alone):
+    """A column or row far below the rest, or entries near the ends of the range: plain fp32 products.  Alone: the self-loop's
+    matrix is all there is, and every column of its products is held to its own size."""
     def change(H0, dH, V, a, W0):
+        if alone: a[:] = 0
         if what == "column": W0[:, 5] *= np.float32(2.0 ** -40)
         elif what == "row": W0[7] *= np.float32(2.0 ** -30)
         elif what == "matrix": W0 *= np.float32(2.0 ** -110)
@@ -82,6 +98,8 @@ def test_matrices_that_are_not_split(what):
     got, want = run(300, 1, 112, 104, 2, change)
     for k in ("out", "dH0"):
         assert np.abs(got[k] - want[k]).max() <= 2 * TOL * np.abs(want[k]).max(), k
+        if alone:
+            assert (np.abs(got[k] - want[k]).max(axis=0) <= 2 * TOL * np.abs(want[k]).max(axis=0)).all(), k
     if what == "column":                          # the column's own sums: only the self-loop's part is tiny, the runs' is not
         assert np.abs(got["out"][:, 5] - want["out"][:, 5]).max() <= 2 * TOL * np.abs(want["out"][:, 5]).max()
 
@@ -93,7 +111,8 @@ def test_numbers_that_are_not_finite(bad, where):
     def change(H0, dH, V, a, W0):
         a[:] = np.abs(a) + np.float32(0.1)
         dict(H0=H0, dH=dH, W0=W0, V=V[0])[where][3, 2] = bad
-    got, want = run(200, 1, 128, 112, 2, change)
+    assert all(takes(300, 1, 128, 112))
+    got, want = run(300, 1, 128, 112, 2, change)
     for k in ("out", "dH0"):
         finite = np.isfinite(want[k])
         assert np.array_equal(np.isfinite(got[k]), finite), k
