@@ -56,8 +56,8 @@ def test_every_class_of_shapes(orc, msg, d, B):
 @pytest.mark.parametrize("n_pos", [2, 60000])
 @pytest.mark.parametrize("d,B", [(64, 10), (200, 6)])
 def test_sub_graphs_of_either_size(orc, d, B, n_pos):
-    """Two positives: the last layer takes few edges and gathers the bases' rows, the first one most of them; many: both
-    take the combined rows.  The rows of the batch equal the oracle's."""
+    """Two positives: both layers take few edges and gather the bases' rows; many: every vertex is active and both take the
+    combined rows.  The rows of the batch equal the oracle's."""
     n, R, m = 6000, 20, 90000
     gp, ts, op, res, pos = forward_case(orc, n, R, m, d, B, "f32", seed=7, cone=True, n_pos=n_pos, acts=(0, 0))
     saved, _ = saved_bytes(gp, B, d, 4)
@@ -71,7 +71,69 @@ def test_sub_graphs_of_either_size(orc, d, B, n_pos):
             assert np.abs(ts.grads[l][k].cpu().numpy() - w).max() <= 1e-4 * np.abs(w).max(), (l, k)
 
 
-def test_an_edge_less_partition_and_sources_without_edges(orc):
+@pytest.mark.parametrize("d,B", [(64, 10), (200, 6)])
+def test_layers_of_either_form_and_sources_that_nothing_reads(orc, d, B):
+    """Two halves without an edge between them and a batch from one: the first layer is above the size at which the combined rows
+    are taken, the last one below, and the other half's sources are skipped, as are those of the batch's half that only the
+    first layer reads in a pass that took the wrong layer's flags.  The workspace is full of NaNs: a row that nothing wrote
+    would show."""
+    import torch
+    from gpu_util import SEED, STEP, gpu_step, oracle_step
+    n, R, m = 6000, 20, 90000
+    head, rel, tail = graph(8, n, R, m)
+    head, tail = head % (n // 2), tail % (n // 2)
+    head[m // 2:] += n // 2; tail[m // 2:] += n // 2
+    spec = synth.scaled(synth.WORKLOADS[0], name="halves", seed=7, n_entities=n, n_relations=R, n_triples=m, d=d, n_bases=B, n_pos=48,
+                        n_neg=0, n_parts=1, part_id=0, acts=[0, 0])
+    pos = np.random.default_rng(9).choice(m // 2, 48, replace=False).astype(np.int32)        # core triples keep the input's order
+    gp, ts, params, pos = gpu_step(spec, head, rel, tail, pos=pos, cone=True)
+    saved, groups = saved_bytes(gp, B, d, 4)
+    assert saved > 1.3e8
+    gate = (gp.n_vert * B * 4.0 + 8.0 * groups) / (B * 4.0 - 4.0)
+    active, stats = ts.cg.export()
+    read, n_read = ts.cg.input_rows()
+    assert stats[0, 1] > gate > stats[1, 1]
+    assert n_read <= n // 2 and active[0].sum() < n_read        # half of the sources unread, more of them read than active
+    first = ts.H_out.clone()
+    ts.workspace.fill_(0xff)
+    ts.run(spec.neg_mode, SEED, STEP)
+    torch.cuda.synchronize()
+    assert torch.equal(ts.H_out, first)
+    op, res = oracle_step(orc, spec, head, rel, tail, params, pos)
+    rows = np.unique(orc.batch_vertices(op, pos, res["neg_ent"]))
+    want = res["Hs"][-1][rows]
+    assert np.abs(ts.H_out.cpu().numpy()[rows] - want).max() <= 1e-5 * np.abs(want).max()
+    for l in range(2):
+        for k in ("dV", "da", "dW0"):
+            w = res["grads"][l][k]
+            assert np.abs(ts.grads[l][k].cpu().numpy() - w).max() <= 1e-4 * np.abs(w).max(), (l, k)
+
+
+def test_an_edge_less_partition():
+    """No hops, no message edges: the self-loop alone."""
+    import torch
+    from paper_2201_02791_amd import binding as kb
+    n, R, d, B = 300, 2, 64, 8
+    head, rel, tail = graph(10, n, R, 900)
+    part = kb.build_partition(head, rel, tail, n, R, 1, 0, 0)
+    assert part.n_edge == 0 and part.n_vert > 0
+    rng = np.random.default_rng(11)
+    t = lambda *s: torch.from_numpy(rng.standard_normal(s).astype(np.float32)).cuda()  # noqa: E731
+    lay = [dict(V=t(B, d, d), a=t(2 * R, B), W0=t(d, d), act=kb.ACT_IDENTITY, order=kb.ORDER_PROJECT_FIRST)]
+    H0, G = t(part.n_vert, d), t(part.n_vert, d)
+    ws = torch.full((kb.workspace_bytes(part, lay, 0),), 0xff, dtype=torch.uint8, device="cuda")
+    out, dH0 = torch.empty_like(H0), torch.empty_like(H0)
+    grads = [{k: torch.empty_like(lay[0][k[1:]]) for k in ("dV", "da", "dW0")}]
+    kb.rgcn_forward(part, lay, H0, ws, out, 0)
+    kb.rgcn_backward(part, lay, H0, ws, G, grads, dH0, 0)
+    torch.cuda.synchronize()
+    W0 = lay[0]["W0"].double()
+    for got, want in ((out, H0.double() @ W0), (dH0, G.double() @ W0.T), (grads[0]["dW0"], H0.double().T @ G.double())):
+        assert float((got.double() - want).abs().max()) <= 1e-5 * float(want.abs().max())
+    assert not grads[0]["dV"].any() and not grads[0]["da"].any()
+
+
+def test_sources_without_edges_and_a_second_step(orc):
     """Vertices that no edge leaves have no group; a second step on the same buffers gives the same bits."""
     n, R, m, d, B = 5000, 4, 60000, 128, 8
     from gpu_util import gpu_step, oracle_step
