@@ -7,9 +7,9 @@
 // keeps, per query, only how many entries lie above / exactly at the answer's score.
 // What the filtered setting removes - the known answers of the same (f, r), from none to thousands per query - is
 // scored again by k_eval_pairs and subtracted.  Both kernels build a score from the same sequence of steps (k ascending,
-// 16 k per step, fp32 accumulator starting at zero; a step is three products of two fp16 parts, split_f16.h, or, for queries
-// whose numbers do not allow that, six products of three bf16 parts, split_bf16.h, and then a score that is not finite comes
-// from v_mfma_f32_32x32x2_f32 steps, two k each), so a pair gets the same bits in both and the subtraction is exact.
+// 16 k per step, fp32 accumulator starting at zero; a step is three products of two fp16 parts, split_f16.h, or, in small
+// evaluations and for queries whose numbers do not allow that, six products of three bf16 parts, split_bf16.h, and then a score
+// that is not finite comes from v_mfma_f32_32x32x2_f32 steps, two k each), so a pair gets the same bits in both and the subtraction is exact.
 // The same per-query kernel ranks against explicit candidate lists.
 #include "common.h"
 #include "split_f16.h"
@@ -38,8 +38,10 @@ struct kge_eval_filter {
 namespace {
 
 // What k_eval_range found of H and of Q, numbers as the bits of their absolute values: the largest ones and the smallest one of
-// H that is not zero, less one.  n_three: the queries that k_eval_pairs found to need three parts.
-struct EvalRange { uint32_t max_h, least_h, max_q, n_three; };
+// H that is not zero, less one, in four places that the blocks of k_eval_range share out.  n_three (the first one's): the
+// queries that k_eval_pairs found to need three parts.
+struct EvalRange { struct alignas(64) Place { uint32_t max_h, least_h, max_q, n_three; } at[4]; };
+static_assert(sizeof(EvalRange) == 256, "what one query's share of the workspace is rounded up to");
 
 // tail queries of all test triples first, then the head queries; their query vectors Q[q][:] = H[fixed][:] * M[rel][:]
 // (one thread per 4 columns) and cleared counters
@@ -50,7 +52,7 @@ __global__ void k_eval_queries(const int32_t *__restrict__ th, const int32_t *__
                                unsigned *__restrict__ cnt_gt, EvalRange *__restrict__ range)
 {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t == 0) *range = EvalRange{0u, 0xffffffffu, 0u, 0u};
+    if (t < 4) range->at[t] = EvalRange::Place{0u, 0xffffffffu, 0u, 0u};
     if (t >= 2 * n_test * d4) return;
     const int64_t i = t / d4;
     const int32_t c = (int32_t)(t - i * d4);
@@ -111,12 +113,15 @@ struct EvalScale { bool half = false, h_loses = false; float h = 1.f, q = 1.f, i
 __device__ __forceinline__ EvalScale eval_scale(const EvalRange *__restrict__ range)
 {
     EvalScale c;
-    const int eh = (int)(range->max_h >> 23) - 127, eq = (int)(range->max_q >> 23) - 127;
+    uint32_t max_h = 0u, least_h = 0xffffffffu, max_q = 0u;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) { max_h = max(max_h, range->at[i].max_h); least_h = min(least_h, range->at[i].least_h); max_q = max(max_q, range->at[i].max_q); }
+    const int eh = (int)(max_h >> 23) - 127, eq = (int)(max_q >> 23) - 127;
     c.half = abs(eh) <= 24 && abs(eq) <= 24;
     auto two_to = [](int e) { return __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((e + 127) << 23)); };
     if (c.half) {
         c.h = two_to(14 - eh); c.q = two_to(14 - eq); c.inv = two_to(eh + eq - 28);
-        c.h_loses = range->least_h + 1u < (uint32_t)(eh + 111) << 23;       // LossBound
+        c.h_loses = least_h + 1u < (uint32_t)(eh + 111) << 23;       // LossBound
         c.q_small = (uint32_t)(eq + 111) << 23;
     }
     return c;
@@ -228,7 +233,7 @@ __host__ __device__ __forceinline__ int query_at(const PairPlace *ptr, PairPlace
 // for each of them.  Bound by the gathered rows (a load touches 32 of them).  40,932 queries of the 14,541-entity graph at
 // width 200: 676 us with one wavefront and one tile per query and fp32 steps, 187 with three bf16 parts, 180 with two
 // fp16 parts (545 with conditions around the row loads: each then waits for the last).  HALF = false: three bf16 parts only, for
-// the narrow rows; both forms in one kernel take 94 registers and leave two blocks per compute unit, this one 78 and three.
+// narrow rows and small evaluations; both forms in one kernel take 94 registers and leave two blocks per compute unit, this one 78 and three.
 template <bool HALF>
 __global__ __launch_bounds__(64 * PW) void k_eval_pairs(const float *__restrict__ Q, const float *__restrict__ H,
                                                     int32_t d, int64_t nq, int64_t n_test,
@@ -302,7 +307,7 @@ __global__ __launch_bounds__(64 * PW) void k_eval_pairs(const float *__restrict_
             const float s = pair_scores<3>(Q + q * d, H, by_three ? answer[q] : -1, d, lane, 1.f, 1.f);
             if (lane < n_here && by_three) { thr[lane] = s; s_answer[q] = s; }
             const int n = __popcll(__ballot(lane < n_here && by_three));
-            if (lane == 0) atomicAdd(&range->n_three, (uint32_t)n);
+            if (lane == 0) atomicAdd(&range->at[0].n_three, (uint32_t)n);
         }
         // k_eval_count finds it where the query's entity was, which only this block reads and wavefront 0 has read
         if (lane < n_here) fixed[q] = by_three ? 1 : 0;
@@ -781,7 +786,7 @@ __device__ __forceinline__ void pick_queries(const int32_t *__restrict__ three, 
 
 // HALF: blocks [0, g.blocks) rank all queries by two parts; those that need three are left to the rest of the grid, which
 // walks its own, smaller space of tiles.  Where no query can take two parts, the first blocks rank all of them by three.
-// HALF = false: three parts (narrow rows).
+// HALF = false: three parts (narrow rows, small evaluations).
 template <int WI, int WJ, bool DUMP, bool HALF>
 __global__ __launch_bounds__(512, 2) void k_eval_count(const EvalRange *__restrict__ range, const int32_t *__restrict__ three,
                                                     const float *__restrict__ Q,
@@ -807,7 +812,7 @@ __global__ __launch_bounds__(512, 2) void k_eval_count(const EvalRange *__restri
                                                     g.tiles_per_block, g.col_tiles, cnt_gt, cnt_eq, dump);
             return;
         }
-        const int64_t n = sc.half ? range->n_three : nq;
+        const int64_t n = sc.half ? range->at[0].n_three : nq;
         if (sc.half != rest || n == 0) return;
         const CountGrid own = rest ? count_grid(cdiv(n, 128 * WJ), g.col_tiles) : g;
         const int64_t first = rest ? blockIdx.x - g.blocks : blockIdx.x, step = rest ? gridDim.x - g.blocks : own.blocks;
@@ -823,22 +828,26 @@ __global__ __launch_bounds__(512, 2) void k_eval_count(const EvalRange *__restri
 
 // EvalRange of H (blocks [0, h_blocks)) and of Q (the rest), as bits of absolute values: ordered as the numbers are, infinities
 // above them and NaN above those.  n4: pieces of 4 numbers.  `out` comes initialised.
-__global__ __launch_bounds__(256) void k_eval_range(const uint4 *__restrict__ H, int64_t h_n4, const uint4 *__restrict__ Q, int64_t q_n4,
-                                                    int32_t h_blocks, EvalRange *__restrict__ out)
+// Bound by a launch and the atomics, which take turns where they meet: few large blocks, eight loads of a thread in flight, and
+// four places for them.  60,000 x 80: 8 us, 28 with 1024 blocks of four loads on one place; 1 M x 256: 174 us, 5.9 TB/s.
+constexpr int RANGE_T = 1024, RANGE_BLOCKS = 256;
+__global__ __launch_bounds__(RANGE_T) void k_eval_range(const uint4 *__restrict__ H, int64_t h_n4, const uint4 *__restrict__ Q, int64_t q_n4,
+                                                        int32_t h_blocks, EvalRange *__restrict__ out)
 {
-    __shared__ uint32_t red[2][4];
+    constexpr int U = 8, NW = RANGE_T / 64;
+    __shared__ uint32_t red[2][NW];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const bool is_h = (int)blockIdx.x < h_blocks;
     const uint4 *X = is_h ? H : Q;
     const int64_t n = is_h ? h_n4 : q_n4;
-    const int64_t first = (is_h ? blockIdx.x : blockIdx.x - h_blocks) * (int64_t)1024, step = (is_h ? h_blocks : gridDim.x - h_blocks) * (int64_t)1024;
+    const int64_t block = is_h ? blockIdx.x : blockIdx.x - h_blocks, step = (is_h ? h_blocks : gridDim.x - h_blocks) * (int64_t)RANGE_T;
     uint32_t most = 0u, least = 0xffffffffu;
-    for (int64_t c0 = first; c0 < n; c0 += step) {
-        uint4 x[4];
+    for (int64_t c0 = block * RANGE_T + threadIdx.x; c0 < n; c0 += U * step) {
+        uint4 x[U];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) { const int64_t c = c0 + u * 256 + threadIdx.x; x[u] = X[c < n ? c : n - 1]; }
+        for (int u = 0; u < U; ++u) { const int64_t c = c0 + u * step; x[u] = X[c < n ? c : c0]; }
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
+        for (int u = 0; u < U; ++u) {
             const uint32_t y[4] = {x[u].x & 0x7fffffffu, x[u].y & 0x7fffffffu, x[u].z & 0x7fffffffu, x[u].w & 0x7fffffffu};
             most = max(most, max(max(y[0], y[1]), max(y[2], y[3])));
             least = min(least, min(min(y[0] - 1u, y[1] - 1u), min(y[2] - 1u, y[3] - 1u)));      // a zero: the largest there is
@@ -852,11 +861,12 @@ __global__ __launch_bounds__(256) void k_eval_range(const uint4 *__restrict__ H,
     if (lane == 0) { red[0][w] = most; red[1][w] = least; }
     __syncthreads();
     if (threadIdx.x == 0) {
-        for (int i = 1; i < 4; ++i) { most = max(most, red[0][i]); least = min(least, red[1][i]); }
-        // most blocks change neither word: a look first keeps them off the one address (1900 blocks that all add: 47 us instead of 28)
-        uint32_t *hi = is_h ? &out->max_h : &out->max_q;
+#pragma unroll
+        for (int i = 1; i < NW; ++i) { most = max(most, red[0][i]); least = min(least, red[1][i]); }
+        EvalRange::Place *at = &out->at[block & 3];
+        uint32_t *hi = is_h ? &at->max_h : &at->max_q;
         if (most > __hip_atomic_load(hi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(hi, most);
-        if (is_h && least < __hip_atomic_load(&out->least_h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMin(&out->least_h, least);
+        if (is_h && least < __hip_atomic_load(&at->least_h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMin(&at->least_h, least);
     }
 }
 
@@ -877,8 +887,8 @@ struct Ks { int32_t k[8]; int32_t n; };
 
 // One block: the sum of 1 / rank in double, in a fixed order, and the numbers of ranks up to each k.  Bound by one compute
 // unit's instructions and a few memory round trips: 8 queries of a thread in flight, ranks doubled so that they are whole
-// numbers, the reciprocal from v_rcp_f64 and two Newton steps (within a unit in the last place; the full division takes
-// twice the instructions).  40,932 queries: 22 us, 32 with divisions, conditions per k and 4 in flight.
+// numbers, the reciprocal from v_rcp_f64 and two Newton steps (all of 400,000 ranks up to 2^31 come out correctly rounded; the
+// full division takes twice the instructions).  40,932 queries: 22 us, 32 with divisions, conditions per k and 4 in flight.
 __global__ __launch_bounds__(1024) void k_eval_metrics(const int32_t *__restrict__ higher,
                                                        const int32_t *__restrict__ equal, int64_t nq, Ks ks,
                                                        double *__restrict__ out)
@@ -948,7 +958,7 @@ EvalWs eval_layout(int64_t nq, int32_t d)
     auto take = [&](size_t bytes) { size_t o = cur; cur = align_up(cur + bytes, 256); return o; };
     w.off_fixed = take(n * 4); w.off_rel = take(n * 4); w.off_answer = take(n * 4);
     w.off_Q = take(n * (size_t)d * 4); w.off_s = take(n * 4);
-    w.off_sub_gt = take(n * 4); w.off_range = take(n * 4);      // 16 bytes are used
+    w.off_sub_gt = take(n * 4); w.off_range = take(n * 4);      // 256 bytes are used
     w.off_cnt_gt = take(n * 4); w.off_cnt_eq = take(n * 4);
     w.total = cur;
     return w;
@@ -997,6 +1007,14 @@ int launch_count(const EvalRange *range, const int32_t *three, const float *Q, i
     return launch_count_tiles<2, 1>(range, three, Q, nq, H, N, d, s_answer, cnt_gt, cnt_eq, dump, st);
 }
 
+// Two fp16 parts cost a launch that looks at the range, and k_eval_pairs blocks that hold both forms, two per compute unit
+// instead of three; what they save grows with the products and, as each tile starts its chain of steps anew, with the width.
+// Whole evaluations, us, three bf16 parts / two fp16 parts where possible: 5000 entities, d = 80, 5000 queries 78 / 85, 10,000
+// queries 124 / 125; d = 128, 1000 queries 58 / 60, 3200 queries 85 / 83; d = 200, 1000 queries 74 / 72; 14,541 entities,
+// d = 80, 2000 queries 79 / 82, 4000 queries 127 / 119; d = 96, 2000 queries 87 / 88; d = 128, 1000 queries 86 / 88, 2000
+// queries 105 / 98; 60,000 entities, d = 80, 1000 queries 143 / 134.
+bool two_parts_pay(int64_t nq, int64_t N, int32_t d) { return d >= HALF_FROM && (double)nq * (double)N * d * d >= 3.4e11; }
+
 // Queries per block of k_eval_pairs: the most that leave 1024 blocks (four of them fill a compute unit), but no fewer than a
 // block's wavefronts, so that long lists never get fewer wavefronts than queries.  2000 queries, half of them with
 // 50,000 known answers, d = 64: 2.1 ms; one wavefront per query 5.7; always 32 neighbouring queries per block 19.2.  200
@@ -1023,7 +1041,7 @@ int rank_all(const kge_eval_filter *f, const float *H, int64_t N, int32_t d, con
     float *Q = (float *)(ws + w.off_Q), *s = (float *)(ws + w.off_s);
     int32_t *sub_gt = (int32_t *)(ws + w.off_sub_gt);
     EvalRange *range = (EvalRange *)(ws + w.off_range);
-    EvalRange *half_range = d >= HALF_FROM ? range : nullptr;      // narrower: three bf16 parts without a look
+    EvalRange *half_range = two_parts_pay(nq, N, d) ? range : nullptr;      // else three bf16 parts without a look
     unsigned *cnt_gt = (unsigned *)(ws + w.off_cnt_gt), *cnt_eq = (unsigned *)(ws + w.off_cnt_eq);
     {
         KGE_PROF("eval_queries", st);
@@ -1031,10 +1049,10 @@ int rank_all(const kge_eval_filter *f, const float *H, int64_t N, int32_t d, con
                                                                          (const float4 *)M, d / 4, fixed, rel, answer,
                                                                          (float4 *)Q, cnt_gt, range);
         KGE_LAUNCH_CHECK();
-        if (d >= HALF_FROM) {
+        if (half_range) {
             const int64_t h_n4 = N * (d / 4), q_n4 = nq * (d / 4);
-            const int32_t h_blocks = (int32_t)std::min<int64_t>(cdiv(h_n4, 1024), 1024), q_blocks = (int32_t)std::min<int64_t>(cdiv(q_n4, 1024), 512);
-            k_eval_range<<<h_blocks + q_blocks, 256, 0, st>>>((const uint4 *)H, h_n4, (const uint4 *)Q, q_n4, h_blocks, range);
+            const int32_t h_blocks = (int32_t)std::min<int64_t>(cdiv(h_n4, RANGE_T), RANGE_BLOCKS), q_blocks = (int32_t)std::min<int64_t>(cdiv(q_n4, RANGE_T), RANGE_BLOCKS);
+            k_eval_range<<<h_blocks + q_blocks, RANGE_T, 0, st>>>((const uint4 *)H, h_n4, (const uint4 *)Q, q_n4, h_blocks, range);
             KGE_LAUNCH_CHECK();
         }
     }

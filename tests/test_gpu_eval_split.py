@@ -49,6 +49,11 @@ def check(kb, H, M, n, R, n_test, seed):
     assert torch.equal(eq.long(), ((scores == ans[:, None]) & others).sum(1))
 
 
+def two_parts(n, n_test, d):
+    """Whether an evaluation of that size is one that two fp16 parts are for."""
+    return d >= 80 and 2 * n_test * n * d * d >= 3.4e11
+
+
 def model(n, R, d, seed):
     rng = np.random.default_rng(seed)
     H, M = rng.normal(size=(n, d)).astype(np.float32), rng.normal(size=(R, d)).astype(np.float32)
@@ -65,19 +70,31 @@ def test_widths(kb, n, n_test, d):
     check(kb, H, M, n, 3, n_test, 52)
 
 
+@pytest.mark.parametrize("n,n_test,d,two", [(30001, 890, 80, True), (30001, 880, 80, False), (30001, 810, 84, True), (9001, 480, 200, True),
+                                            (9001, 470, 200, False), (3001, 70, 1024, True), (700, 90, 1024, False)])
+def test_sizes_around_the_change(kb, n, n_test, d, two):
+    """Evaluations just large enough for two parts and just not, tiles of 128 x 128 and of 256 x 256."""
+    print("[case] around the change", n, n_test, d, file=sys.stderr, flush=True)
+    assert two_parts(n, n_test, d) == two
+    H, M = model(n, 3, d, 59)
+    check(kb, H, M, n, 3, n_test, 60)
+
+
+@pytest.mark.parametrize("n,n_test", [(700, 90), (17001, 640)])          # three parts, two where the numbers allow them
 @pytest.mark.parametrize("what,scale", [("row", 2.0 ** -13), ("row", 2.0 ** -16), ("row", 2.0 ** -40), ("column", 2.0 ** -30),
                                         ("all", 2.0 ** -23), ("all", 2.0 ** -26), ("all", 2.0 ** 23), ("all", 2.0 ** 30),
                                         ("relation", 2.0 ** -20)])
-def test_sizes(kb, what, scale):
+def test_sizes(kb, what, scale, n, n_test):
     """Rows, columns, relations and whole tensors far from the rest in size."""
-    print("[case] sizes", what, scale, file=sys.stderr, flush=True)
-    n, R, d = 700, 3, 128
+    print("[case] sizes", what, scale, n, file=sys.stderr, flush=True)
+    R, d = 3, 128
+    assert two_parts(n, n_test, d) == (n > 700)
     H, M = model(n, R, d, 53)
     if what == "row": H[n - 1] *= scale; H[5] *= scale
     elif what == "column": H[:, 7] *= scale
     elif what == "all": H *= scale
     else: M[1] *= scale
-    check(kb, H, M, n, R, 90, 54)
+    check(kb, H, M, n, R, n_test, 54)
 
 
 def far_apart(what, gap, n, R, d):
@@ -105,16 +122,17 @@ def far_apart(what, gap, n, R, d):
     return H, M
 
 
-@pytest.mark.parametrize("n,n_test", [(700, 90), (17001, 520)])
+@pytest.mark.parametrize("n,n_test,d", [(700, 90, 100), (9001, 520, 200), (17001, 1010, 100)])     # three parts; two, tiles of either size
 @pytest.mark.parametrize("what,gap", [("column", 20), ("column", 24), ("column", 30), ("relations", 26), ("tiny", 24), ("kinds", 20),
                                       ("kinds", 40), ("sizes", 14), ("sizes", 30)])
-def test_scores_far_below_the_largest_numbers(kb, what, gap, n, n_test):
+def test_scores_far_below_the_largest_numbers(kb, what, gap, n, n_test, d):
     """A score is as accurate as its own terms allow, and as accurate as the answer's where that is larger: the sides of the
     answer's score are what is counted.  2^-20 of the terms' sizes: an fp32 sum of 100 terms has rounding errors of 2^-24 of
     its partial sums, some 50 of random sign."""
     import torch
     print("[case] far apart", what, gap, n, n_test, file=sys.stderr, flush=True)
-    R, d = 3, 100
+    R = 3
+    assert two_parts(n, n_test, d) == (n > 700)
     H, M = far_apart(what, gap, n, R, d)
     rng = np.random.default_rng(58)
     th, tr, tt = (rng.integers(0, hi, n_test).astype(np.int32) for hi in (n, R, n))
@@ -143,10 +161,11 @@ def test_scores_far_below_the_largest_numbers(kb, what, gap, n, n_test):
     assert torch.equal(eq.long(), ((scores == ans[:, None]) & left).sum(1))
 
 
-def test_whole_numbers_are_exact(kb):
-    print("[case] whole numbers", file=sys.stderr, flush=True)
+@pytest.mark.parametrize("n,n_test", [(5000, 300), (20001, 950)])
+def test_whole_numbers_are_exact(kb, n, n_test):
+    print("[case] whole numbers", n, file=sys.stderr, flush=True)
     import torch
-    n, R, d, n_test = 5000, 2, 96, 300
+    R, d = 2, 96
     rng = np.random.default_rng(55)
     H = rng.integers(-9, 10, (n, d)).astype(np.float32); M = rng.integers(-3, 4, (R, d)).astype(np.float32)
     th, tr, tt = (rng.integers(0, hi, n_test).astype(np.int32) for hi in (n, R, n))
@@ -170,3 +189,28 @@ def test_counts_of_many_queries(kb):
         got = kb.eval_metrics(torch.from_numpy(hi).cuda(), torch.from_numpy(eq).cuda(), ks).cpu().numpy()
         rank = 1.0 + hi.astype(np.float64) + 0.5 * eq
         np.testing.assert_allclose(got, [np.mean(1.0 / rank)] + [np.mean(rank <= k) for k in ks], rtol=1e-12)
+
+
+def test_reciprocals_round_correctly(kb):
+    """The sum of reciprocal ranks to the last bit: 1024 sums in the order of the queries, 64 of them halved six times over and
+    the 16 results in order."""
+    print("[case] reciprocals", file=sys.stderr, flush=True)
+    import torch
+    lane = np.arange(64)
+    for n in (1, 3, 1025, 30000):
+        rng = np.random.default_rng(n)
+        for top in (50, 10**6, 2**31 - 1):
+            hi, eq = rng.integers(0, top, n).astype(np.int32), rng.integers(0, 4, n).astype(np.int32)
+            x = np.zeros(-(-n // 1024) * 1024)
+            x[:n] = 1.0 / (1.0 + hi.astype(np.float64) + 0.5 * eq)
+            s = np.zeros(1024)
+            for row in x.reshape(-1, 1024):
+                s = s + row
+            s = s.reshape(16, 64)
+            for off in (32, 16, 8, 4, 2, 1):
+                s = s + s[:, lane ^ off]
+            want = 0.0
+            for w in range(16):
+                want = want + s[w, 0]
+            got = kb.eval_metrics(torch.from_numpy(hi).cuda(), torch.from_numpy(eq).cuda(), (1,)).cpu().numpy()[0]
+            assert got == want / n
