@@ -55,32 +55,6 @@ __global__ void k_expand(const int32_t *head, const int32_t *tail, int64_t M, co
     if (prev[s]) cur[t] = 1u;
 }
 
-// Build-time wrappers: the scratch of the scan and of the sort is allocated here (nothing in this file is
-// in the timed training step).
-int exclusive_scan(const uint32_t *in, uint32_t *out, int64_t n, hipStream_t st)
-{
-    uint32_t *scratch = nullptr;
-    const size_t words = scan_scratch_words(n);
-    if (words) KGE_HIP(hipMalloc(&scratch, sizeof(uint32_t) * words));
-    int rc = exclusive_scan_ws(in, out, n, scratch, st);
-    if (rc == KGE_OK && hipStreamSynchronize(st) != hipSuccess) { kge_set_error("scan failed"); rc = KGE_EHIP; }
-    if (scratch) (void)hipFree(scratch);
-    return rc;
-}
-
-template <typename K>
-int radix_sort(K **keys, uint32_t **vals, K **keys_alt, uint32_t **vals_alt, int64_t n, int bits,
-               hipStream_t st)
-{
-    if (n == 0) return KGE_OK;
-    uint32_t *scratch = nullptr;
-    KGE_HIP(hipMalloc(&scratch, sizeof(uint32_t) * radix_scratch_words(n)));
-    int rc = radix_sort_ws<K>(keys, vals, keys_alt, vals_alt, n, bits, scratch, st);
-    (void)hipStreamSynchronize(st);
-    (void)hipFree(scratch);
-    return rc;
-}
-
 // ---------------------------------------------------------------- compaction kernels
 __global__ void k_vert_compact(const uint32_t *flag, const uint32_t *pos, int32_t n_ent,
                                int32_t *vert_gid, int32_t *lid)
@@ -283,10 +257,10 @@ __global__ void k_heavy_flag(const int32_t *ptr, int64_t n_rows, int32_t heavy, 
 
 __global__ void k_heavy_emit(int64_t n_rows, const uint32_t *flag, const uint32_t *hpos,
                              const uint32_t *units, const uint32_t *upos, int32_t *hv_row,
-                             int32_t *hv_unit_ptr, int32_t *unit_hv)
+                             int32_t *hv_unit_ptr, int32_t *unit_hv, uint32_t *totals)
 {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i == n_rows) hv_unit_ptr[hpos[i]] = (int32_t)upos[i];
+    if (i == n_rows) { hv_unit_ptr[hpos[i]] = (int32_t)upos[i]; totals[0] = hpos[i]; totals[1] = upos[i]; }
     if (i >= n_rows || !flag[i]) return;
     uint32_t h = hpos[i], u0 = upos[i], n = units[i];
     hv_row[h] = (int32_t)i;
@@ -333,24 +307,26 @@ template <typename T> int palloc(T **out, size_t count)
 #define TRY(x) do { int rc__ = (x); if (rc__ != KGE_OK) return rc__; } while (0)
 inline unsigned grid_for(int64_t n) { return (unsigned)(n > 0 ? cdiv(n, TB) : 1); }
 
-// scratch: heavy_words(n_rows), free again for the next index (all work is on one stream).  With four buffers of its own, a
-// wait after each scan and an allocation per list, the fifth index took a graph of 14,541 vertices and 272,115 triples from 7.8
-// to 8.7 ms for everything made before the first step; with this scratch all five take no longer than four did.
+// Index of the heavy rows of `ptr`, which holds n_items items in all: n_items / heavy rows at most, and twice as many units.
+// lists: heavy_lists(n_items, heavy) words for its lists; totals: two words of device memory, [n_hv, n_units], which the caller
+// copies; scratch: heavy_words(n_rows), free again for the next index (all work is on one stream).
+// The build waits for the device once for all five indexes, and its scans and sorts share their scratch.  Whole builds, ms, with
+// an allocation and a wait for each scan and sort and two waits per index / now: 14,541 vertices and 272,115 triples 2.7 / 2.1,
+// 50,021 and 1 M 7.3 / 6.3, 290,001 and 3 M as one of four 11.4 / 9.3, 1000 and 5000 0.98 / 0.80.
 size_t heavy_words(int64_t n_rows) { return 4 * ((size_t)n_rows + 1) + scan_scratch_words(n_rows); }
-int build_heavy_index(const int32_t *ptr, int64_t n_rows, uint32_t *scratch, kge_heavy_index *hx, hipStream_t st, int32_t heavy = KGE_HEAVY)
+size_t heavy_lists(int64_t n_items, int32_t heavy) { return 4 * (size_t)(n_items / heavy) + 1; }
+int build_heavy_index(const int32_t *ptr, int64_t n_rows, int64_t n_items, uint32_t *scratch, int32_t **lists, uint32_t *totals,
+                      kge_heavy_index *hx, hipStream_t st, int32_t heavy = KGE_HEAVY)
 {
     uint32_t *flag = scratch, *units = flag + n_rows + 1, *hpos = units + n_rows + 1, *upos = hpos + n_rows + 1;
     if (n_rows > 0) { k_heavy_flag<<<grid_for(n_rows), TB, 0, st>>>(ptr, n_rows, heavy, flag, units); KGE_LAUNCH_CHECK(); }
     TRY(exclusive_scan_ws(flag, hpos, n_rows, upos + n_rows + 1, st));
     TRY(exclusive_scan_ws(units, upos, n_rows, upos + n_rows + 1, st));
-    uint32_t nh = 0, nu = 0;
-    KGE_HIP(hipMemcpy(&nh, hpos + n_rows, sizeof(uint32_t), hipMemcpyDeviceToHost));
-    KGE_HIP(hipMemcpy(&nu, upos + n_rows, sizeof(uint32_t), hipMemcpyDeviceToHost));
-    hx->n_hv = (int32_t)nh; hx->n_units = (int32_t)nu;
-    TRY(palloc(&hx->hv_row, 2 * (size_t)nh + 1 + nu));        // one allocation for the three lists
-    hx->hv_unit_ptr = hx->hv_row + nh;
-    hx->unit_hv = hx->hv_unit_ptr + nh + 1;
-    k_heavy_emit<<<grid_for(n_rows + 1), TB, 0, st>>>(n_rows, flag, hpos, units, upos, hx->hv_row, hx->hv_unit_ptr, hx->unit_hv);
+    hx->hv_row = *lists;
+    hx->hv_unit_ptr = hx->hv_row + n_items / heavy;
+    hx->unit_hv = hx->hv_unit_ptr + n_items / heavy + 1;
+    *lists += heavy_lists(n_items, heavy);
+    k_heavy_emit<<<grid_for(n_rows + 1), TB, 0, st>>>(n_rows, flag, hpos, units, upos, hx->hv_row, hx->hv_unit_ptr, hx->unit_hv, totals);
     KGE_LAUNCH_CHECK();
     return KGE_OK;
 }
@@ -361,6 +337,8 @@ int build_impl(const int32_t *h_head, const int32_t *h_rel, const int32_t *h_tai
 {
     hipStream_t st = nullptr;
     TempBufs tmp;
+    uint32_t *scan_ws;                                     // of all scans of the build: no more inputs than this
+    TRY(tmp.alloc(&scan_ws, scan_scratch_words(std::max<int64_t>(n_ent, 2 * M))));
     int32_t *head, *rel, *tail;
     TRY(tmp.alloc(&head, M)); TRY(tmp.alloc(&rel, M)); TRY(tmp.alloc(&tail, M));
     KGE_HIP(hipMemcpy(head, h_head, sizeof(int32_t) * M, hipMemcpyHostToDevice));
@@ -394,7 +372,7 @@ int build_impl(const int32_t *h_head, const int32_t *h_rel, const int32_t *h_tai
     uint32_t *vpos;
     int32_t *lid;
     TRY(tmp.alloc(&vpos, (size_t)n_ent + 1)); TRY(tmp.alloc(&lid, n_ent));
-    TRY(exclusive_scan(cur, vpos, n_ent, st));
+    TRY(exclusive_scan_ws(cur, vpos, n_ent, scan_ws, st));
     uint32_t N32 = 0;
     KGE_HIP(hipMemcpy(&N32, vpos + n_ent, sizeof(uint32_t), hipMemcpyDeviceToHost));
     const int64_t N = N32;
@@ -407,7 +385,7 @@ int build_impl(const int32_t *h_head, const int32_t *h_rel, const int32_t *h_tai
     if (neg_domain == KGE_DOMAIN_CORE) {
         uint32_t *cpos;
         TRY(tmp.alloc(&cpos, (size_t)n_ent + 1));
-        TRY(exclusive_scan(s0, cpos, n_ent, st));
+        TRY(exclusive_scan_ws(s0, cpos, n_ent, scan_ws, st));
         uint32_t nc = 0;
         KGE_HIP(hipMemcpy(&nc, cpos + n_ent, sizeof(uint32_t), hipMemcpyDeviceToHost));
         p->n_cand = nc;
@@ -424,7 +402,7 @@ int build_impl(const int32_t *h_head, const int32_t *h_rel, const int32_t *h_tai
     {
         uint32_t *kpos;
         TRY(tmp.alloc(&kpos, (size_t)M + 1));
-        TRY(exclusive_scan(core_flag, kpos, M, st));
+        TRY(exclusive_scan_ws(core_flag, kpos, M, scan_ws, st));
         uint32_t nk = 0;
         KGE_HIP(hipMemcpy(&nk, kpos + M, sizeof(uint32_t), hipMemcpyDeviceToHost));
         p->n_core = nk;
@@ -445,7 +423,7 @@ int build_impl(const int32_t *h_head, const int32_t *h_rel, const int32_t *h_tai
     uint32_t *eflag, *epos;
     TRY(tmp.alloc(&eflag, (size_t)2 * M)); TRY(tmp.alloc(&epos, (size_t)2 * M + 1));
     if (M > 0) { k_edge_flag<<<grid_for(2 * M), TB, 0, st>>>(head, tail, M, dstset, eflag); KGE_LAUNCH_CHECK(); }
-    TRY(exclusive_scan(eflag, epos, 2 * M, st));
+    TRY(exclusive_scan_ws(eflag, epos, 2 * M, scan_ws, st));
     uint32_t E32 = 0;
     KGE_HIP(hipMemcpy(&E32, epos + 2 * M, sizeof(uint32_t), hipMemcpyDeviceToHost));
     const int64_t E = E32;
@@ -460,13 +438,15 @@ int build_impl(const int32_t *h_head, const int32_t *h_rel, const int32_t *h_tai
         k_edge_emit<<<grid_for(2 * M), TB, 0, st>>>(head, rel, tail, M, n_rel, eflag, epos, lid, vbits, keys, vals);
         KGE_LAUNCH_CHECK();
     }
-    TRY(radix_sort<uint64_t>(&keys, &vals, &keys_alt, &vals_alt, E, rbits + 2 * vbits, st));
+    uint32_t *sort_ws;                                     // of all sorts: edges, views, runs
+    TRY(tmp.alloc(&sort_ws, radix_scratch_words(E)));
+    TRY(radix_sort_ws<uint64_t>(&keys, &vals, &keys_alt, &vals_alt, E, rbits + 2 * vbits, sort_ws, st));
 
     // --- runs
     uint32_t *sflag, *spos, *edge_seg;
     TRY(tmp.alloc(&sflag, E)); TRY(tmp.alloc(&spos, (size_t)E + 1)); TRY(tmp.alloc(&edge_seg, E));
     if (E > 0) { k_seg_flag<<<grid_for(E), TB, 0, st>>>(keys, E, vbits, sflag); KGE_LAUNCH_CHECK(); }
-    TRY(exclusive_scan(sflag, spos, E, st));
+    TRY(exclusive_scan_ws(sflag, spos, E, scan_ws, st));
     uint32_t S32 = 0;
     KGE_HIP(hipMemcpy(&S32, spos + E, sizeof(uint32_t), hipMemcpyDeviceToHost));
     const int64_t S = S32;
@@ -490,7 +470,7 @@ int build_impl(const int32_t *h_head, const int32_t *h_rel, const int32_t *h_tai
         TRY(tmp.alloc(&mflag, S)); TRY(tmp.alloc(&mpos, (size_t)S + 1));
         k_multi_flag<<<grid_for(S), TB, 0, st>>>(p->seg_ptr, S, mflag);
         KGE_LAUNCH_CHECK();
-        TRY(exclusive_scan(mflag, mpos, S, st));
+        TRY(exclusive_scan_ws(mflag, mpos, S, scan_ws, st));
         uint32_t n_multi = 0;
         KGE_HIP(hipMemcpy(&n_multi, mpos + S, sizeof(uint32_t), hipMemcpyDeviceToHost));
         p->n_mrun = n_multi;
@@ -518,7 +498,7 @@ int build_impl(const int32_t *h_head, const int32_t *h_rel, const int32_t *h_tai
         const int other_shift = view == 0 ? 0 : vbits;
         int32_t *ptr = view == 0 ? p->dm_ptr : p->sm_ptr;
         if (E > 0) { k_view_keys<<<grid_for(E), TB, 0, st>>>(keys, E, key_shift, vmask, k2, v2); KGE_LAUNCH_CHECK(); }
-        TRY(radix_sort<uint32_t>(&k2, &v2, &k2_alt, &v2_alt, E, vbits, st));
+        TRY(radix_sort_ws<uint32_t>(&k2, &v2, &k2_alt, &v2_alt, E, vbits, sort_ws, st));
         if (E > 0) {
             k_view_emit<<<grid_for(E), TB, 0, st>>>(v2, E, keys, vbits, other_shift, edge_seg, p->inv_c,
                                                    view == 0 ? p->dm_src : p->sm_dst,
@@ -532,7 +512,7 @@ int build_impl(const int32_t *h_head, const int32_t *h_rel, const int32_t *h_tai
         if (N > 0) { k_max_degree<<<grid_for(N), TB, 0, st>>>(ptr, N, maxdeg + view); KGE_LAUNCH_CHECK(); }
         if (view == 1) {
             if (E > 0) { k_group_flag<<<grid_for(E), TB, 0, st>>>(k2, p->sm_rel, E, gflag); KGE_LAUNCH_CHECK(); }
-            TRY(exclusive_scan(gflag, gbefore, E, st));
+            TRY(exclusive_scan_ws(gflag, gbefore, E, scan_ws, st));
             uint32_t n_groups = 0;
             KGE_HIP(hipMemcpy(&n_groups, gbefore + E, sizeof(uint32_t), hipMemcpyDeviceToHost));
             p->n_sgrp = n_groups;
@@ -550,13 +530,6 @@ int build_impl(const int32_t *h_head, const int32_t *h_rel, const int32_t *h_tai
             KGE_LAUNCH_CHECK();
         }
     }
-    uint32_t *heavy_ws;
-    TRY(tmp.alloc(&heavy_ws, heavy_words(std::max<int64_t>(N, S))));
-    TRY(build_heavy_index(p->dm_ptr, N, heavy_ws, &p->hv_dm, st));
-    TRY(build_heavy_index(p->sm_ptr, N, heavy_ws, &p->hv_sm, st));
-    TRY(build_heavy_index(p->sg_ptr, N, heavy_ws, &p->hv_sg, st, KGE_HEAVY_GROUPS));
-    TRY(build_heavy_index(p->seg_ptr, S, heavy_ws, &p->hv_seg, st));
-
     // --- the runs grouped by destination: a stable sort of run ids by destination keeps the
     // relation order inside a destination
     TRY(palloc(&p->dr_ptr, N + 1)); TRY(palloc(&p->dr_seg, S)); TRY(palloc(&p->dr_rel, S));
@@ -564,12 +537,29 @@ int build_impl(const int32_t *h_head, const int32_t *h_rel, const int32_t *h_tai
         uint32_t *rk, *rk_alt, *rv, *rv_alt;
         TRY(tmp.alloc(&rk, S)); TRY(tmp.alloc(&rk_alt, S)); TRY(tmp.alloc(&rv, S)); TRY(tmp.alloc(&rv_alt, S));
         if (S > 0) { k_run_keys<<<grid_for(S), TB, 0, st>>>(p->seg_dst, S, rk, rv); KGE_LAUNCH_CHECK(); }
-        TRY(radix_sort<uint32_t>(&rk, &rv, &rk_alt, &rv_alt, S, vbits, st));
+        TRY(radix_sort_ws<uint32_t>(&rk, &rv, &rk_alt, &rv_alt, S, vbits, sort_ws, st));
         if (S > 0) { k_run_emit<<<grid_for(S), TB, 0, st>>>(rv, S, p->seg_rel, p->dr_seg, p->dr_rel); KGE_LAUNCH_CHECK(); }
         k_ptr_from_sorted<uint32_t><<<grid_for(S + 1), TB, 0, st>>>(rk, S, N, p->dr_ptr);
         KGE_LAUNCH_CHECK();
     }
-    TRY(build_heavy_index(p->dr_ptr, N, heavy_ws, &p->hv_dr, st));
+
+    // --- heavy rows of the four views and of the groups; one allocation for all lists, which hv_dm.hv_row owns
+    {
+        const struct { const int32_t *ptr; int64_t rows, items; kge_heavy_index *hx; int32_t heavy; } index[5] = {
+            {p->dm_ptr, N, E, &p->hv_dm, KGE_HEAVY}, {p->sm_ptr, N, E, &p->hv_sm, KGE_HEAVY}, {p->sg_ptr, N, p->n_sgrp, &p->hv_sg, KGE_HEAVY_GROUPS},
+            {p->seg_ptr, S, E, &p->hv_seg, KGE_HEAVY}, {p->dr_ptr, N, S, &p->hv_dr, KGE_HEAVY}};
+        size_t words = 0;
+        for (const auto &x : index) words += heavy_lists(x.items, x.heavy);
+        uint32_t *heavy_ws, *totals, h_totals[10];
+        int32_t *lists;
+        TRY(tmp.alloc(&heavy_ws, heavy_words(std::max<int64_t>(N, S)))); TRY(tmp.alloc(&totals, 10));
+        TRY(palloc(&lists, words));
+        p->hv_dm.hv_row = lists;
+        for (int i = 0; i < 5; ++i)
+            TRY(build_heavy_index(index[i].ptr, index[i].rows, index[i].items, heavy_ws, &lists, totals + 2 * i, index[i].hx, st, index[i].heavy));
+        KGE_HIP(hipMemcpy(h_totals, totals, sizeof(h_totals), hipMemcpyDeviceToHost));
+        for (int i = 0; i < 5; ++i) { index[i].hx->n_hv = (int32_t)h_totals[2 * i]; index[i].hx->n_units = (int32_t)h_totals[2 * i + 1]; }
+    }
 
     // --- chunks of each relation's run range (host side: 2R+1 offsets)
     {
@@ -694,7 +684,7 @@ extern "C" void kge_partition_destroy(kge_partition *p)
     void *arrs[] = {p->vert_gid, p->core_eid, p->core_h, p->core_r, p->core_t, p->seg_ptr, p->seg_rel,
                     p->seg_dst, p->inv_c, p->col_src, p->edge_id, p->cand, p->dm_ptr, p->dm_src,
                     p->dm_rel, p->dm_invc, p->sm_ptr, p->sm_dst, p->sm_rel, p->sm_invc, p->rel_ptr,
-                    p->hv_dm.hv_row, p->hv_sm.hv_row, p->hv_seg.hv_row, p->hv_dr.hv_row, p->hv_sg.hv_row,
+                    p->hv_dm.hv_row,               // and the other four's
                     p->dr_ptr, p->dr_seg, p->dr_rel,
                     p->run_lists, p->sm_seg, p->seg_zrow, p->mrun, p->sg_ptr,
                     p->bad_ids};
