@@ -15,6 +15,7 @@
 // GE = groups / GB across edges.
 #include "common.h"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace {
@@ -1260,9 +1261,30 @@ static double relation_rows_fixed(const kge_partition *p, int32_t B, int32_t d, 
     return d * ((double)p->n_vert * B * (msg_bf16 ? 2 : 4) + 8.0 * (double)p->n_sgrp);
 }
 static double relation_rows_per_edge(int32_t B, int32_t d, int msg_bf16) { return (double)d * (B * (msg_bf16 ? 2 : 4) - 4); }
+// Bytes do not cost the same, though: rows of P, few bases of it above all, come from caches that a larger Q does not fit.  So
+// the form has to pay as well when a gathered byte of an array of 256 MB (the last-level cache) or more counts 1.75, of a
+// smaller one in proportion less, a byte of Q that is written 1.75 and one of P that is read once 1.  Forward passes, us, a row per pair / B rows per edge: 20,000 entities x 1.5
+// M triples, 237 relations, 2.4 edges per pair: d = 64, 2 bases 210 / 151, d = 200, 2 bases 648 / 542, d = 128, 4 bases of
+// bf16 437 / 322; 50,021 entities x 1 M triples, 40 relations, 4 bases of 128 bf16 332 / 294.  Of 1615 shapes that the bytes alone
+// take, 43 were more than 2 % slower so (at most 1.39), with both conditions 16 (at most 1.17); 2 lose what they gained (8 %).
+struct RelationRowsCost { double per_edge, fixed; };
+static RelationRowsCost relation_rows_cached(const kge_partition *p, int32_t B, int32_t d, int msg_bf16)
+{
+    const double P = (double)p->n_vert * d * B * (msg_bf16 ? 2 : 4), Q = 4.0 * d * (double)p->n_sgrp;
+    auto weight = [](double bytes) { return 1.0 + 0.75 * std::min(1.0, bytes / 2.56e8); };
+    return {d * (B * (msg_bf16 ? 2 : 4) * weight(P) - 4 * weight(Q)), P + 1.75 * Q};
+}
 static bool relation_rows_pay(const kge_partition *p, int32_t B, int32_t d, int msg_bf16, double least)
 {
-    return p->n_edge * relation_rows_per_edge(B, d, msg_bf16) > relation_rows_fixed(p, B, d, msg_bf16) + least;
+    const RelationRowsCost c = relation_rows_cached(p, B, d, msg_bf16);
+    return p->n_edge * relation_rows_per_edge(B, d, msg_bf16) > relation_rows_fixed(p, B, d, msg_bf16) + least &&
+           p->n_edge * c.per_edge > c.fixed + least;
+}
+// edges of a sub-graph from which it pays
+static unsigned long long relation_rows_edges(const kge_partition *p, int32_t B, int32_t d, int msg_bf16)
+{
+    const RelationRowsCost c = relation_rows_cached(p, B, d, msg_bf16);
+    return (unsigned long long)std::max(relation_rows_fixed(p, B, d, msg_bf16) / relation_rows_per_edge(B, d, msg_bf16), c.fixed / c.per_edge);
 }
 constexpr double ONE_LAUNCH = 3.2e7;
 bool gather_by_relation(const kge_partition *p, int32_t B, int32_t d, int msg_bf16)
@@ -1303,7 +1325,7 @@ int launch_gather_forward(const kge_partition *p, const void *P, int msg_bf16, c
     EdgeGate gate = {nullptr, 0};
     if (relation_rows_pay(p, B, d, msg_bf16, active ? 4 * ONE_LAUNCH : ONE_LAUNCH)) {
         // with a sub-graph: only if it has the edges that pay for all groups' rows
-        if (active) gate = {n_active_edges, (unsigned long long)(relation_rows_fixed(p, B, d, msg_bf16) / relation_rows_per_edge(B, d, msg_bf16))};
+        if (active) gate = {n_active_edges, relation_rows_edges(p, B, d, msg_bf16)};
         int rc = msg_bf16 ? launch_relation_rows<true>(p, P, a, B, d, rel_rows, src_active, gate, st)
                           : launch_relation_rows<false>(p, P, a, B, d, rel_rows, src_active, gate, st);
         if (rc != KGE_OK) return rc;

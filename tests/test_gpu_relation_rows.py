@@ -149,3 +149,39 @@ def test_sources_without_edges_and_a_second_step(orc):
     ts.run(spec.neg_mode, 1, 1)
     torch.cuda.synchronize()
     assert torch.equal(ts.H_out, first)
+
+
+@pytest.mark.parametrize("B,taken", [(2, False), (10, True)])
+def test_few_bases_beside_more_pairs_than_a_cache_holds(B, taken):
+    """Combined rows of 300 MB save bytes beside two bases of 4 MB that the caches hold, but not time: they are left out."""
+    import torch
+    from paper_2201_02791_amd import binding as kb
+    n, R, m, d = 2000, 120, 375000, 256
+    print("[case] few bases", B, flush=True)
+    head, rel, tail = graph(12, n, R, m)
+    part = kb.build_partition(head, rel, tail, n, R, 1, 0, 2)
+    src = torch.from_numpy(part.export("col_src").astype(np.int64)).cuda()
+    count = torch.from_numpy(np.diff(part.export("seg_ptr")).astype(np.int64)).cuda()
+    run = torch.repeat_interleave(torch.arange(len(count), device="cuda"), count)
+    rel2, dst = (torch.from_numpy(part.export(x).astype(np.int64)).cuda()[run] for x in ("seg_rel", "seg_dst"))
+    groups = len(torch.unique(src * (2 * R) + rel2))
+    assert part.n_edge * d * (B * 4.0 - 4.0) > d * (n * B * 4.0 + 8.0 * groups) + 3.2e7        # bytes alone would take it
+    gen = torch.Generator(device="cuda").manual_seed(13)
+    t = lambda *s: torch.randn(s, generator=gen, device="cuda")  # noqa: E731
+    lay = dict(V=t(B, 16, d), a=t(2 * R, B), W0=t(16, d), act=kb.ACT_IDENTITY, order=kb.ORDER_PROJECT_FIRST)
+    H0, out = t(part.n_vert, 16), torch.empty((part.n_vert, d), device="cuda")
+    ws = torch.empty(kb.workspace_bytes(part, [lay], 0), dtype=torch.uint8, device="cuda")
+    kb.profile_enable(True)
+    kb.rgcn_forward(part, [lay], H0, ws, out, 0)
+    torch.cuda.synchronize()
+    names = kb.profile_collect()
+    kb.profile_enable(False)
+    assert "gather_fwd" in names and ("gather_rows" in names) == taken
+    want = H0.double() @ lay["W0"].double()
+    for e in torch.arange(len(src), device="cuda").split(100000):
+        w = lay["a"].double()[rel2[e]] / count[run[e]].double()[:, None]
+        x = torch.zeros((len(e), d), dtype=torch.float64, device="cuda")
+        for b in range(B):
+            x += w[:, b:b + 1] * (H0.double() @ lay["V"][b].double())[src[e]]
+        want.index_add_(0, dst[e], x)
+    assert float((out.double() - want).abs().max()) <= 1e-5 * float(want.abs().max())
