@@ -63,3 +63,33 @@ def test_a_batch_s_sub_graph_takes_some_of_the_edges(orc, d, B):
     gp, ts, params, pos = gpu_step(spec, head, rel, tail, cone=True)
     op, res = oracle_step(orc, spec, head, rel, tail, params, pos)
     assert_step_close(ts, res, 1e-5, 1e-4, batch_rows=orc.batch_vertices(op, pos, res["neg_ent"]))
+
+
+@pytest.mark.parametrize("d,B", [(64, 9), (128, 12), (200, 10), (256, 16)])
+def test_dot_products_in_short_chains(d, B):
+    """One edge per relation and numbers of one sign: a coefficient's gradient is one dot product of d terms.  In u = 2^-24, a
+    rounding moves a sum by 0.4 u (rms); 16 chains of at most 16 terms, two sums of pairs and d / 64 - 1 more leave about
+    0.4 sqrt(16 / 3 / 4 + 1 + 1 + 1) u = 0.8 u, and the terms' own errors (six bf16 products each, 2 u) another 2 u / sqrt(d).
+    Chains of d / 2 terms: 0.4 sqrt(d / 6) u, 2.3 u at 200."""
+    import torch
+    from paper_2201_02791_amd import binding as kb
+    print("[case] chains", d, B, flush=True)
+    n, R, di = 3000, 1500, 16
+    ids = np.arange(R, dtype=np.int32)
+    part = kb.build_partition(ids, ids, ids + R, n, R, 1, 0, 2)
+    assert part.n_edge == 2 * R and part.n_vert == n
+    gen = torch.Generator(device="cuda").manual_seed(d)
+    t = lambda *s: torch.rand(s, generator=gen, device="cuda") + 0.5  # noqa: E731
+    lay = dict(V=t(B, di, d), a=t(2 * R, B), W0=t(di, d), act=kb.ACT_IDENTITY, order=kb.ORDER_PROJECT_FIRST)
+    H0, G = t(n, di), t(n, d)
+    ws = torch.empty(kb.workspace_bytes(part, [lay], 0), dtype=torch.uint8, device="cuda")
+    grads = [{k: torch.empty_like(lay[k[1:]]) for k in ("dV", "da", "dW0")}]
+    kb.rgcn_forward(part, [lay], H0, ws, torch.empty_like(G), 0)
+    kb.rgcn_backward(part, [lay], H0, ws, G, grads, torch.empty_like(H0), 0)
+    src = torch.from_numpy(part.export("col_src").astype(np.int64)).cuda()          # one run per edge, in relation order
+    dst = torch.from_numpy(part.export("seg_dst").astype(np.int64)).cuda()
+    want = torch.stack([((H0.double() @ lay["V"][b].double())[src] * G.double()[dst]).sum(1) for b in range(B)], 1)
+    off = (grads[0]["da"].double() / want - 1.0) * 2.0 ** 24
+    rms = float(off.square().mean().sqrt())
+    print("rms error in 2^-24:", rms, flush=True)
+    assert rms <= 1.4
