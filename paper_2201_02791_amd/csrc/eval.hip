@@ -432,8 +432,8 @@ __global__ __launch_bounds__(256) void k_eval_candidates(const float4 *__restric
 // ---- all entities.  A block of 8 wavefronts takes QN queries and walks `tiles_per_block` consecutive tiles of EM
 // entities; a wavefront owns WI x WJ accumulators of 32 entities x 32 queries, the wavefronts 2 x 4 of those.  The query
 // is the accumulator's column, so a lane has one threshold and one pair of counts per 32 queries, kept in registers over
-// all tiles.  16-deep steps: a step's rows are split into LDS ([part][row][k], two buffers) one step ahead, their loads
-// issued one step before that, one barrier per step, also from one tile to the next.
+// all tiles.  16-deep steps: a step's rows are split into LDS ([part][row][k]; three parts: two buffers, two parts: three) one
+// step ahead, with two parts two ahead, their loads issued one step before that, one barrier per step, also from one tile to the next.
 // Bound by the matrix cores, which run at 1.7 GHz under this load and are 61 % busy; the rest goes to the barrier of a step
 // and to what no product covers.  20,000 queries x 1 M entities at width 256, NP = 2: 27.6 ms (371 TFLOP/s, 1.1 PFLOP/s of
 // fp16 products); NP = 3, six products per term: 49 (208); fp32 steps: 88.6.  40,932 x 14,541 at width 200: 0.83 ms, 1.34
@@ -887,8 +887,10 @@ struct Ks { int32_t k[8]; int32_t n; };
 
 // One block: the sum of 1 / rank in double, in a fixed order, and the numbers of ranks up to each k.  Bound by one compute
 // unit's instructions and a few memory round trips: 8 queries of a thread in flight, ranks doubled so that they are whole
-// numbers, the reciprocal from v_rcp_f64 and two Newton steps (all of 400,000 ranks up to 2^31 come out correctly rounded; the
-// full division takes twice the instructions).  40,932 queries: 22 us, 32 with divisions, conditions per k and 4 in flight.
+// numbers r < 2^33, the reciprocal from v_rcp_f64 and two Newton steps, which round as a division does: the first leaves a
+// relative error below 2^-46, the second rounds a value within 2^-91 of 1 / r, and no point halfway between two doubles lies
+// within 2^-87 of it, being m / 2^k with k <= 54 + 33 and m r a whole number other than 2^k.  (The full division takes twice
+// the instructions.)  40,932 queries: 22 us, 32 with divisions, conditions per k and 4 in flight.
 __global__ __launch_bounds__(1024) void k_eval_metrics(const int32_t *__restrict__ higher,
                                                        const int32_t *__restrict__ equal, int64_t nq, Ks ks,
                                                        double *__restrict__ out)

@@ -110,7 +110,7 @@ struct RowTiles { const int32_t *id, *beg, *end; int32_t n; int64_t rows; };    
 // A block of 8 wavefronts walks consecutive row tiles.  A tile's rows are loaded while the tile before it is multiplied, scaled
 // and split into LDS in one piece ([part][row][k], an odd number of 16 bytes per row), and stay there; the matrix stays in
 // operand registers for as long as its group's tiles last, so that no product waits for memory.  Wavefronts stand WN across
-// the columns, 32 each; with fewer they share the rows (WN = 8: 128 rows each, 4: 64, less: 32, idle ones past that).
+// the columns, 32 each, and share the rows (WN = 4: 64 each, 2 and 1: 32, those past the rows only load and split).
 // Bound by the bytes of the rows.  5.3 M runs of 128 floats (a layer of 60 M edges): the four products 3.98 ms, 4.96 with six
 // bf16 products per term in tiles of 128 x 128 x 16, whose operands are split once per column tile; 75 % of the rate of a
 // copy.  With the matrix loaded for every tile, four steps ahead, behind the next tile's rows: 4.43.
@@ -120,6 +120,7 @@ __global__ __launch_bounds__(512, 2) void k_row_products(const float *__restrict
                                                          const int32_t *__restrict__ info, const float *__restrict__ W,
                                                          int32_t w_k, int32_t w_n, float *__restrict__ out)
 {
+    static_assert(WN == 1 || WN == 2 || WN == 4, "the rows of a tile are covered");
     constexpr int WM = WN == 4 ? 2 : 4, RB = 4 / WM, NI = (KS * 4 + 7) / 8;
     constexpr int PITCH = KS * 32 + 16, PLANE = RT * PITCH;
     __shared__ __attribute__((aligned(16))) unsigned char lds[2 * PLANE];
