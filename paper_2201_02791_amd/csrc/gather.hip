@@ -390,7 +390,7 @@ __global__ void k_act_backward(const float4 *__restrict__ dH, const float4 *__re
 // them with the same NB bases, and their sums meet in a butterfly per relation.
 // Bound by the vector instructions of the groups (most sources have one edge of a relation), the rows coming from the
 // caches: 544 k edges, 4 bases, d = 200, fp32: 149 us; for more bases the matrix-core form below takes over (10 bases 365
-// against 203 us).
+// against 211 us).
 template <int OFF> __device__ __forceinline__ float lane_xor(float x)
 {
     if constexpr (OFF == 1) return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0xb1, 0xf, 0xf, true));
@@ -603,8 +603,8 @@ __global__ __launch_bounds__(64 * WPB) void k_source_backward(
 // The lane groups of a narrow row take consecutive edges of a pass each; a group of edges cut by that, or by a unit, has two
 // rows.  Unused rows and the columns past the width are zeros (an infinity times a zero would be NaN).
 // W = 16 NBLK >= d columns.  A block is one wavefront (its LDS is what limits their number), 8 rows of G in flight per lane.
-// Bound by the latency of a source's chain at two wavefronts per SIMD: 544 k edges, 355 k groups, 10 bases, d = 200, fp32: 203
-// us, 365 on the vector units; 2 M edges, 16 bases, d = 128, bf16 messages: 442, 754.  (Four wavefronts per block and 4 rows in
+// Bound by the latency of a source's chain at two wavefronts per SIMD: 544 k edges, 355 k groups, 10 bases, d = 200, fp32: 211
+// us, 365 on the vector units; 2 M edges, 16 bases, d = 128, bf16 messages: 443, 754.  (Four wavefronts per block and 4 rows in
 // flight 407 and 542; three wavefronts per SIMD by fewer registers 330 and 560.)
 typedef float sb_f32x4 __attribute__((ext_vector_type(4)));
 
@@ -619,6 +619,7 @@ __global__ __launch_bounds__(64, 2) void k_source_cores(
 {
     constexpr int W = 16 * NBLK, LPR = W > 128 ? 64 : W > 64 ? 32 : 16, NG = 64 / LPR;
     constexpr int RPG = NG == 4 ? 4 : 8, SUB = NG * RPG;              // edges per lane group and per pass (16 at most)
+    constexpr int SUM = NBLK <= 8 ? 4 : (NBLK + 1) / 2;               // blocks of 16 columns that a dot product sums in one go
     constexpr bool NARROW = NG == 4;      // rows of up to four lane groups per pass, more of them: each 16 have a sum of their own in dP
     constexpr int PITCH = W + 4;                                      // 4 rows apart: 16 banks; one: an odd number of 16 bytes
     __shared__ __attribute__((aligned(16))) float Y[16 * PITCH];
@@ -671,15 +672,16 @@ __global__ __launch_bounds__(64, 2) void k_source_cores(
                 const float x = a[(int64_t)(4 * l4 + s < used ? rel[s] : 0) * B + min(b0 + l16, B - 1)];
                 c[s] = 4 * l4 + s < used ? x : 0.f;
             }
-        // a sum of its own for every 64 columns: in one chain dots, and with them da, are up to 30 % further off than the vector
-        // form's (5001 entities, d = 200, relative to 64 bits: 2.5e-7, 1.9e-7 there, 2.0e-7 so)
+        // four chains for every SUM blocks: with two chains over all blocks dots, and with them da, are up to 30 % further off than
+        // the vector form's (5001 entities, d = 200, relative to 64 bits: 2.5e-7, 1.9e-7 there, 2.0e-7 so).  Kernel, us, two chains / a
+        // sum for every 4 blocks / so: step of 8192 triples, d = 200: 206 / 216 / 211; d = 256: 301 / 238 / 230
         const sb_f32x4 zero = {0.f, 0.f, 0.f, 0.f};
         sb_f32x4 dots = zero;
 #pragma unroll
-        for (int t0 = 0; t0 < NBLK; t0 += 4) {
+        for (int t0 = 0; t0 < NBLK; t0 += SUM) {
             sb_f32x4 dot[4];
 #pragma unroll
-            for (int t = t0; t < t0 + 4 && t < NBLK; ++t) {
+            for (int t = t0; t < t0 + SUM && t < NBLK; ++t) {
                 const float4 y = *reinterpret_cast<const float4 *>(Y + l16 * PITCH + 16 * t + 4 * l4);
                 dot[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(y.x, p[t][0], t == t0 ? zero : dot[0], 0, 0, 0);
                 dot[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(y.y, p[t][1], t == t0 ? zero : dot[1], 0, 0, 0);
