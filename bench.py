@@ -24,7 +24,7 @@ PEAK_HBM_GBS = 8000.0
 PEAK_BF16_MFMA_TFLOPS = 2500.0
 # fp32 products run on the bf16 matrix cores, six products of bf16 parts per term
 PEAK_F32_MFMA_TFLOPS = PEAK_BF16_MFMA_TFLOPS / 6
-# the evaluation's scores from 80 columns on: three products of fp16 parts per term, at the same rate
+# the evaluation's scores from 80 columns on, small evaluations apart: three products of fp16 parts per term, at the same rate
 PEAK_EVAL_MFMA_TFLOPS = PEAK_BF16_MFMA_TFLOPS / 3
 # plain vector ALUs: 256 compute units x 4 SIMDs x 32 fp32 FMA lanes per clock x 2 flops x 2.4 GHz
 PEAK_F32_VALU_TFLOPS = 256 * 4 * 32 * 2 * 2.4e9 / 1e12
@@ -274,7 +274,7 @@ def run_eval(args):
     avg_ms = prof[work_name][0] / max(prof[work_name][1], 1)
     if flops is not None:        # dense contraction of fp32 numbers on the matrix cores
         roof = {"kernel": work_name, "bound": "mfma", "achieved": flops / (avg_ms * 1e-3) / 1e12,
-                "peak": PEAK_EVAL_MFMA_TFLOPS if d >= 80 else PEAK_F32_MFMA_TFLOPS, "unit": "TFLOP/s", "traffic": None,
+                "peak": PEAK_EVAL_MFMA_TFLOPS if d >= 80 and float(nq) * N * d * d >= 3.4e11 else PEAK_F32_MFMA_TFLOPS, "unit": "TFLOP/s", "traffic": None,
                 "avg_launch_ms": avg_ms}
     else:                        # gathers one entity row per (query, candidate)
         nbytes = nq * (1000 + 1) * (d * 4.0 + 4.0)

@@ -231,8 +231,8 @@ __host__ __device__ __forceinline__ int query_at(const PairPlace *ptr, PairPlace
 // lists hold a handful of entities (a tile of their own would be nearly empty) and a hub's hundreds are not one
 // wavefront's chain.  A block's queries lie a grid apart: neighbours in a test file often share a hub, whose list is as long
 // for each of them.  Bound by the gathered rows (a load touches 32 of them).  40,932 queries of the 14,541-entity graph at
-// width 200: 676 us with one wavefront and one tile per query and fp32 steps, 187 with three bf16 parts, 180 with two
-// fp16 parts (545 with conditions around the row loads: each then waits for the last).  HALF = false: three bf16 parts only, for
+// width 200: 676 us with one wavefront and one tile per query and fp32 steps, 187 with three bf16 parts, 207 with two
+// fp16 parts and the bounds on what they lose (545 with conditions around the row loads: each then waits for the last).  HALF = false: three bf16 parts only, for
 // narrow rows and small evaluations; both forms in one kernel take 94 registers and leave two blocks per compute unit, this one 78 and three.
 template <bool HALF>
 __global__ __launch_bounds__(64 * PW) void k_eval_pairs(const float *__restrict__ Q, const float *__restrict__ H,

@@ -111,8 +111,8 @@ struct RowTiles { const int32_t *id, *beg, *end; int32_t n; int64_t rows; };    
 // and split into LDS in one piece ([part][row][k], an odd number of 16 bytes per row), and stay there; the matrix stays in
 // operand registers for as long as its group's tiles last, so that no product waits for memory.  Wavefronts stand WN across
 // the columns, 32 each, and share the rows (WN = 4: 64 each, 2 and 1: 32, those past the rows only load and split).
-// Bound by the bytes of the rows.  5.3 M runs of 128 floats (a layer of 60 M edges): the four products 3.98 ms, 4.96 with six
-// bf16 products per term in tiles of 128 x 128 x 16, whose operands are split once per column tile; 75 % of the rate of a
+// Bound by the bytes of the rows.  5.3 M runs of 128 floats (a layer of 60 M edges): the four products 4.09 ms, 4.89 with six
+// bf16 products per term in tiles of 128 x 128 x 16, whose operands are split once per column tile; 73 % of the rate of a
 // copy.  With the matrix loaded for every tile, four steps ahead, behind the next tile's rows: 4.43.
 template <int KS, int WN>
 __global__ __launch_bounds__(512, 2) void k_row_products(const float *__restrict__ A, int64_t lda, const int32_t *__restrict__ aidx,
